@@ -27,6 +27,11 @@
 // so only its first piece can be handed over and only its last piece can wait, and the waiting
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
+//
+// K planes.  Calls of 33 to about a thousand tokens have too few output tiles to fill the chip, and there a piece that
+// hands 64 to 256 KiB of accumulators over and a piece that waits for them are most of the time.  They take tiles of 64
+// rows, as many workgroups per tile as fill the chip, each with an equal range of K, that store their partial sums of Y
+// as planes in the workspace's slots; reduce_planes_kernel adds them in plane order.
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -59,13 +64,20 @@ struct TiledArgs {
     int exp_bias;              // >= 0: exponent nibbles (byte = nibble + exp_bias); -1: exponent bytes
 };
 
+// row stride of a plane of partial sums
+__host__ __device__ constexpr int64_t plane_ld(int64_t N) { return (N + 3) / 4 * 4; }
+
+enum { kWhole = 0, kPieces = 1, kPlanes = 2 };
+
 // MINW = wavefronts per SIMD the register allocation must allow (2 lets two four-wavefront workgroups share a compute unit)
-// SPLIT = the workgroup walks a list of pieces (work split); otherwise it computes output tile blockIdx.x
-// whole, as straight-line code (the loop over pieces costs the main product a few percent)
+// FORM = kWhole: the workgroup computes one output tile, as straight-line code (the loop over pieces costs the main
+// product a few percent); kPieces: it walks a list of pieces (work split); kPlanes: straight-line code for one output
+// tile's share of K, stored as a plane of partial sums
 // WB = mantissa bits of W_q: 4, or 2 (half the code bytes per record, one 32-bit word per block)
-template <int TM, int TN, int WR, int WC, int NS, int MINW, bool SPLIT, int WB>
+template <int TM, int TN, int WR, int WC, int NS, int MINW, int FORM, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) {
     static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
+    constexpr bool SPLIT = FORM == kPieces;
     constexpr int BM = 32 * TM * WR;
     constexpr int NW = WR * WC;
     constexpr int STAGE = BM * 128;                // bytes: BM rows x 64 bf16
@@ -127,7 +139,14 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     int kt0, kt1;
     // The shared K tiles come first: the hand-over between workgroups then overlaps with the whole
     // tiles of other workgroups instead of ending the kernel.
-    if constexpr (!SPLIT) {
+    int plane = 0;
+    if constexpr (FORM == kPlanes) {
+        // neighbouring workgroups of one XCD: neighbouring tiles of the same K range, which share activations or weights
+        plane = lin / (int)a.dp_tiles;
+        tile_lin = lin - plane * (int)a.dp_tiles;
+        kt0 = plane * (int)a.sk_share;
+        kt1 = kt0 + (int)a.sk_share < KT ? kt0 + (int)a.sk_share : KT;
+    } else if constexpr (!SPLIT) {
         tile_lin = lin; kt0 = 0; kt1 = KT;
     } else if (u < u_end) {
         const int64_t rt = u / a.sk_tile_units;
@@ -147,7 +166,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     } else {
         break;
     }
-    const bool owner = !SPLIT || (kt0 == 0);                   // this piece stores the tile
+    const bool owner = FORM == kWhole || (kt0 == 0);           // this piece adds the correction (and, of cut tiles, stores the sum)
     if constexpr (SPLIT) {
         if (!first_piece) __syncthreads();                     // every wavefront is done with the LDS stages
         first_piece = false;
@@ -480,7 +499,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     // ---- store: lane (t, hh) holds columns 8 r4 + 4 hh .. + 3 of token t for every MFMA tile ------
     // As MXINT8 for the next layer: block b of a column group is columns 16 b .. 16 b + 15 = accumulator
     // registers 8 b .. 8 b + 7 of this lane and of lane ^ 32 (the same token).
-    if (a.Yc != nullptr) {
+    if (FORM != kPlanes && a.Yc != nullptr) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             const int64_t row = m0 + (wr * TM + tm) * 32 + t_e;
@@ -508,6 +527,12 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
         }
         if constexpr (!SPLIT) break; else continue;
     }
+    float* out = a.Y;
+    int64_t ldo = a.ldy;
+    if constexpr (FORM == kPlanes) {
+        ldo = plane_ld(a.N);
+        out = a.Part + (int64_t)plane * a.M * ldo;
+    }
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = m0 + (wr * TM + tm) * 32 + t_e;
@@ -519,7 +544,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 const int64_t n = cg * 32 + 8 * r4 + 4 * hh_e;
-                float* dst = a.Y + row * a.ldy + n;
+                float* dst = out + row * ldo + n;
                 const f32x4 v = f32x4{acc[tm][tn][4 * r4], acc[tm][tn][4 * r4 + 1], acc[tm][tn][4 * r4 + 2], acc[tm][tn][4 * r4 + 3]};
                 if (n + 3 < a.N) {
                     *reinterpret_cast<f32x4*>(dst) = v;
@@ -533,6 +558,46 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     }
     if constexpr (!SPLIT) break;
   }   // pieces
+}
+
+// Y = sum of the K planes in plane order (the same bits on every run), as fp32 or as MXINT8 blocks of 16 along N.  Bound
+// by the planes' way back from the caches (about 5.7 TB/s written and read, plus 4 us); a thread adds four columns with
+// eight planes' loads in flight, and for MXINT8 the four lanes of a quad hold one block (N is then a multiple of 16).
+__global__ __launch_bounds__(256) void reduce_planes_kernel(TiledArgs a, int planes) {
+    const int64_t ldp = plane_ld(a.N), n4 = ldp / 4;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= a.M * n4) return;
+    const int64_t r = i / n4, c = 4 * (i - r * n4);
+    const float* src = a.Part + r * ldp + c;
+    const int64_t stride = a.M * ldp;
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int z0 = 0; z0 < planes; z0 += 8) {
+        f32x4 q[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) q[j] = *reinterpret_cast<const f32x4*>(src + (z0 + j < planes ? z0 + j : planes - 1) * stride);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (z0 + j < planes) v = (z0 + j == 0) ? q[0] : v + q[j];
+    }
+    if (a.Yc != nullptr) {
+        float m = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[0]), __builtin_fabsf(v[1])),
+                                  __builtin_fmaxf(__builtin_fabsf(v[2]), __builtin_fabsf(v[3])));
+        m = __builtin_fmaxf(m, __shfl_xor(m, 1));
+        m = __builtin_fmaxf(m, __shfl_xor(m, 2));
+        const uint32_t eb = (f32_bits(m) >> 23) & 0xFFu;
+        uint32_t w = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w |= ((uint32_t)mx8_code(v[j], (int)eb - 127) & 0xFFu) << (8 * j);
+        *reinterpret_cast<uint32_t*>(a.Yc + r * a.ldyc + c) = w;
+        if ((c & 15) == 0) a.Ye[r * (a.N >> 4) + (c >> 4)] = (uint8_t)eb;
+        return;
+    }
+    float* dst = a.Y + r * a.ldy + c;
+    if (c + 3 < a.N) {
+        *reinterpret_cast<f32x4*>(dst) = v;
+    } else {
+        for (int j = 0; c + j < a.N; ++j) dst[j] = v[j];
+    }
 }
 
 // Time estimates in microseconds for one tile shape, launched as one workgroup per tile or with the
@@ -611,6 +676,56 @@ static bool split_pays(const TileShape& sh, int64_t tiles, int64_t KT, int cus) 
     return time_split(sh, tiles, KT, cus) < 0.95 * time_whole(sh, tiles, KT, cus);
 }
 
+// ---- calls that do not fill the chip for long: whole tiles or K planes ------------------------------------------------
+// Time model of these launches: a workgroup takes `unit[r - 1]` per K tile when r of them share a compute unit, `round`
+// per round of workgroups, `fixed` per launch, and the planes `kPlaneUs` plus their bytes written and read at kPlaneMBperUs.
+// Fitted to 5100 timings (K, N from 640 to 28672, 40 to 2048 tokens, 1 to 16 planes; mean error 3 to 5 %).  Picking by it
+// came within 2 % of the fastest form timed on average, and over those sizes took 0.77 times the time of the earlier
+// choice (whole tiles of 128 rows or pieces): 4096 x 4096 at 64 tokens 43 -> 17 us, 11008 x 4096 at 64 tokens 123 -> 24 us,
+// 4112 x 11000 at 203 tokens 54 -> 44 us, 4096 x 4096 at 2048 tokens 73 -> 65 us.
+struct SmallShape { int id, bm, bn, resident; double unit[3], round, fixed; };
+static const SmallShape kSmallShapes[] = {
+    {11, 128, 512, 1, {4.76, 0.0, 0.0}, 7.9, 5.3}, {12, 128, 256, 2, {3.42, 5.56, 0.0}, 5.0, 4.3},
+    {14, 64, 256, 3, {2.03, 3.23, 4.69}, 0.1, 8.3}, {15, 64, 128, 3, {1.75, 2.52, 3.33}, 0.9, 7.5}, {17, 64, 512, 1, {2.74, 0.0, 0.0}, 3.3, 7.0},
+};
+constexpr double kPlaneUs = 3.8, kPlaneMBperUs = 5.7;
+constexpr int kMaxPlanes = 16;
+// Above this many operations the chip is full long enough to lower its clock, which this model does not know; the estimate
+// above is calibrated there (8192 x 28672 at 2048 tokens: its choice 714 us, this model's 770 to 800 us; below it, e.g.
+// 11008 x 4096 at 1500 tokens, 144 us against 126 us).
+constexpr double kSmallFlops = 1.5e11;
+
+struct SmallPick { int id, planes, share; };      // share: K tiles per plane
+
+static double small_us(const SmallShape& sh, int64_t M, int64_t N, int64_t tiles, int64_t KT, int planes, int64_t share, int cus) {
+    const int64_t wgs = tiles * planes, per_round = (int64_t)cus * sh.resident;
+    const int64_t full = wgs / per_round, rest = wgs - full * per_round;
+    double t = sh.fixed + (double)full * (sh.unit[sh.resident - 1] * (double)share + sh.round);
+    if (rest > 0) t += sh.unit[(rest + cus - 1) / cus - 1] * (double)share + sh.round;
+    if (planes > 1) t += kPlaneUs + (double)planes * (double)M * (double)plane_ld(N) * 8e-6 / kPlaneMBperUs;
+    return t;
+}
+
+// part_bytes: room for planes (0: whole tiles only)
+static SmallPick pick_small(int64_t M, int64_t N, int64_t KT, int64_t part_bytes, int cus) {
+    SmallPick best{0, 1, (int)KT};
+    double best_us = 0.0;
+    for (const SmallShape& sh : kSmallShapes) {
+        const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
+        // shapes of 64 rows move twice the weights per operation: not for launches of more than two rounds
+        if (sh.bm < 128 && tiles > 2 * (int64_t)cus * sh.resident) continue;
+        for (int p = 1; p <= kMaxPlanes && p <= KT; ++p) {
+            const int64_t share = (KT + p - 1) / p;
+            const int planes = (int)((KT + share - 1) / share);
+            if (planes != p) continue;                       // the same planes as a smaller p
+            if (p > 1 && (sh.bm == 128 || (int64_t)p * M * plane_ld(N) * 4 > part_bytes)) continue;
+            const double us = small_us(sh, M, N, tiles, KT, planes, share, cus);
+            if (best.id == 0 || us < best_us) { best = SmallPick{sh.id, planes, (int)share}; best_us = us; }
+        }
+    }
+    return best;
+}
+
 // What has to be established once per kernel instance and process: the dynamic LDS limit, and how many of its
 // workgroups one compute unit really holds (the work split launches exactly as many workgroups as are resident
 // at once, because owners wait for flags that later workgroups raise).
@@ -658,7 +773,7 @@ static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipS
     // bounds; should it ever be lower than the shape assumes, tiles are not cut.
     bool can_split = CAN_SPLIT;
     if constexpr (CAN_SPLIT) {
-        const hipError_t e = prepare_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, true, WB>, setup_split, LDS_BYTES, 64 * WR * WC);
+        const hipError_t e = prepare_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kPieces, WB>, setup_split, LDS_BYTES, 64 * WR * WC);
         if (e != hipSuccess) return e;
         if (setup_split.resident < MINW) can_split = false;
     }
@@ -675,9 +790,29 @@ static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipS
     a.dp_tiles = sp.dp_tiles; a.sk_units = sp.sk_units; a.sk_share = sp.sk_share; a.sk_tile_units = sp.sk_tile_units;
     if constexpr (CAN_SPLIT) {
         if (sp.sk_units > 0)
-            return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, true, WB>, setup_split, LDS_BYTES, sp.grid, 64 * WR * WC, a, s);
+            return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kPieces, WB>, setup_split, LDS_BYTES, sp.grid, 64 * WR * WC, a, s);
     }
-    return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, false, WB>, setup_whole, LDS_BYTES, tiles, 64 * WR * WC, a, s);
+    return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kWhole, WB>, setup_whole, LDS_BYTES, tiles, 64 * WR * WC, a, s);
+}
+
+// The forms pick_small chooses: whole tiles, or K planes and their sum.
+template <int WB, int TM, int TN, int WR, int WC, int NS, int MINW>
+static hipError_t launch_small_t(TiledArgs a, const SmallPick& pick, hipStream_t s) {
+    constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
+    constexpr int LDS_BYTES = NS * BM * 128;
+    a.grid_m = (int)((a.M + BM - 1) / BM);
+    a.grid_n = (int)((a.N + BN - 1) / BN);
+    a.dp_tiles = (int64_t)a.grid_m * a.grid_n;
+    a.sk_share = pick.share;
+    static KernelSetup setup_whole, setup_planes;
+    if (pick.planes == 1)
+        return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kWhole, WB>, setup_whole, LDS_BYTES, a.dp_tiles, 64 * WR * WC, a, s);
+    const hipError_t e = launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kPlanes, WB>, setup_planes, LDS_BYTES,
+                                       a.dp_tiles * pick.planes, 64 * WR * WC, a, s);
+    if (e != hipSuccess) return e;
+    const int64_t items = a.M * (plane_ld(a.N) / 4);
+    hipLaunchKernelGGL(reduce_planes_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, a, pick.planes);
+    return hipGetLastError();
 }
 
 __global__ void clear_flags_kernel(uint32_t* flags, int n) {
@@ -726,6 +861,16 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     int mode = variant / 100;
     variant %= 100;
     if (mode < 0 || mode > 3) return hipErrorInvalidValue;
+    if (variant == 0 && mode <= 1 && L.w_bits == 4 && L.kp <= 64 && 2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
+        const int64_t part_bytes = (mode == 0 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
+        const SmallPick pick = pick_small(M, L.N, L.KT, part_bytes, cus);
+        switch (pick.id) {
+            case 14: return launch_small_t<4, 2, 2, 1, 4, 4, 3>(a, pick, s);
+            case 15: return launch_small_t<4, 1, 2, 2, 2, 4, 3>(a, pick, s);
+            case 17: return launch_small_t<4, 2, 2, 1, 8, 4, 2>(a, pick, s);
+            default: variant = pick.id; mode = 1; break;     // 128 rows: the launches below, tiles never cut
+        }
+    }
     if (variant == 0) {
         // pick the tile shape (and the split) with the lowest estimated time
         double best = 0.0;
