@@ -28,10 +28,11 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
-// K planes.  Calls of 33 to about a thousand tokens have too few output tiles to fill the chip, and there a piece that
-// hands 64 to 256 KiB of accumulators over and a piece that waits for them are most of the time.  They take tiles of 64
-// rows, as many workgroups per tile as fill the chip, each with an equal range of K, that store their partial sums of Y
-// as planes in the workspace's slots; reduce_planes_kernel adds them in plane order.
+// Calls that do not fill the chip for long (33 to about a thousand tokens) take staged_kernel: tiles of 64 rows, every
+// operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
+// the tiles are too few, several workgroups per tile, each with an equal range of K ("planes"), that store their partial
+// sums of Y in the workspace's slots; reduce_planes_kernel adds them in plane order.  A piece of tiled_kernel that hands
+// its accumulators over and another that waits for them cost more than such a call's product.
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -67,17 +68,13 @@ struct TiledArgs {
 // row stride of a plane of partial sums
 __host__ __device__ constexpr int64_t plane_ld(int64_t N) { return (N + 3) / 4 * 4; }
 
-enum { kWhole = 0, kPieces = 1, kPlanes = 2 };
-
 // MINW = wavefronts per SIMD the register allocation must allow (2 lets two four-wavefront workgroups share a compute unit)
-// FORM = kWhole: the workgroup computes one output tile, as straight-line code (the loop over pieces costs the main
-// product a few percent); kPieces: it walks a list of pieces (work split); kPlanes: straight-line code for one output
-// tile's share of K, stored as a plane of partial sums
+// SPLIT = the workgroup walks a list of pieces (work split); otherwise it computes output tile blockIdx.x
+// whole, as straight-line code (the loop over pieces costs the main product a few percent)
 // WB = mantissa bits of W_q: 4, or 2 (half the code bytes per record, one 32-bit word per block)
-template <int TM, int TN, int WR, int WC, int NS, int MINW, int FORM, int WB>
+template <int TM, int TN, int WR, int WC, int NS, int MINW, bool SPLIT, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) {
     static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
-    constexpr bool SPLIT = FORM == kPieces;
     constexpr int BM = 32 * TM * WR;
     constexpr int NW = WR * WC;
     constexpr int STAGE = BM * 128;                // bytes: BM rows x 64 bf16
@@ -139,14 +136,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     int kt0, kt1;
     // The shared K tiles come first: the hand-over between workgroups then overlaps with the whole
     // tiles of other workgroups instead of ending the kernel.
-    int plane = 0;
-    if constexpr (FORM == kPlanes) {
-        // neighbouring workgroups of one XCD: neighbouring tiles of the same K range, which share activations or weights
-        plane = lin / (int)a.dp_tiles;
-        tile_lin = lin - plane * (int)a.dp_tiles;
-        kt0 = plane * (int)a.sk_share;
-        kt1 = kt0 + (int)a.sk_share < KT ? kt0 + (int)a.sk_share : KT;
-    } else if constexpr (!SPLIT) {
+    if constexpr (!SPLIT) {
         tile_lin = lin; kt0 = 0; kt1 = KT;
     } else if (u < u_end) {
         const int64_t rt = u / a.sk_tile_units;
@@ -166,7 +156,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     } else {
         break;
     }
-    const bool owner = FORM == kWhole || (kt0 == 0);           // this piece adds the correction (and, of cut tiles, stores the sum)
+    const bool owner = !SPLIT || (kt0 == 0);                   // this piece stores the tile
     if constexpr (SPLIT) {
         if (!first_piece) __syncthreads();                     // every wavefront is done with the LDS stages
         first_piece = false;
@@ -499,7 +489,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     // ---- store: lane (t, hh) holds columns 8 r4 + 4 hh .. + 3 of token t for every MFMA tile ------
     // As MXINT8 for the next layer: block b of a column group is columns 16 b .. 16 b + 15 = accumulator
     // registers 8 b .. 8 b + 7 of this lane and of lane ^ 32 (the same token).
-    if (FORM != kPlanes && a.Yc != nullptr) {
+    if (a.Yc != nullptr) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
             const int64_t row = m0 + (wr * TM + tm) * 32 + t_e;
@@ -527,12 +517,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
         }
         if constexpr (!SPLIT) break; else continue;
     }
-    float* out = a.Y;
-    int64_t ldo = a.ldy;
-    if constexpr (FORM == kPlanes) {
-        ldo = plane_ld(a.N);
-        out = a.Part + (int64_t)plane * a.M * ldo;
-    }
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = m0 + (wr * TM + tm) * 32 + t_e;
@@ -544,7 +528,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 const int64_t n = cg * 32 + 8 * r4 + 4 * hh_e;
-                float* dst = out + row * ldo + n;
+                float* dst = a.Y + row * a.ldy + n;
                 const f32x4 v = f32x4{acc[tm][tn][4 * r4], acc[tm][tn][4 * r4 + 1], acc[tm][tn][4 * r4 + 2], acc[tm][tn][4 * r4 + 3]};
                 if (n + 3 < a.N) {
                     *reinterpret_cast<f32x4*>(dst) = v;
@@ -558,6 +542,389 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     }
     if constexpr (!SPLIT) break;
   }   // pieces
+}
+
+// ---- the same product with every operand staged by direct-to-LDS loads -----------------------------------------------
+// What bounds these launches is not the loads' latency (three or seven stages ahead measure the same) but one or two
+// wavefronts on a SIMD issuing an instruction every eight cycles each, and LDS reads: 64 x 128 tiles of four 64 x 32
+// wavefronts, two workgroups on a compute unit, are the fastest where there are enough of them.  Main product,
+// tiled_kernel's form of the same tile -> this one: 4112 x 11000 at 203 tokens 45 -> 40 us (512 TFLOP/s on 344
+// workgroups), 11008 x 4096 at 64 tokens 26 -> 20 us; 2-bit weights with rank 256, 4096 x 4096 at 2048 tokens
+// 104 -> 83 us, at 64 tokens 99 -> 31 us (there the correction: its operands are asked for in one go per two chunks).
+// 1 KiB (64 lanes x 16 bytes) or 256 B from `base` + this lane's byte offset to LDS address at + ADD + 16 (4) * lane.
+// Written as asm because the compiler answers its own builtin with a full drain of the loads in flight in front of every
+// LDS read; nothing is returned in registers, and the kernel counts these loads itself (staged_wait).  M0 has no other use.
+template <int ADD>
+__device__ __forceinline__ void lds_dma16(uint32_t at, uint32_t off, const uint8_t* base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+}
+template <int ADD>
+__device__ __forceinline__ void lds_dma4(uint32_t at, uint32_t off, const uint8_t* base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+}
+// All but this wavefront's newest `LEFT` loads have landed, its LDS reads have returned, and so have everybody's.
+template <int LEFT>
+__device__ __forceinline__ void staged_wait() {
+    static_assert(LEFT >= 0 && LEFT < 64, "a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+}
+
+// D = stages of 64 K in LDS: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN] 1 KiB of codes
+// [wave][TN] 256 B of exponent words; chunk ch + D - 1 is asked for when chunk ch starts.
+template <int TM, int TN, int WR, int WC, int D, int MINW, bool PLANES, int WB>
+__global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a) {
+    static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
+    constexpr int BM = 32 * TM * WR, NW = WR * WC, NT = 64 * NW;
+    constexpr int XB = BM * 128, WOFF = XB, EOFF = XB + NW * TN * 1024, STAGE = EOFF + NW * TN * 256;
+    constexpr int XL = XB / 1024 / NW;             // activation loads per wavefront and chunk
+    static_assert(XB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
+    constexpr int L = XL + 2 * TN;                 // loads per wavefront and chunk
+    static_assert(D >= 3, "a chunk computed, one read ahead, one on its way");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / WC, wc = wave % WC;
+    const int t = lane & 31, hh = lane >> 5;
+    // workgroup -> output tile (and K plane): consecutive positions land on one XCD
+    int lin;
+    {
+        const int nwg = gridDim.x, pid = blockIdx.x;
+        const int xcd = pid & 7, local = pid >> 3, per = nwg >> 3, rem = nwg & 7;
+        lin = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
+    }
+    const int KT = (int)a.KT;
+    int plane = 0, kt0 = 0, kt1 = KT;
+    if constexpr (PLANES) {
+        // neighbouring workgroups of one XCD: neighbouring tiles of the same K range, which share activations or weights
+        plane = lin / (int)a.dp_tiles;
+        lin -= plane * (int)a.dp_tiles;
+        kt0 = plane * (int)a.sk_share;
+        kt1 = kt0 + (int)a.sk_share < KT ? kt0 + (int)a.sk_share : KT;
+    }
+    int tile_m, tile_n;                            // bands of group_m tile rows
+    {
+        const int width = a.group_m * a.grid_n, grp = lin / width, in = lin - grp * width, first_m = grp * a.group_m;
+        const int gsize = (a.grid_m - first_m < a.group_m) ? a.grid_m - first_m : a.group_m;
+        tile_m = first_m + in % gsize;
+        tile_n = in / gsize;
+    }
+    const int64_t m0 = (int64_t)tile_m * BM;
+    const int64_t g0 = ((int64_t)tile_n * WC + wc) * TN;       // first column group of this wavefront
+    auto group_of = [&](int tn) { return g0 + tn < a.N32 ? g0 + tn : a.N32 - 1; };   // clamped; the store is masked
+
+    // ---- loads ---------------------------------------------------------------------------------------------------
+    // Activations: load j of this wavefront brings rows 8 (NW j + wave) .. + 7; lane -> row lane / 8 of them, LDS cell
+    // lane % 8, which holds the row's cell (lane % 8) ^ ((row >> 1) & 7).  (Rows past M are workspace rows: see there.)
+    // What differs between the loads of a chunk is in the lanes' offsets, so that one scalar address serves all of a kind.
+    uint32_t x_off[XL], w_off[TN], e_off[TN];
+#pragma unroll
+    for (int j = 0; j < XL; ++j)
+        x_off[j] = (uint32_t)((8 * (NW * j + wave) + (lane >> 3)) * (int)a.ldxh * 2) +
+                   (((uint32_t)(lane & 7) ^ (uint32_t)(((wave & 1) * 4 + (lane >> 4)) & 7)) << 4);
+    const bool exp4 = a.exp_bias >= 0;             // wave-uniform
+    const int64_t g_first = group_of(0);
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+        const uint32_t rec = (uint32_t)(group_of(tn) - g_first) * (uint32_t)a.rec_bytes;
+        w_off[tn] = rec + lane * 16 + (exp4 ? kWCompactCodeOffset : 0);
+        e_off[tn] = rec + (exp4 ? lane * 4 : w_code_bytes(WB) + lane * 8);
+    }
+    const int64_t tile_stride = a.N32 * a.rec_bytes;
+    const uint8_t* x_ptr = reinterpret_cast<const uint8_t*>(a.Xh + m0 * a.ldxh + kt0 * kTileK);
+    const uint8_t* w_ptr = a.Wt + g_first * a.rec_bytes + kt0 * tile_stride;       // record of the K tile being asked for
+    int cc_in = 0;                                 // its chunk
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds);
+    auto issue = [&](uint32_t stage) {             // the next chunk of the row -> the stage at that byte offset
+        const uint32_t at_x = lds0 + stage + wave * 1024, at_w = lds0 + stage + wave * (TN * 1024), at_e = lds0 + stage + wave * (TN * 256);
+        lds_dma16<0>(at_x, x_off[0], x_ptr);
+        if constexpr (XL > 1) lds_dma16<NW * 1024>(at_x, x_off[1], x_ptr);
+        if constexpr (XL > 2) lds_dma16<2 * NW * 1024>(at_x, x_off[2], x_ptr);
+        if constexpr (XL > 3) lds_dma16<3 * NW * 1024>(at_x, x_off[3], x_ptr);
+        const uint8_t* wp = w_ptr + (WB == 4 ? cc_in : cc_in >> 1) * 1024;
+        // exponent word of the chunk: with nibbles the record's only one, with bytes the first or second four of a lane's eight
+        const uint8_t* ep = w_ptr + (exp4 ? 0 : (cc_in >> 1) * 4);
+        lds_dma16<WOFF>(at_w, w_off[0], wp);
+        lds_dma4<EOFF>(at_e, e_off[0], ep);
+        if constexpr (TN > 1) {
+            lds_dma16<WOFF + 1024>(at_w, w_off[TN - 1], wp);
+            lds_dma4<EOFF + 256>(at_e, e_off[TN - 1], ep);
+        }
+        x_ptr += 128;
+        cc_in = (cc_in + 1) & 3;
+        w_ptr += cc_in == 0 ? tile_stride : 0;
+    };
+    static_assert(XL <= 4 && TN <= 2, "issue() spells its loads out");
+
+    // ---- operands ------------------------------------------------------------------------------------------------
+    int rd_off[4];                                 // step s: logical cell 4 hh + s of this lane's TM rows
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) rd_off[s4] = (wr * TM * 32 + t) * 128 + (((4 * hh + s4) ^ ((t >> 1) & 7)) << 4);
+    auto read_x = [&](Frag (&dst)[TM], const uint8_t* stage, int s4) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) dst[tm].u = *reinterpret_cast<const u32x4*>(stage + rd_off[s4] + tm * 4096);
+    };
+    typedef typename std::conditional<WB == 4, u32x4, u32x2>::type WVec;   // a lane's two blocks of one chunk
+    struct WSet { WVec c[TN]; uint32_t e[TN]; };
+    auto read_w = [&](WSet& w, const uint8_t* stage, int cc) {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+            const uint8_t* src = stage + WOFF + (wave * TN + tn) * 1024 + lane * 16;
+            if constexpr (WB == 4) w.c[tn] = *reinterpret_cast<const u32x4*>(src);
+            else w.c[tn] = *reinterpret_cast<const u32x2*>(src + (cc & 1) * 8);
+            w.e[tn] = *reinterpret_cast<const uint32_t*>(stage + EOFF + (wave * TN + tn) * 256 + lane * 4);
+        }
+    };
+    const int es0 = exp4 ? 4 : 8;
+    const uint32_t emask = exp4 ? 0xFu : 0xFFu;
+    const uint32_t ebase = ((exp4 ? (uint32_t)a.exp_bias : 0u) + (WB == 4 ? 7u : 9u)) << 23;   // w_scale / w2_scale of exponent 0
+
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[tm][tn][r] = 0.f;
+
+    // ---- main product --------------------------------------------------------------------------------------------
+    const int chunks = (kt1 - kt0) * 4;            // of this workgroup
+    // Software pipeline of MFMA steps (16 of K): while the MFMAs of one step run, the weights of the next are expanded
+    // and its activations read from LDS.  A wavefront issues a vector instruction every eight cycles at best, so what
+    // bounds these launches - one or two wavefronts on a SIMD - is the instructions between its MFMAs: the pattern
+    // below puts a few behind every MFMA, where they cost nothing.
+    Frag xa[TM];
+    bf16x8 wv[TN];
+    float sc[TN][2];
+    auto scales = [&](const WSet& w, int cc) {
+        const int esh = exp4 ? (cc & 3) * 8 : (cc & 1) * 16;
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+            const uint32_t ew = w.e[tn] >> esh;
+            sc[tn][0] = f32_from_bits(((ew & emask) << 23) + ebase);
+            sc[tn][1] = f32_from_bits((((ew >> es0) & emask) << 23) + ebase);
+        }
+    };
+    auto expand = [&](const WSet& w, int s4) {
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+            if constexpr (WB == 4) wv[tn] = unpack_w8(w.c[tn][s4], sc[tn][s4 >> 1]);
+            else wv[tn] = unpack_w8_b2(w.c[tn][s4 >> 1], s4 & 1, sc[tn][s4 >> 1]);
+        }
+    };
+    // Chunk ch: on entry xa and wv hold its step 0 and w its codes; on exit xa and wv hold step 0 of chunk ch + 1 and wn its codes.
+    auto chunk = [&](const WSet& w, WSet& wn, int ch, const uint8_t* cur, const uint8_t* nxt) {
+        read_w(wn, nxt, ch + 1);
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) {
+            Frag xn[TM];
+            bf16x8 now[TN];
+            if (s4 < 3) read_x(xn, cur, s4 + 1);
+            else read_x(xn, nxt, 0);
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) now[tn] = wv[tn];
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm) acc[tm][tn] = mfma32(now[tn], xa[tm].v, acc[tm][tn]);
+            if (s4 < 3) {
+                expand(w, s4 + 1);
+            } else {
+                scales(wn, ch + 1);
+                expand(wn, 0);
+            }
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) xa[tm] = xn[tm];
+            __builtin_amdgcn_sched_group_barrier(0x100, TM, 0);                                    // LDS reads
+#pragma unroll
+            for (int i = 0; i < TM * TN; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // an MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, (10 * TN + TM * TN - 1) / (TM * TN), 0);   // vector instructions
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto next_stage = [](uint32_t s) { return s + STAGE == D * STAGE ? 0u : s + STAGE; };
+    uint32_t st_in = 0;                            // stage the next chunk goes to
+#pragma unroll
+    for (int i = 0; i < D - 1; ++i) {
+        if (i < chunks) {
+            issue(st_in);
+            st_in = next_stage(st_in);
+        }
+    }
+    // (a range of fewer than D - 1 chunks has fewer loads in flight: only a full drain is sure to cover its first chunk)
+    if (chunks >= D - 1) staged_wait<(D - 2) * L>();
+    else staged_wait<0>();
+    WSet w0, w1;
+    read_x(xa, lds, 0);
+    read_w(w0, lds, 0);
+    scales(w0, 0);
+    expand(w0, 0);
+    uint32_t st = 0;                               // stage of chunk ch
+    auto step = [&](const WSet& w, WSet& wn, int ch) {
+        if (ch + D <= chunks) {
+            // chunks ch and ch + 1 have landed; the stage of chunk ch - 1 has been read by everybody and takes chunk ch + D - 1
+            staged_wait<(D - 3) * L>();
+            issue(st_in);
+            st_in = next_stage(st_in);
+        } else {
+            staged_wait<0>();                      // nothing left to ask for
+        }
+        const uint32_t nx = next_stage(st);
+        chunk(w, wn, ch, lds + st, lds + nx);      // (the last one reads ahead what nobody uses)
+        st = nx;
+    };
+    for (int ch = 0; ch < chunks; ch += 2) {       // (four chunks per K tile)
+        step(w0, w1, ch);
+        step(w1, w0, ch + 1);
+    }
+
+    // ---- rank-kp correction: [T_hi | T_lo | 0] against B_k, by the workgroup with the start of K -----------------------
+    const int nb2 = 2 * a.kp16, tail_chunks = (nb2 + 3) / 4;
+    const int my_tail = (kt0 == 0) ? tail_chunks : 0;
+    constexpr int LPT = BM * 8 / NT;               // 16-byte cells each thread moves per chunk
+    constexpr int ROWS_PER_PASS = NT / 8;
+    static_assert(ROWS_PER_PASS % 16 == 0, "swizzle must not depend on the pass");
+    const int ld_row0 = tid >> 3;
+    const int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4);
+    for (int cc0 = 0; cc0 < my_tail; cc0 += 2) {   // two correction chunks at a time (ranks up to 64 need one round)
+        u32x4 bw[2][2][TN];                        // B_k's codes and exponents of both chunks: asked for ahead of T
+        uint32_t be[2][2][TN];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int jb = 4 * (cc0 + q) + 2 * hh + j;
+                const int rb = jb < nb2 ? (jb < a.kp16 ? jb : jb - a.kp16) : 0;
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    const uint8_t* rec = a.Bt + (group_of(tn) * a.kp16 + rb) * kBRecordBytes;
+                    bw[q][j][tn] = *reinterpret_cast<const u32x4*>(rec + t * 16);
+                    be[q][j][tn] = rec[512 + t];
+                }
+            }
+        u32x4 tst[2][LPT];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int j = 0; j < LPT; ++j) {
+                const int col = (cc0 + q) * 64 + 8 * (tid & 7);
+                const int64_t row = m0 + ld_row0 + j * ROWS_PER_PASS;
+                tst[q][j] = u32x4{0, 0, 0, 0};
+                if (col >= 2 * a.kp) continue;
+                if (a.S <= 1) {
+                    tst[q][j] = *reinterpret_cast<const u32x4*>(a.Xh + row * a.ldxh + (int64_t)KT * kTileK + col);
+                    continue;
+                }
+                // T as S fp32 partial sums: added in slice order, then the bf16 term this cell holds
+                const bool lo = col >= a.kp;
+                const float* src = a.Tpart + row * a.kp + (lo ? col - a.kp : col);
+                f32x4 p0[8], p1[8];
+#pragma unroll
+                for (int sl = 0; sl < 8; ++sl) {   // all slices' loads in flight together
+                    const int64_t o = (int64_t)(sl < a.S ? sl : a.S - 1) * a.tp_stride;
+                    p0[sl] = *reinterpret_cast<const f32x4*>(src + o);
+                    p1[sl] = *reinterpret_cast<const f32x4*>(src + o + 4);
+                }
+#pragma unroll
+                for (int sl = 1; sl < 8; ++sl)
+                    if (sl < a.S) { p0[0] += p0[sl]; p1[0] += p1[sl]; }
+                uint32_t h[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = e < 4 ? p0[0][e & 3] : p1[0][e & 3];
+                    const uint32_t hb = f32_bits(v) & 0xFFFF0000u;
+                    h[e] = lo ? f32_bits(v - f32_from_bits(hb)) >> 16 : hb >> 16;
+                }
+                tst[q][j] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
+            }
+        __syncthreads();                           // every wavefront is done with the stages (or the previous two chunks)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int j = 0; j < LPT; ++j)
+                *reinterpret_cast<u32x4*>(lds + q * XB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (cc0 + q >= my_tail) continue;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int jb = 4 * (cc0 + q) + 2 * hh + j;     // lane half hh owns rank blocks 4 cc + 2 hh + {0, 1}
+                Frag bf[TN][2];
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+                    int8x16_to_frags(jb < nb2 ? bw[q][j][tn] : u32x4{0, 0, 0, 0}, h_scale(be[q][j][tn]), bf[tn][0], bf[tn][1]);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    Frag xt[TM];
+                    read_x(xt, lds + q * XB, 2 * j + h);
+#pragma unroll
+                    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                        for (int tm = 0; tm < TM; ++tm) acc[tm][tn] = mfma32(bf[tn][h].v, xt[tm].v, acc[tm][tn]);
+                }
+            }
+        }
+    }
+
+    // ---- store: lane (t, hh) holds columns 8 r4 + 4 hh .. + 3 of token t for every MFMA tile ------------------------------
+    if (!PLANES && a.Yc != nullptr) {              // as MXINT8: block b of a column group is registers 8 b .. + 7 of two lanes
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            const int64_t row = m0 + (wr * TM + tm) * 32 + t;
+            if (row >= a.M) continue;
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                if (g0 + tn >= a.N32) continue;
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    float v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = acc[tm][tn][8 * b + i];
+                    uint32_t w0, w1;
+                    const uint32_t eb = requant_half_block(v, w0, w1);
+                    const int64_t n0 = (g0 + tn) * 32 + 16 * b;
+                    if (n0 < a.N) {
+                        int8_t* dst = a.Yc + row * a.ldyc + n0 + 4 * hh;
+                        *reinterpret_cast<uint32_t*>(dst) = w0;
+                        *reinterpret_cast<uint32_t*>(dst + 8) = w1;
+                        if (hh == 0) a.Ye[row * (a.N >> 4) + (n0 >> 4)] = (uint8_t)eb;
+                    }
+                }
+            }
+        }
+        return;
+    }
+    float* out = a.Y;
+    int64_t ldo = a.ldy;
+    if constexpr (PLANES) {
+        ldo = plane_ld(a.N);
+        out = a.Part + (int64_t)plane * a.M * ldo;
+    }
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+        const int64_t row = m0 + (wr * TM + tm) * 32 + t;
+        if (row >= a.M) continue;
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+            if (g0 + tn >= a.N32) continue;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const int64_t n = (g0 + tn) * 32 + 8 * r4 + 4 * hh;
+                float* dst = out + row * ldo + n;
+                const f32x4 v = f32x4{acc[tm][tn][4 * r4], acc[tm][tn][4 * r4 + 1], acc[tm][tn][4 * r4 + 2], acc[tm][tn][4 * r4 + 3]};
+                if (n + 3 < a.N) {
+                    *reinterpret_cast<f32x4*>(dst) = v;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (n + j < a.N) dst[j] = v[j];
+                }
+            }
+        }
+    }
 }
 
 // Y = sum of the K planes in plane order (the same bits on every run), as fp32 or as MXINT8 blocks of 16 along N.  Bound
@@ -676,51 +1043,66 @@ static bool split_pays(const TileShape& sh, int64_t tiles, int64_t KT, int cus) 
     return time_split(sh, tiles, KT, cus) < 0.95 * time_whole(sh, tiles, KT, cus);
 }
 
-// ---- calls that do not fill the chip for long: whole tiles or K planes ------------------------------------------------
-// Time model of these launches: a workgroup takes `unit[r - 1]` per K tile when r of them share a compute unit, `round`
-// per round of workgroups, `fixed` per launch, and the planes `kPlaneUs` plus their bytes written and read at kPlaneMBperUs.
-// Fitted to 5100 timings (K, N from 640 to 28672, 40 to 2048 tokens, 1 to 16 planes; mean error 3 to 5 %).  Picking by it
-// came within 2 % of the fastest form timed on average, and over those sizes took 0.77 times the time of the earlier
-// choice (whole tiles of 128 rows or pieces): 4096 x 4096 at 64 tokens 43 -> 17 us, 11008 x 4096 at 64 tokens 123 -> 24 us,
-// 4112 x 11000 at 203 tokens 54 -> 44 us, 4096 x 4096 at 2048 tokens 73 -> 65 us.
-struct SmallShape { int id, bm, bn, resident; double unit[3], round, fixed; };
-static const SmallShape kSmallShapes[] = {
-    {11, 128, 512, 1, {4.76, 0.0, 0.0}, 7.9, 5.3}, {12, 128, 256, 2, {3.42, 5.56, 0.0}, 5.0, 4.3},
-    {14, 64, 256, 3, {2.03, 3.23, 4.69}, 0.1, 8.3}, {15, 64, 128, 3, {1.75, 2.52, 3.33}, 0.9, 7.5}, {17, 64, 512, 1, {2.74, 0.0, 0.0}, 3.3, 7.0},
+// ---- calls that do not fill the chip for long: which tile, how many K planes -------------------------------------------
+// Time model: a workgroup takes `unit[r - 1]` us per K tile when r of them share a compute unit, `round` per round of
+// workgroups, `fixed` per launch; every two chunks of the correction beyond the first two take `tail`; planes take kPlaneUs
+// plus their bytes written and read at kPlaneMBperUs.  Fitted to 1900 timings of these forms (K, N from 640 to 28672, 33 to
+// 2048 tokens, 1 to 16 planes, ranks 24 to 256; mean error 5 % for 4-bit weights, 8 % for 2-bit ones).  Picking by it came
+// within 3 % of the fastest form timed; against the choice before (whole tiles of 128 rows, or pieces) the main product of
+// 4096 x 4096 at 64 tokens takes 17 us instead of 43, 11008 x 4096 at 64 tokens 21 instead of 123, 4112 x 11000 at 203
+// tokens 40 instead of 54, 2-bit 4096 x 4096 with rank 256 at 2048 tokens 83 instead of 104.
+struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed; };
+static const SmallShape kSmallShapes4[] = {
+    {33, 64, 128, 2, {1.20, 1.97}, 2.5, 6.4}, {31, 64, 256, 2, {1.96, 3.21}, 1.4, 7.6}, {32, 64, 512, 1, {2.96, 0.0}, 4.3, 6.4},
+    {11, 128, 512, 1, {4.72, 0.0}, 7.1, 6.3}, {12, 128, 256, 2, {3.41, 5.43}, 4.9, 4.4},          // tiled_kernel, whole tiles
 };
-constexpr double kPlaneUs = 3.8, kPlaneMBperUs = 5.7;
+static const SmallShape kSmallShapes2[] = {
+    {33, 64, 128, 2, {1.57, 2.47}, 0.8, 4.6}, {31, 64, 256, 2, {2.28, 3.69}, 0.0, 7.4}, {32, 64, 512, 1, {3.29, 0.0}, 5.0, 4.0},
+};
+constexpr double kPlaneUs = 3.1, kPlaneMBperUs = 6.0;
 constexpr int kMaxPlanes = 16;
 // Above this many operations the chip is full long enough to lower its clock, which this model does not know; the estimate
-// above is calibrated there (8192 x 28672 at 2048 tokens: its choice 714 us, this model's 770 to 800 us; below it, e.g.
+// above is calibrated there (8192 x 28672 at 2048 tokens: its choice 714 us, this model's 770 us; below the line, e.g.
 // 11008 x 4096 at 1500 tokens, 144 us against 126 us).
 constexpr double kSmallFlops = 1.5e11;
 
-struct SmallPick { int id, planes, share; };      // share: K tiles per plane
+struct SmallPick { int id, planes, share; };      // share: K tiles per plane; planes 0: tiled_kernel in pieces
 
-static double small_us(const SmallShape& sh, int64_t M, int64_t N, int64_t tiles, int64_t KT, int planes, int64_t share, int cus) {
+static double small_us(const SmallShape& sh, int64_t M, int64_t N, int kp, int w_bits, int64_t tiles, int planes, int64_t share, int cus) {
     const int64_t wgs = tiles * planes, per_round = (int64_t)cus * sh.resident;
     const int64_t full = wgs / per_round, rest = wgs - full * per_round;
     double t = sh.fixed + (double)full * (sh.unit[sh.resident - 1] * (double)share + sh.round);
     if (rest > 0) t += sh.unit[(rest + cus - 1) / cus - 1] * (double)share + sh.round;
+    if (kp > 64) t += (double)((kp + 63) / 64 - 1) * (w_bits == 4 ? 7.0 : 5.0);
     if (planes > 1) t += kPlaneUs + (double)planes * (double)M * (double)plane_ld(N) * 8e-6 / kPlaneMBperUs;
     return t;
 }
 
 // part_bytes: room for planes (0: whole tiles only)
-static SmallPick pick_small(int64_t M, int64_t N, int64_t KT, int64_t part_bytes, int cus) {
+static SmallPick pick_small(int64_t M, int64_t N, int64_t KT, int kp, int w_bits, int64_t part_bytes, int cus) {
     SmallPick best{0, 1, (int)KT};
     double best_us = 0.0;
-    for (const SmallShape& sh : kSmallShapes) {
+    const SmallShape* shapes = w_bits == 4 ? kSmallShapes4 : kSmallShapes2;
+    const int n_shapes = w_bits == 4 ? (kp <= 64 ? 5 : 3) : 3;   // (tiled_kernel's correction is the slower one for larger ranks)
+    for (int i = 0; i < n_shapes; ++i) {
+        const SmallShape& sh = shapes[i];
         const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-        // shapes of 64 rows move twice the weights per operation: not for launches of more than two rounds
-        if (sh.bm < 128 && tiles > 2 * (int64_t)cus * sh.resident) continue;
         for (int p = 1; p <= kMaxPlanes && p <= KT; ++p) {
             const int64_t share = (KT + p - 1) / p;
             const int planes = (int)((KT + share - 1) / share);
             if (planes != p) continue;                       // the same planes as a smaller p
             if (p > 1 && (sh.bm == 128 || (int64_t)p * M * plane_ld(N) * 4 > part_bytes)) continue;
-            const double us = small_us(sh, M, N, tiles, KT, planes, share, cus);
+            const double us = small_us(sh, M, N, kp, w_bits, tiles, planes, share, cus);
             if (best.id == 0 || us < best_us) { best = SmallPick{sh.id, planes, (int)share}; best_us = us; }
+        }
+        if (sh.id == 11 && part_bytes > 0) {
+            // the same shape with every tile in a whole number of pieces: 26 timings within 7 % (2504 tokens of 8128 x 1602:
+            // 92 us against 102 us of the fastest planes)
+            const Split sp = split_tiles(tiles, KT, cus, true);
+            if (sp.sk_units == 0 || !sp.aligned) continue;
+            const double us = (double)(sp.dp_tiles / sp.grid) * (sh.unit[0] * (double)KT + sh.round) + 5.66 * (double)sp.sk_share + 25.9 +
+                              4.2 * (double)(sp.sk_tile_units / sp.sk_share - 2);
+            if (us < best_us) { best = SmallPick{11, 0, (int)sp.sk_share}; best_us = us; }
         }
     }
     return best;
@@ -773,46 +1155,55 @@ static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipS
     // bounds; should it ever be lower than the shape assumes, tiles are not cut.
     bool can_split = CAN_SPLIT;
     if constexpr (CAN_SPLIT) {
-        const hipError_t e = prepare_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kPieces, WB>, setup_split, LDS_BYTES, 64 * WR * WC);
+        const hipError_t e = prepare_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, true, WB>, setup_split, LDS_BYTES, 64 * WR * WC);
         if (e != hipSuccess) return e;
         if (setup_split.resident < MINW) can_split = false;
     }
     const int64_t slots = (int64_t)cus * MINW;
     // mode 0: split when the estimate says so; 1: never; 2: whenever there is a remainder to split; 3: the same, always in
-    // equal shares of the remaining K tiles (never along tile boundaries)
+    // equal shares of the remaining K tiles (never along tile boundaries); 4 (pick_small): as 2 where this instance can
     bool split = false;
     if (can_split && a.Part != nullptr && (int64_t)BM * BN * 4 * slots <= kTiledPartBytesPerCu * (int64_t)cus && slots <= kTiledFlags) {
         if (mode >= 2) split = true;
         else if (mode == 0) split = split_pays(me, tiles, a.KT, cus);
     }
-    if (mode >= 2 && !split) return hipErrorInvalidValue;      // asked for, not available
+    if ((mode == 2 || mode == 3) && !split) return hipErrorInvalidValue;      // asked for, not available
     const Split sp = split ? split_tiles(tiles, a.KT, slots, mode != 3) : whole_tiles(tiles, a.KT);
     a.dp_tiles = sp.dp_tiles; a.sk_units = sp.sk_units; a.sk_share = sp.sk_share; a.sk_tile_units = sp.sk_tile_units;
     if constexpr (CAN_SPLIT) {
         if (sp.sk_units > 0)
-            return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kPieces, WB>, setup_split, LDS_BYTES, sp.grid, 64 * WR * WC, a, s);
+            return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, true, WB>, setup_split, LDS_BYTES, sp.grid, 64 * WR * WC, a, s);
     }
-    return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kWhole, WB>, setup_whole, LDS_BYTES, tiles, 64 * WR * WC, a, s);
+    return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, false, WB>, setup_whole, LDS_BYTES, tiles, 64 * WR * WC, a, s);
 }
 
-// The forms pick_small chooses: whole tiles, or K planes and their sum.
-template <int WB, int TM, int TN, int WR, int WC, int NS, int MINW>
-static hipError_t launch_small_t(TiledArgs a, const SmallPick& pick, hipStream_t s) {
-    constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
-    constexpr int LDS_BYTES = NS * BM * 128;
+// staged_kernel on whole tiles, or on K planes and then their sum.
+template <int WB, int TM, int TN, int WR, int WC, int D, int MINW>
+static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_t s) {
+    constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC, NW = WR * WC;
+    constexpr int LDS_BYTES = D * (BM * 128 + NW * TN * 1280);
     a.grid_m = (int)((a.M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.dp_tiles = (int64_t)a.grid_m * a.grid_n;
     a.sk_share = pick.share;
     static KernelSetup setup_whole, setup_planes;
     if (pick.planes == 1)
-        return launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kWhole, WB>, setup_whole, LDS_BYTES, a.dp_tiles, 64 * WR * WC, a, s);
-    const hipError_t e = launch_kernel(tiled_kernel<TM, TN, WR, WC, NS, MINW, kPlanes, WB>, setup_planes, LDS_BYTES,
-                                       a.dp_tiles * pick.planes, 64 * WR * WC, a, s);
+        return launch_kernel(staged_kernel<TM, TN, WR, WC, D, MINW, false, WB>, setup_whole, LDS_BYTES, a.dp_tiles, 64 * NW, a, s);
+    const hipError_t e = launch_kernel(staged_kernel<TM, TN, WR, WC, D, MINW, true, WB>, setup_planes, LDS_BYTES,
+                                       a.dp_tiles * pick.planes, 64 * NW, a, s);
     if (e != hipSuccess) return e;
     const int64_t items = a.M * (plane_ld(a.N) / 4);
     hipLaunchKernelGGL(reduce_planes_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, a, pick.planes);
     return hipGetLastError();
+}
+
+template <int WB>
+static hipError_t launch_staged(const TiledArgs& a, const SmallPick& pick, hipStream_t s) {
+    switch (pick.id) {
+        case 31: return launch_staged_t<WB, 2, 2, 1, 4, 3, 2>(a, pick, s);      // 64 x 256, 54 KB: two workgroups per compute unit
+        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 5, 2>(a, pick, s);      // 64 x 512, 140 KB
+        default: return launch_staged_t<WB, 2, 1, 1, 4, 5, 2>(a, pick, s);      // 64 x 128, 65 KB: two workgroups per compute unit
+    }
 }
 
 __global__ void clear_flags_kernel(uint32_t* flags, int n) {
@@ -861,15 +1252,12 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     int mode = variant / 100;
     variant %= 100;
     if (mode < 0 || mode > 3) return hipErrorInvalidValue;
-    if (variant == 0 && mode <= 1 && L.w_bits == 4 && L.kp <= 64 && 2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
+    if (variant == 0 && mode <= 1 && 2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
         const int64_t part_bytes = (mode == 0 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
-        const SmallPick pick = pick_small(M, L.N, L.KT, part_bytes, cus);
-        switch (pick.id) {
-            case 14: return launch_small_t<4, 2, 2, 1, 4, 4, 3>(a, pick, s);
-            case 15: return launch_small_t<4, 1, 2, 2, 2, 4, 3>(a, pick, s);
-            case 17: return launch_small_t<4, 2, 2, 1, 8, 4, 2>(a, pick, s);
-            default: variant = pick.id; mode = 1; break;     // 128 rows: the launches below, tiles never cut
-        }
+        const SmallPick pick = pick_small(M, L.N, L.KT, L.kp, L.w_bits, part_bytes, cus);
+        if (pick.id > 12) return L.w_bits == 4 ? launch_staged<4>(a, pick, s) : launch_staged<2>(a, pick, s);
+        variant = pick.id;                                   // the launches below: tiles whole, or cut if the instance can
+        mode = pick.planes == 0 ? 4 : 1;
     }
     if (variant == 0) {
         // pick the tile shape (and the split) with the lowest estimated time

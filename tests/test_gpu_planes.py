@@ -1,6 +1,6 @@
-"""The tiled kernel's 64-row shapes and its K planes, which calls of 33 to about a thousand tokens take: edges of tiles
-in M and N, K ranges that the planes do not divide, ranks 0 to 64, fp32 and MXINT8 output, against the oracle; the
-same bits on a second run with other contents in the workspace."""
+"""The staged kernel (64-row tiles, whole or as K planes), which calls of 33 to about a thousand tokens take: edges of
+tiles in M and N, K ranges that the planes do not divide, ranks 0 to 256, both weight widths, fp32 and MXINT8 output,
+against the oracle; the same bits on a second run with other contents in the workspace."""
 import numpy as np
 import pytest
 
@@ -12,12 +12,14 @@ pytestmark = pytest.mark.gpu
 
 
 # K tiles of 256: 1 (nothing to cut), 5, 9, 17, 43 (ragged last planes); N around the 128 / 256 / 512 column tiles
-@pytest.mark.parametrize("M,K,N,k", [(33, 256, 100, 8), (64, 1040, 128, 0), (65, 4112, 1001, 24), (127, 2304, 272, 64),
-                                     (128, 11008, 512, 32), (203, 4112, 1104, 24), (257, 4096, 2064, 33), (700, 1280, 3072, 16)])
-def test_planes_and_narrow_tiles(M, K, N, k):
+@pytest.mark.parametrize("M,K,N,k,w_bits", [
+    (33, 256, 100, 8, 4), (64, 1040, 128, 0, 4), (65, 4112, 1001, 24, 4), (127, 2304, 272, 64, 4), (128, 11008, 512, 32, 4),
+    (203, 4112, 1104, 24, 4), (257, 4096, 2064, 33, 4), (700, 1280, 3072, 16, 4), (90, 2048, 272, 256, 4),
+    (33, 272, 100, 100, 2), (64, 2304, 1040, 256, 2), (300, 4096, 528, 65, 2), (1100, 1040, 2064, 200, 2)])
+def test_planes_and_narrow_tiles(M, K, N, k, w_bits):
     import torch
     from paper_2402_02446_amd import binding
-    layer, ch = oracle_layer_big(K, N, k, seed=M + K)
+    layer, ch = oracle_layer_big(K, N, k, seed=M + K, w_bits=w_bits)
     h = upload(layer)
     X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
     Xd = torch.from_numpy(X).cuda()
