@@ -24,12 +24,12 @@ struct IntGemmArgs {
     int64_t g_per_z;
     int64_t out_z_stride;
     const float* T; int64_t ldt;
-    int S; int64_t t_stride;
     const uint8_t* Bt; const float* Bsc;
     int kp16;
     int tail_plane;
 };
-hipError_t launch_int_gemm(bool projection, const IntGemmArgs& a, hipStream_t s);
+hipError_t launch_int_projection(const IntGemmArgs& a, hipStream_t s);
+hipError_t launch_int_main(const IntGemmArgs& a, hipStream_t s);
 hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_stride, int64_t M, int64_t N, int64_t ldp,
                                     float* Y, int64_t ldy, hipStream_t s);
 
@@ -102,9 +102,24 @@ static int main_planes(const Layer& L, int64_t M) {
     return (int)((G + g - 1) / g);
 }
 
+// Few tokens take the two launches of kernels_int_few.hip, 32 tokens per workgroup: one block of them always, more as long
+// as the work is small (blocks x column groups x K groups; us, this form against the general one): 4096 x 4096 at 128 tokens
+// (16384) 26 against 34, 11008 x 4096 at 64 (22016) 38 against 42, at 100 (33024) 54 against 45.
+static bool few_tokens(const Layer& L, int64_t M) { return M <= 32 || (M <= 128 && ((M + 31) / 32) * L.N32 * (L.K / 128) <= 24576); }
+
+// K groups per slice of its projection: eight slices, and at most seven groups (28 KB of codes beside 32 KB of sums) each
+static int few_slice_groups(const Layer& L) {
+    const int64_t G = L.K / 128, per = (G + 7) / 8;
+    return (int)(per < 7 ? per : 7);
+}
+
 size_t int_workspace_bytes(const Layer& L, int64_t M) {
     if (M <= 0) return 0;
     const int64_t mp = round_up(M, 128);
+    if (few_tokens(L, M)) {
+        const int64_t S = (L.K / 128 + few_slice_groups(L) - 1) / few_slice_groups(L);
+        return (size_t)(round_up(round_up(M, 32) * L.K, 256) + round_up(mp * 4, 256) + round_up(S * M * (int64_t)L.kp32 * 32 * 4, 256));
+    }
     const int sm = main_planes(L, M);
     return (size_t)(round_up(mp * L.K, 256) + round_up(mp * 4, 256) +
                     round_up((int64_t)projection_planes(L, M) * mp * (int64_t)L.kp32 * 32 * 4, 256) +
@@ -115,6 +130,20 @@ int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y
                 hipStream_t s) {
     if (int_workspace_bytes(L, M) > ws_bytes) return LQER_ERR_WORKSPACE;
     const int64_t mp = round_up(M, 128);
+    if (few_tokens(L, M)) {
+        IntFewArgs f;
+        f.X = X; f.ldx = ldx; f.M = M; f.K = L.K; f.N = L.N; f.N32 = L.N32; f.G = L.K / 128;
+        f.Xc = (uint8_t*)ws;
+        f.lr = M <= 4 ? 2 : (M <= 16 ? 4 : 5);
+        f.Xs = (float*)((uint8_t*)ws + round_up(round_up(M, 32) * L.K, 256));
+        f.T = (float*)((uint8_t*)f.Xs + round_up(mp * 4, 256));
+        f.slice_groups = few_slice_groups(L);
+        f.S = (int)((f.G + f.slice_groups - 1) / f.slice_groups);
+        f.At = L.At; f.Asc = L.Asc; f.kp32 = L.kp32;
+        f.Wt = L.Wt; f.Wsc = L.Wsc; f.Bt = L.Bt; f.Bsc = L.Bsc; f.kp16 = L.kp16;
+        f.Y = Y; f.ldy = ldy;
+        return launch_int_few(f, s) == hipSuccess ? LQER_OK : LQER_ERR_HIP;
+    }
     int8_t* Xc = (int8_t*)ws;
     float* Xs = (float*)((uint8_t*)ws + round_up(mp * L.K, 256));
     float* T = (float*)((uint8_t*)Xs + round_up(mp * 4, 256));
@@ -124,16 +153,15 @@ int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y
     a.Xc = Xc; a.ldxc = L.K; a.Xs = Xs; a.G = L.K / 128; a.M = M;
     const int S = projection_planes(L, M);
     a.T = nullptr; a.ldt = ldt; a.Bt = nullptr; a.Bsc = nullptr; a.kp16 = 0;
-    a.S = S; a.t_stride = mp * ldt; a.tail_plane = 0;
+    a.tail_plane = 0;
     if (L.kp > 0) {
         a.Wt = L.At; a.Wsc = L.Asc; a.N = ldt; a.N32 = L.kp32; a.Out = T; a.ldo = ldt;
         a.g_per_z = (a.G + S - 1) / S; a.out_z_stride = mp * ldt;
-        if (launch_int_gemm(true, a, s) != hipSuccess) return LQER_ERR_HIP;
+        if (launch_int_projection(a, s) != hipSuccess) return LQER_ERR_HIP;
         const int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z);
         // the planes' partial T are added up (in plane order, into the first) before the main kernel reads them: inside
         // it that sum would be a chain of dependent loads in front of every rank block
         if (planes > 1 && launch_int_reduce_planes(T, planes, mp * ldt, mp, ldt, ldt, T, ldt, s) != hipSuccess) return LQER_ERR_HIP;
-        a.S = 1;
     }
     a.Wt = L.Wt; a.Wsc = L.Wsc; a.N = L.N; a.N32 = L.N32; a.Out = Y; a.ldo = ldy;
     a.g_per_z = a.G; a.out_z_stride = 0;
@@ -143,13 +171,13 @@ int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y
         float* P = (float*)((uint8_t*)T + round_up((int64_t)S * mp * ldt * 4, 256));
         const int64_t ldp = round_up(L.N, 4);
         a.Out = P; a.ldo = ldp; a.g_per_z = (a.G + sm - 1) / sm; a.out_z_stride = M * ldp;
-        a.tail_plane = L.kp > 0 ? 1 : 0;
-        if (launch_int_gemm(false, a, s) != hipSuccess) return LQER_ERR_HIP;
-        const int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z) + a.tail_plane;
+        int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z);
+        if (L.kp > 0) a.tail_plane = planes++;
+        if (launch_int_main(a, s) != hipSuccess) return LQER_ERR_HIP;
         if (launch_int_reduce_planes(P, planes, M * ldp, M, L.N, ldp, Y, ldy, s) != hipSuccess) return LQER_ERR_HIP;
         return LQER_OK;
     }
-    if (launch_int_gemm(false, a, s) != hipSuccess) return LQER_ERR_HIP;
+    if (launch_int_main(a, s) != hipSuccess) return LQER_ERR_HIP;
     return LQER_OK;
 }
 

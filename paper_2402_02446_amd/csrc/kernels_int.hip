@@ -6,11 +6,10 @@
 // the int8 matrix cores (32x32x32, exact in i32) and every group's sum is converted and scaled once, in fp32.
 //
 //   quant_token_kernel   per-token INT8 quantizer (one workgroup per token row: row maximum, then codes)
-//   int_gemm_kernel      128 tokens x 128 columns per workgroup, four wavefronts of 64 x 64; one K group per step:
-//                        activation codes and the group's 128 scales through double-buffered LDS (the tile XOR-swizzled),
-//                        packed weights straight into registers, all asked for one group ahead at the top of the step.  <4, true>: the main product with the rank-k correction
-//                        (T_hi | T_lo against B_k's codes on the bf16 matrix cores, one scale per column) in the
-//                        epilogue; <8, false>: the projection T = X_q A_k, A_k as 8-bit "weights".
+//   int_main_kernel      the main product with the rank-k correction (T_hi | T_lo against B_k's codes on the bf16 matrix
+//                        cores, one scale per column) in the epilogue; operands by direct-to-LDS loads
+//   int_gemm_kernel      the projection T = X_q A_k, A_k as 8-bit "weights": 128 tokens x 128 ranks per workgroup, four
+//                        wavefronts of 64 x 64, one K group per step, all of it asked for one group ahead
 //
 // Weight codes keep their canonical nibbles: of a 32-bit word (8 elements) `(w << 4) & 0xF0F0F0F0` are the even
 // elements times 16 as int8 and `w & 0xF0F0F0F0` the odd ones - two instructions per 8 weights; the factor 16 is
@@ -92,20 +91,18 @@ struct IntGemmArgs {
     const float* Wsc;                    // scales [N32][G][32] (4 bits: already divided by 16)
     int64_t M, N, N32, G;
     float* Out; int64_t ldo;             // Y [M][ldo], or T [S][rows padded][ldo] for the projection
-    int64_t g_per_z;                     // K groups per plane of grid.z (the projection splits K over S planes; G otherwise)
+    int64_t g_per_z;                     // K groups per plane of workgroups
     int64_t out_z_stride;                // floats between the planes' outputs
-    // rank-k correction (TAIL)
-    const float* T; int64_t ldt;         // [S][rows padded][ldt] fp32 partial sums of T, added in plane order
-    int S; int64_t t_stride;
+    // rank-k correction
+    const float* T; int64_t ldt;         // [rows padded][ldt] fp32
     const uint8_t* Bt; const float* Bsc; // B_k records [N32][kp16][kBRecordBytes], scales [N32 * 32]
     int kp16;
-    int tail_plane;                      // 1: grid.z has one more plane than K planes, which computes only the correction
+    int tail_plane;                      // plane that adds the correction: 0, or one of its own behind the K planes
 };
 
-template <int WB, bool TAIL>
 __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
     constexpr int TM = 2, TN = 2;
-    constexpr int NL = (WB == 4) ? 2 : 4;            // 16-byte loads per lane, column group and K group
+    constexpr int NL = 4;                            // 16-byte loads per lane, column group and K group
     constexpr int REC = NL * 1024;
     __shared__ __attribute__((aligned(1024))) uint8_t xs[2][128 * 128];
     __shared__ __attribute__((aligned(16))) float ss[2][128];      // the K group's scales of the tile's 128 columns
@@ -167,9 +164,8 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
     for (int tm = 0; tm < TM; ++tm) st[tm] = a.Xs[m0 + wr * 64 + tm * 32 + t];
 
     // this workgroup's K groups [gb, ge)
-    const bool tail_only = TAIL && a.tail_plane && blockIdx.z + 1 == gridDim.z;    // (its range is empty: acc stays zero)
-    const int64_t gb = tail_only ? 0 : (int64_t)blockIdx.z * a.g_per_z;
-    const int64_t ge = tail_only ? 0 : (gb + a.g_per_z < a.G ? gb + a.g_per_z : a.G);
+    const int64_t gb = (int64_t)blockIdx.z * a.g_per_z;
+    const int64_t ge = gb + a.g_per_z < a.G ? gb + a.g_per_z : a.G;
     WSet w0, w1;
     XStage stx;
     fetch_x(stx, gb);
@@ -198,14 +194,7 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
             for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
-                    i32x4 wv;
-                    if constexpr (WB == 4) {
-                        const u32x4 c = cur.c[tn][sp];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) wv[e] = (int)((p == 0 ? c[e] << 4 : c[e]) & 0xF0F0F0F0u);
-                    } else {
-                        wv = __builtin_bit_cast(i32x4, cur.c[tn][2 * sp + p]);
-                    }
+                    const i32x4 wv = __builtin_bit_cast(i32x4, cur.c[tn][2 * sp + p]);
 #pragma unroll
                     for (int tm = 0; tm < TM; ++tm) {
                         if (sp == 0 && p == 0) {
@@ -250,91 +239,16 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
         if (g + 1 < ge) step(w1, w0, g + 1);
     }
 
-    // ---- epilogue: token scale, rank-k correction, store ----------------------------------------------------------
+    // ---- epilogue: token scale, store (padded rows too: the main kernel reads them) ----------------------------------------------------------
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[tm][tn][r] *= st[tm];
-    if constexpr (TAIL) {
-        if (a.kp16 > 0 && (a.tail_plane ? tail_only : blockIdx.z == 0)) {
-            f32x16 ta[TM][TN];
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) ta[tm][tn][r] = 0.f;
-            // one 32x32x16 step per rank block and bf16 term: lane half hh takes ranks 8 hh .. + 7 of the block on both sides
-            for (int rb = 0; rb < a.kp16; ++rb) {
-                Frag bf[TN];
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    const uint8_t* rec = a.Bt + (group_of(tn) * a.kp16 + rb) * kBRecordBytes;
-                    const u32x4 cw = *reinterpret_cast<const u32x4*>(rec + t * 16);
-                    Frag f0, f1;
-                    int8x16_to_frags(cw, 1.0f, f0, f1);
-                    bf[tn] = hh ? f1 : f0;
-                }
-#pragma unroll
-                for (int tm = 0; tm < TM; ++tm) {
-                    const float* src = a.T + (m0 + wr * 64 + tm * 32 + t) * a.ldt + rb * 16 + 8 * hh;
-                    f32x4 p0 = *reinterpret_cast<const f32x4*>(src), p1 = *reinterpret_cast<const f32x4*>(src + 4);
-                    for (int z0 = 1; z0 < a.S; z0 += 8) {                // the projection's K planes, in plane order;
-                        f32x4 q[8][2];                                   // eight planes' loads in flight at a time
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const int z = z0 + j < a.S ? z0 + j : a.S - 1;
-                            q[j][0] = *reinterpret_cast<const f32x4*>(src + z * a.t_stride);
-                            q[j][1] = *reinterpret_cast<const f32x4*>(src + z * a.t_stride + 4);
-                        }
-#pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            if (z0 + j < a.S) {
-                                p0 += q[j][0];
-                                p1 += q[j][1];
-                            }
-                    }
-                    const float v[8] = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
-                    Frag hi, lo;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        uint32_t h2[2], l2[2];
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const uint32_t hb = f32_bits(v[2 * e + j]) & 0xFFFF0000u;
-                            h2[j] = hb >> 16;
-                            l2[j] = f32_bits(v[2 * e + j] - f32_from_bits(hb)) >> 16;
-                        }
-                        hi.u[e] = h2[0] | (h2[1] << 16);
-                        lo.u[e] = l2[0] | (l2[1] << 16);
-                    }
-#pragma unroll
-                    for (int tn = 0; tn < TN; ++tn) {
-                        ta[tm][tn] = mfma32(bf[tn].v, hi.v, ta[tm][tn]);
-                        ta[tm][tn] = mfma32(bf[tn].v, lo.v, ta[tm][tn]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                const float* s = a.Bsc + group_of(tn) * 32 + 4 * hh;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 sb = *reinterpret_cast<const f32x4*>(s + 8 * q);
-#pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) acc[tm][tn][4 * q + j] += ta[tm][tn][4 * q + j] * sb[j];
-                }
-            }
-        }
-    }
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = m0 + wr * 64 + tm * 32 + t;
-        if (TAIL && row >= a.M) continue;            // (the projection writes its padded rows too: the tail reads them)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
             const int64_t cg = g0 + tn;
@@ -352,6 +266,228 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
                         if (n + j < a.N) dst[j] = v[j];
                 }
             }
+        }
+    }
+}
+
+// ---- the main product ----------------------------------------------------------------------------------------------
+// Y = s_t sum_g sW I_W + T B_k on 128 tokens x 128 columns per workgroup, four wavefronts of 128 x 32, one K group of 128
+// at a time.  Beside the int8 matrix pipe (16 MFMAs of 32 cycles a group and wavefront) it is bound by vector
+// instructions: converting and scaling the group's exact sums costs two per accumulator register, 128 a group (the FP16
+// group scales leave no way round it), the nibbles' expansion 24.  A loop of just these, two wavefronts on a SIMD, takes
+// 0.90 us a group against 0.67 us of its MFMAs alone (at the clock each of them sustains).  So
+//   * activations, nibbles and scales reach LDS by direct loads two groups ahead (three stages of 25 KB, two workgroups on
+//     a compute unit), counted by the kernel itself: no registers, no address arithmetic per load;
+//   * a wavefront owns all 128 tokens of 32 columns, so a nibble is expanded once per workgroup;
+//   * tokens are the rows and columns the lanes of the MFMA's result: a lane needs one scale per group;
+//   * the sums of two 32 x 32 tiles are folded beside the MFMAs of the other two, laced instruction by instruction.
+// Whole calls, before -> after: 2048 tokens of 4096 x 11008 197 -> 173 us, of 11008 x 4096 193 -> 167 us, 65536 tokens of
+// 4096 x 4096 1914 -> 1744 us.  Left out one at a time, the loads cost 8 % of the time, the folding 12 %, the LDS reads 22 %,
+// three quarters of the MFMAs 24 %: what is left is the phases of a group waiting for each other.
+constexpr int kIntStages = 3, kIntStage = 128 * 128 + 4 * (2048 + 256);
+
+__global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
+    constexpr int NW = 4, BN = 32 * NW, WOFF = 128 * 128, SOFF = WOFF + NW * 2048;
+    constexpr int XL = 16 / NW, L = XL + 3;          // loads per wavefront and group: 4 activations, 2 nibbles, 1 scales
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = lane & 31, hh = lane >> 5;
+
+    // workgroup -> K plane and output tile: consecutive positions land on one XCD and walk bands of eight tile rows
+    const int grid_n = (int)((a.N + BN - 1) / BN), grid_m = (int)((a.M + 127) / 128);
+    int lin;
+    {
+        const int nwg = gridDim.x, pid = blockIdx.x;
+        const int xcd = pid & 7, local = pid >> 3, per = nwg >> 3, rem = nwg & 7;
+        lin = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
+    }
+    const int plane = lin / (grid_m * grid_n);
+    lin -= plane * (grid_m * grid_n);
+    int tile_m, tile_n;
+    {
+        const int width = 8 * grid_n, grp = lin / width, in = lin - grp * width, first_m = grp * 8;
+        const int gsize = (grid_m - first_m < 8) ? grid_m - first_m : 8;
+        tile_m = first_m + in % gsize;
+        tile_n = in / gsize;
+    }
+    const int64_t m0 = (int64_t)tile_m * 128;
+    const int64_t cg = (int64_t)tile_n * NW + wave, cgc = cg < a.N32 ? cg : a.N32 - 1;   // this wavefront's column group (the store is masked)
+    const int gb = plane * (int)a.g_per_z;                         // K groups [gb, gb + count)
+    const int count = gb + (int)a.g_per_z < (int)a.G ? (int)a.g_per_z : (gb < (int)a.G ? (int)a.G - gb : 0);   // (0: a plane for the correction only)
+
+    // ---- loads: activations 8 rows each (cells XOR-swizzled by row), codes and scales of the wavefront's column group
+    uint32_t x_off[XL];
+#pragma unroll
+    for (int j = 0; j < XL; ++j)
+        x_off[j] = (uint32_t)((8 * (NW * j + wave) + (lane >> 3)) * (int)a.ldxc) +
+                   (((uint32_t)(lane & 7) ^ (uint32_t)(((wave & 1) * 4 + (lane >> 4)) & 7)) << 4);
+    const uint32_t w_off = lane * 16;
+    const uint32_t s_off = t * 4;                    // (both lane halves bring the same 32 scales)
+    const uint8_t* x_ptr = reinterpret_cast<const uint8_t*>(a.Xc + m0 * a.ldxc + (int64_t)gb * 128);
+    const uint8_t* w_ptr = a.Wt + (cgc * a.G + gb) * 2048;
+    const uint8_t* s_ptr = reinterpret_cast<const uint8_t*>(a.Wsc + (cgc * a.G + gb) * 32);
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds);
+    auto issue = [&](uint32_t stage) {               // the next group -> the stage at that byte offset
+        const uint32_t at_x = lds0 + stage + wave * 1024, at_w = lds0 + stage + wave * 2048, at_s = lds0 + stage + wave * 256;
+        lds_dma16<0>(at_x, x_off[0], x_ptr);
+        lds_dma16<NW * 1024>(at_x, x_off[1], x_ptr);
+        lds_dma16<2 * NW * 1024>(at_x, x_off[2], x_ptr);
+        lds_dma16<3 * NW * 1024>(at_x, x_off[3], x_ptr);
+        lds_dma16<WOFF>(at_w, w_off, w_ptr);
+        lds_dma16<WOFF + 1024>(at_w, w_off, w_ptr + 1024);
+        lds_dma4<SOFF>(at_s, s_off, s_ptr);
+        x_ptr += 128;
+        w_ptr += 2048;
+        s_ptr += 128;
+    };
+
+    // ---- operands: MFMA (sp, p) of a group uses bytes 64 sp + 32 hh + 16 p .. + 15 of the token's 128: cell 4 sp + 2 hh + p
+    int rd_x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rd_x[q] = t * 128 + (((4 * (q >> 1) + 2 * hh + (q & 1)) ^ ((t >> 1) & 7)) << 4);
+    const int rd_w = WOFF + wave * 2048 + lane * 16, rd_s = SOFF + wave * 256 + t * 4;
+
+    f32x16 acc[4];                                   // [tm]: register r = token 8 (r / 4) + 4 hh + r % 4, lane t = column
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    i32x16 pend[2];                                  // sums of tiles 2 and 3 of the group before, not folded yet
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pend[i][r] = 0;
+    float pend_sc = 0.f;
+    auto fold = [&](f32x16& c, const i32x16& i, float s) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) c[r] += (float)i[r] * s;
+    };
+    // the 128 products of two tiles, one K quarter after the other
+    auto products = [&](i32x16 (&s)[2], const i32x4 (&x)[2][4], const i32x4 (&w)[4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                i32x16 z;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = 0;
+                s[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(x[i][q], w[q], q == 0 ? z : s[i], 0, 0, 0);
+            }
+    };
+    auto expand = [&](i32x4 (&w)[4], const u32x4 (&c)[2]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[q][e] = (int)(((q & 1) ? c[q >> 1][e] : c[q >> 1][e] << 4) & 0xF0F0F0F0u);
+    };
+    auto group = [&](const uint8_t* st) {
+        u32x4 cw[2];
+        i32x4 x0[2][4], x1[2][4], w[4];
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp) cw[sp] = *reinterpret_cast<const u32x4*>(st + rd_w + sp * 1024);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) x0[i][q] = *reinterpret_cast<const i32x4*>(st + rd_x[q] + i * 4096);
+        const float sc = *reinterpret_cast<const float*>(st + rd_s);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) x1[i][q] = *reinterpret_cast<const i32x4*>(st + rd_x[q] + (2 + i) * 4096);
+        __builtin_amdgcn_sched_barrier(0);
+        fold(acc[2], pend[0], pend_sc);              // while the reads are on their way
+        __builtin_amdgcn_sched_barrier(0);
+        // behind every MFMA a few vector instructions: the rest of the group before, then the first two tiles
+        i32x16 s[2];
+        expand(w, cw);
+        products(s, x0, w);
+        fold(acc[3], pend[1], pend_sc);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x2, 7, 0);
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        products(pend, x1, w);
+        fold(acc[0], s[0], sc);
+        fold(acc[1], s[1], sc);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        pend_sc = sc;
+    };
+    auto next_stage = [](uint32_t s) { return s + kIntStage == kIntStages * kIntStage ? 0u : s + kIntStage; };
+    if (count > 0) issue(0);
+    if (count > 1) issue(kIntStage);
+    uint32_t st = 0, st_in = 2 * kIntStage;
+    for (int g = 0; g < count; ++g) {
+        // group g has landed; the stage of group g - 1 has been read by everybody and takes group g + 2
+        if (g + 1 < count) staged_wait<L>();
+        else staged_wait<0>();
+        if (g + 2 < count) {
+            issue(st_in);
+            st_in = next_stage(st_in);
+        }
+        group(lds + st);
+        st = next_stage(st);
+    }
+    fold(acc[2], pend[0], pend_sc);
+    fold(acc[3], pend[1], pend_sc);
+
+    // ---- token scales, rank-k correction (by one plane), store --------------------------------------------------
+    const bool tail = a.kp16 > 0 && plane == a.tail_plane;
+    const int64_t n = cg * 32 + t;
+    const float sb = tail ? a.Bsc[cgc * 32 + t] : 0.f;
+    float* dst = a.Out + (int64_t)plane * a.out_z_stride + n;
+#pragma unroll
+    for (int tm = 0; tm < 4; ++tm) {
+        const int64_t row0 = m0 + tm * 32;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 s4 = *reinterpret_cast<const f32x4*>(a.Xs + row0 + 8 * q + 4 * hh);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[tm][4 * q + j] *= s4[j];
+        }
+        if (tail) {
+            // one 32x32x16 step per rank block and bf16 term of T: lane half hh takes ranks 8 hh .. + 7 of the block on both sides
+            f32x16 ta;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ta[r] = 0.f;
+            for (int rb = 0; rb < a.kp16; ++rb) {
+                const float* src = a.T + (row0 + t) * a.ldt + rb * 16 + 8 * hh;
+                const f32x4 p0 = *reinterpret_cast<const f32x4*>(src), p1 = *reinterpret_cast<const f32x4*>(src + 4);
+                const uint8_t* rec = a.Bt + (cgc * a.kp16 + rb) * kBRecordBytes;
+                Frag hi, lo, f0, f1;
+                int8x16_to_frags(*reinterpret_cast<const u32x4*>(rec + t * 16), 1.0f, f0, f1);
+                const Frag bf = hh ? f1 : f0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint32_t h2[2], l2[2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const float v = e < 2 ? p0[(2 * e + j) & 3] : p1[(2 * e + j) & 3];
+                        const uint32_t hb = f32_bits(v) & 0xFFFF0000u;
+                        h2[j] = hb >> 16;
+                        l2[j] = f32_bits(v - f32_from_bits(hb)) >> 16;
+                    }
+                    hi.u[e] = h2[0] | (h2[1] << 16);
+                    lo.u[e] = l2[0] | (l2[1] << 16);
+                }
+                ta = mfma32(hi.v, bf.v, ta);
+                ta = mfma32(lo.v, bf.v, ta);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[tm][r] += ta[r] * sb;
+        }
+        if (cg >= a.N32 || n >= a.N) continue;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t row = row0 + 8 * (r >> 2) + 4 * hh + (r & 3);
+            if (row < a.M) dst[row * a.ldo] = acc[tm][r];
         }
     }
 }
@@ -390,13 +526,29 @@ hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_st
     return hipGetLastError();
 }
 
-// Projection T = X_q A_k (Out = T, N = padded rank) or main product with the correction.
-hipError_t launch_int_gemm(bool projection, const IntGemmArgs& a, hipStream_t s) {
+// Projection T = X_q A_k: Out = T, N = padded rank.
+hipError_t launch_int_projection(const IntGemmArgs& a, hipStream_t s) {
     if (a.M == 0) return hipSuccess;
-    const unsigned planes = (unsigned)((a.G + a.g_per_z - 1) / a.g_per_z) + (projection ? 0u : (unsigned)a.tail_plane);
+    const unsigned planes = (unsigned)((a.G + a.g_per_z - 1) / a.g_per_z);
     const dim3 grid((unsigned)((a.N + 127) / 128), (unsigned)((a.M + 127) / 128), planes), block(256);
-    if (projection) hipLaunchKernelGGL((int_gemm_kernel<8, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((int_gemm_kernel<4, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL(int_gemm_kernel, grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+// Main product with the correction, in ceil(G / g_per_z) K planes (and one more where the correction has its own).
+hipError_t launch_int_main(const IntGemmArgs& a, hipStream_t s) {
+    if (a.M == 0) return hipSuccess;
+    constexpr int LDS_BYTES = kIntStages * kIntStage;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(int_main_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    int64_t planes = (a.G + a.g_per_z - 1) / a.g_per_z;
+    if (a.tail_plane >= planes) planes = a.tail_plane + 1;
+    const int64_t wgs = ((a.M + 127) / 128) * ((a.N + 127) / 128) * planes;
+    hipLaunchKernelGGL(int_main_kernel, dim3((unsigned)wgs), dim3(256), LDS_BYTES, s, a);
     return hipGetLastError();
 }
 

@@ -551,24 +551,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 // tiled_kernel's form of the same tile -> this one: 4112 x 11000 at 203 tokens 45 -> 40 us (512 TFLOP/s on 344
 // workgroups), 11008 x 4096 at 64 tokens 26 -> 20 us; 2-bit weights with rank 256, 4096 x 4096 at 2048 tokens
 // 104 -> 83 us, at 64 tokens 99 -> 31 us (there the correction: its operands are asked for in one go per two chunks).
-// 1 KiB (64 lanes x 16 bytes) or 256 B from `base` + this lane's byte offset to LDS address at + ADD + 16 (4) * lane.
-// Written as asm because the compiler answers its own builtin with a full drain of the loads in flight in front of every
-// LDS read; nothing is returned in registers, and the kernel counts these loads itself (staged_wait).  M0 has no other use.
-template <int ADD>
-__device__ __forceinline__ void lds_dma16(uint32_t at, uint32_t off, const uint8_t* base) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
-}
-template <int ADD>
-__device__ __forceinline__ void lds_dma4(uint32_t at, uint32_t off, const uint8_t* base) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
-}
-// All but this wavefront's newest `LEFT` loads have landed, its LDS reads have returned, and so have everybody's.
-template <int LEFT>
-__device__ __forceinline__ void staged_wait() {
-    static_assert(LEFT >= 0 && LEFT < 64, "a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
-}
-
 // D = stages of 64 K in LDS: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN] 1 KiB of codes
 // [wave][TN] 256 B of exponent words; chunk ch + D - 1 is asked for when chunk ch starts.
 template <int TM, int TN, int WR, int WC, int D, int MINW, bool PLANES, int WB>

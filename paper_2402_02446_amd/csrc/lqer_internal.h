@@ -178,6 +178,19 @@ int scale_from_magnitudes(const std::vector<double>& abar, std::vector<double>& 
 // ---- the scaled-integer variant (int_host.cpp, kernels_int.hip) ------------------------------------------------------
 hipError_t launch_quant_token(const float* X, int64_t rows, int64_t K, int64_t ldx, int8_t* codes, int64_t ldc,
                               float* scale_f32, uint16_t* scale_f16, bool perm, hipStream_t s);
+// The few-token form of the INT variant (kernels_int_few.hip).
+struct IntFewArgs {
+    const float* X; int64_t ldx;
+    int64_t M, K, N, N32, G;             // G = K / 128 groups
+    uint8_t* Xc; int lr;                 // codes [blocks of 32 tokens][K / 16][1 << lr token rows][16 B]
+    float* Xs;                           // [M] token scales
+    const uint8_t* At; const float* Asc; int kp32;
+    float* T; int S; int slice_groups;   // [S][M][kp32 * 32] partial sums of T, one per slice of slice_groups K groups
+    const uint8_t* Wt; const float* Wsc;
+    const uint8_t* Bt; const float* Bsc; int kp16;
+    float* Y; int64_t ldy;
+};
+hipError_t launch_int_few(const IntFewArgs& a, hipStream_t s);
 size_t int_workspace_bytes(const Layer& L, int64_t M);
 int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y, int64_t ldy, void* ws, size_t ws_bytes,
                 hipStream_t s);

@@ -130,4 +130,23 @@ __device__ __forceinline__ int mx8_code(float v, int e_unbiased) {
     return (int)r;
 }
 
+// ---- direct-to-LDS loads ----------------------------------------------------------------------------------------------
+// 1 KiB (64 lanes x 16 bytes) or 256 B from `base` + this lane's byte offset to LDS address at + ADD + 16 (4) * lane.
+// Written as asm because the compiler answers its own builtin with a full drain of the loads in flight in front of every
+// LDS read; nothing is returned in registers, and the kernel counts these loads itself (staged_wait).  M0 has no other use.
+template <int ADD>
+__device__ __forceinline__ void lds_dma16(uint32_t at, uint32_t off, const uint8_t* base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+}
+template <int ADD>
+__device__ __forceinline__ void lds_dma4(uint32_t at, uint32_t off, const uint8_t* base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+}
+// All but this wavefront's newest `LEFT` loads have landed, its LDS reads have returned, and so have everybody's.
+template <int LEFT>
+__device__ __forceinline__ void staged_wait() {
+    static_assert(LEFT >= 0 && LEFT < 64, "a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+}
+
 }  // namespace lqer

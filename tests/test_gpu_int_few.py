@@ -1,0 +1,34 @@
+"""The INT variant's few-token launches: edges of the blocks of 32 tokens, column counts around a workgroup's 32, K groups
+that slices, wavefronts and register sets do not divide, ranks to 128, all-zero tokens; against the oracle, and the same bits
+on a second run with other contents in the workspace."""
+import numpy as np
+import pytest
+
+from paper_2402_02446_amd import synth
+from test_gpu_int import _check, _standin_layer, _upload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,K,N,k", [(1, 128, 33, 16), (4, 1152, 64, 128), (5, 7296, 65, 33), (17, 4224, 100, 8), (31, 11008, 96, 32),
+                                     (32, 2304, 31, 0), (33, 4096, 1040, 64), (128, 1024, 528, 100)])
+def test_few_tokens(M, K, N, k):
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, ch = _standin_layer(K, N, min(k, N), seed=K + M, n_outlier=4)
+    h = _upload(layer)
+    X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 30.0)
+    if M > 2:
+        X[M // 2] = 0.0
+    ws = h.workspace(M)
+    first = None
+    for fill in (0, 255):
+        ws.fill_(fill)
+        buf = torch.full((M, (N + 7) // 4 * 4), 7.0, dtype=torch.float32, device="cuda")
+        binding.lqer_linear_forward(h, torch.from_numpy(X).cuda(), Y=buf[:, :N])
+        torch.cuda.synchronize()
+        assert (buf[:, N:] == 7.0).all()
+        first = buf[:, :N].clone() if first is None else first
+        assert torch.equal(buf[:, :N], first)
+    _check(first.cpu().numpy(), X, layer)
+    h.free()
