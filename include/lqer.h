@@ -243,7 +243,7 @@ int lqer_linear_forward_requant(const lqer_layer* layer, const float* X_dev, int
  *   layers   n_layers handles with the same K and the same activation width (LQER_ERR_SHAPE otherwise)
  *   Y_dev    n_layers device pointers, Y_dev[i] fp32 [M][ldy[i]], ldy[i] >= N of layer i
  *   workspace_dev  at least lqer_linear_shared_workspace_bytes(layers, n_layers, M) bytes
- * For token counts that take the streaming kernel the call is n_layers full forward passes.
+ * For token counts that take the streaming kernel, layers in a row that take the same shape of it share their two launches.
  * Same contract as lqer_linear_forward otherwise.
  */
 size_t lqer_linear_shared_workspace_bytes(const lqer_layer* const* layers, int n_layers, int64_t M);

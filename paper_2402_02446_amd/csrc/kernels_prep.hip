@@ -62,7 +62,7 @@ __device__ __forceinline__ float dpp_quad(float v) {
 }
 
 template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false>
-__global__ __launch_bounds__(64 * kPrepWaves, RW ? 4 : 1) void prep_kernel(PrepArgs a) {
+__device__ __forceinline__ void prep_body(const PrepArgs& a) {
     static_assert(!RW || (SRC == 0 && !CELLS), "the row-wise form reads fp32 rows and writes row-major bf16");
     // ROWWISE (fp32 X in, row-major bf16 out: the prefill case, bound by HBM): a wavefront reads and writes whole rows
     // of its 16 x 256 tile - 1 KiB per load, 512 B per store, every cache line touched by one instruction - with the
@@ -356,6 +356,44 @@ __global__ __launch_bounds__(64 * kPrepWaves, RW ? 4 : 1) void prep_kernel(PrepA
     }
 }
 
+template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false>
+__global__ __launch_bounds__(64 * kPrepWaves, RW ? 4 : 1) void prep_kernel(PrepArgs a) {
+    prep_body<SRC, FINAL, MAXG, CELLS, RW>(a);
+}
+
+// Several layers applied to the same few tokens: grid.z holds the rank groups of all of them (the first plane stores the
+// activations), workgroups behind the K slices clear whichever Y a main kernel adds into.
+struct PrepLayer { const uint8_t* At; float* Tpart; float* Yz; int64_t ldy, N; int kp, kp16, z0; };
+struct PrepGroup { PrepArgs a; int n; PrepLayer layer[kGroupLayers]; };
+
+__global__ __launch_bounds__(64 * kPrepWaves) void prep_group_kernel(PrepGroup g) {
+    if ((int)blockIdx.y >= g.a.nslices) {
+        if (blockIdx.z != 0) return;
+        const int64_t nthreads = (int64_t)gridDim.x * (gridDim.y - g.a.nslices) * blockDim.x;
+        const int64_t me = ((int64_t)(blockIdx.y - g.a.nslices) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+        for (int li = 0; li < g.n; ++li) {
+            const PrepLayer& L = g.layer[li];
+            const int64_t n4 = (L.N + 3) / 4;
+            for (int64_t i = me; i < g.a.M * n4; i += nthreads) {
+                const int64_t r = i / n4, c = 4 * (i - r * n4);
+                if (c + 3 < L.N) {
+                    *reinterpret_cast<f32x4*>(L.Yz + r * L.ldy + c) = f32x4{0.f, 0.f, 0.f, 0.f};
+                } else {
+                    for (int64_t j = c; j < L.N; ++j) L.Yz[r * L.ldy + j] = 0.f;
+                }
+            }
+        }
+        return;
+    }
+    int li = 0;
+    while (li + 1 < g.n && (int)blockIdx.z >= g.layer[li + 1].z0) ++li;
+    const PrepLayer& L = g.layer[li];
+    PrepArgs a = g.a;
+    a.At = L.At; a.Tpart = L.Tpart; a.kp = L.kp; a.kp16 = L.kp16;
+    a.g_first = -L.z0;
+    prep_body<0, false, 1, true>(a);
+}
+
 template <int SRC, bool FINAL, int MAXG, bool CELLS>
 static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& a, bool rowwise) {
     if constexpr (SRC == 0 && !CELLS) {
@@ -448,6 +486,38 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
 #undef LQER_PREP_C
 #undef LQER_PREP_G
 #undef LQER_PREP
+    return hipGetLastError();
+}
+
+// The projection step of launch_stream_group: what launch_prep does for each layer alone, in one launch.
+hipError_t launch_prep_group(const Layer* const* layers, int n, const float* X, int64_t ldx, int64_t M, const Workspace& ws,
+                             float* const* Tpart, float* const* Y, const int64_t* ldy, bool zero_y, hipStream_t s) {
+    if (M == 0) return hipSuccess;
+    if (n < 1 || n > kGroupLayers || !ws.cells) return hipErrorInvalidValue;
+    const Layer& L0 = *layers[0];
+    PrepGroup g{};
+    PrepArgs& a = g.a;
+    a.X = X; a.ldx = ldx; a.M = M; a.K = L0.K; a.KT = L0.KT;
+    a.tiles_per_slice = (int)((L0.KT + ws.S - 1) / ws.S);
+    a.groups_per_wg = 1;
+    a.Xh = ws.Xh; a.ldxh = ws.ldxh; a.tp_rows = M; a.lr = ws.lr; a.x8 = ws.x8;
+    a.act_frac = L0.act_bits - 2;
+    a.nslices = ws.S;
+    g.n = n;
+    int z = 0;
+    int64_t cols4 = 0;
+    for (int i = 0; i < n; ++i) {
+        const Layer& L = *layers[i];
+        g.layer[i] = PrepLayer{L.At, Tpart[i], Y[i], ldy[i], L.N, L.kp, L.kp16, z};
+        z += L.kp16;
+        cols4 += (L.N + 3) / 4;
+    }
+    int nwaves = a.tiles_per_slice < kPrepWaves ? a.tiles_per_slice : kPrepWaves;
+    if (nwaves < 1) nwaves = 1;
+    const dim3 block(64 * nwaves);
+    const int64_t rg = (M + 15) / 16;
+    const int64_t zero_wgs = zero_y ? (M * cols4 + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;
+    hipLaunchKernelGGL(prep_group_kernel, dim3((unsigned)rg, (unsigned)(ws.S + zero_wgs), (unsigned)(z > 0 ? z : 1)), block, 0, s, g);
     return hipGetLastError();
 }
 

@@ -61,7 +61,7 @@ struct StreamArgs {
 // BIGK: padded ranks above 64 (up to 256): the correction's operands are then not fetched ahead of the main
 //      product - there are up to four times as many - but behind it, all of a wavefront's together.
 template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
-__global__ __launch_bounds__(64 * NWC * NWK) void stream_kernel(StreamArgs a) {
+__device__ __forceinline__ void stream_body(const StreamArgs& a, const int block) {
     static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
     constexpr int NC = (WB == 4) ? 4 : 2;            // 1 KiB loads per weight record
     static_assert(KSP == 1 || KSP == 2, "one workgroup per column block, or a pair");
@@ -100,8 +100,8 @@ __global__ __launch_bounds__(64 * NWC * NWK) void stream_kernel(StreamArgs a) {
     const int t = lane & 31, hh = lane >> 5;
 
     // column groups of this wavefront (clamped; stores are masked)
-    const int64_t cb = blockIdx.x / KSP;             // column block
-    const int kh = blockIdx.x % KSP;                 // which of the KSP workgroups of the block
+    const int64_t cb = block / KSP;                  // column block
+    const int kh = block % KSP;                      // which of the KSP workgroups of the block
     const int64_t g0 = (cb * NWC + wc) * G;
     const uint8_t* wrec[G];
 #pragma unroll
@@ -575,15 +575,52 @@ __global__ __launch_bounds__(64 * NWC * NWK) void stream_kernel(StreamArgs a) {
     }
 }
 
+template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
+__global__ __launch_bounds__(64 * NWC * NWK) void stream_kernel(StreamArgs a) {
+    stream_body<G, NWC, NWK, DT, LR, ONE, KSP, WB, BIGK>(a, (int)blockIdx.x);
+}
+
+// Several layers on the same activation cells (q/k/v, gate/up) in one launch: what each does alone, column block by column
+// block.  A few-token launch is mostly its ramp and its last round trips - 4096 x 4096 takes 6.0 us for 9.4 MB, 4096 x 11008
+// 10.8 us for 24 MB - so one launch of 28 or 48 MB runs at nearly the rate of a wide layer.  4-bit weights, ranks to 64.
+struct StreamLayer {
+    const uint8_t* Wt; const uint8_t* Bt; const float* Tpart;
+    float* Y; int64_t ldy, N, N32;
+    int kp, kp16, rec_bytes, exp_bias;
+    int block0;                    // first workgroup
+};
+struct StreamGroup {
+    const uint8_t* Xcell;
+    int64_t M, KT;
+    int S, n;
+    StreamLayer layer[kGroupLayers];
+};
+
+template <int G, int NWC, int NWK, int LR, bool ONE, int KSP>
+__global__ __launch_bounds__(64 * NWC * NWK) void stream_group_kernel(StreamGroup g) {
+    int li = 0;
+    while (li + 1 < g.n && (int)blockIdx.x >= g.layer[li + 1].block0) ++li;
+    const StreamLayer& L = g.layer[li];
+    const StreamArgs a{L.Wt, L.Bt, g.Xcell, L.Tpart, g.S, L.Y, L.ldy, nullptr, nullptr, 0, g.M, L.N, g.KT, L.N32,
+                       L.kp, L.kp16, L.rec_bytes, L.exp_bias};
+    stream_body<G, NWC, NWK, 1, LR, ONE, KSP, 4, false>(a, (int)blockIdx.x - L.block0);
+}
+
 int stream_max_rows() { return 64; }
 int stream_cell_rows_log2(int64_t M) { return M <= 4 ? 2 : (M <= 16 ? 4 : (M <= 32 ? 5 : 6)); }
 
-template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
-static hipError_t launch_stream_t(const StreamArgs& a, hipStream_t s) {
+template <int G, int NWC, int NWK, int LR, bool ONE, int KSP, bool BIGK>
+constexpr int stream_lds_bytes() {
     constexpr int STAGING = (ONE ? 1 : 2) * NWK * (1 << LR) * 512;
     constexpr int MB = (LR == 6) ? 2 : 1;
     constexpr int REDUCE = NWK * NWC * G * MB * 4096 + (KSP == 2 ? NWC * G * 4096 : 0);
-    constexpr int LDS_BYTES = (BIGK ? kStreamTBytesBig : kStreamTBytes) * MB + (STAGING > REDUCE ? STAGING : REDUCE);
+    return (BIGK ? kStreamTBytesBig : kStreamTBytes) * MB + (STAGING > REDUCE ? STAGING : REDUCE);
+}
+
+template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
+static hipError_t launch_stream_t(const StreamArgs& a, hipStream_t s) {
+    constexpr int MB = (LR == 6) ? 2 : 1;
+    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, KSP, BIGK>();
     if constexpr (LDS_BYTES > 160 * 1024 || (MB == 2 && KSP == 2)) {
         return hipErrorInvalidValue;                 // this shape does not fit the 160 KB of LDS
     } else {
@@ -693,6 +730,67 @@ hipError_t launch_stream(const Layer& L, int64_t M, const Workspace& ws, float* 
         case 22421: return launch_stream_rows<2, 4, 2, 1, 2, 4, false>(a, s);
         case 21441: return launch_stream_rows<1, 4, 4, 1, 2, 4, false>(a, s);
         case 21101: return launch_stream_rows<1, 1, 16, 1, 2, 4, false>(a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// ---- groups of layers ---------------------------------------------------------------------------------------------------
+template <int G, int NWC, int NWK, int LR, bool ONE, int KSP>
+static hipError_t launch_group_t(StreamGroup& g, hipStream_t s) {
+    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, KSP, false>();
+    static_assert(LDS_BYTES <= 160 * 1024, "fits");
+    auto kern = stream_group_kernel<G, NWC, NWK, LR, ONE, KSP>;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    int64_t blocks = 0;
+    for (int i = 0; i < g.n; ++i) {
+        g.layer[i].block0 = (int)blocks;
+        blocks += (g.layer[i].N32 + NWC * G - 1) / (NWC * G) * KSP;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * NWC * NWK), LDS_BYTES, s, g);
+    return hipGetLastError();
+}
+
+template <int G, int NWC, int NWK, int LR, int KSP>
+static hipError_t launch_group_one(StreamGroup& g, hipStream_t s) {
+    return g.KT <= NWK * KSP ? launch_group_t<G, NWC, NWK, LR, true, KSP>(g, s) : launch_group_t<G, NWC, NWK, LR, false, KSP>(g, s);
+}
+
+// the shapes the automatic choice has for up to 16 tokens, and for 17 to 32
+bool stream_group_takes(const Layer& L, int64_t M) { return L.format == 0 && L.w_bits == 4 && L.kp <= 64 && M <= 32; }
+
+hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, const Workspace& ws, float* const* Tpart,
+                               float* const* Y, const int64_t* ldy, hipStream_t s) {
+    if (M == 0) return hipSuccess;
+    if (n < 1 || n > kGroupLayers) return hipErrorInvalidValue;
+    const int v = stream_variant(*layers[0], M, 0);
+    StreamGroup g;
+    g.Xcell = reinterpret_cast<const uint8_t*>(ws.Xh);
+    g.M = M; g.KT = layers[0]->KT; g.S = ws.S; g.n = n;
+    for (int i = 0; i < n; ++i) {
+        const Layer& L = *layers[i];
+        if (!stream_group_takes(L, M) || stream_variant(L, M, 0) != v || L.KT != g.KT) return hipErrorInvalidValue;
+        g.layer[i] = StreamLayer{L.Wt, L.Bt, Tpart[i], Y[i], ldy[i], L.N, L.N32, L.kp, L.kp16, L.w_rec_bytes, L.w_exp_bias, 0};
+    }
+    const int lr = stream_cell_rows_log2(M);
+    if (lr == 5) {
+        switch (v) {
+            case 12241: return launch_group_one<2, 2, 4, 5, 1>(g, s);
+            case 12141: return launch_group_one<2, 1, 4, 5, 1>(g, s);
+            case 21141: return launch_group_one<1, 1, 4, 5, 2>(g, s);
+            case 11241: return launch_group_one<1, 2, 4, 5, 1>(g, s);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    switch (v) {
+        case 12241: return lr == 2 ? launch_group_one<2, 2, 4, 2, 1>(g, s) : launch_group_one<2, 2, 4, 4, 1>(g, s);
+        case 12181: return lr == 2 ? launch_group_one<2, 1, 8, 2, 1>(g, s) : launch_group_one<2, 1, 8, 4, 1>(g, s);
+        case 21181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 2>(g, s) : launch_group_one<1, 1, 8, 4, 2>(g, s);
+        case 11181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 1>(g, s) : launch_group_one<1, 1, 8, 4, 1>(g, s);
         default: return hipErrorInvalidValue;
     }
 }

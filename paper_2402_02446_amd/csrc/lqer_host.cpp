@@ -446,6 +446,62 @@ static bool shared_group_tiled(const lqer_layer* const* layers, int n, int64_t M
     return true;
 }
 
+// ---- few tokens: layers that take the same streaming shape run as one launch pair --------------------------------------
+// How many layers from `first` on can: same shape of the streaming kernel, at most kGroupLayers.
+static int stream_run_length(const lqer_layer* const* layers, int n, int first, int64_t M) {
+    if (pick_path(layers[first]->L, M) != 1 || !stream_group_takes(layers[first]->L, M)) return 1;
+    const int v = stream_variant(layers[first]->L, M, 0);
+    int k = 1;
+    while (first + k < n && k < kGroupLayers && pick_path(layers[first + k]->L, M) == 1 &&
+           stream_group_takes(layers[first + k]->L, M) && stream_variant(layers[first + k]->L, M, 0) == v)
+        ++k;
+    return k;
+}
+
+// Workspace of such a run: the activation cells once, then each layer's partial sums of T.  Tpart may be null.
+static size_t plan_stream_run(const lqer_layer* const* layers, int n, int64_t M, void* base, Workspace* ws, float** Tpart) {
+    Layer plain = layers[0]->L;
+    plain.kp = plain.kp16 = 0;
+    Workspace w = plan_workspace(plain, M, 1, base);
+    size_t bytes = w.bytes;
+    for (int i = 0; i < n; ++i) {
+        const Layer& L = layers[i]->L;
+        if (Tpart) Tpart[i] = L.kp > 0 ? (float*)((uint8_t*)base + bytes) : nullptr;
+        bytes += (size_t)round_up((int64_t)w.S * M * L.kp * 4, 256);
+    }
+    w.bytes = bytes;
+    if (ws) *ws = w;
+    return bytes;
+}
+
+static int forward_stream_run(const lqer_layer* const* layers, int n, const float* X, int64_t M, int64_t ldx, float* const* Y,
+                              const int64_t* ldy, void* base, hipStream_t s) {
+    const Layer* L[kGroupLayers];
+    float* Tpart[kGroupLayers];
+    Workspace ws;
+    for (int i = 0; i < n; ++i) L[i] = &layers[i]->L;
+    plan_stream_run(layers, n, M, base, &ws, Tpart);
+    const int v = stream_variant(*L[0], M, 0);
+    ws.x8 = stream_takes_codes(v, ws.lr);
+    if (launch_prep_group(L, n, X, ldx, M, ws, Tpart, Y, ldy, stream_variant_adds_into_y(v), s) != hipSuccess) return LQER_ERR_HIP;
+    if (launch_stream_group(L, n, M, ws, Tpart, Y, ldy, s) != hipSuccess) return LQER_ERR_HIP;
+    return LQER_OK;
+}
+
+// What any layer of the group needs alone: the least a call takes.
+static size_t shared_least_bytes(const lqer_layer* const* layers, int n, int64_t M) {
+    size_t need = 0;
+    for (int i = 0; i < n; ++i) {
+        const size_t b = plan_workspace(layers[i]->L, M, pick_path(layers[i]->L, M), nullptr).bytes;
+        if (b > need) need = b;
+    }
+    if (shared_group_tiled(layers, n, M)) {
+        const size_t b = plan_workspace(shared_plan_layer(layers, n), M, 2, nullptr).bytes;
+        if (b > need) need = b;
+    }
+    return need;
+}
+
 int forward_in_scratch(const lqer_layer* layer, const float* X, int64_t M, int64_t ldx, float* Y, int64_t ldy,
                        void* scratch, size_t scratch_bytes, void* stream) {
     return forward_impl(layer, X, ldx, nullptr, nullptr, M, Y, ldy, scratch, scratch_bytes, stream, nullptr,
@@ -625,14 +681,12 @@ int lqer_linear_forward_requant(const lqer_layer* layer, const float* X_dev, int
 
 size_t lqer_linear_shared_workspace_bytes(const lqer_layer* const* layers, int n_layers, int64_t M) {
     if (!shared_group_ok(layers, n_layers) || M <= 0) return 0;
-    size_t need = 0;
-    for (int i = 0; i < n_layers; ++i) {
-        const size_t b = plan_workspace(layers[i]->L, M, pick_path(layers[i]->L, M), nullptr).bytes;
+    size_t need = shared_least_bytes(layers, n_layers, M);
+    for (int i = 0; i < n_layers;) {
+        const int k = stream_run_length(layers, n_layers, i, M);
+        const size_t b = k > 1 ? plan_stream_run(layers + i, k, M, nullptr, nullptr, nullptr) : 0;
         if (b > need) need = b;
-    }
-    if (shared_group_tiled(layers, n_layers, M)) {
-        const size_t b = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, nullptr).bytes;
-        if (b > need) need = b;
+        i += k;
     }
     return need;
 }
@@ -652,13 +706,22 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
     for (int i = 0; i < n_layers; ++i)
         if (ldy[i] < layers[i]->L.N || (ldy[i] & 3) != 0 || ((uintptr_t)Y_dev[i] & 15) != 0) return LQER_ERR_SHAPE;
     if (!workspace_dev || ((uintptr_t)workspace_dev & 255) != 0) return LQER_ERR_WORKSPACE;
-    if (workspace_bytes < lqer_linear_shared_workspace_bytes(layers, n_layers, M)) return LQER_ERR_WORKSPACE;
+    if (workspace_bytes < shared_least_bytes(layers, n_layers, M)) return LQER_ERR_WORKSPACE;
     if (!shared_group_tiled(layers, n_layers, M)) {
-        // few tokens: the streaming path keeps its per-layer activation layouts; one full call per layer
-        for (int i = 0; i < n_layers; ++i) {
+        // few tokens: layers that take the same shape of the streaming kernel share their launches, if the workspace has room
+        // for all their T; the others are full calls
+        for (int i = 0; i < n_layers;) {
+            const int k = stream_run_length(layers, n_layers, i, M);
+            if (k > 1 && plan_stream_run(layers + i, k, M, nullptr, nullptr, nullptr) <= workspace_bytes) {
+                const int st = forward_stream_run(layers + i, k, X_dev, M, ldx, Y_dev + i, ldy + i, workspace_dev, (hipStream_t)hip_stream);
+                if (st != LQER_OK) return st;
+                i += k;
+                continue;
+            }
             const int st = forward_impl(layers[i], X_dev, ldx, nullptr, nullptr, M, Y_dev[i], ldy[i], workspace_dev,
                                         workspace_bytes, hip_stream, nullptr);
             if (st != LQER_OK) return st;
+            ++i;
         }
         return LQER_OK;
     }

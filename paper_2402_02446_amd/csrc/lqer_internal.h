@@ -164,6 +164,15 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
                         int variant, hipStream_t s);
 
 hipError_t launch_clear_flags(const Workspace& ws, hipStream_t s);
+
+// Up to kGroupLayers layers on the same few tokens, each with the launch shape it has alone (all the same one), its T at
+// Tpart[i]: projection and main product of all of them in one launch each.  zero_y: the shape adds into Y.
+constexpr int kGroupLayers = 4;
+bool stream_group_takes(const Layer& L, int64_t M);
+hipError_t launch_prep_group(const Layer* const* layers, int n, const float* X, int64_t ldx, int64_t M, const Workspace& ws,
+                             float* const* Tpart, float* const* Y, const int64_t* ldy, bool zero_y, hipStream_t s);
+hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, const Workspace& ws, float* const* Tpart,
+                               float* const* Y, const int64_t* ldy, hipStream_t s);
 // polls of a hand-over flag before a waiting workgroup of the tiled kernel gives up and stores NaN
 int tiled_wait_limit();
 void set_tiled_wait_limit(int polls);
