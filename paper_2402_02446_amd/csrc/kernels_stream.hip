@@ -58,8 +58,7 @@ struct StreamArgs {
 //      kernel has zeroed, with hardware fp32 atomics.  0 + a + b does not depend on which of the two
 //      arrives first, so the result is the same bits on every run.
 // WB: mantissa bits of W_q, 4 or 2 (half the code bytes per record: two 1 KiB loads per record instead of four).
-// BIGK: padded ranks above 64 (up to 256): the correction's operands are then not fetched ahead of the main
-//      product - there are up to four times as many - but behind it, all of a wavefront's together.
+// BIGK: padded ranks above 64 (up to 256): T takes 33 KB of LDS and up to four times as many registers on its way there.
 template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
 __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block) {
     static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
@@ -222,25 +221,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     const int nb2 = (kh == 0) ? 2 * a.kp16 : 0;      // the correction is added once: by workgroup 0 of a pair
     const int nchunks = (nb2 + 3) / 4;               // 0, 1 or 2; up to 8 with BIGK
     constexpr int NJ = ((BIGK ? 8 : 2) * G + NWK - 1) / NWK;
-    constexpr int NJP = BIGK ? 1 : NJ;               // jobs whose operands are fetched ahead
-    u32x4 tail_cw[NJP][2];
-    uint32_t tail_eb[NJP][2];
-    auto load_tail = [&](int job, int j, u32x4& cw, uint32_t& eb) {
-        const int g = nchunks ? job / nchunks : 0, ch = nchunks ? job % nchunks : 0;
-        cw = u32x4{0, 0, 0, 0};
-        eb = 0;
-        const int jb = 4 * ch + 2 * hh + j;
-        if (job < G * nchunks && jb < nb2) {
-            const int rb = jb >= a.kp16 ? jb - a.kp16 : jb;
-            int64_t grp = g0 + g;
-            if (grp >= a.N32) grp = a.N32 - 1;
-            const uint8_t* rec = a.Bt + (grp * a.kp16 + rb) * kBRecordBytes;
-            cw = *reinterpret_cast<const u32x4*>(rec + t * 16);
-            eb = rec[512 + t];
-        }
-    };
+    u32x4 tail_cw[NJ][2];
+    uint32_t tail_eb[NJ][2];
+    auto load_tail = [&]() {
 #pragma unroll
-    for (int q = 0; q < (BIGK ? 0 : NJ); ++q) {
+    for (int q = 0; q < NJ; ++q) {
         const int job = wk + NWK * q;                // wave-uniform
         const int g = nchunks ? job / nchunks : 0, ch = nchunks ? job % nchunks : 0;
 #pragma unroll
@@ -258,9 +243,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
             }
         }
     }
+    };
+    if constexpr (!BIGK) load_tail();
     // T: the workgroup adds the S (<= 8) partial sums of the projection kernel in slice order and
     // leaves T_hi | T_lo as bf16 in LDS.  One item = 4 consecutive ranks of a token.
-    constexpr int TI = BIGK ? 1 : (32 * MB * 16 + NW * 64 - 1) / (NW * 64);
+    // (ranks above 64: up to four items a thread, 128 registers that one or two wavefronts on a SIMD have to spare; one item
+    // after the other they were four round trips, 4 us of the 4096 x 4096 step at rank 256)
+    constexpr int TI = ((BIGK ? R * 64 : 32 * MB * 16) + NW * 64 - 1) / (NW * 64);
     constexpr int SMAX = 8;
     const int t_rows = a.M < 32 * MB ? (int)a.M : 32 * MB;
     const int kp4 = a.kp >> 2;
@@ -268,8 +257,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     // The loads are issued here; the sums are formed (finish_t) once the first weight loads are on
     // their way, so that those do not wait for this round trip.
     f32x4 tpart[TI][SMAX];
+    auto load_t = [&]() {
 #pragma unroll
-    for (int i = 0; i < (BIGK ? 0 : TI); ++i) {
+    for (int i = 0; i < TI; ++i) {
         const int item = threadIdx.x + i * NW * 64;
 #pragma unroll
         for (int sl = 0; sl < SMAX; ++sl) {
@@ -278,31 +268,19 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
                 tpart[i][sl] = *reinterpret_cast<const f32x4*>(a.Tpart + (int64_t)sl * a.M * a.kp + 4 * item);
         }
     }
+    };
+    if constexpr (!BIGK) load_t();
     auto finish_t = [&]() {
-        constexpr int TIL = BIGK ? (32 * MB * 64 + NW * 64 - 1) / (NW * 64) : TI;
 #pragma unroll
-        for (int i = 0; i < TIL; ++i) {
+        for (int i = 0; i < TI; ++i) {
             const int item = threadIdx.x + i * NW * 64;
             if (item >= t_items) continue;
             const int row = item / kp4, r4 = item - row * kp4;
-            f32x4 sum;
-            if constexpr (BIGK) {
-                // loaded here, one item at a time, its slices' loads in flight together (slice order as below)
-                f32x4 o[SMAX];
+            f32x4 sum = tpart[i][0];
 #pragma unroll
-                for (int sl = 0; sl < SMAX; ++sl)
-                    o[sl] = *reinterpret_cast<const f32x4*>(a.Tpart + (int64_t)(sl < a.S ? sl : a.S - 1) * a.M * a.kp + 4 * item);
-                sum = o[0];
-#pragma unroll
-                for (int sl = 1; sl < SMAX; ++sl)
-                    if (sl < a.S) { sum[0] += o[sl][0]; sum[1] += o[sl][1]; sum[2] += o[sl][2]; sum[3] += o[sl][3]; }
-            } else {
-                sum = tpart[i][0];
-#pragma unroll
-                for (int sl = 1; sl < SMAX; ++sl) {
-                    sum[0] += tpart[i][sl][0]; sum[1] += tpart[i][sl][1];
-                    sum[2] += tpart[i][sl][2]; sum[3] += tpart[i][sl][3];
-                }
+            for (int sl = 1; sl < SMAX; ++sl) {
+                sum[0] += tpart[i][sl][0]; sum[1] += tpart[i][sl][1];
+                sum[2] += tpart[i][sl][2]; sum[3] += tpart[i][sl][3];
             }
             uint32_t hi[4], lo[4];
 #pragma unroll
@@ -341,6 +319,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
 #pragma unroll
                         for (int g = 0; g < G; ++g) wcd[1][g][c] = load_wc(g, tile_at(1), c);
                 }
+            }
+            // With ranks above 64 these are up to 130 KB a workgroup, which the first weights would wait behind.
+            if constexpr (BIGK) {
+                load_t();
+                load_tail();
             }
             store_x(st, 0);
             finish_t();
@@ -433,17 +416,6 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     }
 
     // ---- rank-kp correction, part 2: the arithmetic ---------------------------------------------------
-    // (ranks above 64: the operands of all of this wavefront's jobs are asked for here, in the registers the weight sets
-    // have left, instead of one round trip per job)
-    constexpr int NJB = BIGK ? NJ : 1;
-    u32x4 big_cw[NJB][2];
-    uint32_t big_eb[NJB][2];
-    if constexpr (BIGK) {
-#pragma unroll
-        for (int q = 0; q < NJ; ++q)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) load_tail(wk + NWK * q, j, big_cw[q][j], big_eb[q][j]);
-    }
 #pragma unroll
     for (int q = 0; q < NJ; ++q) {
         const int job = wk + NWK * q;
@@ -464,11 +436,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
                 }
             }
             Frag bf[2];
-            if constexpr (BIGK) {
-                int8x16_to_frags(big_cw[q][j], h_scale(big_eb[q][j]), bf[0], bf[1]);
-            } else {
-                int8x16_to_frags(tail_cw[q][j], h_scale(tail_eb[q][j]), bf[0], bf[1]);
-            }
+            int8x16_to_frags(tail_cw[q][j], h_scale(tail_eb[q][j]), bf[0], bf[1]);
             // g is wave-uniform: pick the accumulator by unrolled comparison so all stay in registers
 #pragma unroll
             for (int gg = 0; gg < G; ++gg) {
