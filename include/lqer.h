@@ -297,8 +297,8 @@ int lqer_quantize_int8_token(const float* x_dev, int64_t rows, int64_t cols, int
  * are not cut between workgroups; the scratch that call takes as `workspace_dev` is a device array
  * inside the library, 32 MiB on every GPU the library is used on, held until the process ends.
  *   - Sizes whose scratch need exceeds 32 MiB return LQER_ERR_WORKSPACE before anything is launched
- *     (the need is about 2 (M + 255) (K + 128) bytes for more than 64 tokens - e.g. M = 1024 at
- *     K = 8192 fits, M = 4096 does not - and well under 2 MiB up to 64 tokens).
+ *     (the need is about 2 (M + 255) (K + 128) bytes for more than 32 tokens - e.g. M = 1024 at
+ *     K = 8192 fits, M = 4096 does not - and well under 2 MiB up to 32 tokens).
  *   - The call allocates and frees nothing and synchronises nothing.  Its first use on a device looks
  *     up the address of that device's array (with that device current): make one call outside any
  *     graph capture first.

@@ -350,11 +350,10 @@ static Workspace plan_workspace(const Layer& L, int64_t M, int path, void* base,
 
 static int pick_path(const Layer& L, int64_t M) {
     if (L.format == 1) return 3;                     // the scaled-integer variant has one kernel for every token count
-    // The streaming kernel takes up to 32 tokens for any layer, and up to 64 (two blocks of 32 per
-    // wavefront) for layers wide enough to fill the chip with four column groups per workgroup.
+    // The streaming kernel takes up to 32 tokens.  Its form for 33 to 64 (two blocks of 32 per wavefront) is reached by
+    // forcing the path only: the tiled path's staged kernel is faster on every layer measured (whole step, 33 / 64 tokens:
+    // 8192 x 28672 58 / 63 against 64 / 67 us, 4096 x 16384 30 / 32 against 33 / 34, 11008 x 20000 51 / 57 against 76 / 78).
     if (M <= 32) return 1;
-    // (with ranks above 64 the T rows of 64 tokens do not fit the streaming kernel's LDS)
-    if (M <= stream_max_rows() && L.N32 >= 512 && L.kp <= 64) return 1;
     return 2;
 }
 
