@@ -28,6 +28,7 @@ def _layers(K, specs):
     (4096, [(1040, 32, 4), (1040, 16, 4), (528, 0, 4)]),                                 # pairs of workgroups
     (2304, [(100, 0, 4), (272, 33, 4), (1001, 64, 4), (33, 8, 4), (64, 24, 4), (272, 16, 2), (272, 40, 4)]),
     (1040, [(11008, 8, 4), (10300, 24, 4)]),                                             # two column groups per wavefront
+    (4624, [(10272, 0, 4), (10300, 64, 4)]),                                             # and two slices of K each
 ])
 @pytest.mark.parametrize("M", [1, 4, 5, 16, 17, 32])
 def test_shared_few_tokens(K, specs, M):
