@@ -544,11 +544,11 @@ def run_int_variant(rng, peaks):
                    "ring_layers": n, "ms_per_step": ms, "tops": ops / (ms * 1e-3) / 1e12}
             if M <= 16:
                 ach = by / (ms * 1e-3) / 1e9
-                rec["roofline"] = {"bound": "hbm", "kernel": "whole step (quant_token_kernel + 2 x (int_gemm_kernel + int_reduce_planes_kernel))", "achieved": ach,
+                rec["roofline"] = {"bound": "hbm", "kernel": "whole step (int_few_prep_kernel + int_few_kernel)", "achieved": ach,
                                    "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "traffic": None}
             else:
                 ach = ops / (ms * 1e-3) / 1e12
-                rec["roofline"] = {"bound": "mfma", "kernel": "whole step (quant_token_kernel + 2 x int_gemm_kernel)", "achieved": ach,
+                rec["roofline"] = {"bound": "mfma", "kernel": "whole step (quant_token_kernel + int_gemm_kernel + int_main_kernel)", "achieved": ach,
                                    "peak": MFMA_INT8_PEAK_TOPS, "unit": "TOP/s", "frac": ach / MFMA_INT8_PEAK_TOPS, "traffic": None}
                 # what the int8 pipe delivers with this kernel's 12 vector instructions per MFMA beside it (probe)
                 lim = (peaks or {}).get("mfma_beside_valu_tera_per_s", {}).get("int8_12_valu")
