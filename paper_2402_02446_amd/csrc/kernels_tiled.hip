@@ -561,7 +561,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     constexpr int XL = XB / 1024 / NW;             // activation loads per wavefront and chunk
     static_assert(XB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
     constexpr int L = XL + 2 * TN;                 // loads per wavefront and chunk
-    static_assert(D >= 3, "a chunk computed, one read ahead, one on its way");
+    static_assert(D >= 3 && D <= 5, "a chunk computed, one read ahead, one on its way; a K tile has the D - 1 chunks asked for first");
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -661,13 +661,17 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     const uint32_t emask = exp4 ? 0xFu : 0xFFu;
     const uint32_t ebase = ((exp4 ? (uint32_t)a.exp_bias : 0u) + (WB == 4 ? 7u : 9u)) << 23;   // w_scale / w2_scale of exponent 0
 
-    f32x16 acc[TM][TN];
+    // The terms are summed as two chains - the correction and then the first half of the K range, the second half - since
+    // an fp32 chain rounds at the size its sum has reached: the correction's steps come while that is small.  Relative
+    // distance from the 64-bit result, 4096 x 4096 at 512 tokens, one chain with the correction last -> so: rank 32 2.29e-7 ->
+    // 2.22e-7, rank 128 2.91e-7 -> 2.57e-7, rank 256 3.37e-7 -> 2.72e-7.
+    f32x16 acc0[TM][TN], acc1[TM][TN];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tm][tn][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc0[tm][tn][r] = acc1[tm][tn][r] = 0.f;
 
     // ---- main product --------------------------------------------------------------------------------------------
     const int chunks = (kt1 - kt0) * 4;            // of this workgroup
@@ -695,7 +699,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
         }
     };
     // Chunk ch: on entry xa and wv hold its step 0 and w its codes; on exit xa and wv hold step 0 of chunk ch + 1 and wn its codes.
-    auto chunk = [&](const WSet& w, WSet& wn, int ch, const uint8_t* cur, const uint8_t* nxt) {
+    auto chunk = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, int ch, const uint8_t* cur, const uint8_t* nxt) {
         read_w(wn, nxt, ch + 1);
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) {
@@ -729,40 +733,13 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     auto next_stage = [](uint32_t s) { return s + STAGE == D * STAGE ? 0u : s + STAGE; };
     uint32_t st_in = 0;                            // stage the next chunk goes to
 #pragma unroll
-    for (int i = 0; i < D - 1; ++i) {
-        if (i < chunks) {
-            issue(st_in);
-            st_in = next_stage(st_in);
-        }
-    }
-    // (a range of fewer than D - 1 chunks has fewer loads in flight: only a full drain is sure to cover its first chunk)
-    if (chunks >= D - 1) staged_wait<(D - 2) * L>();
-    else staged_wait<0>();
-    WSet w0, w1;
-    read_x(xa, lds, 0);
-    read_w(w0, lds, 0);
-    scales(w0, 0);
-    expand(w0, 0);
-    uint32_t st = 0;                               // stage of chunk ch
-    auto step = [&](const WSet& w, WSet& wn, int ch) {
-        if (ch + D <= chunks) {
-            // chunks ch and ch + 1 have landed; the stage of chunk ch - 1 has been read by everybody and takes chunk ch + D - 1
-            staged_wait<(D - 3) * L>();
-            issue(st_in);
-            st_in = next_stage(st_in);
-        } else {
-            staged_wait<0>();                      // nothing left to ask for
-        }
-        const uint32_t nx = next_stage(st);
-        chunk(w, wn, ch, lds + st, lds + nx);      // (the last one reads ahead what nobody uses)
-        st = nx;
-    };
-    for (int ch = 0; ch < chunks; ch += 2) {       // (four chunks per K tile)
-        step(w0, w1, ch);
-        step(w1, w0, ch + 1);
+    for (int i = 0; i < D - 2; ++i) {
+        issue(st_in);
+        st_in = next_stage(st_in);
     }
 
     // ---- rank-kp correction: [T_hi | T_lo | 0] against B_k, by the workgroup with the start of K -----------------------
+    // (its tiles of T take the memory of the last two stages, which the loads on their way do not write)
     const int nb2 = 2 * a.kp16, tail_chunks = (nb2 + 3) / 4;
     const int my_tail = (kt0 == 0) ? tail_chunks : 0;
     constexpr int LPT = BM * 8 / NT;               // 16-byte cells each thread moves per chunk
@@ -770,6 +747,9 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     static_assert(ROWS_PER_PASS % 16 == 0, "swizzle must not depend on the pass");
     const int ld_row0 = tid >> 3;
     const int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4);
+    // Asked for beside the first chunks instead of behind the last: rank 128 at 512 tokens 56 -> 54 us, 2-bit rank 256 at 64
+    // tokens 51 -> 48 us a call; nothing slower.
+    uint8_t* const t_tiles = lds + (D - 2) * STAGE;
     for (int cc0 = 0; cc0 < my_tail; cc0 += 2) {   // two correction chunks at a time (ranks up to 64 need one round)
         u32x4 bw[2][2][TN];                        // B_k's codes and exponents of both chunks: asked for ahead of T
         uint32_t be[2][2][TN];
@@ -821,12 +801,12 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
                 }
                 tst[q][j] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
             }
-        __syncthreads();                           // every wavefront is done with the stages (or the previous two chunks)
+        if (cc0 > 0) __syncthreads();              // every wavefront is done with the previous two chunks
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int j = 0; j < LPT; ++j)
-                *reinterpret_cast<u32x4*>(lds + q * XB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
+                *reinterpret_cast<u32x4*>(t_tiles + q * XB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -841,15 +821,54 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     Frag xt[TM];
-                    read_x(xt, lds + q * XB, 2 * j + h);
+                    read_x(xt, t_tiles + q * XB, 2 * j + h);
 #pragma unroll
                     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                        for (int tm = 0; tm < TM; ++tm) acc[tm][tn] = mfma32(bf[tn][h].v, xt[tm].v, acc[tm][tn]);
+                        for (int tm = 0; tm < TM; ++tm) acc0[tm][tn] = mfma32(bf[tn][h].v, xt[tm].v, acc0[tm][tn]);
                 }
             }
         }
     }
+    if (my_tail > 0) __syncthreads();              // the tiles of T have been read by everybody
+
+    issue(st_in);
+    st_in = next_stage(st_in);
+    staged_wait<(D - 2) * L>();
+    WSet w0, w1;
+    read_x(xa, lds, 0);
+    read_w(w0, lds, 0);
+    scales(w0, 0);
+    expand(w0, 0);
+    uint32_t st = 0;                               // stage of chunk ch
+    auto step = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, int ch) {
+        if (ch + D <= chunks) {
+            // chunks ch and ch + 1 have landed; the stage of chunk ch - 1 has been read by everybody and takes chunk ch + D - 1
+            staged_wait<(D - 3) * L>();
+            issue(st_in);
+            st_in = next_stage(st_in);
+        } else {
+            staged_wait<0>();                      // nothing left to ask for
+        }
+        const uint32_t nx = next_stage(st);
+        chunk(acc, w, wn, ch, lds + st, lds + nx);      // (the last one reads ahead what nobody uses)
+        st = nx;
+    };
+    const int half = (kt1 - kt0 + 1) / 2 * 4;      // (four chunks per K tile)
+    for (int ch = 0; ch < half; ch += 2) {
+        step(acc0, w0, w1, ch);
+        step(acc0, w1, w0, ch + 1);
+    }
+    for (int ch = half; ch < chunks; ch += 2) {
+        step(acc1, w0, w1, ch);
+        step(acc1, w1, w0, ch + 1);
+    }
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc0[tm][tn][r] += acc1[tm][tn][r];
 
     // ---- store: lane (t, hh) holds columns 8 r4 + 4 hh .. + 3 of token t for every MFMA tile ------------------------------
     if (!PLANES && a.Yc != nullptr) {              // as MXINT8: block b of a column group is registers 8 b .. + 7 of two lanes
@@ -864,7 +883,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
                 for (int b = 0; b < 2; ++b) {
                     float v[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) v[i] = acc[tm][tn][8 * b + i];
+                    for (int i = 0; i < 8; ++i) v[i] = acc0[tm][tn][8 * b + i];
                     uint32_t w0, w1;
                     const uint32_t eb = requant_half_block(v, w0, w1);
                     const int64_t n0 = (g0 + tn) * 32 + 16 * b;
@@ -896,7 +915,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             for (int r4 = 0; r4 < 4; ++r4) {
                 const int64_t n = (g0 + tn) * 32 + 8 * r4 + 4 * hh;
                 float* dst = out + row * ldo + n;
-                const f32x4 v = f32x4{acc[tm][tn][4 * r4], acc[tm][tn][4 * r4 + 1], acc[tm][tn][4 * r4 + 2], acc[tm][tn][4 * r4 + 3]};
+                const f32x4 v = f32x4{acc0[tm][tn][4 * r4], acc0[tm][tn][4 * r4 + 1], acc0[tm][tn][4 * r4 + 2], acc0[tm][tn][4 * r4 + 3]};
                 if (n + 3 < a.N) {
                     *reinterpret_cast<f32x4*>(dst) = v;
                 } else {

@@ -42,3 +42,19 @@ def test_planes_and_narrow_tiles(M, K, N, k, w_bits):
         oc, oe = mxint.mx_quantize(Y, 8, axis=-1)
         assert np.array_equal(exps.cpu().numpy(), oe) and np.array_equal(codes.cpu().numpy(), oc)
     h.free()
+
+
+# fp32 rounds once per MFMA step at the size the sum has reached.  As the kernel sums - the correction, then half of K; the
+# other half - these are 2.7e-7 (both widths) from the oracle; one chain over K with the correction last is 3.4e-7.
+@pytest.mark.parametrize("w_bits", [4, 2])
+def test_large_rank_is_summed_in_short_chains(w_bits):
+    import torch
+    from paper_2402_02446_amd import binding
+    M, K, N, k = 512, 4096, 4096, 256
+    layer, ch = oracle_layer_big(K, N, k, seed=5, w_bits=w_bits)
+    h = upload(layer)
+    X = synth.gen_activations(np.random.default_rng(5), M, K, ch, 50.0)
+    cols = np.arange(0, N, 8)
+    Y = binding.lqer_linear_forward(h, torch.from_numpy(X).cuda()).cpu().numpy()[:, cols]
+    assert_forward_matches(Y, X, layer, cols=cols, tol=3.0e-7)
+    h.free()
