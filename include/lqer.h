@@ -199,7 +199,9 @@ int lqer_linear_forward_q(const lqer_layer* layer, const int8_t* Xc_dev, const u
  *           path does not have returns LQER_ERR_SHAPE).  Tiled path: 100 * mode + shape, mode 0 = cut
  *           output tiles along K between workgroups when the estimate says it pays, 1 = never,
  *           2 = whenever tiles are left over, 3 = the same in equal shares of the left-over K tiles
- *           instead of along tile boundaries
+ *           instead of along tile boundaries.  Shapes 31, 32, 33 (64 x 256, 64 x 512, 64 x 128) are the
+ *           staged kernel's: mode 0 = planes of K when the estimate says they pay, 1 = whole tiles,
+ *           2 = planes (LQER_ERR_SHAPE with K of one tile of 256), no mode 3
  *   stages  bit 0 = quantize + T, bit 1 = main product; 0 = both
  * Same contract as lqer_linear_forward otherwise.  Running stage bit 1 alone reuses
  * what an earlier call with bit 0 left in the same workspace - with the same M, path and

@@ -1079,16 +1079,18 @@ static double small_us(const SmallShape& sh, int64_t M, int64_t N, int kp, int w
     return t;
 }
 
-// part_bytes: room for planes (0: whole tiles only)
-static SmallPick pick_small(int64_t M, int64_t N, int64_t KT, int kp, int w_bits, int64_t part_bytes, int cus) {
+// part_bytes: room for planes (0: whole tiles only).  only: this shape of the staged kernel, in at least min_planes planes
+// (id 0: not to be had).
+static SmallPick pick_small(int64_t M, int64_t N, int64_t KT, int kp, int w_bits, int64_t part_bytes, int cus, int only = 0, int min_planes = 1) {
     SmallPick best{0, 1, (int)KT};
     double best_us = 0.0;
     const SmallShape* shapes = w_bits == 4 ? kSmallShapes4 : kSmallShapes2;
     const int n_shapes = w_bits == 4 ? (kp <= 64 ? 5 : 3) : 3;   // (tiled_kernel's correction is the slower one for larger ranks)
     for (int i = 0; i < n_shapes; ++i) {
         const SmallShape& sh = shapes[i];
+        if (only != 0 && sh.id != only) continue;
         const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-        for (int p = 1; p <= kMaxPlanes && p <= KT; ++p) {
+        for (int p = min_planes; p <= kMaxPlanes && p <= KT; ++p) {
             const int64_t share = (KT + p - 1) / p;
             const int planes = (int)((KT + share - 1) / share);
             if (planes != p) continue;                       // the same planes as a smaller p
@@ -1253,6 +1255,14 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     int mode = variant / 100;
     variant %= 100;
     if (mode < 0 || mode > 3) return hipErrorInvalidValue;
+    if (variant >= 31 && variant <= 33) {
+        // a shape of the staged kernel by force: 0 = planes when the estimate says so, 1 = whole tiles, 2 = planes
+        if (mode == 3) return hipErrorInvalidValue;
+        const int64_t part_bytes = (mode != 1 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
+        const SmallPick pick = pick_small(M, L.N, L.KT, L.kp, L.w_bits, part_bytes, cus, variant, mode == 2 ? 2 : 1);
+        if (pick.id == 0) return hipErrorInvalidValue;       // one K tile, or no room: no planes
+        return L.w_bits == 4 ? launch_staged<4>(a, pick, s) : launch_staged<2>(a, pick, s);
+    }
     if (variant == 0 && mode <= 1 && 2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
         const int64_t part_bytes = (mode == 0 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
         const SmallPick pick = pick_small(M, L.N, L.KT, L.kp, L.w_bits, part_bytes, cus);
