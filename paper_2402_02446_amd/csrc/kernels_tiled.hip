@@ -1045,22 +1045,35 @@ static bool split_pays(const TileShape& sh, int64_t tiles, int64_t KT, int cus) 
 }
 
 // ---- calls that do not fill the chip for long: which tile, how many K planes -------------------------------------------
-// Time model: a workgroup takes `unit[r - 1]` us per K tile when r of them share a compute unit, `round` per round of
-// workgroups, `fixed` per launch; every two chunks of the correction beyond the first two take `tail`; planes take kPlaneUs
-// plus their bytes written and read at kPlaneMBperUs.  Fitted to 1900 timings of these forms (K, N from 640 to 28672, 33 to
-// 2048 tokens, 1 to 16 planes, ranks 24 to 256; mean error 5 % for 4-bit weights, 8 % for 2-bit ones).  Picking by it came
-// within 3 % of the fastest form timed; against the choice before (whole tiles of 128 rows, or pieces) the main product of
-// 4096 x 4096 at 64 tokens takes 17 us instead of 43, 11008 x 4096 at 64 tokens 21 instead of 123, 4112 x 11000 at 203
-// tokens 40 instead of 54, 2-bit 4096 x 4096 with rank 256 at 2048 tokens 83 instead of 104.
-struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed; };
+// Time model, in us: a workgroup takes `unit[r - 1]` per K tile when r of them share a compute unit, `round` more per round of
+// workgroups, `fixed` per launch; every two chunks of the correction beyond the first two take `corr` and `slice` per partial
+// sum of T in each round of workgroups that has them, Y takes `out` per MB; planes take `plane` and `plane_mb` per MB of
+// partial sums written and read.  Fitted to 16000 timings of 1250 calls (K 256 to 14336, N 256 to 28672, 33 to 65536 tokens,
+// ranks 0 to 256): mean error 3 to 8 % a shape.  On 690 other calls its choice was 0.7 % from the fastest form timed on
+// average, within 6 % on 95 % of them and 30 % off at the very worst (11264 x 1555 with rank 256 at 943 tokens, 99 us against
+// 76 in other planes).  With whole tiles of 128 rows
+// or pieces by the estimate above, the main product of 4096 x 4096 at 64 tokens took 43 us, now 17, 11008 x 4096 at 64 tokens
+// 123, now 21, 4112 x 11000 at 203 tokens 54, now 40 (64 x 128), 2-bit 4096 x 4096 with rank 256 at 2048 tokens 104, now 75
+// (64 x 256).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits and large ranks: without
+// them 384 x 27648 with rank 128 at 4627 tokens took 276 us, now 241, 2-bit 592 x 912 at 63752 tokens 168, now 142.
+struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed, corr, slice, out, plane, plane_mb; };
 static const SmallShape kSmallShapes4[] = {
-    {33, 64, 128, 2, {1.20, 1.97}, 2.5, 6.4}, {31, 64, 256, 2, {1.96, 3.21}, 1.4, 7.6}, {32, 64, 512, 1, {2.96, 0.0}, 4.3, 6.4},
-    {11, 128, 512, 1, {4.72, 0.0}, 7.1, 6.3}, {12, 128, 256, 2, {3.41, 5.43}, 4.9, 4.4},          // tiled_kernel, whole tiles
+    {33, 64, 128, 2, {1.16, 1.84}, 2.4, 6.6, 1.6, 0.57, 0.055, 3.9, 0.122}, {31, 64, 256, 2, {1.89, 3.00}, 1.0, 7.4, 2.5, 0.62, 0.186, 4.2, 0.149},
+    {32, 64, 512, 1, {3.00, 0.0}, 2.6, 6.1, 3.4, 0.41, 0.202, 4.4, 0.157},
+    {11, 128, 512, 1, {4.71, 0.0}, 2.9, 6.6, 4.5, 1.08, 0.214, 0.0, 0.0}, {12, 128, 256, 2, {3.17, 5.40}, 0.0, 8.1, 3.1, 2.24, 0.200, 0.0, 0.0},  // tiled_kernel, whole tiles
 };
 static const SmallShape kSmallShapes2[] = {
-    {33, 64, 128, 2, {1.57, 2.47}, 0.8, 4.6}, {31, 64, 256, 2, {2.28, 3.69}, 0.0, 7.4}, {32, 64, 512, 1, {3.29, 0.0}, 5.0, 4.0},
+    {33, 64, 128, 2, {1.24, 1.84}, 2.6, 6.7, 0.6, 0.82, 0.076, 3.8, 0.132}, {31, 64, 256, 2, {1.94, 3.01}, 1.1, 7.6, 1.3, 0.89, 0.199, 4.2, 0.155},
+    {32, 64, 512, 1, {2.99, 0.0}, 3.2, 6.6, 2.4, 0.65, 0.180, 3.6, 0.165},
+    {11, 128, 512, 1, {4.50, 0.0}, 3.4, 8.0, 3.1, 1.59, 0.197, 0.0, 0.0}, {12, 128, 256, 2, {3.17, 5.31}, 0.0, 8.8, 1.4, 2.90, 0.197, 0.0, 0.0},
 };
-constexpr double kPlaneUs = 3.1, kPlaneMBperUs = 6.0;
+// The 128 x 512 shape with tiles cut in pieces, for 4 and 2 bits: us per launch, K tile of a piece, K tile and number of whole
+// rounds, piece beyond two, the correction as above.  Whole pieces per tile (300 timings, 5 %), and equal shares, whose
+// estimate is the rougher one (250 timings, 6 %) and counts only where the launch is long enough for them to pay.
+struct SmallPieces { double fixed, share, unit, round, piece, corr, slice; };
+static const SmallPieces kSmallWhole[2] = {{24.8, 5.64, 5.07, 11.7, 3.6, 4.4, 1.35}, {24.4, 5.46, 4.95, 11.1, 3.9, 4.2, 1.32}};
+static const SmallPieces kSmallShares[2] = {{21.0, 6.24, 6.10, 11.5, 0.0, 3.2, 2.0}, {18.9, 6.16, 6.16, 7.6, 0.0, 2.9, 1.96}};
+constexpr double kSharesFlops = 6e10;
 constexpr int kMaxPlanes = 16;
 // Above this many operations the chip is full long enough to lower its clock, which this model does not know; the estimate
 // above is calibrated there (8192 x 28672 at 2048 tokens: its choice 714 us, this model's 770 us; below the line, e.g.
@@ -1069,42 +1082,47 @@ constexpr double kSmallFlops = 1.5e11;
 
 struct SmallPick { int id, planes, share; };      // share: K tiles per plane; planes 0: tiled_kernel in pieces
 
-static double small_us(const SmallShape& sh, int64_t M, int64_t N, int kp, int w_bits, int64_t tiles, int planes, int64_t share, int cus) {
+// pairs of correction chunks beyond the first
+static int more_pairs(int kp) { return kp > 64 ? (kp + 63) / 64 - 1 : 0; }
+
+static double small_us(const SmallShape& sh, const Layer& L, int64_t M, int S, int64_t tiles, int planes, int64_t share, int cus) {
     const int64_t wgs = tiles * planes, per_round = (int64_t)cus * sh.resident;
     const int64_t full = wgs / per_round, rest = wgs - full * per_round;
-    double t = sh.fixed + (double)full * (sh.unit[sh.resident - 1] * (double)share + sh.round);
-    if (rest > 0) t += sh.unit[(rest + cus - 1) / cus - 1] * (double)share + sh.round;
-    if (kp > 64) t += (double)((kp + 63) / 64 - 1) * (w_bits == 4 ? 7.0 : 5.0);
-    if (planes > 1) t += kPlaneUs + (double)planes * (double)M * (double)plane_ld(N) * 8e-6 / kPlaneMBperUs;
+    const int64_t rounds = full + (rest > 0 ? 1 : 0), corr_rounds = (tiles + per_round - 1) / per_round;   // (one plane of a tile has the correction)
+    double t = sh.fixed + (double)full * sh.unit[sh.resident - 1] * (double)share + (double)rounds * sh.round + sh.out * (double)M * (double)L.N * 4e-6;
+    if (rest > 0) t += sh.unit[(rest + cus - 1) / cus - 1] * (double)share;
+    t += more_pairs(L.kp) * (double)corr_rounds * (sh.corr + sh.slice * (double)S);
+    if (planes > 1) t += sh.plane + sh.plane_mb * (double)planes * (double)M * (double)plane_ld(L.N) * 8e-6;
     return t;
 }
 
-// part_bytes: room for planes (0: whole tiles only).  only: this shape of the staged kernel, in at least min_planes planes
-// (id 0: not to be had).
-static SmallPick pick_small(int64_t M, int64_t N, int64_t KT, int kp, int w_bits, int64_t part_bytes, int cus, int only = 0, int min_planes = 1) {
-    SmallPick best{0, 1, (int)KT};
+static double pieces_us(const SmallPieces& c, const Layer& L, int S, const Split& sp) {
+    const double rounds = (double)(sp.dp_tiles / sp.grid);
+    double t = c.fixed + c.share * (double)sp.sk_share + rounds * (c.unit * (double)L.KT + c.round);
+    if (sp.aligned) t += c.piece * (double)(sp.sk_tile_units / sp.sk_share - 2);
+    return t + more_pairs(L.kp) * (rounds + 1.0) * (c.corr + c.slice * (double)S);
+}
+
+// S: partial sums of T.  part_bytes: room for planes (0: whole tiles only).  only: this shape of the staged kernel, in at
+// least min_planes planes (id 0: not to be had).
+static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus, int only = 0, int min_planes = 1) {
+    SmallPick best{0, 1, (int)L.KT};
     double best_us = 0.0;
-    const SmallShape* shapes = w_bits == 4 ? kSmallShapes4 : kSmallShapes2;
-    const int n_shapes = w_bits == 4 ? (kp <= 64 ? 5 : 3) : 3;   // (tiled_kernel's correction is the slower one for larger ranks)
-    for (int i = 0; i < n_shapes; ++i) {
-        const SmallShape& sh = shapes[i];
+    for (const SmallShape& sh : L.w_bits == 4 ? kSmallShapes4 : kSmallShapes2) {
         if (only != 0 && sh.id != only) continue;
-        const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-        for (int p = min_planes; p <= kMaxPlanes && p <= KT; ++p) {
-            const int64_t share = (KT + p - 1) / p;
-            const int planes = (int)((KT + share - 1) / share);
+        const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((L.N + sh.bn - 1) / sh.bn);
+        for (int p = min_planes; p <= kMaxPlanes && p <= L.KT; ++p) {
+            const int64_t share = (L.KT + p - 1) / p;
+            const int planes = (int)((L.KT + share - 1) / share);
             if (planes != p) continue;                       // the same planes as a smaller p
-            if (p > 1 && (sh.bm == 128 || (int64_t)p * M * plane_ld(N) * 4 > part_bytes)) continue;
-            const double us = small_us(sh, M, N, kp, w_bits, tiles, planes, share, cus);
+            if (p > 1 && (sh.bm == 128 || (int64_t)p * M * plane_ld(L.N) * 4 > part_bytes)) continue;
+            const double us = small_us(sh, L, M, S, tiles, planes, share, cus);
             if (best.id == 0 || us < best_us) { best = SmallPick{sh.id, planes, (int)share}; best_us = us; }
         }
         if (sh.id == 11 && part_bytes > 0) {
-            // the same shape with every tile in a whole number of pieces: 26 timings within 7 % (2504 tokens of 8128 x 1602:
-            // 92 us against 102 us of the fastest planes)
-            const Split sp = split_tiles(tiles, KT, cus, true);
-            if (sp.sk_units == 0 || !sp.aligned) continue;
-            const double us = (double)(sp.dp_tiles / sp.grid) * (sh.unit[0] * (double)KT + sh.round) + 5.66 * (double)sp.sk_share + 25.9 +
-                              4.2 * (double)(sp.sk_tile_units / sp.sk_share - 2);
+            const Split sp = split_tiles(tiles, L.KT, cus, true);
+            if (sp.sk_units == 0 || (!sp.aligned && 2.0 * (double)M * (double)L.N * (double)L.K < kSharesFlops)) continue;
+            const double us = pieces_us((sp.aligned ? kSmallWhole : kSmallShares)[L.w_bits == 4 ? 0 : 1], L, S, sp);
             if (us < best_us) { best = SmallPick{11, 0, (int)sp.sk_share}; best_us = us; }
         }
     }
@@ -1259,13 +1277,13 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
         // a shape of the staged kernel by force: 0 = planes when the estimate says so, 1 = whole tiles, 2 = planes
         if (mode == 3) return hipErrorInvalidValue;
         const int64_t part_bytes = (mode != 1 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
-        const SmallPick pick = pick_small(M, L.N, L.KT, L.kp, L.w_bits, part_bytes, cus, variant, mode == 2 ? 2 : 1);
+        const SmallPick pick = pick_small(L, M, ws.S, part_bytes, cus, variant, mode == 2 ? 2 : 1);
         if (pick.id == 0) return hipErrorInvalidValue;       // one K tile, or no room: no planes
         return L.w_bits == 4 ? launch_staged<4>(a, pick, s) : launch_staged<2>(a, pick, s);
     }
     if (variant == 0 && mode <= 1 && 2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
         const int64_t part_bytes = (mode == 0 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
-        const SmallPick pick = pick_small(M, L.N, L.KT, L.kp, L.w_bits, part_bytes, cus);
+        const SmallPick pick = pick_small(L, M, ws.S, part_bytes, cus);
         if (pick.id > 12) return L.w_bits == 4 ? launch_staged<4>(a, pick, s) : launch_staged<2>(a, pick, s);
         variant = pick.id;                                   // the launches below: tiles whole, or cut if the instance can
         mode = pick.planes == 0 ? 4 : 1;

@@ -112,3 +112,19 @@ def test_large_rank_is_summed_in_short_chains(w_bits):
     Y = binding.lqer_linear_forward(h, torch.from_numpy(X).cuda()).cpu().numpy()[:, cols]
     assert_forward_matches(Y, X, layer, cols=cols, tol=3.0e-7)
     h.free()
+
+
+# Many tokens on a small layer: tiles of 128 rows are the faster ones there, also with a rank above 64 and with 2-bit weights
+# (384 x 2816 with rank 256 at 20710 tokens 147 us against 169, 2-bit 592 x 912 at 63752 tokens 142 against 168).  The two
+# kernels add the correction at different ends, which tells their results apart.
+@pytest.mark.parametrize("M,K,N,k,w_bits", [(20710, 384, 2816, 256, 4), (63752, 592, 912, 64, 2)])
+def test_many_tokens_take_tiles_of_128_rows(M, K, N, k, w_bits):
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, _ = oracle_layer_big(K, N, k, seed=M, w_bits=w_bits)
+    h = upload(layer)
+    X = torch.randn((M, K), generator=torch.Generator(device="cuda").manual_seed(M), device="cuda")
+    Y = binding.lqer_linear_forward(h, X)
+    same = {v for v in (111, 112, 211, 131, 132, 133) if torch.equal(Y, binding.lqer_linear_forward_ex(h, X, path=2, variant=v))}
+    assert same & {111, 112, 211} and not same & {131, 132, 133}, same
+    h.free()
