@@ -168,7 +168,9 @@ int lqer_layer_free(lqer_layer* layer);
  *   workspace_dev  device scratch of at least lqer_linear_workspace_bytes(layer, M)
  *                  bytes, 256-byte aligned, caller-owned; its contents are scratch.
  *                  (lqer_linear_workspace_bytes_ex: the same for a forced path of lqer_linear_forward_ex,
- *                  0 = the automatic one; a few hundred KiB for small M, 64 MiB more for the tiled kernel)
+ *                  0 = the automatic one; a few hundred KiB for small M, 64 MiB more for the tiled kernel).
+ *                  With 33 to 64 tokens and more than 16352 columns, up to rank 64, what path 1 needs is
+ *                  enough: the call is then streamed where it would otherwise be tiled.
  * Steps, all in this library's kernels: quantize X to MXINT8 (Sec. 4.1), T = X_q A_k,
  * Y = X_q W_q + T B_k accumulated in fp32 in one pass over Y.  M == 0 is a no-op.
  * Calls on different streams need distinct workspaces.  The library allocates nothing here,
@@ -300,7 +302,8 @@ int lqer_quantize_int8_token(const float* x_dev, int64_t rows, int64_t cols, int
  * inside the library, 32 MiB on every GPU the library is used on, held until the process ends.
  *   - Sizes whose scratch need exceeds 32 MiB return LQER_ERR_WORKSPACE before anything is launched
  *     (the need is about 2 (M + 255) (K + 128) bytes for more than 32 tokens - e.g. M = 1024 at
- *     K = 8192 fits, M = 4096 does not - and well under 2 MiB up to 32 tokens).
+ *     K = 8192 fits, M = 4096 does not - and well under 2 MiB up to 32 tokens; with 33 to 64 tokens and
+ *     more than 16352 columns, up to rank 64, calls beyond that are streamed and need a quarter of it).
  *   - The call allocates and frees nothing and synchronises nothing.  Its first use on a device looks
  *     up the address of that device's array (with that device current): make one call outside any
  *     graph capture first.

@@ -348,13 +348,26 @@ static Workspace plan_workspace(const Layer& L, int64_t M, int path, void* base,
     return ws;
 }
 
+// 33 to 64 tokens: layers wide enough for the streaming kernel's form with two blocks of 32 per wavefront (with ranks above
+// 64 the T rows of 64 tokens do not fit its LDS)
+static bool stream_takes_64(const Layer& L, int64_t M) {
+    return L.format == 0 && M > 32 && M <= stream_max_rows() && L.N32 >= 512 && L.kp <= 64;
+}
+
 static int pick_path(const Layer& L, int64_t M) {
-    if (L.format == 1) return 3;                     // the scaled-integer variant has one kernel for every token count
-    // The streaming kernel takes up to 32 tokens.  Its form for 33 to 64 (two blocks of 32 per wavefront) is reached by
-    // forcing the path only: the tiled path's staged kernel is faster on every layer measured (whole step, 33 / 64 tokens:
-    // 8192 x 28672 58 / 63 against 64 / 67 us, 4096 x 16384 30 / 32 against 33 / 34, 11008 x 20000 51 / 57 against 76 / 78).
+    if (L.format == 1) return 3;                     // the scaled-integer variant has kernels of its own
+    // The streaming kernel takes up to 32 tokens.  For 33 to 64 the tiled path's staged kernel is the faster one on every layer
+    // measured (whole step, 33 / 64 tokens: 8192 x 28672 58 / 63 against 64 / 67 us, 4096 x 16384 30 / 32 against 33 / 34,
+    // 11008 x 20000 51 / 57 against 76 / 78).
     if (M <= 32) return 1;
     return 2;
+}
+
+// The path of a call that forces none, with this much workspace: where the tiled plan does not fit, the streaming kernel
+// still takes what it can.
+static int pick_path_in(const Layer& L, int64_t M, size_t ws_bytes, bool with_slots) {
+    const int path = pick_path(L, M);
+    return path == 2 && stream_takes_64(L, M) && plan_workspace(L, M, 2, nullptr, with_slots).bytes > ws_bytes ? 1 : path;
 }
 
 static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, const int8_t* Xc,
@@ -396,7 +409,8 @@ static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, co
     int variant = opts ? opts->variant : 0;
     int stages = opts ? opts->stages : 0;
     if (path < 0 || path > 2 || (stages & ~3) != 0) return LQER_ERR_SHAPE;
-    if (path == 0) path = pick_path(L, M);
+    // (a shape of the streaming kernel names its path wherever the automatic choice may be either)
+    if (path == 0) path = (variant >= 10000 && stream_takes_64(L, M)) ? 1 : pick_path_in(L, M, ws_bytes, with_slots);
     if (path == 1 && M > stream_max_rows()) return LQER_ERR_SHAPE;
     // a pair of workgroups completes its sum only in memory: with MXINT8 output take the unpaired shape
     if (requant && path == 1 && variant == 0 && stream_variant_adds_into_y(stream_variant(L, M, 0)))
@@ -487,17 +501,18 @@ static int forward_stream_run(const lqer_layer* const* layers, int n, const floa
     return LQER_OK;
 }
 
-// What any layer of the group needs alone: the least a call takes.
+// The least a call takes: what any layer of the group needs alone on the path that needs less, and one plan for the group
+// where none of them can be streamed.
 static size_t shared_least_bytes(const lqer_layer* const* layers, int n, int64_t M) {
     size_t need = 0;
+    bool all_tiled = true;
     for (int i = 0; i < n; ++i) {
-        const size_t b = plan_workspace(layers[i]->L, M, pick_path(layers[i]->L, M), nullptr).bytes;
-        if (b > need) need = b;
+        const Layer& L = layers[i]->L;
+        const int path = stream_takes_64(L, M) ? 1 : pick_path(L, M);
+        all_tiled = all_tiled && path == 2;
+        need = std::max(need, plan_workspace(L, M, path, nullptr).bytes);
     }
-    if (shared_group_tiled(layers, n, M)) {
-        const size_t b = plan_workspace(shared_plan_layer(layers, n), M, 2, nullptr).bytes;
-        if (b > need) need = b;
-    }
+    if (all_tiled) need = std::max(need, plan_workspace(shared_plan_layer(layers, n), M, 2, nullptr).bytes);
     return need;
 }
 
@@ -680,11 +695,13 @@ int lqer_linear_forward_requant(const lqer_layer* layer, const float* X_dev, int
 
 size_t lqer_linear_shared_workspace_bytes(const lqer_layer* const* layers, int n_layers, int64_t M) {
     if (!shared_group_ok(layers, n_layers) || M <= 0) return 0;
-    size_t need = shared_least_bytes(layers, n_layers, M);
+    if (shared_group_tiled(layers, n_layers, M)) return plan_workspace(shared_plan_layer(layers, n_layers), M, 2, nullptr).bytes;
+    size_t need = 0;
+    for (int i = 0; i < n_layers; ++i)
+        need = std::max(need, plan_workspace(layers[i]->L, M, pick_path(layers[i]->L, M), nullptr).bytes);
     for (int i = 0; i < n_layers;) {
         const int k = stream_run_length(layers, n_layers, i, M);
-        const size_t b = k > 1 ? plan_stream_run(layers + i, k, M, nullptr, nullptr, nullptr) : 0;
-        if (b > need) need = b;
+        if (k > 1) need = std::max(need, plan_stream_run(layers + i, k, M, nullptr, nullptr, nullptr));
         i += k;
     }
     return need;
@@ -706,7 +723,9 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
         if (ldy[i] < layers[i]->L.N || (ldy[i] & 3) != 0 || ((uintptr_t)Y_dev[i] & 15) != 0) return LQER_ERR_SHAPE;
     if (!workspace_dev || ((uintptr_t)workspace_dev & 255) != 0) return LQER_ERR_WORKSPACE;
     if (workspace_bytes < shared_least_bytes(layers, n_layers, M)) return LQER_ERR_WORKSPACE;
-    if (!shared_group_tiled(layers, n_layers, M)) {
+    const bool tiled = shared_group_tiled(layers, n_layers, M) &&
+                       plan_workspace(shared_plan_layer(layers, n_layers), M, 2, nullptr).bytes <= workspace_bytes;
+    if (!tiled) {
         // few tokens: layers that take the same shape of the streaming kernel share their launches, if the workspace has room
         // for all their T; the others are full calls
         for (int i = 0; i < n_layers;) {

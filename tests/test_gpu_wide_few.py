@@ -1,0 +1,61 @@
+"""33 to 64 tokens on layers of at least 512 column groups: calls that the streaming kernel takes are taken whatever the
+automatic choice needs - with the workspace of the streaming path, on the static scratch from K of 65000 on, with a shape of
+the streaming kernel and no path forced - and give that path's bits."""
+import numpy as np
+import pytest
+
+from oracle import factors
+from paper_2402_02446_amd import synth
+from helpers import upload
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(K, N, k, w_bits=4, seed=0):
+    return upload(factors.PackedLayer(**synth.random_packed_layer(np.random.default_rng(seed), K, N, k, w_bits)))
+
+
+@pytest.mark.parametrize("K,N,k,w_bits", [(4352, 16384, 16, 4), (528, 16353, 0, 4), (528, 16400, 64, 2)])
+@pytest.mark.parametrize("M", [33, 64])
+def test_workspace_of_the_streaming_path_is_enough(M, K, N, k, w_bits):
+    import torch
+    from paper_2402_02446_amd import binding
+    h, narrow = _layer(K, N, k, w_bits), _layer(K, 96, 16)
+    X = torch.randn((M, K), device="cuda")
+    out = lambda n: torch.full((M, (n + 3) // 4 * 4), 7.0, device="cuda")[:, :n]
+    want = binding.lqer_linear_forward_ex(h, X, Y=out(N), path=1)
+    ws = torch.full((binding.lqer_linear_workspace_bytes(h, M, 1),), 255, dtype=torch.uint8, device="cuda")
+    assert torch.equal(binding.lqer_linear_forward(h, X, Y=out(N), workspace=ws), want)
+    Xc, Xe = binding.lqer_quantize_mx(X, 8)
+    assert torch.equal(binding.lqer_linear_forward_q(h, Xc, Xe, Y=out(N), workspace=ws), want)
+    assert torch.equal(binding.lqer_linear_forward_ex(h, X, Y=out(N), variant=11421), want)          # path 0: the index names it
+    if N % 16 == 0:
+        a, b = (binding.lqer_linear_forward_requant(h, X, workspace=w, path=p) for w, p in ((ws, 0), (None, 1)))
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    Ys = binding.lqer_linear_forward_shared([h, h], X, Ys=[out(N), out(N)], workspace=ws)
+    assert torch.equal(Ys[0], want) and torch.equal(Ys[1], want)
+    # beside a layer that needs the tiled path, its workspace is enough
+    wn = torch.full((max(ws.numel(), binding.lqer_linear_workspace_bytes(narrow, M)),), 255, dtype=torch.uint8, device="cuda")
+    Ys = binding.lqer_linear_forward_shared([narrow, h], X, Ys=[out(96), out(N)], workspace=wn)
+    assert torch.equal(Ys[0], binding.lqer_linear_forward(narrow, X)) and Ys[1].isfinite().all()
+    with pytest.raises(binding.LqerError):
+        binding.lqer_linear_forward(h, X, workspace=ws[:-256])
+    with pytest.raises(binding.LqerError):
+        binding.lqer_linear_forward_shared([h, h], X, Ys=[out(N), out(N)], workspace=ws[:-256])
+    full = binding.lqer_linear_shared_workspace_bytes([h, h], M)
+    Ys = binding.lqer_linear_forward_shared([h, h], X, Ys=[out(N), out(N)], workspace=torch.full((full,), 255, dtype=torch.uint8, device="cuda"))
+    own = binding.lqer_linear_forward(h, X, Y=out(N))
+    assert torch.equal(Ys[0], own) and torch.equal(Ys[1], own)
+    h.free()
+    narrow.free()
+
+
+def test_static_scratch_beyond_the_tiled_plan():
+    import torch
+    from paper_2402_02446_amd import binding
+    K, N, M = 66048, 16384, 64                                   # 256 rows of 66048 bf16 are more than 32 MiB
+    h = _layer(K, N, 0, w_bits=2)
+    X = torch.randn((M, K), device="cuda")
+    Y = binding.lqer_linear_forward_static(h, X)
+    assert torch.equal(Y, binding.lqer_linear_forward_ex(h, X, path=1))
+    h.free()
