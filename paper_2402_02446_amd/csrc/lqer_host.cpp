@@ -356,10 +356,14 @@ static bool stream_takes_64(const Layer& L, int64_t M) {
 
 static int pick_path(const Layer& L, int64_t M) {
     if (L.format == 1) return 3;                     // the scaled-integer variant has kernels of its own
-    // The streaming kernel takes up to 32 tokens.  For 33 to 64 the tiled path's staged kernel is the faster one on every layer
-    // measured (whole step, 33 / 64 tokens: 8192 x 28672 58 / 63 against 64 / 67 us, 4096 x 16384 30 / 32 against 33 / 34,
-    // 11008 x 20000 51 / 57 against 76 / 78).
+    // The streaming kernel takes up to 32 tokens.  For 33 to 64 its time goes with K alone while its workgroups of four column
+    // groups are one round of the chip (16384 to 32768 columns: 10 us and 1.5 per K tile, whole call at rank 32), the tiled
+    // path's with K N and with the projection of T, which at so few tokens is most of its preparation.  Streamed / tiled, 48
+    // tokens: 2048 x 28672 rank 32 22 / 26 us, 4096 x 28672 34 / 35, 8192 x 28672 57 / 50, 4096 x 16384 rank 0 31 / 24,
+    // rank 32 32 / 30, rank 64 33 / 35, 2048 x 40000 37 / 31; 2-bit ones within 2 us of these.  The line is 0.2 % from the
+    // faster one on average over 370 such calls of both widths, 14 % at worst; always tiled 5 %, always streamed 9 %.
     if (M <= 32) return 1;
+    if (stream_takes_64(L, M) && L.kp > 0 && (L.N32 + 3) / 4 <= compute_units() && L.KT * (184 - L.kp) <= 4 * L.N32) return 1;
     return 2;
 }
 

@@ -59,3 +59,15 @@ def test_static_scratch_beyond_the_tiled_plan():
     Y = binding.lqer_linear_forward_static(h, X)
     assert torch.equal(Y, binding.lqer_linear_forward_ex(h, X, path=1))
     h.free()
+
+
+# The streaming kernel's time goes with K alone up to 32768 columns, the tiled path's with K N and the rank: short K and
+# larger ranks are streamed (2048 x 28672, rank 32, 48 tokens: 22 us against 26), the others tiled (4352 x 16384, rank 16: 34
+# against 30; 528 x 40000: 18 against 15).
+@pytest.mark.parametrize("K,N,k,path", [(528, 16384, 16, 1), (2048, 16384, 64, 1), (2048, 16384, 0, 2), (4352, 16384, 16, 2), (528, 40000, 32, 2)])
+@pytest.mark.parametrize("w_bits", [4, 2])
+def test_which_wide_layers_are_streamed(K, N, k, path, w_bits):
+    from paper_2402_02446_amd import binding
+    h = _layer(K, N, k, w_bits)
+    assert [binding.lqer_linear_path(h, M) for M in (32, 33, 64, 65)] == [1, path, path, 2]
+    h.free()
