@@ -435,14 +435,76 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
         group(lds + st);
         st = next_stage(st);
     }
-    fold(acc[2], pend[0], pend_sc);
-    fold(acc[3], pend[1], pend_sc);
-
     // ---- token scales, rank-k correction (by one plane), store --------------------------------------------------
     const bool tail = a.kp16 > 0 && plane == a.tail_plane;
     const int64_t n = cg * 32 + t;
     const float sb = tail ? a.Bsc[cgc * 32 + t] : 0.f;
     float* dst = a.Out + (int64_t)plane * a.out_z_stride + n;
+    // Its operands: wavefront w asks for T of token tile w (the others need the same tiles: split into two bf16 terms once,
+    // through LDS) and for B_k's codes of its own columns, all rank blocks in flight together.  With every wavefront fetching
+    // and splitting all four tiles block by block, 16 tokens of 512 x 2048 at rank 128 took 30 us by this path, now 24, and
+    // 1024 tokens of 4096 x 4096 at rank 64 55, now 52.
+    constexpr int RB = 8;                            // rank blocks of 16
+    f32x4 p[RB][2];
+    u32x4 bw[RB];
+    if (tail) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb >= a.kp16) continue;
+            const float* src = a.T + (m0 + wave * 32 + t) * a.ldt + rb * 16 + 8 * hh;
+            p[rb][0] = *reinterpret_cast<const f32x4*>(src);
+            p[rb][1] = *reinterpret_cast<const f32x4*>(src + 4);
+            bw[rb] = *reinterpret_cast<const u32x4*>(a.Bt + (cgc * a.kp16 + rb) * kBRecordBytes + t * 16);
+        }
+    }
+    fold(acc[2], pend[0], pend_sc);
+    fold(acc[3], pend[1], pend_sc);
+    f32x16 ta[4];
+#pragma unroll
+    for (int tm = 0; tm < 4; ++tm)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ta[tm][r] = 0.f;
+    if (tail) {                                      // (the same for the whole workgroup)
+        static_assert(RB * 2 * 4 * 1024 <= kIntStages * kIntStage, "[rank block][term][token tile][64 lanes][16 B]");
+        __syncthreads();                             // every wavefront is done with the stages
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb >= a.kp16) continue;
+            Frag hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t h2[2], l2[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float v = p[rb][e >> 1][(2 * e + j) & 3];
+                    const uint32_t hb = f32_bits(v) & 0xFFFF0000u;
+                    h2[j] = hb >> 16;
+                    l2[j] = f32_bits(v - f32_from_bits(hb)) >> 16;
+                }
+                hi.u[e] = h2[0] | (h2[1] << 16);
+                lo.u[e] = l2[0] | (l2[1] << 16);
+            }
+            *reinterpret_cast<u32x4*>(lds + (((rb * 2 + 0) * 4 + wave) * 64 + lane) * 16) = hi.u;
+            *reinterpret_cast<u32x4*>(lds + (((rb * 2 + 1) * 4 + wave) * 64 + lane) * 16) = lo.u;
+        }
+        __syncthreads();
+        // one 32x32x16 step per rank block and bf16 term of T: lane half hh takes ranks 8 hh .. + 7 of the block on both sides
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            if (rb >= a.kp16) continue;
+            Frag f0, f1;
+            int8x16_to_frags(bw[rb], 1.0f, f0, f1);
+            const Frag bf = hh ? f1 : f0;
+#pragma unroll
+            for (int term = 0; term < 2; ++term)
+#pragma unroll
+                for (int tm = 0; tm < 4; ++tm) {
+                    Frag x;
+                    x.u = *reinterpret_cast<const u32x4*>(lds + (((rb * 2 + term) * 4 + tm) * 64 + lane) * 16);
+                    ta[tm] = mfma32(x.v, bf.v, ta[tm]);
+                }
+        }
+    }
 #pragma unroll
     for (int tm = 0; tm < 4; ++tm) {
         const int64_t row0 = m0 + tm * 32;
@@ -453,35 +515,8 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
             for (int j = 0; j < 4; ++j) acc[tm][4 * q + j] *= s4[j];
         }
         if (tail) {
-            // one 32x32x16 step per rank block and bf16 term of T: lane half hh takes ranks 8 hh .. + 7 of the block on both sides
-            f32x16 ta;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) ta[r] = 0.f;
-            for (int rb = 0; rb < a.kp16; ++rb) {
-                const float* src = a.T + (row0 + t) * a.ldt + rb * 16 + 8 * hh;
-                const f32x4 p0 = *reinterpret_cast<const f32x4*>(src), p1 = *reinterpret_cast<const f32x4*>(src + 4);
-                const uint8_t* rec = a.Bt + (cgc * a.kp16 + rb) * kBRecordBytes;
-                Frag hi, lo, f0, f1;
-                int8x16_to_frags(*reinterpret_cast<const u32x4*>(rec + t * 16), 1.0f, f0, f1);
-                const Frag bf = hh ? f1 : f0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    uint32_t h2[2], l2[2];
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const float v = e < 2 ? p0[(2 * e + j) & 3] : p1[(2 * e + j) & 3];
-                        const uint32_t hb = f32_bits(v) & 0xFFFF0000u;
-                        h2[j] = hb >> 16;
-                        l2[j] = f32_bits(v - f32_from_bits(hb)) >> 16;
-                    }
-                    hi.u[e] = h2[0] | (h2[1] << 16);
-                    lo.u[e] = l2[0] | (l2[1] << 16);
-                }
-                ta = mfma32(hi.v, bf.v, ta);
-                ta = mfma32(lo.v, bf.v, ta);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tm][r] += ta[r] * sb;
+            for (int r = 0; r < 16; ++r) acc[tm][r] += ta[tm][r] * sb;
         }
         if (cg >= a.N32 || n >= a.N) continue;
 #pragma unroll

@@ -1,6 +1,7 @@
 """The INT variant's few-token launches: edges of the blocks of 32 tokens, column counts around a workgroup's 32, K groups
-that slices, wavefronts and register sets do not divide, ranks to 128, all-zero tokens; against the oracle, and the same bits
-on a second run with other contents in the workspace."""
+that slices, wavefronts and register sets do not divide, ranks to 128, all-zero tokens; its general launches on the fewest
+tokens that take them - K planes of both products, a plane of its own for the correction, ragged row tiles; against the
+oracle, and the same bits on a second run with other contents in the workspace."""
 import numpy as np
 import pytest
 
@@ -13,6 +14,17 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,k", [(1, 128, 33, 16), (4, 1152, 64, 128), (5, 7296, 65, 33), (17, 4224, 100, 8), (31, 11008, 96, 32),
                                      (32, 2304, 31, 0), (33, 4096, 1040, 64), (128, 1024, 528, 100)])
 def test_few_tokens(M, K, N, k):
+    _run(M, K, N, k)
+
+
+# more than 128 tokens, or more work than the few-token launches take; 7 ranks blocks of 16, an odd number, and 8
+@pytest.mark.parametrize("M,K,N,k", [(129, 2304, 528, 33), (200, 4096, 1100, 64), (100, 11008, 4096, 32), (130, 512, 300, 128),
+                                     (257, 1024, 2080, 112), (70, 8192, 11008, 16)])
+def test_general_launches(M, K, N, k):
+    _run(M, K, N, k)
+
+
+def _run(M, K, N, k):
     import torch
     from paper_2402_02446_amd import binding
     layer, ch = _standin_layer(K, N, min(k, N), seed=K + M, n_outlier=4)
