@@ -27,11 +27,12 @@ struct IntGemmArgs {
     const uint8_t* Bt; const float* Bsc;
     int kp16;
     int tail_plane;
+    bool planes;
 };
 hipError_t launch_int_projection(const IntGemmArgs& a, hipStream_t s);
 hipError_t launch_int_main(const IntGemmArgs& a, hipStream_t s);
 hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_stride, int64_t M, int64_t N, int64_t ldp,
-                                    float* Y, int64_t ldy, hipStream_t s);
+                                    float* Y, int64_t ldy, const float* Xs, int tail, hipStream_t s);
 
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -157,24 +158,26 @@ int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y
     if (L.kp > 0) {
         a.Wt = L.At; a.Wsc = L.Asc; a.N = ldt; a.N32 = L.kp32; a.Out = T; a.ldo = ldt;
         a.g_per_z = (a.G + S - 1) / S; a.out_z_stride = mp * ldt;
-        if (launch_int_projection(a, s) != hipSuccess) return LQER_ERR_HIP;
         const int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z);
+        a.planes = planes > 1;
+        if (launch_int_projection(a, s) != hipSuccess) return LQER_ERR_HIP;
         // the planes' partial T are added up (in plane order, into the first) before the main kernel reads them: inside
         // it that sum would be a chain of dependent loads in front of every rank block
-        if (planes > 1 && launch_int_reduce_planes(T, planes, mp * ldt, mp, ldt, ldt, T, ldt, s) != hipSuccess) return LQER_ERR_HIP;
+        if (planes > 1 && launch_int_reduce_planes(T, planes, mp * ldt, mp, ldt, ldt, T, ldt, Xs, 0, s) != hipSuccess) return LQER_ERR_HIP;
     }
     a.Wt = L.Wt; a.Wsc = L.Wsc; a.N = L.N; a.N32 = L.N32; a.Out = Y; a.ldo = ldy;
     a.g_per_z = a.G; a.out_z_stride = 0;
     a.T = T; a.Bt = L.Bt; a.Bsc = L.Bsc; a.kp16 = L.kp16;
     const int sm = main_planes(L, M);
+    a.planes = sm > 1;
     if (sm > 1) {
         float* P = (float*)((uint8_t*)T + round_up((int64_t)S * mp * ldt * 4, 256));
         const int64_t ldp = round_up(L.N, 4);
         a.Out = P; a.ldo = ldp; a.g_per_z = (a.G + sm - 1) / sm; a.out_z_stride = M * ldp;
-        int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z);
-        if (L.kp > 0) a.tail_plane = planes++;
+        const int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z), tail = L.kp > 0 ? 1 : 0;
+        if (tail) a.tail_plane = planes;
         if (launch_int_main(a, s) != hipSuccess) return LQER_ERR_HIP;
-        if (launch_int_reduce_planes(P, planes, M * ldp, M, L.N, ldp, Y, ldy, s) != hipSuccess) return LQER_ERR_HIP;
+        if (launch_int_reduce_planes(P, planes, M * ldp, M, L.N, ldp, Y, ldy, Xs, tail, s) != hipSuccess) return LQER_ERR_HIP;
         return LQER_OK;
     }
     if (launch_int_main(a, s) != hipSuccess) return LQER_ERR_HIP;

@@ -98,6 +98,7 @@ struct IntGemmArgs {
     const uint8_t* Bt; const float* Bsc; // B_k records [N32][kp16][kBRecordBytes], scales [N32 * 32]
     int kp16;
     int tail_plane;                      // plane that adds the correction: 0, or one of its own behind the K planes
+    bool planes;                         // Out is planes of sums: int_reduce_planes_kernel gives them their token scales
 };
 
 __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
@@ -240,12 +241,14 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
     }
 
     // ---- epilogue: token scale, store (padded rows too: the main kernel reads them) ----------------------------------------------------------
+    if (!a.planes) {
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
+        for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
+            for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tm][tn][r] *= st[tm];
+                for (int r = 0; r < 16; ++r) acc[tm][tn][r] *= st[tm];
+    }
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = m0 + wr * 64 + tm * 32 + t;
@@ -508,11 +511,13 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
 #pragma unroll
     for (int tm = 0; tm < 4; ++tm) {
         const int64_t row0 = m0 + tm * 32;
+        if (!a.planes) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 s4 = *reinterpret_cast<const f32x4*>(a.Xs + row0 + 8 * q + 4 * hh);
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 s4 = *reinterpret_cast<const f32x4*>(a.Xs + row0 + 8 * q + 4 * hh);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[tm][4 * q + j] *= s4[j];
+                for (int j = 0; j < 4; ++j) acc[tm][4 * q + j] *= s4[j];
+            }
         }
         if (tail) {
 #pragma unroll
@@ -529,15 +534,20 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
 
 // Few-token calls split the K groups of the projection and of the main product over planes of workgroups, each leaving
 // its share of T or Y in the workspace; this adds the planes in plane order (the same bits on every run).
+// The sum of the K planes gets its token scale here, once (scaled plane by plane, 200 tokens of 512 x 11008 were 3.7e-8 from
+// the 64-bit result, now 2.5e-8, one rounding), and then the correction's plane, if there is one (tail = 1).
 // Y may be the first plane itself (a thread reads all of its elements before it writes them).
 __global__ __launch_bounds__(256) void int_reduce_planes_kernel(const float* P, int planes, int64_t plane_stride,
-                                                                int64_t M, int64_t N, int64_t ldp, float* Y, int64_t ldy) {
+                                                                int64_t M, int64_t N, int64_t ldp, float* Y, int64_t ldy,
+                                                                const float* Xs, int tail) {
     const int64_t n4 = (N + 3) / 4;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= M * n4) return;
     const int64_t r = i / n4, c = 4 * (i - r * n4);
     const float* src = P + r * ldp + c;
-    f32x4 v = *reinterpret_cast<const f32x4*>(src);
+    f32x4 v = *reinterpret_cast<const f32x4*>(src), corr = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (tail != 0) corr = *reinterpret_cast<const f32x4*>(src + planes * plane_stride);
+    const float s = Xs[r];
     for (int z0 = 1; z0 < planes; z0 += 8) {         // eight loads in flight, added in plane order
         f32x4 q[8];
 #pragma unroll
@@ -546,6 +556,7 @@ __global__ __launch_bounds__(256) void int_reduce_planes_kernel(const float* P, 
         for (int j = 0; j < 8; ++j)
             if (z0 + j < planes) v += q[j];
     }
+    v = v * s + corr;
     float* dst = Y + r * ldy + c;
     if (c + 3 < N) {
         *reinterpret_cast<f32x4*>(dst) = v;
@@ -554,10 +565,11 @@ __global__ __launch_bounds__(256) void int_reduce_planes_kernel(const float* P, 
     }
 }
 
+// `planes` K planes, and tail (0 or 1) of the correction behind them
 hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_stride, int64_t M, int64_t N, int64_t ldp,
-                                    float* Y, int64_t ldy, hipStream_t s) {
+                                    float* Y, int64_t ldy, const float* Xs, int tail, hipStream_t s) {
     const int64_t items = M * ((N + 3) / 4);
-    hipLaunchKernelGGL(int_reduce_planes_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, P, planes, plane_stride, M, N, ldp, Y, ldy);
+    hipLaunchKernelGGL(int_reduce_planes_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, P, planes, plane_stride, M, N, ldp, Y, ldy, Xs, tail);
     return hipGetLastError();
 }
 

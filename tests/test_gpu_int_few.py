@@ -44,3 +44,19 @@ def _run(M, K, N, k):
         assert torch.equal(buf[:, :N], first)
     _check(first.cpu().numpy(), X, layer)
     h.free()
+
+
+# Without a correction Y is a sum of K / 128 scaled group sums times one token scale.  One fp32 rounding of it is 2.5e-8 rms
+# (2^-24 / sqrt(3), over a factor of 2 of values); the few additions before are small beside it.  With the scale applied to
+# each of two planes it is 3.7e-8.
+def test_token_scale_is_applied_once():
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, ch = _standin_layer(512, 11008, 0, seed=1)
+    h = _upload(layer)
+    X = synth.gen_activations(np.random.default_rng(1), 200, 512, ch, 50.0)
+    cols = np.arange(0, 11008, 7)
+    Y = binding.lqer_linear_forward(h, torch.from_numpy(X).cuda()).cpu().numpy()[:, cols]
+    err, _ = _check(Y, X, layer, cols)
+    assert err <= 3.0e-8, err
+    h.free()
