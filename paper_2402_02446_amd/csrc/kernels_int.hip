@@ -297,10 +297,12 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t = lane & 31, hh = lane >> 5;
 
-    // workgroup -> K plane and output tile: consecutive positions land on one XCD and walk bands of eight tile rows
+    // workgroup -> K plane and output tile, in bands of eight tile rows.  From 16 tile rows on consecutive positions land on one
+    // XCD, which then shares weights and activations (16384 tokens of 4096 x 4096 455 us, as numbered 461); with fewer the
+    // workgroups of a column's few tiles are close enough as numbered, and 64 tokens of 2048 x 16384 take 22.7 us instead of 27.2.
     const int grid_n = (int)((a.N + BN - 1) / BN), grid_m = (int)((a.M + 127) / 128);
-    int lin;
-    {
+    int lin = blockIdx.x;
+    if (grid_m >= 16) {
         const int nwg = gridDim.x, pid = blockIdx.x;
         const int xcd = pid & 7, local = pid >> 3, per = nwg >> 3, rem = nwg & 7;
         lin = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
