@@ -300,12 +300,15 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
     // workgroup -> K plane and output tile, in bands of eight tile rows.  From 16 tile rows on consecutive positions land on one
     // XCD, which then shares weights and activations (16384 tokens of 4096 x 4096 455 us, as numbered 461); with fewer the
     // workgroups of a column's few tiles are close enough as numbered, and 64 tokens of 2048 x 16384 take 22.7 us instead of 27.2.
+    // (Both numbers, and a select: a branch here or at the token scales below changes the order the compiler gives the loop's
+    // LDS reads and MFMAs, up to 4 % of a prefill call.)
     const int grid_n = (int)((a.N + BN - 1) / BN), grid_m = (int)((a.M + 127) / 128);
-    int lin = blockIdx.x;
-    if (grid_m >= 16) {
+    int lin;
+    {
         const int nwg = gridDim.x, pid = blockIdx.x;
         const int xcd = pid & 7, local = pid >> 3, per = nwg >> 3, rem = nwg & 7;
-        lin = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
+        const int walk = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
+        lin = __builtin_amdgcn_readfirstlane(grid_m >= 16 ? walk : pid);
     }
     const int plane = lin / (grid_m * grid_n);
     lin -= plane * (grid_m * grid_n);
@@ -513,13 +516,12 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
 #pragma unroll
     for (int tm = 0; tm < 4; ++tm) {
         const int64_t row0 = m0 + tm * 32;
-        if (!a.planes) {
+        // (a select, not a branch: see above)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 s4 = *reinterpret_cast<const f32x4*>(a.Xs + row0 + 8 * q + 4 * hh);
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 s4 = *reinterpret_cast<const f32x4*>(a.Xs + row0 + 8 * q + 4 * hh);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[tm][4 * q + j] *= s4[j];
-            }
+            for (int j = 0; j < 4; ++j) acc[tm][4 * q + j] *= a.planes ? 1.0f : s4[j];
         }
         if (tail) {
 #pragma unroll
