@@ -297,9 +297,10 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t = lane & 31, hh = lane >> 5;
 
-    // workgroup -> K plane and output tile, in bands of eight tile rows.  From 16 tile rows on consecutive positions land on one
-    // XCD, which then shares weights and activations (16384 tokens of 4096 x 4096 455 us, as numbered 461); with fewer the
-    // workgroups of a column's few tiles are close enough as numbered, and 64 tokens of 2048 x 16384 take 22.7 us instead of 27.2.
+    // workgroup -> K plane and output tile, in bands of eight tile rows.  Consecutive positions land on one XCD, which then shares
+    // activations or weights - but where one tile row is all there is and its tiles alone fill the chip's XCDs, that only crowds
+    // each XCD's part of the weights: 64 tokens of 2048 x 16384 take 27.2 us so and 22.7 as numbered, of 1920 x 20848 1 to 4 %
+    // more (as numbered everywhere up to 1000 tokens, 50 layers took 1.4 % longer on average, 800 tokens of 11008 x 800 18 %).
     // (Both numbers, and a select: a branch here or at the token scales below changes the order the compiler gives the loop's
     // LDS reads and MFMAs, up to 4 % of a prefill call.)
     const int grid_n = (int)((a.N + BN - 1) / BN), grid_m = (int)((a.M + 127) / 128);
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
         const int nwg = gridDim.x, pid = blockIdx.x;
         const int xcd = pid & 7, local = pid >> 3, per = nwg >> 3, rem = nwg & 7;
         const int walk = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
-        lin = __builtin_amdgcn_readfirstlane(grid_m >= 16 ? walk : pid);
+        lin = __builtin_amdgcn_readfirstlane(grid_m == 1 && grid_n >= 96 ? pid : walk);
     }
     const int plane = lin / (grid_m * grid_n);
     lin -= plane * (grid_m * grid_n);
