@@ -103,10 +103,24 @@ static int main_planes(const Layer& L, int64_t M) {
     return (int)((G + g - 1) / g);
 }
 
-// Few tokens take the two launches of kernels_int_few.hip, 32 tokens per workgroup: one block of them always, more as long
-// as the work is small (blocks x column groups x K groups; us, this form against the general one): 4096 x 4096 at 128 tokens
-// (16384) 26 against 34, 11008 x 4096 at 64 (22016) 38 against 42, at 100 (33024) 54 against 45.
-static bool few_tokens(const Layer& L, int64_t M) { return M <= 32 || (M <= 128 && ((M + 31) / 32) * L.N32 * (L.K / 128) <= 24576); }
+// Up to 128 tokens: the two launches of kernels_int_few.hip, 32 tokens and 32 columns per workgroup, or the general ones,
+// whichever two linear models (us; fitted to 620 timings of both, 128 to 28672 x 512 to 28672, ranks 0 to 128: 7 % and 4 %
+// mean error) say is the faster.  The choice is 0.2 % from the faster one on average, 20 % at worst; the few-token form
+// always 20 %, up to 32 tokens and 24576 workgroups x K groups beyond 7 %: 128 tokens of 512 x 11008 27.5 us by it, 18.5 by
+// the general launches, 32 tokens of 28672 x 1024 63 and 35; 64 tokens of 4096 x 4096 18 and 30.
+static bool few_tokens(const Layer& L, int64_t M) {
+    if (M > 128) return false;
+    const double G = (double)(L.K / 128), rows = (double)std::min<int64_t>(M, 32), kp16 = (double)L.kp16;
+    const int64_t wgs = (M + 31) / 32 * L.N32;
+    const double rounds = (double)((wgs + 255) / 256);
+    const double few = 8.9 + 0.0028 * G * rows + 0.0069 * kp16 * G + 0.00101 * (double)wgs * kp16 +
+                       rounds * (2.13 + 0.029 * G + 0.0030 * G * rows + 0.33 * kp16);
+    const int sm = main_planes(L, M), S = projection_planes(L, M);
+    double general = 10.8 + 0.07 * G + 0.76 * std::ceil(G / sm) + 1.04e-4 * G * (double)((L.N + 127) / 128) + 1.45e-6 * (double)sm * (double)M * (double)L.N;
+    if (sm > 1) general += 3.3;
+    if (L.kp > 0) general += 1.3 + 1.66 * std::ceil(G / S) + 0.51 * kp16;
+    return few < 0.97 * general;
+}
 
 // K groups per slice of its projection: eight slices, and at most seven groups (28 KB of codes beside 32 KB of sums) each
 static int few_slice_groups(const Layer& L) {
@@ -114,24 +128,34 @@ static int few_slice_groups(const Layer& L) {
     return (int)(per < 7 ? per : 7);
 }
 
-size_t int_workspace_bytes(const Layer& L, int64_t M) {
-    if (M <= 0) return 0;
+static size_t few_workspace_bytes(const Layer& L, int64_t M) {
+    const int64_t S = (L.K / 128 + few_slice_groups(L) - 1) / few_slice_groups(L);
+    return (size_t)(round_up(round_up(M, 32) * L.K, 256) + round_up(round_up(M, 128) * 4, 256) + round_up(S * M * (int64_t)L.kp32 * 32 * 4, 256));
+}
+
+static size_t general_workspace_bytes(const Layer& L, int64_t M) {
     const int64_t mp = round_up(M, 128);
-    if (few_tokens(L, M)) {
-        const int64_t S = (L.K / 128 + few_slice_groups(L) - 1) / few_slice_groups(L);
-        return (size_t)(round_up(round_up(M, 32) * L.K, 256) + round_up(mp * 4, 256) + round_up(S * M * (int64_t)L.kp32 * 32 * 4, 256));
-    }
     const int sm = main_planes(L, M);
     return (size_t)(round_up(mp * L.K, 256) + round_up(mp * 4, 256) +
                     round_up((int64_t)projection_planes(L, M) * mp * (int64_t)L.kp32 * 32 * 4, 256) +
                     (sm > 1 ? (int64_t)(sm + 1) * M * round_up(L.N, 4) * 4 : 0));       // (the planes of Y hold the M real rows only)
 }
 
+size_t int_workspace_bytes(const Layer& L, int64_t M) {
+    if (M <= 0) return 0;
+    return few_tokens(L, M) ? few_workspace_bytes(L, M) : general_workspace_bytes(L, M);
+}
+
 int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y, int64_t ldy, void* ws, size_t ws_bytes,
                 hipStream_t s) {
-    if (int_workspace_bytes(L, M) > ws_bytes) return LQER_ERR_WORKSPACE;
+    bool few = few_tokens(L, M);
+    if (int_workspace_bytes(L, M) > ws_bytes) {
+        // up to 128 tokens the other form may fit (a workspace sized for other token counts, or the static scratch)
+        if (M > 128 || (few ? general_workspace_bytes(L, M) : few_workspace_bytes(L, M)) > ws_bytes) return LQER_ERR_WORKSPACE;
+        few = !few;
+    }
     const int64_t mp = round_up(M, 128);
-    if (few_tokens(L, M)) {
+    if (few) {
         IntFewArgs f;
         f.X = X; f.ldx = ldx; f.M = M; f.K = L.K; f.N = L.N; f.N32 = L.N32; f.G = L.K / 128;
         f.Xc = (uint8_t*)ws;

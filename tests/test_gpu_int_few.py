@@ -60,3 +60,26 @@ def test_token_scale_is_applied_once():
     err, _ = _check(Y, X, layer, cols)
     assert err <= 3.0e-8, err
     h.free()
+
+
+# Which launches a call takes shows in the workspace it asks for: the general ones keep 128 rows of codes and planes of Y, the
+# few-token ones whole blocks of 32 rows.  Either form's workspace is enough for the call, and both give the oracle's result.
+@pytest.mark.parametrize("M,K,N,general", [(32, 512, 11008, False), (128, 512, 11008, True), (96, 4096, 2048, False), (32, 28672, 1024, True),
+                                           (1, 28672, 1024, False), (70, 1024, 16384, True)])
+def test_which_launches_and_either_workspace(M, K, N, general):
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, ch = _standin_layer(K, N, 0, seed=M)
+    h = _upload(layer)
+    need = binding.lqer_linear_workspace_bytes(h, M)
+    few = (M + 31) // 32 * 32 * K + 512                          # rank 0: codes and token scales
+    assert need > few if general else need == few
+    X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
+    cols = np.arange(0, N, 5)
+    for nbytes in (need, few):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
+        Y = binding.lqer_linear_forward(h, torch.from_numpy(X).cuda(), workspace=ws)
+        _check(Y.cpu().numpy()[:, cols], X, layer, cols)
+    with pytest.raises(binding.LqerError):
+        binding.lqer_linear_forward(h, torch.from_numpy(X).cuda(), workspace=ws[:few - 256])
+    h.free()
