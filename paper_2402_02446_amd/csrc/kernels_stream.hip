@@ -756,16 +756,13 @@ hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, con
     }
     switch (v) {
         case 12241: return lr == 2 ? launch_group_one<2, 2, 4, 2, 1>(g, s) : launch_group_one<2, 2, 4, 4, 1>(g, s);
-        case 12181: {
-            // One workgroup fills a compute unit's LDS at 5 to 16 tokens: beyond one round of them, two column groups share a
-            // workgroup (the same K slices and correction jobs per wavefront, hence the same bits).  16 tokens, two layers,
-            // whole call: 4096 x 11008 24.7 -> 22.8 us, 5120 x 13824 31.2 -> 28.8, 8192 x 10300 37.2 -> 32.0.  With up to 4
-            // tokens several workgroups fit and the small ones are the faster: 20.7 against 21.7, 24.9 against 26.8.
-            int64_t blocks = 0;
-            for (int i = 0; i < n; ++i) blocks += (layers[i]->N32 + 1) / 2;
-            if (lr == 2) return launch_group_one<2, 1, 8, 2, 1>(g, s);
-            return blocks > compute_units() ? launch_group_one<2, 2, 8, 4, 1>(g, s) : launch_group_one<2, 1, 8, 4, 1>(g, s);
-        }
+        case 12181:
+            // One workgroup fills a compute unit's LDS at 5 to 16 tokens, and such layers have at least 160 of them each, more
+            // than a round of the chip together: two column groups share a workgroup (the same K slices and correction jobs
+            // per wavefront, hence the same bits).  16 tokens, two layers, whole call: 4096 x 11008 24.7 -> 22.8 us,
+            // 5120 x 13824 31.2 -> 28.8, 8192 x 10300 37.2 -> 30.9.  With up to 4 tokens several workgroups fit and the small
+            // ones are the faster: 20.7 against 21.7, 24.9 against 26.8.
+            return lr == 2 ? launch_group_one<2, 1, 8, 2, 1>(g, s) : launch_group_one<2, 2, 8, 4, 1>(g, s);
         case 21181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 2>(g, s) : launch_group_one<1, 1, 8, 4, 2>(g, s);
         case 11181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 1>(g, s) : launch_group_one<1, 1, 8, 4, 1>(g, s);
         default: return hipErrorInvalidValue;

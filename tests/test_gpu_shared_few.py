@@ -32,6 +32,25 @@ def _layers(K, specs):
 ])
 @pytest.mark.parametrize("M", [1, 4, 5, 16, 17, 32])
 def test_shared_few_tokens(K, specs, M):
+    _run(K, specs, M)
+
+
+# The shapes that those layers, pairs of workgroups nearly all, do not take: one workgroup per column group or two, K in one
+# step (272, 1552: one tile, seven) or several (2304: nine) - 11181 / 11241 - and two wavefronts of two column groups - 12241 -
+# in one step and in several.
+@pytest.mark.parametrize("K,specs", [
+    (272, [(100, 8, 4), (272, 33, 4), (1001, 0, 4)]),
+    (1552, [(2080, 24, 4), (65, 64, 4)]),
+    (2304, [(5200, 32, 4), (5281, 16, 4)]),
+    (272, [(25504, 16, 4), (25600, 64, 4)]),
+    (2576, [(25504, 0, 4), (25540, 32, 4)]),
+])
+@pytest.mark.parametrize("M", [4, 16, 32])
+def test_shared_few_tokens_other_shapes(K, specs, M):
+    _run(K, specs, M)
+
+
+def _run(K, specs, M):
     import torch
     from paper_2402_02446_amd import binding
     layers = _layers(K, specs)
