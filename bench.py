@@ -24,7 +24,8 @@ delivers for a kernel that does nothing else (`frac_measured`: a streaming read 
 kernel's access pattern, a register-resident MFMA loop; csrc/bench_probes.hip), and gives the fraction
 the whole step reaches (`frac_step`).
 
-Prints ONE JSON line.  `cpu_baseline` is the fp64 oracle timed on the host cores on a bounded sample
+Prints ONE JSON line on stdout, the headline with its roofline and the step time of every other workload, short enough
+to survive in the tail of a log; everything measured goes to stderr as one JSON line before it.  `cpu_baseline` is the fp64 oracle timed on the host cores on a bounded sample
 of the headline workload.
 """
 from __future__ import annotations
@@ -187,10 +188,11 @@ def measure_peaks():
     ms = min(_event_ms(f, 3) for _ in range(3))
     out["mfma_bf16_tflops_random_operands"] = cus * 2 * 4 * 4096 * 4 * 32768.0 / (ms * 1e-3) / 1e12
     # the matrix pipe beside vector work: two wavefronts per SIMD, n independent fp32 instructions behind every MFMA
-    # (the tiled MXINT kernel has 2.7 per MFMA, the INT kernel 12: 8 of them the per-group conversion and scaling)
+    # (the tiled MXINT kernel has 2.7 per MFMA, int_main_kernel 10: 8 of them the per-group conversion and scaling, 1.5 the
+    # nibbles' expansion)
     beside = {}
     for int8, name, per in ((0, "bf16", 32768.0), (1, "int8", 65536.0)):
-        for nv in (0, 4, 8, 12):
+        for nv in (0, 4, 8, 10, 12):
             iters, wgs = 4096, cus * 2
             f = lambda i: chk(P.lqer_probe_mfma_valu(wgs, iters, nv, int8, sink.data_ptr(), cur()))
             f(0)
@@ -548,13 +550,13 @@ def run_int_variant(rng, peaks):
                                    "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "traffic": None}
             else:
                 ach = ops / (ms * 1e-3) / 1e12
-                rec["roofline"] = {"bound": "mfma", "kernel": "whole step (quant_token_kernel + int_gemm_kernel + int_main_kernel)", "achieved": ach,
+                rec["roofline"] = {"bound": "mfma", "kernel": "whole step (quant_token_kernel + int_gemm_kernel + int_main_kernel, int_reduce_planes_kernel where K is split)", "achieved": ach,
                                    "peak": MFMA_INT8_PEAK_TOPS, "unit": "TOP/s", "frac": ach / MFMA_INT8_PEAK_TOPS, "traffic": None}
-                # what the int8 pipe delivers with this kernel's 12 vector instructions per MFMA beside it (probe)
-                lim = (peaks or {}).get("mfma_beside_valu_tera_per_s", {}).get("int8_12_valu")
+                # what the int8 pipe delivers with int_main_kernel's 10 vector instructions per MFMA beside it (probe)
+                lim = (peaks or {}).get("mfma_beside_valu_tera_per_s", {}).get("int8_10_valu")
                 if lim:
-                    rec["roofline"]["peak_with_12_valu_per_mfma"] = lim
-                    rec["roofline"]["frac_with_12_valu_per_mfma"] = ach / lim
+                    rec["roofline"]["peak_with_10_valu_per_mfma"] = lim
+                    rec["roofline"]["frac_with_10_valu_per_mfma"] = ach / lim
             out.append(rec)
             del X, Y
         for l in layers:
@@ -639,8 +641,10 @@ def pmc_probe(rng, which):
     WRITE_SIZE in the same run.  `headline` / `cfg4_prefill`: the 70B-shaped layer at M = 4096;
     `cfg4_decode`: the same layer at M = 16 on a ring of device copies; `cfg2_decode`: the 7B-shaped
     q_proj at M = 16 on its ring; `cfg3`: the two 7B-shaped MLP layers at M = 2048; `cfg5_prep`: the 7B block's
-    4096- and 11008-wide linears at M = 65536 (projection kernel and main kernel); `int_prefill`: the INT variant's
-    three kernels on a 4096 x 4096 layer at 16384 tokens."""
+    4096- and 11008-wide linears at M = 65536 (projection kernel and main kernel); `mid`: a 4112 x 11000 layer at 203
+    tokens (staged kernel); `int_prefill`: the INT variant's three kernels on a 4096 x 4096 layer at 16384 tokens;
+    `int_decode`: its two few-token kernels on the same layer at 16; `shared_decode`: three 4096 x 4096 layers on the same
+    16 tokens (one launch pair)."""
     import torch
     from paper_2402_02446_amd import binding, synth
     if which == "build":
@@ -659,17 +663,27 @@ def pmc_probe(rng, which):
         "cfg2_decode": [(16, 4096, 4096, 32, 1.25 * LLC_BYTES, 3)],
         "cfg3": [(2048, 4096, 11008, 32, 0, 10), (2048, 11008, 4096, 32, 0, 10)],
         "cfg5_prep": [(65536, 4096, 4096, 32, 0, 4), (65536, 11008, 4096, 32, 0, 4)],
+        "mid": [(203, 4112, 11000, 24, 0, 10)],
     }
-    if which == "int_prefill":
-        # the scaled-integer variant: 4096 x 4096, k = 32 at 16384 tokens (quantizer, projection, main product)
+    if which in ("int_prefill", "int_decode"):
+        # the scaled-integer variant: 4096 x 4096, k = 32
+        M = 16384 if which == "int_prefill" else 16
         d = synth.random_int_layer(rng, 4096, 4096, 32)
         layer = binding.lqer_int_layer_import(4096, 4096, 32, d["Wc"], d["Ws"], d["Ac"], d["As"], d["Bc"], d["Bs"])
-        X = torch.randn((16384, 4096), device="cuda", dtype=torch.float32)
-        Y = torch.empty((16384, 4096), dtype=torch.float32, device="cuda")
-        for _ in range(4):
+        X = torch.randn((M, 4096), device="cuda", dtype=torch.float32)
+        Y = torch.empty((M, 4096), dtype=torch.float32, device="cuda")
+        for _ in range(4 if M > 16 else 20):
             binding.lqer_linear_forward(layer, X, Y=Y)
         torch.cuda.synchronize()
-        print("pmc-probe int_prefill done")
+        print("pmc-probe %s done" % which)
+        return
+    if which == "shared_decode":
+        layers, _ = make_ring(rng, 4096, 4096, 32, 3 * 4096 * 4096 * 0.5)
+        X = torch.randn((16, 4096), device="cuda", dtype=torch.float32)
+        for _ in range(20):
+            binding.lqer_linear_forward_shared(layers[:3], X)
+        torch.cuda.synchronize()
+        print("pmc-probe shared_decode done: %d layers" % len(layers[:3]))
         return
     for (M, K, N, k, ring, reps) in plans[which]:
         layers, _ = make_ring(rng, K, N, k, ring)
@@ -703,6 +717,26 @@ def read_pmc_traffic(kernel):
     return None
 
 
+def short_record(out):
+    """The result line: the headline's record without its details, and milliseconds per step of the other workloads."""
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config")
+    line = {k: out[k] for k in keep}
+    rnd = lambda x: float("%.4g" % x) if isinstance(x, float) else x
+    line["roofline"] = {k: rnd(v) for k, v in out["roofline"].items()}
+    line["cpu_baseline"] = {k: rnd(v) for k, v in out["cpu_baseline"].items() if k != "sample"}
+    ms = {}
+    for c in out["cases"]:
+        if "ms_per_step" in c:
+            ms["%sx%s M%s" % (c.get("K"), c.get("N"), c.get("M"))] = rnd(c["ms_per_step"])
+    for c in out.get("w2a8_rank256", []):
+        ms["w2 %sx%s M%s" % (c["K"], c["N"], c["M"])] = rnd(c["ms_per_step"])
+    for c in out.get("int_variant", []):
+        ms["int %sx%s M%s" % (c["K"], c["N"], c["M"])] = rnd(c["ms_per_step"])
+    line["other_ms_per_step"] = ms
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -711,7 +745,7 @@ def main():
     ap.add_argument("--cases", default="all", choices=["headline", "all"],
                     help="headline: the 70B-shaped layer at M = 4096 only; all (default): every workload")
     ap.add_argument("--pmc-probe", nargs="?", const="headline", default=None,
-                    choices=["headline", "cfg4_decode", "cfg4_prefill", "cfg2_decode", "cfg3", "cfg5_prep", "int_prefill", "build"],
+                    choices=["headline", "cfg4_decode", "cfg4_prefill", "cfg2_decode", "cfg3", "cfg5_prep", "mid", "int_prefill", "int_decode", "shared_decode", "build"],
                     help="run one workload a few times and exit, for rocprofv3 runs (each after plain 1 GiB "
                          "copies that calibrate the byte counters; build: the offline step per layer shape "
                          "of cfg5, host and device path, timings printed as JSON)")
@@ -775,7 +809,8 @@ def main():
         "seconds_gpu_part": t_gpu,
     }
     out.update(extra)
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(short_record(out)))
 
 
 if __name__ == "__main__":

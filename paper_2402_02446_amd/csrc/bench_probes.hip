@@ -139,6 +139,7 @@ int launch_mfma_valu(int workgroups, int iters, int valu, float* sink, hipStream
         case 0: hipLaunchKernelGGL((mfma_valu_kernel<0, I8>), grid, block, 0, s, iters, sink, 1.0f, 0.0f); break;
         case 4: hipLaunchKernelGGL((mfma_valu_kernel<4, I8>), grid, block, 0, s, iters, sink, 1.0f, 0.0f); break;
         case 8: hipLaunchKernelGGL((mfma_valu_kernel<8, I8>), grid, block, 0, s, iters, sink, 1.0f, 0.0f); break;
+        case 10: hipLaunchKernelGGL((mfma_valu_kernel<10, I8>), grid, block, 0, s, iters, sink, 1.0f, 0.0f); break;
         case 12: hipLaunchKernelGGL((mfma_valu_kernel<12, I8>), grid, block, 0, s, iters, sink, 1.0f, 0.0f); break;
         default: return (int)hipErrorInvalidValue;
     }
@@ -190,7 +191,7 @@ int lqer_probe_mfma_random(int workgroups, int iters, int chains, void* sink_dev
     return (int)hipGetLastError();
 }
 
-// Launches workgroups x 4 wavefronts, each doing iters x 4 MFMAs with `valu` (0, 4, 8 or 12) fp32 vector instructions
+// Launches workgroups x 4 wavefronts, each doing iters x 4 MFMAs with `valu` (0, 4, 8, 10 or 12) fp32 vector instructions
 // behind each one.  int8 = 0: bf16 32x32x16 (32768 flops per MFMA); 1: int8 32x32x32 (65536 operations).
 int lqer_probe_mfma_valu(int workgroups, int iters, int valu, int int8, void* sink_dev, void* hip_stream) {
     if (workgroups <= 0 || iters <= 0) return (int)hipErrorInvalidValue;
