@@ -1046,33 +1046,39 @@ static bool split_pays(const TileShape& sh, int64_t tiles, int64_t KT, int cus) 
 
 // ---- calls that do not fill the chip for long: which tile, how many K planes -------------------------------------------
 // Time model, in us: a workgroup takes `unit[r - 1]` per K tile when r of them share a compute unit, `round` more per round of
-// workgroups, `fixed` per launch; every two chunks of the correction beyond the first two take `corr` and `slice` per partial
-// sum of T in each round of workgroups that has them, Y takes `out` per MB; planes take `plane` and `plane_mb` per MB of
-// partial sums written and read.  Fitted to 16000 timings of 1250 calls (K 256 to 14336, N 256 to 28672, 33 to 65536 tokens,
-// ranks 0 to 256): mean error 3 to 8 % a shape.  On 690 other calls its choice was 0.7 % from the fastest form timed on
-// average, within 6 % on 95 % of them and 30 % off at the very worst (11264 x 1555 with rank 256 at 943 tokens, 99 us against
-// 76 in other planes).  With whole tiles of 128 rows
-// or pieces by the estimate above, the main product of 4096 x 4096 at 64 tokens took 43 us, now 17, 11008 x 4096 at 64 tokens
-// 123, now 21, 4112 x 11000 at 203 tokens 54, now 40 (64 x 128), 2-bit 4096 x 4096 with rank 256 at 2048 tokens 104, now 75
-// (64 x 256).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits and large ranks: without
-// them 384 x 27648 with rank 128 at 4627 tokens took 276 us, now 241, 2-bit 592 x 912 at 63752 tokens 168, now 142.
-struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed, corr, slice, out, plane, plane_mb; };
+// workgroups, `fixed` per launch; every two chunks of the correction beyond the first two take corr[0] + corr[1] S, S the
+// partial sums of T, per round of workgroups that have it, and tile[0] + tile[1] S per output tile of the busiest compute unit
+// (two workgroups there share its way to the caches); Y takes `out` per MB; planes take `plane` and `plane_mb` per MB of partial
+// sums written and read.  Fitted to 25000 timings of 1900 calls (K 256 to 14336, N 256 to 28672, 33 to 65536 tokens, ranks 0 to
+// 256): mean error 3 to 8 % a shape.  Fitted to two thirds of them, its choice on the others is 1 % from the fastest form timed
+// on average, within 6 to 7 % on 95 % of the calls, 34 % off at the very worst (8720 x 896 with rank 256 at 3236 tokens).
+// With whole tiles of 128 rows or pieces by the estimate above, the main product of 4096 x 4096 at 64 tokens took 43 us, now
+// 17, 11008 x 4096 at 64 tokens 123, now 21, 4112 x 11000 at 203 tokens 54, now 40 (64 x 128), 2-bit 4096 x 4096 with rank 256
+// at 2048 tokens 104, now 79 (64 x 512).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits
+// and large ranks: without them 384 x 27648 with rank 128 at 4627 tokens took 276 us, now 241, 2-bit 592 x 912 at 63752 tokens
+// 168, now 142.
+struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed, corr[2], tile[2], out, plane, plane_mb; };
 static const SmallShape kSmallShapes4[] = {
-    {33, 64, 128, 2, {1.16, 1.84}, 2.4, 6.6, 1.6, 0.57, 0.055, 3.9, 0.122}, {31, 64, 256, 2, {1.89, 3.00}, 1.0, 7.4, 2.5, 0.62, 0.186, 4.2, 0.149},
-    {32, 64, 512, 1, {3.00, 0.0}, 2.6, 6.1, 3.4, 0.41, 0.202, 4.4, 0.157},
-    {11, 128, 512, 1, {4.71, 0.0}, 2.9, 6.6, 4.5, 1.08, 0.214, 0.0, 0.0}, {12, 128, 256, 2, {3.17, 5.40}, 0.0, 8.1, 3.1, 2.24, 0.200, 0.0, 0.0},  // tiled_kernel, whole tiles
+    {33, 64, 128, 2, {1.17, 1.77}, 2.6, 6.5, {0.0, 0.0}, {0.55, 0.65}, 0.058, 4.2, 0.116},
+    {31, 64, 256, 2, {1.91, 2.96}, 1.1, 7.2, {0.79, 0.04}, {0.74, 0.70}, 0.186, 4.6, 0.146},
+    {32, 64, 512, 1, {3.01, 0.0}, 2.7, 6.0, {0.0, 0.0}, {3.00, 0.46}, 0.205, 4.4, 0.157},
+    {12, 128, 256, 2, {3.18, 5.28}, 0.0, 8.1, {2.35, 1.05}, {0.0, 1.31}, 0.208, 0.0, 0.0},          // tiled_kernel, whole tiles
+    {11, 128, 512, 1, {4.69, 0.0}, 2.7, 7.2, {0.0, 0.0}, {4.15, 1.16}, 0.220, 0.0, 0.0},
 };
 static const SmallShape kSmallShapes2[] = {
-    {33, 64, 128, 2, {1.24, 1.84}, 2.6, 6.7, 0.6, 0.82, 0.076, 3.8, 0.132}, {31, 64, 256, 2, {1.94, 3.01}, 1.1, 7.6, 1.3, 0.89, 0.199, 4.2, 0.155},
-    {32, 64, 512, 1, {2.99, 0.0}, 3.2, 6.6, 2.4, 0.65, 0.180, 3.6, 0.165},
-    {11, 128, 512, 1, {4.50, 0.0}, 3.4, 8.0, 3.1, 1.59, 0.197, 0.0, 0.0}, {12, 128, 256, 2, {3.17, 5.31}, 0.0, 8.8, 1.4, 2.90, 0.197, 0.0, 0.0},
+    {33, 64, 128, 2, {1.24, 1.82}, 3.0, 6.4, {0.0, 0.0}, {0.36, 0.65}, 0.042, 4.1, 0.119},
+    {31, 64, 256, 2, {1.93, 3.00}, 1.55, 7.1, {0.14, 0.26}, {0.98, 0.50}, 0.178, 4.4, 0.148},
+    {32, 64, 512, 1, {3.00, 0.0}, 3.2, 6.3, {0.0, 0.0}, {2.60, 0.48}, 0.186, 3.7, 0.163},
+    {12, 128, 256, 2, {3.19, 5.33}, 0.0, 8.7, {1.44, 1.44}, {0.41, 0.91}, 0.198, 0.0, 0.0},
+    {11, 128, 512, 1, {4.53, 0.0}, 3.2, 7.8, {0.0, 0.0}, {3.50, 1.30}, 0.205, 0.0, 0.0},
 };
 // The 128 x 512 shape with tiles cut in pieces, for 4 and 2 bits: us per launch, K tile of a piece, K tile and number of whole
-// rounds, piece beyond two, the correction as above.  Whole pieces per tile (300 timings, 5 %), and equal shares, whose
-// estimate is the rougher one (250 timings, 6 %) and counts only where the launch is long enough for them to pay.
+// rounds, piece beyond two, the correction per round.  Whole pieces per tile (460 timings, 5 %), and equal shares, whose
+// estimate is the rougher one (370 timings, 6 %): it counts only where the launch is long enough for them to pay, and has to
+// promise 3 %.
 struct SmallPieces { double fixed, share, unit, round, piece, corr, slice; };
-static const SmallPieces kSmallWhole[2] = {{24.8, 5.64, 5.07, 11.7, 3.6, 4.4, 1.35}, {24.4, 5.46, 4.95, 11.1, 3.9, 4.2, 1.32}};
-static const SmallPieces kSmallShares[2] = {{21.0, 6.24, 6.10, 11.5, 0.0, 3.2, 2.0}, {18.9, 6.16, 6.16, 7.6, 0.0, 2.9, 1.96}};
+static const SmallPieces kSmallWhole[2] = {{24.3, 5.73, 5.17, 12.3, 3.6, 4.5, 1.30}, {24.6, 5.46, 5.23, 10.5, 3.9, 4.4, 1.27}};
+static const SmallPieces kSmallShares[2] = {{22.3, 6.11, 6.03, 10.0, 0.0, 3.6, 1.82}, {21.0, 6.14, 6.14, 9.6, 0.0, 3.4, 1.76}};
 constexpr double kSharesFlops = 6e10;
 constexpr int kMaxPlanes = 16;
 // Above this many operations the chip is full long enough to lower its clock, which this model does not know; the estimate
@@ -1088,10 +1094,13 @@ static int more_pairs(int kp) { return kp > 64 ? (kp + 63) / 64 - 1 : 0; }
 static double small_us(const SmallShape& sh, const Layer& L, int64_t M, int S, int64_t tiles, int planes, int64_t share, int cus) {
     const int64_t wgs = tiles * planes, per_round = (int64_t)cus * sh.resident;
     const int64_t full = wgs / per_round, rest = wgs - full * per_round;
-    const int64_t rounds = full + (rest > 0 ? 1 : 0), corr_rounds = (tiles + per_round - 1) / per_round;   // (one plane of a tile has the correction)
+    const int64_t rounds = full + (rest > 0 ? 1 : 0);
     double t = sh.fixed + (double)full * sh.unit[sh.resident - 1] * (double)share + (double)rounds * sh.round + sh.out * (double)M * (double)L.N * 4e-6;
     if (rest > 0) t += sh.unit[(rest + cus - 1) / cus - 1] * (double)share;
-    t += more_pairs(L.kp) * (double)corr_rounds * (sh.corr + sh.slice * (double)S);
+    // the correction, by one plane of a tile
+    const int64_t left = tiles % per_round, corr_rounds = tiles / per_round + (left > 0 ? 1 : 0);
+    const int64_t on_cu = tiles / per_round * sh.resident + (left + cus - 1) / cus;
+    t += more_pairs(L.kp) * ((double)corr_rounds * (sh.corr[0] + sh.corr[1] * (double)S) + (double)on_cu * (sh.tile[0] + sh.tile[1] * (double)S));
     if (planes > 1) t += sh.plane + sh.plane_mb * (double)planes * (double)M * (double)plane_ld(L.N) * 8e-6;
     return t;
 }
@@ -1123,7 +1132,7 @@ static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes
             const Split sp = split_tiles(tiles, L.KT, cus, true);
             if (sp.sk_units == 0 || (!sp.aligned && 2.0 * (double)M * (double)L.N * (double)L.K < kSharesFlops)) continue;
             const double us = pieces_us((sp.aligned ? kSmallWhole : kSmallShares)[L.w_bits == 4 ? 0 : 1], L, S, sp);
-            if (us < best_us) { best = SmallPick{11, 0, (int)sp.sk_share}; best_us = us; }
+            if (us * (sp.aligned ? 1.0 : 1.03) < best_us) { best = SmallPick{11, 0, (int)sp.sk_share}; best_us = us; }
         }
     }
     return best;
