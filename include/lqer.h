@@ -279,7 +279,8 @@ int lqer_set_wait_limit(int polls);
  * are zero, negative or not finite, are excluded (LQER_ERR_VALUE).
  * lqer_build_factors with cfg = {4, 8, 16, 128} builds such a layer (same steps, Sec. 3.1-3.2 and App. A).
  * An INT layer runs through lqer_linear_forward, lqer_linear_forward_static and lqer_linear_workspace_bytes
- * (lqer_linear_path reports 3: one kernel, int8 matrix cores, for every token count); the entry points that take
+ * (lqer_linear_path reports 3 for every token count: int8 matrix cores, one pair of kernels for few tokens and one
+ * set for the rest, chosen by the library; up to 128 tokens either runs if only its workspace is there); the entry points that take
  * MXINT codes, launch options, MXINT8 output or layer groups return LQER_ERR_UNSUPPORTED for it, and
  * lqer_layer_export does too (lqer_int_layer_export is its counterpart).
  * lqer_quantize_int8_token is the stand-alone per-token quantizer: x_dev [rows][ld] fp32 (16-byte aligned, ld and
@@ -321,7 +322,7 @@ int lqer_linear_forward_static(const lqer_layer* layer, const float* X_dev, int6
  */
 int lqer_selftest_layouts(void);
 
-/* Which path the dispatcher picks for this layer at M tokens: 1 = streaming, 2 = tiled MFMA, 3 = the INT variant's kernel. */
+/* Which path the dispatcher picks for this layer at M tokens: 1 = streaming, 2 = tiled MFMA, 3 = the INT variant. */
 int lqer_linear_path(const lqer_layer* layer, int64_t M);
 
 #ifdef __cplusplus

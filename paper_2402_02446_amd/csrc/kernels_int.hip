@@ -7,7 +7,8 @@
 //
 //   quant_token_kernel   per-token INT8 quantizer (one workgroup per token row: row maximum, then codes)
 //   int_main_kernel      the main product with the rank-k correction (T_hi | T_lo against B_k's codes on the bf16 matrix
-//                        cores, one scale per column) in the epilogue; operands by direct-to-LDS loads
+//                        cores, one scale per column) in the epilogue; operands by direct-to-LDS loads.  Few tiles: K in
+//                        planes, one more for the correction, that int_reduce_planes_kernel adds and scales per token
 //   int_gemm_kernel      the projection T = X_q A_k, A_k as 8-bit "weights": 128 tokens x 128 ranks per workgroup, four
 //                        wavefronts of 64 x 64, one K group per step, all of it asked for one group ahead
 //
@@ -284,8 +285,8 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
 //   * a wavefront owns all 128 tokens of 32 columns, so a nibble is expanded once per workgroup;
 //   * tokens are the rows and columns the lanes of the MFMA's result: a lane needs one scale per group;
 //   * the sums of two 32 x 32 tiles are folded beside the MFMAs of the other two, laced instruction by instruction.
-// Whole calls, before -> after: 2048 tokens of 4096 x 11008 197 -> 173 us, of 11008 x 4096 193 -> 167 us, 65536 tokens of
-// 4096 x 4096 1914 -> 1744 us.  Left out one at a time, the loads cost 8 % of the time, the folding 12 %, the LDS reads 22 %,
+// Whole calls at rank 32, by int_gemm_kernel's tiles -> so: 2048 tokens of 4096 x 11008 162 -> 141 us, of 11008 x 4096
+// 163 -> 149, 65536 tokens of 4096 x 4096 1849 -> 1672.  Left out one at a time, the loads cost 8 % of the time, the folding 12 %, the LDS reads 22 %,
 // three quarters of the MFMAs 24 %: what is left is the phases of a group waiting for each other.
 constexpr int kIntStages = 3, kIntStage = 128 * 128 + 4 * (2048 + 256);
 

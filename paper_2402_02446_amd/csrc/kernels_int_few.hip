@@ -10,7 +10,8 @@
 //                         meet in LDS in wavefront order
 //
 // Five launches (quantizer, projection in planes and their sum, product in planes and their sum) before; 4096 x 4096 at
-// 16 tokens 23.3 -> 14.1 us a call in a stream of them, 8192 x 28672 at 16 tokens 85 -> 55 us.
+// 16 tokens 23.2 -> 13.4 us a call in a stream of them, 8192 x 28672 at 16 tokens 80 -> 49 us.  How far up these two are the
+// faster ones: few_tokens in int_host.cpp.
 #include "lqer_internal.h"
 #include "mx_device.h"
 

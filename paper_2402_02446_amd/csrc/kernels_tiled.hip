@@ -14,7 +14,7 @@
 //       registers (fully coalesced 16-byte loads), three chunks ahead, into four register sets used
 //       by name in turn (a copy between sets would force a wait on the newest load), and expands
 //       them there;
-//   the rank-kp correction is ceil(2 kp / 64) more chunks whose weight operand comes from B_k.
+//   the rank-kp correction is ceil(2 kp / 64) more chunks behind the others whose weight operand comes from B_k.
 // MFMA operands are swapped (weights first) so a lane ends up with runs of four consecutive
 // output columns of one token and stores each as one 16-byte write.
 //
@@ -28,10 +28,11 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
-// Calls that do not fill the chip for long (33 to about a thousand tokens) take staged_kernel: tiles of 64 rows, every
+// Calls that do not fill the chip for long mostly take staged_kernel (pick_small says which): tiles of 64 rows, every
 // operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
 // the tiles are too few, several workgroups per tile, each with an equal range of K ("planes"), that store their partial
-// sums of Y in the workspace's slots; reduce_planes_kernel adds them in plane order.  A piece of tiled_kernel that hands
+// sums of Y in the workspace's slots; reduce_planes_kernel adds them in plane order.  There the correction comes first, by
+// the plane with the start of K.  A piece of tiled_kernel that hands
 // its accumulators over and another that waits for them cost more than such a call's product.
 #include <atomic>
 #include <mutex>
@@ -547,10 +548,10 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 // ---- the same product with every operand staged by direct-to-LDS loads -----------------------------------------------
 // What bounds these launches is not the loads' latency (three or seven stages ahead measure the same) but one or two
 // wavefronts on a SIMD issuing an instruction every eight cycles each, and LDS reads: 64 x 128 tiles of four 64 x 32
-// wavefronts, two workgroups on a compute unit, are the fastest where there are enough of them.  Main product,
-// tiled_kernel's form of the same tile -> this one: 4112 x 11000 at 203 tokens 45 -> 40 us (512 TFLOP/s on 344
-// workgroups), 11008 x 4096 at 64 tokens 26 -> 20 us; 2-bit weights with rank 256, 4096 x 4096 at 2048 tokens
-// 104 -> 83 us, at 64 tokens 99 -> 31 us (there the correction: its operands are asked for in one go per two chunks).
+// wavefronts, two workgroups on a compute unit, are the fastest where the launch is a round or two.  Main product, the
+// fastest form of tiled_kernel -> the fastest of this one: 4112 x 11000 at 203 tokens 52 -> 38 us (480 TFLOP/s on 344
+// workgroups), 11008 x 4096 at 64 tokens 65 -> 21 us (in planes); 2-bit weights with rank 256, 4096 x 4096 at 2048 tokens
+// 101 -> 80 us, at 64 tokens 84 -> 30 us (there the correction: its operands are asked for in one go per two chunks).
 // D = stages of 64 K in LDS: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN] 1 KiB of codes
 // [wave][TN] 256 B of exponent words; chunk ch + D - 1 is asked for when chunk ch starts.
 template <int TM, int TN, int WR, int WC, int D, int MINW, bool PLANES, int WB>
@@ -1052,11 +1053,11 @@ static bool split_pays(const TileShape& sh, int64_t tiles, int64_t KT, int cus) 
 // sums written and read.  Fitted to 25000 timings of 1900 calls (K 256 to 14336, N 256 to 28672, 33 to 65536 tokens, ranks 0 to
 // 256): mean error 3 to 8 % a shape.  Fitted to two thirds of them, its choice on the others is 1 % from the fastest form timed
 // on average, within 6 to 7 % on 95 % of the calls, 34 % off at the very worst (8720 x 896 with rank 256 at 3236 tokens).
-// With whole tiles of 128 rows or pieces by the estimate above, the main product of 4096 x 4096 at 64 tokens took 43 us, now
-// 17, 11008 x 4096 at 64 tokens 123, now 21, 4112 x 11000 at 203 tokens 54, now 40 (64 x 128), 2-bit 4096 x 4096 with rank 256
-// at 2048 tokens 104, now 79 (64 x 512).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits
-// and large ranks: without them 384 x 27648 with rank 128 at 4627 tokens took 276 us, now 241, 2-bit 592 x 912 at 63752 tokens
-// 168, now 142.
+// Main product, best form of tiled_kernel against what is chosen: 4096 x 4096 at 64 tokens 43 us and 15 (64 x 128 in planes),
+// 11008 x 4096 at 64 tokens 65 and 21, 4112 x 11000 at 203 tokens 52 and 38 (64 x 128), 2-bit 4096 x 4096 with rank 256 at 2048
+// tokens 101 and 80 (64 x 512).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits and
+// large ranks: best staged form against what is chosen, 384 x 27648 with rank 128 at 4627 tokens 265 us and 243, 2-bit
+// 592 x 912 with rank 64 at 63752 tokens 170 and 140.
 struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed, corr[2], tile[2], out, plane, plane_mb; };
 static const SmallShape kSmallShapes4[] = {
     {33, 64, 128, 2, {1.17, 1.77}, 2.6, 6.5, {0.0, 0.0}, {0.55, 0.65}, 0.058, 4.2, 0.116},
@@ -1082,8 +1083,8 @@ static const SmallPieces kSmallShares[2] = {{22.3, 6.11, 6.03, 10.0, 0.0, 3.6, 1
 constexpr double kSharesFlops = 6e10;
 constexpr int kMaxPlanes = 16;
 // Above this many operations the chip is full long enough to lower its clock, which this model does not know; the estimate
-// above is calibrated there (8192 x 28672 at 2048 tokens: its choice 714 us, this model's 770 us; below the line, e.g.
-// 11008 x 4096 at 1500 tokens, 144 us against 126 us).
+// above is calibrated there (8192 x 28672 at 2048 tokens: its choice 714 us, this model's 770 us; below the line, main product
+// of 11008 x 4096 at 1500 tokens, 146 to 149 us by the estimate's forms, 142 by the model's choice).
 constexpr double kSmallFlops = 1.5e11;
 
 struct SmallPick { int id, planes, share; };      // share: K tiles per plane; planes 0: tiled_kernel in pieces

@@ -324,7 +324,7 @@ static Workspace plan_workspace(const Layer& L, int64_t M, int path, void* base,
     ws.cells = (path == 1);
     ws.lr = stream_cell_rows_log2(M);
     ws.x8 = false;
-    // the tiled kernel reads whole tiles of Xh, 96 to 256 rows high (rows past M hold whatever was there)
+    // the tiled path's kernels read whole tiles of Xh, 64 to 256 rows high (rows past M hold whatever was there)
     const int64_t xh_rows = (path == 2) ? round_up(M + 95, 256) : (ws.cells ? (int64_t)1 << ws.lr : M);
     const size_t xh_bytes = (size_t)round_up(xh_rows * ws.ldxh * 2, 256);
     // T travels as partial sums on the streaming path and whenever the projection kernel splits K
@@ -382,7 +382,7 @@ static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, co
     const Layer& L = layer->L;
     if (M < 0) return LQER_ERR_SHAPE;
     if (L.format == 1) {
-        // the scaled-integer variant: fp32 in, fp32 out, one launch shape
+        // the scaled-integer variant: fp32 in, fp32 out, its launches chosen by itself
         if (Xc || rq.codes || (opts && (opts->path != 0 || opts->variant != 0 || opts->stages != 0))) return LQER_ERR_UNSUPPORTED;
         if (M == 0) return LQER_OK;
         if (!X || !Y) return LQER_ERR_NULL;
