@@ -2,12 +2,19 @@
 // W4A6 setup of Table 2) and compute the low-rank projection T = X_q A_k (Eq. 3 / Eq. 6, first small
 // matmul).
 //
-// One workgroup owns 16 token rows and a K slice; its eight wavefronts take the slice's 256-wide
-// K tiles in turn.  Lane (t = lane % 16, q = lane / 16) owns the blocks q + 4p (p = 0..3) of a
-// tile for token t: it finds the block maximum, quantizes, and keeps the dequantized values
+// One workgroup owns 16 token rows and a K slice; its wavefronts take the quarters (64 columns) of the
+// slice's 256-wide K tiles in turn.  Lane (t = lane % 16, q = lane / 16) owns block q of a quarter for
+// token t: it finds the block maximum, quantizes, and keeps the dequantized values
 // code * 2^(e-6) - exact in bf16 - both for the store to the bf16 activation matrix the main
 // kernels read and as its MFMA operand.  A_k arrives already dequantized to bf16 (exactly, at
 // import), so every product entering the fp32 MFMA accumulator is exact.
+//
+// Few-token calls are bound by the latency of this step, mid-sized ones nearly so: it is one memory round trip and one
+// block's arithmetic per wavefront.  With whole tiles per wavefront and each quarter's loads behind a branch it was four round
+// trips and 64 values' arithmetic one after the other; whole calls replayed from a graph (4-bit weights, rank 32):
+// 4096 x 4096 at 1 token 9.4 -> 8.4 us, at 16 11.4 -> 10.4, at 40 20.6 -> 16.9, 2048 x 2048 at 64 19.0 -> 15.3,
+// 4096 x 11008 at 128 36.6 -> 32.7.  Launches of 256 and more workgroups take as many wavefronts as tiles, four quarters each:
+// there the chip is full, and 16 wavefronts of a quarter each were 3 % slower for a call of 2048 tokens at rank 256.
 //
 // S == 1: T is final; it is split into two bf16 terms T_hi + T_lo and stored behind the
 //         activations of the same row, where the main kernel treats it as 2*kp more K columns.
@@ -15,6 +22,8 @@
 // For the streaming kernel the activations are stored as 16-byte cells [K / 8][token row] instead
 // (or as the codes themselves, see the store below); extra workgroups clear Y or the tiled
 // kernel's flags where the main kernel needs that.
+#include <type_traits>
+
 #include "lqer_internal.h"
 #include "mx_device.h"
 
@@ -39,6 +48,7 @@ struct PrepArgs {
     bool x8;               // CELLS: store MXINT8 codes [block][row][16] and exponent bytes [block][row] instead of bf16 cells
     float* Yz; int64_t ldy, N;   // Yz != null: extra workgroups clear Y[M][N] for a main kernel that adds into it
     int nslices;                 // K slices = the part of grid.y that does the projection
+    int nwaves;                  // wavefronts of a workgroup (an argument: blockDim costs a vector load ahead of everything else)
     uint32_t* flags; int nflags; // flags != null: words the first workgroup clears for the main kernel
 };
 
@@ -49,7 +59,8 @@ __device__ __forceinline__ void split_bf16(float t, uint16_t& hi, uint16_t& lo) 
     lo = (uint16_t)(f32_bits(rem) >> 16);
 }
 
-constexpr int kPrepWaves = 8;
+constexpr int kPrepWaves = 16;     // quarter-tile form, at most
+constexpr int kPrepRowWaves = 8;   // row-wise form
 
 // CELLS: the activations are stored for the streaming kernel, as 16-byte cells (8 consecutive K
 // elements) ordered [K / 8][token row]; otherwise row-major for the tiled kernel.
@@ -73,14 +84,14 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     // compute unit cost more than the coalescing gains (measured: 8192 wide, 4096 tokens 46 -> 52 us; 65536 tokens of
     // 4096 channels 373 -> 308 us), and the lane-per-block form below is used.
     constexpr bool ROWWISE = RW;
-    constexpr int RED_BYTES = kPrepWaves * MAXG * 64 * 16;
-    constexpr int SMEM_BYTES = ROWWISE ? (kPrepWaves * 8192 > RED_BYTES ? kPrepWaves * 8192 : RED_BYTES) : RED_BYTES;
+    constexpr int RED_BYTES = (RW ? kPrepRowWaves : kPrepWaves) * MAXG * 64 * 16;
+    constexpr int SMEM_BYTES = ROWWISE ? (kPrepRowWaves * 8192 > RED_BYTES ? kPrepRowWaves * 8192 : RED_BYTES) : RED_BYTES;
     __shared__ __attribute__((aligned(16))) uint8_t smem[SMEM_BYTES];
     float (*red)[MAXG][64][4] = reinterpret_cast<float (*)[MAXG][64][4]>(smem);
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int nwaves = blockDim.x >> 6;              // 1 .. kPrepWaves
+    const int nwaves = a.nwaves, nthreads = 64 * nwaves;
     const int t = lane & 15, q = lane >> 4;
     const int64_t row = (int64_t)blockIdx.x * 16 + t;
     const bool row_ok = row < a.M;
@@ -95,16 +106,16 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     for (int g = 0; g < MAXG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     if (a.flags != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
-        for (int i = threadIdx.x; i < a.nflags; i += blockDim.x) a.flags[i] = 0u;
+        for (int i = threadIdx.x; i < a.nflags; i += nthreads) a.flags[i] = 0u;
 
     // Workgroups behind the a.nslices K slices (grid.y) only clear Y for a main kernel that adds into it,
     // so the clearing runs beside the projection instead of in front of it.
     if ((int)blockIdx.y >= a.nslices) {
         if (blockIdx.z != 0) return;                 // one plane of grid.z clears
         const int64_t n4 = (a.N + 3) / 4;
-        const int64_t nthreads = (int64_t)gridDim.x * (gridDim.y - a.nslices) * blockDim.x;
-        const int64_t me = ((int64_t)(blockIdx.y - a.nslices) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-        for (int64_t i = me; i < a.M * n4; i += nthreads) {
+        const int64_t all = (int64_t)gridDim.x * (gridDim.y - a.nslices) * nthreads;
+        const int64_t me = ((int64_t)(blockIdx.y - a.nslices) * gridDim.x + blockIdx.x) * nthreads + threadIdx.x;
+        for (int64_t i = me; i < a.M * n4; i += all) {
             const int64_t r = i / n4, c = 4 * (i - r * n4);
             float* dst = a.Yz + r * a.ldy + c;
             if (c + 3 < a.N) {
@@ -120,25 +131,9 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     int64_t tile_end = tile_begin + a.tiles_per_slice;
     if (tile_end > a.KT) tile_end = a.KT;
 
-    for (int64_t tile = tile_begin + wave; tile < tile_end; tile += nwaves) {
-        Frag xf[4][2];                                       // [p][half]
-        // Few-token calls are bound by latency, not bandwidth: request A_k's records before the
-        // activations are even loaded, so that one memory round trip covers both.
-        Frag apre[CELLS ? MAXG : 1][4][2];
-        if constexpr (CELLS) {
-#pragma unroll
-            for (int g = 0; g < MAXG; ++g) {
-                if (g < ng) {
-                    const uint8_t* rec = a.At + ((int64_t)(g0 + g) * a.KT + tile) * kARecordBytes;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) {
-                        apre[g][p][0].u = *reinterpret_cast<const u32x4*>(rec + (2 * p) * 1024 + lane * 16);
-                        apre[g][p][1].u = *reinterpret_cast<const u32x4*>(rec + (2 * p + 1) * 1024 + lane * 16);
-                    }
-                }
-            }
-        }
-        if constexpr (ROWWISE) {
+    if constexpr (ROWWISE) {
+        for (int64_t tile = tile_begin + wave; tile < tile_end; tile += nwaves) {
+            Frag xf[4][2];                                   // [p][half]
             uint8_t* tl = smem + wave * 8192;                 // [16 rows][32 cells of 16 B], cell index XOR row
             const int64_t col = tile * kTileK + 4 * lane;     // this lane's four columns (K is a multiple of 16: all in or all out)
             const bool col_ok = col < a.K;
@@ -200,25 +195,98 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     xf[p][h].u = *reinterpret_cast<const u32x4*>(tl + t * 512 + (((2 * (q + 4 * p) + h) ^ t) << 4));
-        }
 #pragma unroll
-        for (int p = 0; p < (ROWWISE ? 0 : 4); ++p) {
-            const int64_t kb = tile * 16 + q + 4 * p;        // block index along K
-            const bool ok = row_ok && kb < nblk;
-            float scale = 0.f;
-            float r[16];
-            u32x4 cw = u32x4{0, 0, 0, 0};                     // the block's 16 codes as bytes (FROM_CODES, or CELLS of 16+ rows)
-            uint32_t eb = 0;
+            for (int g = 0; g < MAXG; ++g) {
+                if (g < ng) {
+                    const uint8_t* rec = a.At + ((int64_t)(g0 + g) * a.KT + tile) * kARecordBytes;
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        Frag af[2];
+                        af[0].u = *reinterpret_cast<const u32x4*>(rec + (2 * p) * 1024 + lane * 16);
+                        af[1].u = *reinterpret_cast<const u32x4*>(rec + (2 * p + 1) * 1024 + lane * 16);
+                        acc[g] = mfma16(af[0].v, xf[p][0].v, acc[g]);
+                        acc[g] = mfma16(af[1].v, xf[p][1].v, acc[g]);
+                    }
+                    // one rank group's eight loads in flight at a time: all of them at once cost the registers of a second workgroup
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    } else {
+        // The unit of work is a quarter of a tile (64 columns, one block per lane), so that a wavefront's chain is one round trip
+        // to memory and 16 values' arithmetic; the next unit's operands are asked for ahead of it.  No load is conditional: a
+        // branch around it would have the compiler wait for it at the branch's end.
+        struct Unit {
+            u32x4 x[SRC == 0 ? 4 : (SRC == 2 ? 2 : 1)];     // the block: fp32, codes, or bf16
+            uint32_t eb;
+            Frag af[CELLS ? MAXG : 1][2];
+        };
+        const int64_t rowc = row_ok ? row : a.M - 1;
+        const float* xrow = a.X + rowc * a.ldx;
+        const int8_t* crow = a.Xc + rowc * a.K;
+        const uint8_t* erow = a.Xe + rowc * nblk;
+        const uint16_t* hrow = a.Xh + rowc * a.ldxh;
+        const uint8_t* alane = a.At + lane * 16;
+        const int units = (int)(tile_end - tile_begin) * 4;
+        auto load_a = [&](Frag (&af)[2], int g, int unit) {
+            const int gc = g < ng ? g : 0;
+            const uint8_t* rec = alane + ((int64_t)(g0 + gc) * a.KT + tile_begin + (unit >> 2)) * kARecordBytes + (unit & 3) * 2048;
+            af[0].u = *reinterpret_cast<const u32x4*>(rec);
+            af[1].u = *reinterpret_cast<const u32x4*>(rec + 1024);
+        };
+        auto load_unit = [&](Unit& u, int unit) {
+            const int64_t kb = (tile_begin + (unit >> 2)) * 16 + q + 4 * (unit & 3);
+            const int64_t kbc = kb < nblk ? kb : nblk - 1;
+            if constexpr (CELLS) {
+                if (a.kp > 0) {                              // (the same for the whole launch)
+#pragma unroll
+                    for (int g = 0; g < MAXG; ++g) load_a(u.af[g], g, unit);
+                }
+            }
             if constexpr (SRC == 2) {
                 static_assert(SRC != 2 || !CELLS, "the stored matrix is read back in its row-major form only");
-                const uint16_t* src = a.Xh + row * a.ldxh + kb * 16;
-                xf[p][0].u = ok ? *reinterpret_cast<const u32x4*>(src) : u32x4{0, 0, 0, 0};
-                xf[p][1].u = ok ? *reinterpret_cast<const u32x4*>(src + 8) : u32x4{0, 0, 0, 0};
+                u.x[0] = *reinterpret_cast<const u32x4*>(hrow + kbc * 16);
+                u.x[1] = *reinterpret_cast<const u32x4*>(hrow + kbc * 16 + 8);
             } else if constexpr (SRC == 1) {
-                if (ok) {
-                    cw = *reinterpret_cast<const u32x4*>(a.Xc + row * a.K + kb * 16);
-                    eb = a.Xe[row * nblk + kb];
+                u.x[0] = *reinterpret_cast<const u32x4*>(crow + kbc * 16);
+                u.eb = erow[kbc];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u.x[i] = *reinterpret_cast<const u32x4*>(xrow + kbc * 16 + 4 * i);
+            }
+        };
+        // more: the wavefront has another unit behind this one.  (Two instances: where loads may or may not follow, the compiler
+        // waits for all of them.)
+        auto process = [&](Unit& cur, Unit& nxt, int unit, auto more) {
+            Frag af[MAXG][2];
+            if constexpr (CELLS) {
+#pragma unroll
+                for (int g = 0; g < MAXG; ++g) {
+                    af[g][0] = cur.af[g][0];
+                    af[g][1] = cur.af[g][1];
                 }
+            } else if (a.kp > 0) {
+#pragma unroll
+                for (int g = 0; g < MAXG; ++g) load_a(af[g], g, unit);
+            }
+            if constexpr (decltype(more)::value) load_unit(nxt, unit + nwaves);
+            __builtin_amdgcn_sched_barrier(0);
+            const int64_t blk = (tile_begin + (unit >> 2)) * 16 + q + 4 * (unit & 3);   // block index along K
+            const bool ok = row_ok && blk < nblk;
+            Frag xf[2];
+            float scale = 0.f;
+            float r[16];
+            u32x4 cw = u32x4{0, 0, 0, 0};                    // the block's 16 codes as bytes (SRC 1, or CELLS of 16+ rows)
+            uint32_t eb = 0;
+            if constexpr (SRC == 2) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) xf[h].u[i] = ok ? cur.x[h][i] : 0u;
+            } else if constexpr (SRC == 1) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cw[i] = ok ? cur.x[0][i] : 0u;
+                eb = ok ? cur.eb : 0u;
                 scale = x_scale(eb, a.act_frac);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -229,30 +297,26 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                     r[4 * i + 3] = (float)(int)(int8_t)(w >> 24);
                 }
             } else {
-                float4 v[4];
+                float v[16];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    v[i] = ok ? *reinterpret_cast<const float4*>(a.X + row * a.ldx + kb * 16 + 4 * i)
-                              : make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int i = 0; i < 16; ++i) v[i] = ok ? f32_from_bits(cur.x[i >> 2][i & 3]) : 0.f;
                 float m = 0.f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[i].x), __builtin_fabsf(v[i].y)),
-                                                           __builtin_fmaxf(__builtin_fabsf(v[i].z), __builtin_fabsf(v[i].w))));
-                }
+                for (int i = 0; i < 16; i += 4)
+                    m = __builtin_fmaxf(m, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[i]), __builtin_fabsf(v[i + 1])),
+                                                           __builtin_fmaxf(__builtin_fabsf(v[i + 2]), __builtin_fabsf(v[i + 3]))));
                 eb = (f32_bits(m) >> 23) & 0xFFu;
                 const int sh = a.act_frac - ((int)eb - 127);
                 const float lim = (float)((2 << a.act_frac) - 1);             // 127 or 31
                 scale = x_scale(eb, a.act_frac);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float in[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+                for (int i = 0; i < 16; ++i) {
+                    const float c = __builtin_rintf(__builtin_amdgcn_ldexpf(v[i], sh));
+                    r[i] = __builtin_fminf(__builtin_fmaxf(c, -lim), lim);
+                }
+                if constexpr (CELLS) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        float c = __builtin_rintf(__builtin_amdgcn_ldexpf(in[j], sh));
-                        r[4 * i + j] = __builtin_fminf(__builtin_fmaxf(c, -lim), lim);
-                    }
-                    if constexpr (CELLS)
+                    for (int i = 0; i < 4; ++i)
                         cw[i] = ((uint32_t)(int)r[4 * i] & 0xFFu) | (((uint32_t)(int)r[4 * i + 1] & 0xFFu) << 8) |
                                 (((uint32_t)(int)r[4 * i + 2] & 0xFFu) << 16) | ((uint32_t)(int)r[4 * i + 3] << 24);
                 }
@@ -262,11 +326,10 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        xf[p][h].u[i] = pack_bf16_exact(r[8 * h + 2 * i] * scale, r[8 * h + 2 * i + 1] * scale);
+                        xf[h].u[i] = pack_bf16_exact(r[8 * h + 2 * i] * scale, r[8 * h + 2 * i + 1] * scale);
             }
             if (store_x && row_ok) {
                 if (CELLS) {
-                    const int64_t blk = tile * 16 + q + 4 * p;
                     if (a.x8) {
                         // 16 token rows and more: MXINT8 as it is, 16 code bytes per (block, row), and the
                         // exponent bytes [block][row] behind all codes; the main kernel converts
@@ -278,36 +341,32 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                         base[((a.KT * 16) << (a.lr + 4)) + entry] = (uint8_t)(ebs < 254u ? ebs : 254u);
                     } else {
                         uint16_t* dst = a.Xh + ((((blk * 2) << a.lr) + row) << 3);
-                        *reinterpret_cast<u32x4*>(dst) = xf[p][0].u;
-                        *reinterpret_cast<u32x4*>(dst + (8 << a.lr)) = xf[p][1].u;
+                        *reinterpret_cast<u32x4*>(dst) = xf[0].u;
+                        *reinterpret_cast<u32x4*>(dst + (8 << a.lr)) = xf[1].u;
                     }
                 } else {
-                    uint16_t* dst = a.Xh + row * a.ldxh + (tile * 16 + q + 4 * p) * 16;
-                    *reinterpret_cast<u32x4*>(dst) = xf[p][0].u;
-                    *reinterpret_cast<u32x4*>(dst + 8) = xf[p][1].u;
+                    uint16_t* dst = a.Xh + row * a.ldxh + blk * 16;
+                    *reinterpret_cast<u32x4*>(dst) = xf[0].u;
+                    *reinterpret_cast<u32x4*>(dst + 8) = xf[1].u;
                 }
             }
-        }
+            if (a.kp > 0) {
 #pragma unroll
-        for (int g = 0; g < MAXG; ++g) {
-            if (g < ng) {
-                const uint8_t* rec = a.At + ((int64_t)(g0 + g) * a.KT + tile) * kARecordBytes;
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    Frag af[2];
-                    if constexpr (CELLS) {
-                        af[0] = apre[g][p][0];
-                        af[1] = apre[g][p][1];
-                    } else {
-                        af[0].u = *reinterpret_cast<const u32x4*>(rec + (2 * p) * 1024 + lane * 16);
-                        af[1].u = *reinterpret_cast<const u32x4*>(rec + (2 * p + 1) * 1024 + lane * 16);
-                    }
-                    acc[g] = mfma16(af[0].v, xf[p][0].v, acc[g]);
-                    acc[g] = mfma16(af[1].v, xf[p][1].v, acc[g]);
+                for (int g = 0; g < MAXG; ++g) {
+                    acc[g] = mfma16(af[g][0].v, xf[0].v, acc[g]);
+                    acc[g] = mfma16(af[g][1].v, xf[1].v, acc[g]);
                 }
-                // one rank group's eight loads in flight at a time: all of them at once cost the registers of a second workgroup
-                if constexpr (ROWWISE) __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        Unit cur, nxt;
+        int unit = wave;
+        if (unit < units) {
+            load_unit(cur, unit);
+            for (; unit + nwaves < units; unit += nwaves) {
+                process(cur, nxt, unit, std::true_type{});
+                cur = nxt;
+            }
+            process(cur, nxt, unit, std::false_type{});
         }
     }
 
@@ -322,7 +381,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     for (int g = 0; g < MAXG; ++g)
         *reinterpret_cast<f32x4*>(&red[wave][g][lane][0]) = acc[g];
     __syncthreads();
-    for (int item = threadIdx.x; item < ng * 64; item += blockDim.x) {
+    for (int item = threadIdx.x; item < ng * 64; item += nthreads) {
         const int g = item >> 6, l = item & 63;
         f32x4 s = *reinterpret_cast<const f32x4*>(&red[0][g][l][0]);
         for (int w = 1; w < nwaves; ++w) {
@@ -349,7 +408,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     // zero the padding behind T_hi | T_lo so the main kernel can read whole 64-column chunks
     if (FINAL && blockIdx.z == 0) {
         const int pad = (int)(a.tail_cols - 2 * a.kp);
-        for (int item = threadIdx.x; item < 16 * pad; item += blockDim.x) {
+        for (int item = threadIdx.x; item < 16 * pad; item += nthreads) {
             const int64_t orow = (int64_t)blockIdx.x * 16 + item / pad;
             if (orow < a.M) a.Xh[orow * a.ldxh + a.KT * kTileK + 2 * a.kp + item % pad] = 0;
         }
@@ -357,7 +416,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
 }
 
 template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false>
-__global__ __launch_bounds__(64 * kPrepWaves, RW ? 4 : 1) void prep_kernel(PrepArgs a) {
+__global__ __launch_bounds__(64 * (RW ? kPrepRowWaves : kPrepWaves), RW ? 4 : 1) void prep_kernel(PrepArgs a) {
     prep_body<SRC, FINAL, MAXG, CELLS, RW>(a);
 }
 
@@ -369,8 +428,8 @@ struct PrepGroup { PrepArgs a; int n; PrepLayer layer[kGroupLayers]; };
 __global__ __launch_bounds__(64 * kPrepWaves) void prep_group_kernel(PrepGroup g) {
     if ((int)blockIdx.y >= g.a.nslices) {
         if (blockIdx.z != 0) return;
-        const int64_t nthreads = (int64_t)gridDim.x * (gridDim.y - g.a.nslices) * blockDim.x;
-        const int64_t me = ((int64_t)(blockIdx.y - g.a.nslices) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+        const int64_t nthreads = (int64_t)gridDim.x * (gridDim.y - g.a.nslices) * 64 * g.a.nwaves;
+        const int64_t me = ((int64_t)(blockIdx.y - g.a.nslices) * gridDim.x + blockIdx.x) * 64 * g.a.nwaves + threadIdx.x;
         for (int li = 0; li < g.n; ++li) {
             const PrepLayer& L = g.layer[li];
             const int64_t n4 = (L.N + 3) / 4;
@@ -422,6 +481,16 @@ int prep_slices(const Layer& L, int64_t M, int path) {
     return (int)s;
 }
 
+// wavefronts of a workgroup: one per tile of the slice where the launch fills the chip anyway, otherwise one per quarter of a tile
+// in as few and as even rounds as fit
+static int prep_waves(int tiles, bool filled) {
+    if (filled) return tiles < kPrepRowWaves ? (tiles < 1 ? 1 : tiles) : kPrepRowWaves;
+    const int units = 4 * tiles;
+    if (units <= kPrepWaves) return units < 1 ? 1 : units;
+    const int rounds = (units + kPrepWaves - 1) / kPrepWaves;
+    return (units + rounds - 1) / rounds;
+}
+
 hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t* Xc, const uint8_t* Xe,
                        int64_t M, const Workspace& ws, float* y_zero, int64_t ldy, hipStream_t s, bool reuse_xh) {
     if (M == 0) return hipSuccess;
@@ -454,34 +523,37 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     a.nslices = ws.S;
     a.flags = ws.flags; a.nflags = ws.flags ? kTiledFlags : 0;
     const bool cells = ws.cells;
-    int nwaves = a.tiles_per_slice;
-    if (nwaves > kPrepWaves) nwaves = kPrepWaves;
-    if (nwaves < 1) nwaves = 1;
-    dim3 block(64 * nwaves);
-    // clearing workgroups: about four 16-byte stores per thread
+    const int src = reuse_xh ? 2 : (Xc != nullptr ? 1 : 0);
     const int64_t rg = (M + 15) / 16;
+    // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
+    const bool rowwise = !cells && src == 0 && rg * ws.S * gz >= 2048;
+    a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S * gz >= 256);
+    dim3 block(64 * a.nwaves);
+    // clearing workgroups: about four 16-byte stores per thread
     const int64_t zero_wgs = y_zero ? (M * ((L.N + 3) / 4) + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;
     dim3 grid((unsigned)rg, (unsigned)(ws.S + zero_wgs), (unsigned)gz);
-    const int src = reuse_xh ? 2 : (Xc != nullptr ? 1 : 0);
     const bool fin = (ws.Tpart == nullptr);          // T final (hi/lo behind the row) or partial sums
     if (cells && fin && L.kp > 0) return hipErrorInvalidValue;
     if (a.groups_per_wg > 4) return hipErrorInvalidValue;
-    // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
-    const bool rowwise = !cells && src == 0 && (int64_t)grid.x * ws.S * gz >= 2048;
 #define LQER_PREP(FC, FN, MG, CL) launch_prep_t<FC, FN, MG, CL>(grid, block, s, a, rowwise)
-#define LQER_PREP_G(FC, FN, CL) do { if (a.groups_per_wg <= 1) LQER_PREP(FC, FN, 1, CL); else LQER_PREP(FC, FN, 4, CL); } while (0)
-#define LQER_PREP_C(FN, CL) do { if (src == 1) LQER_PREP_G(1, FN, CL); else LQER_PREP_G(0, FN, CL); } while (0)
-    if (cells) LQER_PREP_C(false, true);
-    else if (src == 2) { if (fin) LQER_PREP_G(2, true, false); else LQER_PREP_G(2, false, false); }
-    else if (fin) LQER_PREP_C(true, false);
-    else LQER_PREP_C(false, false);
+#define LQER_PREP_G(FC, FN) do { if (a.groups_per_wg <= 1) LQER_PREP(FC, FN, 1, false); else if (a.groups_per_wg == 2) LQER_PREP(FC, FN, 2, false); else LQER_PREP(FC, FN, 4, false); } while (0)
+#define LQER_PREP_C(FN) do { if (src == 1) LQER_PREP_G(1, FN); else LQER_PREP_G(0, FN); } while (0)
+    if (cells) {
+        if (src == 1) LQER_PREP(1, false, 1, true);
+        else LQER_PREP(0, false, 1, true);
+    }
+    else if (src == 2) { if (fin) LQER_PREP_G(2, true); else LQER_PREP_G(2, false); }
+    else if (fin) LQER_PREP_C(true);
+    else LQER_PREP_C(false);
     if (two_launches) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         a.g_first = 4;
         grid.z = (unsigned)((L.kp16 - 4 + 3) / 4);
         grid.y = (unsigned)ws.S;
-        if (fin) LQER_PREP_G(2, true, false); else LQER_PREP_G(2, false, false);
+        a.nwaves = prep_waves(a.tiles_per_slice, rg * ws.S * grid.z >= 256);
+        block.x = 64 * a.nwaves;
+        if (fin) LQER_PREP_G(2, true); else LQER_PREP_G(2, false);
     }
 #undef LQER_PREP_C
 #undef LQER_PREP_G
@@ -512,9 +584,8 @@ hipError_t launch_prep_group(const Layer* const* layers, int n, const float* X, 
         z += L.kp16;
         cols4 += (L.N + 3) / 4;
     }
-    int nwaves = a.tiles_per_slice < kPrepWaves ? a.tiles_per_slice : kPrepWaves;
-    if (nwaves < 1) nwaves = 1;
-    const dim3 block(64 * nwaves);
+    a.nwaves = prep_waves(a.tiles_per_slice, false);
+    const dim3 block(64 * a.nwaves);
     const int64_t rg = (M + 15) / 16;
     const int64_t zero_wgs = zero_y ? (M * cols4 + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;
     hipLaunchKernelGGL(prep_group_kernel, dim3((unsigned)rg, (unsigned)(ws.S + zero_wgs), (unsigned)(z > 0 ? z : 1)), block, 0, s, g);
