@@ -28,6 +28,13 @@
 // and keeps in LDS as two bf16 terms.  At the end the NWK partial sums of every column group are
 // added through LDS in slice order and stored as fp32, or as MXINT8 blocks of 16 along N for the
 // next layer.  Up to 64 tokens are two blocks of 32 per wavefront sharing each expanded weight operand.
+//
+// Below about 20 MB of weights a launch is a chain of latencies, and what counts is how soon the first weights are asked for
+// and how little follows the last: activations, then weights, then T and B_k (needed only after the main product) are
+// requested in that order with little address arithmetic before them - no divisions - and T is added up and converted behind the
+// main product, between two barriers that are there anyway.  The sums leave in cache lines, a pair's without
+// a second pass through LDS.  Whole calls replayed from a graph, 4-bit weights, rank 32: 4096 x 4096 at 1 token 8.45 -> 7.86 us,
+// at 16 10.4 -> 9.5, 2048 x 2048 at 1 7.75 -> 7.06, 4096 x 11008 at 1 12.6 -> 11.9; MXINT2 at rank 256, 16 tokens 13.9 -> 12.9.
 #include <mutex>
 #include <type_traits>
 
@@ -39,6 +46,8 @@ namespace lqer {
 constexpr int kStreamTBytes = 9 * 1024;          // 32 rows x (128 + 8) bf16, rounded up to keep what follows 1 KiB aligned
 constexpr int kStreamTBytesBig = 33 * 1024;      // the same for ranks up to 256: 32 rows x (512 + 8) bf16
 
+constexpr int kRedRun = 32 * 4 + 8;              // floats of a run of 32 tokens x 4 columns of partial sums
+
 struct StreamArgs {
     const uint8_t* Wt; const uint8_t* Bt;
     const uint8_t* Xcell;          // activations: bf16 as 16-byte cells [KT*32][R rows] (R = 4), or MXINT8 codes [KT*16][R][16] + exponent bytes [KT*16][R]
@@ -47,9 +56,14 @@ struct StreamArgs {
     int8_t* Yc; uint8_t* Ye; int64_t ldyc;           // Yc != null: store Y as MXINT8 (blocks of 16 along N) instead of fp32
     int64_t M, N, KT, N32;
     int kp, kp16;
+    uint32_t kp4_inv;              // stream_kp4_inv(kp)
     int rec_bytes;                 // bytes of a weight record
     int exp_bias;                  // >= 0: exponent nibbles (byte = nibble + exp_bias); -1: exponent bytes
 };
+
+// item / (kp / 4) = (item * this) >> 20 for the at most 1024 items of T (16 rows x 256 ranks, 64 x 64): this exceeds
+// 2^20 / (kp / 4) by less than 1, and 1024 * 64 < 2^20
+static inline uint32_t stream_kp4_inv(int kp) { return kp > 0 ? ((1u << 20) + (uint32_t)(kp / 4) - 1) / (uint32_t)(kp / 4) : 0u; }
 
 // LR = log2 of the token rows per activation cell column (4, 16 or 32 rows).
 // ONE: the whole K range of the workgroup is a single step: one activation stage, no loop.
@@ -71,6 +85,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     static_assert(!ONE || DT == 1, "a single step prefetches nothing");
     constexpr int NW = NWC * NWK;
     constexpr int NG = NWC * G;                      // column groups of the workgroup
+    // 16 wavefronts have 128 registers each, too few to hold the partial sums of T through the main product
+    constexpr bool kTFirst = NW >= 16;
     constexpr int R = 1 << LR;
     constexpr int XT = NWK * R * 512;                // bytes of one stage in LDS: NWK tiles x R rows of bf16
     // With 16 token rows and more the activations travel as MXINT8 (16 code bytes per block and row,
@@ -91,7 +107,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     uint16_t* tlds = reinterpret_cast<uint16_t*>(lds);                 // [32][2 kp + 8] bf16, kept all along
     const int t_ld = 2 * a.kp + 8;                                     // row stride of tlds in elements
     uint8_t* xlds = lds + kTBytes;                                     // two activation stages
-    float* red = reinterpret_cast<float*>(lds + kTBytes);              // reused afterwards: [NWK][NG][4][64 lanes][4]
+    float* red = reinterpret_cast<float*>(lds + kTBytes);              // reused afterwards: partial sums (red_at)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -99,9 +115,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     const int t = lane & 31, hh = lane >> 5;
 
     // column groups of this wavefront (clamped; stores are masked)
-    const int64_t cb = block / KSP;                  // column block
-    const int kh = block % KSP;                      // which of the KSP workgroups of the block
-    const int64_t g0 = (cb * NWC + wc) * G;
+    const int cb = (int)((unsigned)block / KSP);     // column block
+    const int kh = (int)((unsigned)block % KSP);     // which of the KSP workgroups of the block
+    const int64_t g0 = ((int64_t)cb * NWC + wc) * G;
     const uint8_t* wrec[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -213,7 +229,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[g][b][r] = 0.f;
 
-    // ---- rank-kp correction, part 1: fetch its operands first ---------------------------------------
+    // ---- rank-kp correction, part 1: its operands ----------------------------------------------------
     // The correction is 2 kp more "K columns" in 64-wide chunks of [T_hi | T_lo].  Lane half hh owns
     // rank blocks jb = 4 ch + 2 hh + {0, 1} of chunk ch: jb < kp16 is T_hi for ranks 16 jb..,
     // otherwise T_lo for ranks 16 (jb - kp16)...  Job j = g * nchunks + ch of this wavefront's column
@@ -221,67 +237,65 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     const int nb2 = (kh == 0) ? 2 * a.kp16 : 0;      // the correction is added once: by workgroup 0 of a pair
     const int nchunks = (nb2 + 3) / 4;               // 0, 1 or 2; up to 8 with BIGK
     constexpr int NJ = ((BIGK ? 8 : 2) * G + NWK - 1) / NWK;
+    static_assert(G <= 2, "the column group of a job is found by one comparison");
+    // Behind a branch the compiler no longer knows how many loads are in flight and waits for all of them.  Up to rank 64 only
+    // one or two wavefronts have such loads and a branch around them is the cheaper (4096 x 4096 at 1 token 7.80 us a call, 7.94
+    // without it); above, all of them do, and the loads are unconditional, with offsets past the buffer's end (no memory
+    // access, zeros) where there is nothing to fetch (MXINT2, rank 256, 16 tokens: 12.85 against 13.23).
     u32x4 tail_cw[NJ][2];
     uint32_t tail_eb[NJ][2];
     auto load_tail = [&]() {
 #pragma unroll
     for (int q = 0; q < NJ; ++q) {
         const int job = wk + NWK * q;                // wave-uniform
-        const int g = nchunks ? job / nchunks : 0, ch = nchunks ? job % nchunks : 0;
+        const bool has = job < G * nchunks;
+        if (!BIGK && !has) continue;
+        const int g = G == 2 && has && job >= nchunks ? 1 : 0, ch = has ? job - g * nchunks : 0;
+        int64_t grp = g0 + g;
+        if (grp >= a.N32) grp = a.N32 - 1;
+        const BufferRsrc recs = buffer_rsrc(a.Bt + grp * a.kp16 * kBRecordBytes, (uint32_t)(a.kp16 * kBRecordBytes));
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            tail_cw[q][j] = u32x4{0, 0, 0, 0};
-            tail_eb[q][j] = 0;
             const int jb = 4 * ch + 2 * hh + j;
-            if (job < G * nchunks && jb < nb2) {
-                const int rb = jb >= a.kp16 ? jb - a.kp16 : jb;
-                int64_t grp = g0 + g;
-                if (grp >= a.N32) grp = a.N32 - 1;
-                const uint8_t* rec = a.Bt + (grp * a.kp16 + rb) * kBRecordBytes;
-                tail_cw[q][j] = *reinterpret_cast<const u32x4*>(rec + t * 16);
-                tail_eb[q][j] = rec[512 + t];
-            }
+            const int rec = (jb >= a.kp16 ? jb - a.kp16 : jb) * kBRecordBytes;
+            const int none = ((int)has & (int)(jb < nb2)) ? 0 : kNoOffset;
+            tail_cw[q][j] = buffer_load16(recs, (rec + t * 16) | none);
+            tail_eb[q][j] = buffer_load1(recs, (rec + 512 + t) | none);
         }
     }
     };
-    if constexpr (!BIGK) load_tail();
     // T: the workgroup adds the S (<= 8) partial sums of the projection kernel in slice order and
-    // leaves T_hi | T_lo as bf16 in LDS.  One item = 4 consecutive ranks of a token.
-    // (ranks above 64: up to four items a thread, 128 registers that one or two wavefronts on a SIMD have to spare; one item
-    // after the other they were four round trips, 4 us of the 4096 x 4096 step at rank 256)
+    // leaves T_hi | T_lo as bf16 in LDS.  One item = 4 consecutive ranks of a token.  All partial sums are asked for at
+    // once; ranks above 64 take up to four items a thread, 128 registers that one or two wavefronts on a SIMD have to spare.
     constexpr int TI = ((BIGK ? R * 64 : 32 * MB * 16) + NW * 64 - 1) / (NW * 64);
     constexpr int SMAX = 8;
     const int t_rows = a.M < 32 * MB ? (int)a.M : 32 * MB;
     const int kp4 = a.kp >> 2;
     const int t_items = (kh == 0) ? t_rows * kp4 : 0;
-    // The loads are issued here; the sums are formed (finish_t) once the first weight loads are on
-    // their way, so that those do not wait for this round trip.
     f32x4 tpart[TI][SMAX];
     auto load_t = [&]() {
+    const int slice = (int)a.M * a.kp * 4;           // bytes
+    const BufferRsrc parts = buffer_rsrc(a.Tpart, (uint32_t)(a.S * slice));
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
+        if (!BIGK && wave * 64 + i * NW * 64 >= t_items) continue;
         const int item = threadIdx.x + i * NW * 64;
+        const int none = item < t_items ? 0 : kNoOffset;
 #pragma unroll
-        for (int sl = 0; sl < SMAX; ++sl) {
-            tpart[i][sl] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (item < t_items && sl < a.S)
-                tpart[i][sl] = *reinterpret_cast<const f32x4*>(a.Tpart + (int64_t)sl * a.M * a.kp + 4 * item);
-        }
+        for (int sl = 0; sl < SMAX; ++sl)
+            tpart[i][sl] = __builtin_bit_cast(f32x4, buffer_load16(parts, (item * 16 + sl * slice) | none | (sl < a.S ? 0 : kNoOffset)));
     }
     };
-    if constexpr (!BIGK) load_t();
     auto finish_t = [&]() {
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
             const int item = threadIdx.x + i * NW * 64;
             if (item >= t_items) continue;
-            const int row = item / kp4, r4 = item - row * kp4;
+            const int row = (int)(((uint32_t)item * a.kp4_inv) >> 20), r4 = item - row * kp4;
             f32x4 sum = tpart[i][0];
 #pragma unroll
-            for (int sl = 1; sl < SMAX; ++sl) {
-                sum[0] += tpart[i][sl][0]; sum[1] += tpart[i][sl][1];
-                sum[2] += tpart[i][sl][2]; sum[3] += tpart[i][sl][3];
-            }
+            for (int sl = 1; sl < SMAX; ++sl)
+                sum += tpart[i][sl];                 // (zeros from slice S on)
             uint32_t hi[4], lo[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -303,6 +317,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
         u32x2 wex[DT][G];            // exponent bytes
         {
             XStage st;
+            if constexpr (kTFirst) {
+                load_tail();
+                load_t();
+            }
             fetch_x(st, 0);
 #pragma unroll
             for (int g = 0; g < G; ++g) wex[0][g] = load_we(g, tile_at(0));
@@ -320,13 +338,14 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
                         for (int g = 0; g < G; ++g) wcd[1][g][c] = load_wc(g, tile_at(1), c);
                 }
             }
-            // With ranks above 64 these are up to 130 KB a workgroup, which the first weights would wait behind.
-            if constexpr (BIGK) {
+            // T and B_k are needed last: nothing waits behind them.  (At ranks above 64 they are up to 130 KB a workgroup.)
+            if constexpr (!kTFirst) {
+                __builtin_amdgcn_sched_barrier(0);
                 load_t();
                 load_tail();
             }
             store_x(st, 0);
-            finish_t();
+            if constexpr (kTFirst) finish_t();
         }
         // PFX: the step fetches the activations of the next one; PFW: it refills its weight set
         auto step = [&](u32x4 (&wc_)[G][NC], u32x2 (&we_)[G], int64_t it, auto pfx, auto pfw) {
@@ -416,11 +435,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     }
 
     // ---- rank-kp correction, part 2: the arithmetic ---------------------------------------------------
+    if constexpr (!kTFirst) finish_t();
+    __syncthreads();                                 // T is complete, and every wavefront is done with the activation stages
 #pragma unroll
     for (int q = 0; q < NJ; ++q) {
         const int job = wk + NWK * q;
         if (job >= G * nchunks) continue;
-        const int g = job / nchunks, ch = job % nchunks;
+        const int g = job >= nchunks ? 1 : 0, ch = job - g * nchunks;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int jb = 4 * ch + 2 * hh + j;
@@ -452,26 +473,21 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     }
 
     // ---- add the K slices of every column group in slice order -----------------------------------------
-    // every wavefront leaves its partial sums in LDS; wavefront v then finishes unit v, v + NW, ... where
-    // unit u = (column group, token block, accumulator quarter u % 4)
+    // Every wavefront leaves its partial sums in LDS; then a thread adds the NWK of one (token row, column), the lanes of a
+    // wavefront side by side along the columns: whole cache lines are stored, or added by a pair's atomics.
     constexpr int NGV = NG * MB;                     // (column group, token block) pairs of the workgroup
-    __syncthreads();                                 // every wavefront is done with the activation stages
-    auto red_at = [&](int k, int q, int r4) {          // lanes side by side: no bank conflicts
-        return reinterpret_cast<f32x4*>(red + (((((size_t)k * NGV + q) * 4 + r4) * 64 + lane) * 4));
-    };
+    // element (slice k, pair qv, column 4 b + j, token t): runs of 32 tokens x 4 columns, 8 floats apart so that 32 columns x
+    // two tokens are in 64 different banks
+    auto red_at = [&](int k, int qv, int b, int tok) { return red + ((k * NGV + qv) * 8 + b) * kRedRun + tok * 4; };
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int b = 0; b < MB; ++b)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4)
-                *red_at(wk, (wc * G + g) * MB + b, r4) =
+                *reinterpret_cast<f32x4*>(red_at(wk, (wc * G + g) * MB + b, 2 * r4 + hh, t)) =
                     f32x4{acc[g][b][4 * r4], acc[g][b][4 * r4 + 1], acc[g][b][4 * r4 + 2], acc[g][b][4 * r4 + 3]};
     __syncthreads();
-    // A pair of workgroups adds into Y with atomics.  They are issued so that one instruction covers two
-    // rows of 32 consecutive columns (two cache lines) instead of 64 scattered dwords: the finished
-    // sums go through LDS once more to change the lane order.
-    float* yt = red + NWK * NGV * 1024;                                // [NG][32 rows][32 columns], behind the partial sums
     // As MXINT8 for the next layer (one workgroup per column block only): a unit is one block of 16
     // columns of a (group, token block) - quarters 2 b and 2 b + 1, eight values in this lane and
     // eight in lane ^ 32 (the same token).
@@ -482,18 +498,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
             float v[8];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                f32x4 s4 = *red_at(0, qv, 2 * b + h);
+                f32x4 s4 = *reinterpret_cast<const f32x4*>(red_at(0, qv, 2 * (2 * b + h) + hh, t));
 #pragma unroll
-                for (int k = 1; k < NWK; ++k) {
-                    const f32x4 o = *red_at(k, qv, 2 * b + h);
-                    s4[0] += o[0]; s4[1] += o[1]; s4[2] += o[2]; s4[3] += o[3];
-                }
+                for (int k = 1; k < NWK; ++k) s4 += *reinterpret_cast<const f32x4*>(red_at(k, qv, 2 * (2 * b + h) + hh, t));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) v[4 * h + j] = s4[j];
             }
             uint32_t w0, w1;
             const uint32_t eb = requant_half_block(v, w0, w1);
-            const int64_t grp = cb * NG + q;
+            const int64_t grp = (int64_t)cb * NG + q;
             const int64_t n0 = grp * 32 + 16 * b;
             if (grp < a.N32 && row < a.M && n0 < a.N) {
                 int8_t* dst = a.Yc + (int64_t)row * a.ldyc + n0 + 4 * hh;
@@ -504,42 +517,17 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
         }
         return;
     }
-    for (int u = wave; u < NGV * 4; u += NW) {
-        const int qv = u >> 2, r4 = u & 3;
-        const int q = qv / MB, row = t + 32 * (qv % MB);
-        f32x4 v = *red_at(0, qv, r4);
+    for (int item = threadIdx.x; item < NG * R * 32; item += NW * 64) {
+        const int n32 = item & 31, row = (item >> 5) & (R - 1), q = item >> (5 + LR);
+        const int qv = q * MB + (row >> 5);
+        const int64_t n = ((int64_t)cb * NG + q) * 32 + n32;
+        if (row >= a.M || n >= a.N) continue;
+        float v = red_at(0, qv, n32 >> 2, row & 31)[n32 & 3];
 #pragma unroll
-        for (int k = 1; k < NWK; ++k) {
-            const f32x4 o = *red_at(k, qv, r4);
-            v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
-        }
-        if constexpr (KSP == 2) {
-            *reinterpret_cast<f32x4*>(yt + (q * 32 + t) * 32 + 8 * r4 + 4 * hh) = v;
-        } else {
-            const int64_t grp = cb * NG + q;
-            if (grp < a.N32 && row < a.M) {
-                const int64_t n = grp * 32 + 8 * r4 + 4 * hh;              // this lane's 4 consecutive columns
-                float* dst = a.Y + (int64_t)row * a.ldy + n;
-                if (n + 3 < a.N) {
-                    *reinterpret_cast<f32x4*>(dst) = v;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (n + j < a.N) dst[j] = v[j];
-                }
-            }
-        }
-    }
-    if constexpr (KSP == 2) {
-        __syncthreads();
-        const int pairs = ((int)a.M + 1) >> 1;                         // row pairs per column group
-        for (int item = wave; item < NG * pairs; item += NW) {
-            const int q = item / pairs, row = 2 * (item - q * pairs) + hh;
-            const int64_t grp = cb * NG + q;
-            const int64_t n = grp * 32 + t;
-            if (grp < a.N32 && row < a.M && n < a.N)
-                unsafeAtomicAdd(a.Y + (int64_t)row * a.ldy + n, yt[(q * 32 + row) * 32 + t]);
-        }
+        for (int k = 1; k < NWK; ++k) v += red_at(k, qv, n32 >> 2, row & 31)[n32 & 3];
+        float* dst = a.Y + (int64_t)row * a.ldy + n;
+        if constexpr (KSP == 2) unsafeAtomicAdd(dst, v);
+        else *dst = v;
     }
 }
 
@@ -554,7 +542,9 @@ __global__ __launch_bounds__(64 * NWC * NWK) void stream_kernel(StreamArgs a) {
 struct StreamLayer {
     const uint8_t* Wt; const uint8_t* Bt; const float* Tpart;
     float* Y; int64_t ldy, N, N32;
-    int kp, kp16, rec_bytes, exp_bias;
+    int kp, kp16;
+    uint32_t kp4_inv;
+    int rec_bytes, exp_bias;
     int block0;                    // first workgroup
 };
 struct StreamGroup {
@@ -570,25 +560,25 @@ __global__ __launch_bounds__(64 * NWC * NWK) void stream_group_kernel(StreamGrou
     while (li + 1 < g.n && (int)blockIdx.x >= g.layer[li + 1].block0) ++li;
     const StreamLayer& L = g.layer[li];
     const StreamArgs a{L.Wt, L.Bt, g.Xcell, L.Tpart, g.S, L.Y, L.ldy, nullptr, nullptr, 0, g.M, L.N, g.KT, L.N32,
-                       L.kp, L.kp16, L.rec_bytes, L.exp_bias};
+                       L.kp, L.kp16, L.kp4_inv, L.rec_bytes, L.exp_bias};
     stream_body<G, NWC, NWK, 1, LR, ONE, KSP, 4, false>(a, (int)blockIdx.x - L.block0);
 }
 
 int stream_max_rows() { return 64; }
 int stream_cell_rows_log2(int64_t M) { return M <= 4 ? 2 : (M <= 16 ? 4 : (M <= 32 ? 5 : 6)); }
 
-template <int G, int NWC, int NWK, int LR, bool ONE, int KSP, bool BIGK>
+template <int G, int NWC, int NWK, int LR, bool ONE, bool BIGK>
 constexpr int stream_lds_bytes() {
     constexpr int STAGING = (ONE ? 1 : 2) * NWK * (1 << LR) * 512;
     constexpr int MB = (LR == 6) ? 2 : 1;
-    constexpr int REDUCE = NWK * NWC * G * MB * 4096 + (KSP == 2 ? NWC * G * 4096 : 0);
+    constexpr int REDUCE = NWK * NWC * G * MB * 8 * kRedRun * 4;
     return (BIGK ? kStreamTBytesBig : kStreamTBytes) * MB + (STAGING > REDUCE ? STAGING : REDUCE);
 }
 
 template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
 static hipError_t launch_stream_t(const StreamArgs& a, hipStream_t s) {
     constexpr int MB = (LR == 6) ? 2 : 1;
-    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, KSP, BIGK>();
+    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, BIGK>();
     if constexpr (LDS_BYTES > 160 * 1024 || (MB == 2 && KSP == 2)) {
         return hipErrorInvalidValue;                 // this shape does not fit the 160 KB of LDS
     } else {
@@ -675,6 +665,7 @@ hipError_t launch_stream(const Layer& L, int64_t M, const Workspace& ws, float* 
     a.Tpart = ws.Tpart; a.S = ws.S;
     a.Y = Y; a.ldy = ldy; a.M = M; a.N = L.N; a.KT = L.KT; a.N32 = L.N32; a.kp = L.kp; a.kp16 = L.kp16;
     a.Yc = rq.codes; a.Ye = rq.exps; a.ldyc = rq.ld;
+    a.kp4_inv = stream_kp4_inv(L.kp);
     a.rec_bytes = L.w_rec_bytes; a.exp_bias = L.w_exp_bias;
     const int v = stream_variant(L, M, variant);
     if (rq.codes != nullptr && stream_variant_adds_into_y(v)) return hipErrorInvalidValue;   // a pair's sum is complete only in memory
@@ -705,7 +696,7 @@ hipError_t launch_stream(const Layer& L, int64_t M, const Workspace& ws, float* 
 // ---- groups of layers ---------------------------------------------------------------------------------------------------
 template <int G, int NWC, int NWK, int LR, bool ONE, int KSP>
 static hipError_t launch_group_t(StreamGroup& g, hipStream_t s) {
-    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, KSP, false>();
+    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, false>();
     static_assert(LDS_BYTES <= 160 * 1024, "fits");
     auto kern = stream_group_kernel<G, NWC, NWK, LR, ONE, KSP>;
     static std::once_flag once;
@@ -742,7 +733,7 @@ hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, con
     for (int i = 0; i < n; ++i) {
         const Layer& L = *layers[i];
         if (!stream_group_takes(L, M) || stream_variant(L, M, 0) != v || L.KT != g.KT) return hipErrorInvalidValue;
-        g.layer[i] = StreamLayer{L.Wt, L.Bt, Tpart[i], Y[i], ldy[i], L.N, L.N32, L.kp, L.kp16, L.w_rec_bytes, L.w_exp_bias, 0};
+        g.layer[i] = StreamLayer{L.Wt, L.Bt, Tpart[i], Y[i], ldy[i], L.N, L.N32, L.kp, L.kp16, stream_kp4_inv(L.kp), L.w_rec_bytes, L.w_exp_bias, 0};
     }
     const int lr = stream_cell_rows_log2(M);
     if (lr == 5) {

@@ -130,6 +130,16 @@ __device__ __forceinline__ int mx8_code(float v, int e_unbiased) {
     return (int)r;
 }
 
+// ---- buffer loads -----------------------------------------------------------------------------------------------------
+// A load whose offset lies past the buffer's end accesses no memory and returns zeros.
+typedef __amdgpu_buffer_rsrc_t BufferRsrc;
+constexpr int kNoOffset = (int)0x80000000;           // or-ed to an offset: past the end of any buffer of at most 2 GiB
+__device__ __forceinline__ BufferRsrc buffer_rsrc(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 buffer_load16(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
+__device__ __forceinline__ uint32_t buffer_load1(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0); }
+
 // ---- direct-to-LDS loads ----------------------------------------------------------------------------------------------
 // 1 KiB (64 lanes x 16 bytes) or 256 B from `base` + this lane's byte offset to LDS address at + ADD + 16 (4) * lane.
 // Written as asm because the compiler answers its own builtin with a full drain of the loads in flight in front of every
