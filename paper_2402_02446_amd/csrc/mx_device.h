@@ -130,6 +130,52 @@ __device__ __forceinline__ int mx8_code(float v, int e_unbiased) {
     return (int)r;
 }
 
+// ---- per-token INT8 codes ---------------------------------------------------------------------------------------------
+// rint(x / s) in [-127, 127], the quotient rounded to fp32 as a division rounds it, in three instructions instead of ten
+// (P. Markstein, "Computation of elementary functions on the IBM RISC System/6000 processor", 1990): with y = 1 / s correctly
+// rounded and q = x y, the remainder r = x - q s is exact in one fused multiply-add, and q + r y is within 2^-47 of the quotient
+// before it is rounded.  s is an fp16 value of 11 significant bits, so no quotient lies within 2^-36 of the middle between two
+// fp32 values: the rounding is the division's.  (Where x y underflows the code is 0 either way.)  Scales that are zero or
+// infinite - row maxima below 127 2^-25 or from 127 65520 on - keep the division.
+struct Int8Coder {
+    float s, y;
+    __device__ __forceinline__ explicit Int8Coder(float scale) : s(scale), y(__fdiv_rn(1.0f, scale)) {}
+    static __device__ __forceinline__ uint32_t clamp(float q) {
+        q = __builtin_rintf(q);
+        return (uint32_t)(int)__builtin_fminf(__builtin_fmaxf(q, -127.0f), 127.0f) & 0xFFu;
+    }
+    template <int N>
+    __device__ __forceinline__ void codes(const f32x4 (&x)[N], uint32_t (&c)[N][4]) const {
+        if (__builtin_expect(!(s > 0.f && s < __builtin_inff()), 0)) {
+            asm volatile("");                        // (a branch: left alone, the divisions are done everywhere and one of two results taken)
+#pragma unroll
+            for (int i = 0; i < 4 * N; ++i) c[i >> 2][i & 3] = clamp(__fdiv_rn(x[i >> 2][i & 3], s));
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 4 * N; ++i) {
+            const float v = x[i >> 2][i & 3], q = v * y;
+            c[i >> 2][i & 3] = clamp(__builtin_fmaf(__builtin_fmaf(-q, s, v), y, q));
+        }
+    }
+};
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+// the maximum over the wavefront, in every lane: within 16 lanes by lane permutations of the instruction itself, then the four
+__device__ __forceinline__ float wave_max(float m) {
+    m = __builtin_fmaxf(m, dpp_move<0xB1>(m));       // quad_perm [1,0,3,2]
+    m = __builtin_fmaxf(m, dpp_move<0x4E>(m));       // quad_perm [2,3,0,1]
+    m = __builtin_fmaxf(m, dpp_move<0x141>(m));      // row_half_mirror
+    m = __builtin_fmaxf(m, dpp_move<0x140>(m));      // row_mirror
+    float r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = f32_from_bits((uint32_t)__builtin_amdgcn_readlane((int)f32_bits(m), 16 * i));
+    return __builtin_fmaxf(__builtin_fmaxf(r[0], r[1]), __builtin_fmaxf(r[2], r[3]));
+}
+
 // ---- buffer loads -----------------------------------------------------------------------------------------------------
 // A load whose offset lies past the buffer's end accesses no memory and returns zeros.
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
@@ -138,6 +184,8 @@ __device__ __forceinline__ BufferRsrc buffer_rsrc(const void* p, uint32_t bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 __device__ __forceinline__ u32x4 buffer_load16(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
+__device__ __forceinline__ u32x4 buffer_load16_nt(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 2); }
+__device__ __forceinline__ uint32_t buffer_load4(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
 __device__ __forceinline__ uint32_t buffer_load1(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0); }
 
 // ---- direct-to-LDS loads ----------------------------------------------------------------------------------------------
