@@ -547,14 +547,16 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 
 // ---- the same product with every operand staged by direct-to-LDS loads -----------------------------------------------
 // What bounds these launches is not the loads' latency (three or seven stages ahead measure the same) but one or two
-// wavefronts on a SIMD issuing an instruction every eight cycles each, and LDS reads: 64 x 128 tiles of four 64 x 32
-// wavefronts, two workgroups on a compute unit, are the fastest where the launch is a round or two.  Main product, the
-// fastest form of tiled_kernel -> the fastest of this one: 4112 x 11000 at 203 tokens 52 -> 38 us (480 TFLOP/s on 344
-// workgroups), 11008 x 4096 at 64 tokens 65 -> 21 us (in planes); 2-bit weights with rank 256, 4096 x 4096 at 2048 tokens
-// 101 -> 80 us, at 64 tokens 84 -> 30 us (there the correction: its operands are asked for in one go per two chunks).
-// D = stages of 64 K in LDS: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN] 1 KiB of codes
-// [wave][TN] 256 B of exponent words; chunk ch + D - 1 is asked for when chunk ch starts.
-template <int TM, int TN, int WR, int WC, int D, int MINW, bool PLANES, int WB>
+// wavefronts on a SIMD issuing an instruction every four to eight cycles each, and the waits for their LDS reads: 64 x 128 tiles of four
+// 64 x 32 wavefronts, two or three workgroups on a compute unit, are the fastest where the launch is a round or two.  A K tile of such
+// a workgroup takes 0.83 us alone and 1.5 us beside another (its MFMAs: 0.45 and 0.9), 1.17 and 1.77 by a loop of two chunks
+// over five stages with the reads one step ahead (45 scalar instructions a chunk and ten vector ones for addresses: now 18 and none).
+// Whole calls, that loop -> this one: 4096 x 4096 at 40 tokens 16.9 -> 15.9 us, 4096 x 11008 at 128 32.7 -> 27.2,
+// 4112 x 11000 at 203 44.9 -> 38.9, 4096 x 4096 at 512 36.8 -> 31.2, rank 64 at 1024 57.4 -> 53.9; 2-bit rank 128 at 512 50.0 -> 43.5.
+// (The correction's operands are asked for in one go per two chunks: 2-bit weights with rank 256 at 64 tokens 84 -> 30 us.)
+// Four stages of 64 K in LDS, one per chunk of a K tile: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN]
+// 1 KiB of codes [wave][TN] 256 B of exponent words; chunk ch + 3 is asked for when chunk ch starts.
+template <int TM, int TN, int WR, int WC, int MINW, bool PLANES, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a) {
     static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
     constexpr int BM = 32 * TM * WR, NW = WR * WC, NT = 64 * NW;
@@ -562,7 +564,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     constexpr int XL = XB / 1024 / NW;             // activation loads per wavefront and chunk
     static_assert(XB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
     constexpr int L = XL + 2 * TN;                 // loads per wavefront and chunk
-    static_assert(D >= 3 && D <= 5, "a chunk computed, one read ahead, one on its way; a K tile has the D - 1 chunks asked for first");
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -616,26 +617,25 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     const int64_t tile_stride = a.N32 * a.rec_bytes;
     const uint8_t* x_ptr = reinterpret_cast<const uint8_t*>(a.Xh + m0 * a.ldxh + kt0 * kTileK);
     const uint8_t* w_ptr = a.Wt + g_first * a.rec_bytes + kt0 * tile_stride;       // record of the K tile being asked for
-    int cc_in = 0;                                 // its chunk
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds);
-    auto issue = [&](uint32_t stage) {             // the next chunk of the row -> the stage at that byte offset
-        const uint32_t at_x = lds0 + stage + wave * 1024, at_w = lds0 + stage + wave * (TN * 1024), at_e = lds0 + stage + wave * (TN * 256);
-        lds_dma16<0>(at_x, x_off[0], x_ptr);
-        if constexpr (XL > 1) lds_dma16<NW * 1024>(at_x, x_off[1], x_ptr);
-        if constexpr (XL > 2) lds_dma16<2 * NW * 1024>(at_x, x_off[2], x_ptr);
-        if constexpr (XL > 3) lds_dma16<3 * NW * 1024>(at_x, x_off[3], x_ptr);
-        const uint8_t* wp = w_ptr + (WB == 4 ? cc_in : cc_in >> 1) * 1024;
-        // exponent word of the chunk: with nibbles the record's only one, with bytes the first or second four of a lane's eight
-        const uint8_t* ep = w_ptr + (exp4 ? 0 : (cc_in >> 1) * 4);
-        lds_dma16<WOFF>(at_w, w_off[0], wp);
-        lds_dma4<EOFF>(at_e, e_off[0], ep);
+    const uint32_t at_x = lds0 + wave * 1024, at_w = lds0 + wave * (TN * 1024), at_e = lds0 + wave * (TN * 256);
+    const uint32_t e_half = exp4 ? 0 : 4;          // exponent words: with nibbles the record's only one, with bytes the first or second four of a lane's eight
+    auto issue = [&](auto cc) {                    // the next chunk of the row, number CC of its K tile -> stage CC
+        constexpr int CC = decltype(cc)::value, ST = CC * STAGE;
+        lds_dma16<ST>(at_x, x_off[0], x_ptr);
+        if constexpr (XL > 1) lds_dma16<ST + NW * 1024>(at_x, x_off[1], x_ptr);
+        if constexpr (XL > 2) lds_dma16<ST + 2 * NW * 1024>(at_x, x_off[2], x_ptr);
+        if constexpr (XL > 3) lds_dma16<ST + 3 * NW * 1024>(at_x, x_off[3], x_ptr);
+        const uint8_t* wp = w_ptr + (WB == 4 ? CC : CC >> 1) * 1024;
+        const uint8_t* ep = CC < 2 ? w_ptr : w_ptr + e_half;
+        lds_dma16<ST + WOFF>(at_w, w_off[0], wp);
+        lds_dma4<ST + EOFF>(at_e, e_off[0], ep);
         if constexpr (TN > 1) {
-            lds_dma16<WOFF + 1024>(at_w, w_off[TN - 1], wp);
-            lds_dma4<EOFF + 256>(at_e, e_off[TN - 1], ep);
+            lds_dma16<ST + WOFF + 1024>(at_w, w_off[TN - 1], wp);
+            lds_dma4<ST + EOFF + 256>(at_e, e_off[TN - 1], ep);
         }
         x_ptr += 128;
-        cc_in = (cc_in + 1) & 3;
-        w_ptr += cc_in == 0 ? tile_stride : 0;
+        if constexpr (CC == 3) w_ptr += tile_stride;
     };
     static_assert(XL <= 4 && TN <= 2, "issue() spells its loads out");
 
@@ -675,12 +675,15 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             for (int r = 0; r < 16; ++r) acc0[tm][tn][r] = acc1[tm][tn][r] = 0.f;
 
     // ---- main product --------------------------------------------------------------------------------------------
-    const int chunks = (kt1 - kt0) * 4;            // of this workgroup
-    // Software pipeline of MFMA steps (16 of K): while the MFMAs of one step run, the weights of the next are expanded
-    // and its activations read from LDS.  A wavefront issues a vector instruction every eight cycles at best, so what
-    // bounds these launches - one or two wavefronts on a SIMD - is the instructions between its MFMAs: the pattern
-    // below puts a few behind every MFMA, where they cost nothing.
-    Frag xa[TM];
+    const int tiles = kt1 - kt0;                   // K tiles of this workgroup
+    // Software pipeline of MFMA steps (16 of K), four to a chunk, four chunks to a K tile, all of them spelled out so that
+    // every LDS address is a constant behind a lane's: while the MFMAs of one step run, the weights of the next are expanded and
+    // the activations of the third one after it (AHEAD) read from LDS.  A wavefront issues an instruction every four to eight
+    // cycles and an LDS read takes longer than a step, so what bounds these launches - one or two wavefronts on a SIMD -
+    // is the instructions between its MFMAs and the waits for operands: the pattern below puts a few vector instructions
+    // behind every MFMA, where they cost nothing.
+    constexpr int AHEAD = TN == 1 ? 3 : 2;         // steps (a step of two column groups is twice as long, and short of registers)
+    Frag xr[4][TM];                                // activations of step s of this chunk or the next
     bf16x8 wv[TN];
     float sc[TN][2];
     auto scales = [&](const WSet& w, int cc) {
@@ -699,30 +702,30 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             else wv[tn] = unpack_w8_b2(w.c[tn][s4 >> 1], s4 & 1, sc[tn][s4 >> 1]);
         }
     };
-    // Chunk ch: on entry xa and wv hold its step 0 and w its codes; on exit xa and wv hold step 0 of chunk ch + 1 and wn its codes.
-    auto chunk = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, int ch, const uint8_t* cur, const uint8_t* nxt) {
-        read_w(wn, nxt, ch + 1);
+    // Chunk CC: on entry xr holds its first AHEAD steps, wv the weights of step 0 and w its codes; on exit the same of the next chunk, in wn its codes.
+    auto chunk = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        const uint8_t* const cur = lds + CC * STAGE;
+        const uint8_t* const nxt = lds + (CC + 1) % 4 * STAGE;
+        read_w(wn, nxt, CC + 1);
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) {
-            Frag xn[TM];
             bf16x8 now[TN];
-            if (s4 < 3) read_x(xn, cur, s4 + 1);
-            else read_x(xn, nxt, 0);
+            read_x(xr[(s4 + AHEAD) & 3], s4 + AHEAD < 4 ? cur : nxt, (s4 + AHEAD) & 3);
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) now[tn] = wv[tn];
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) acc[tm][tn] = mfma32(now[tn], xa[tm].v, acc[tm][tn]);
+                for (int tm = 0; tm < TM; ++tm) acc[tm][tn] = mfma32(now[tn], xr[s4][tm].v, acc[tm][tn]);
             if (s4 < 3) {
                 expand(w, s4 + 1);
             } else {
-                scales(wn, ch + 1);
+                scales(wn, CC + 1);
                 expand(wn, 0);
             }
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) xa[tm] = xn[tm];
-            __builtin_amdgcn_sched_group_barrier(0x100, TM, 0);                                    // LDS reads
+            if (s4 == 0) __builtin_amdgcn_sched_group_barrier(0x100, TM + 2 * TN, 0);              // LDS reads
+            else __builtin_amdgcn_sched_group_barrier(0x100, TM, 0);
 #pragma unroll
             for (int i = 0; i < TM * TN; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // an MFMA
@@ -731,13 +734,12 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto next_stage = [](uint32_t s) { return s + STAGE == D * STAGE ? 0u : s + STAGE; };
-    uint32_t st_in = 0;                            // stage the next chunk goes to
-#pragma unroll
-    for (int i = 0; i < D - 2; ++i) {
-        issue(st_in);
-        st_in = next_stage(st_in);
-    }
+    constexpr std::integral_constant<int, 0> C0{};
+    constexpr std::integral_constant<int, 1> C1{};
+    constexpr std::integral_constant<int, 2> C2{};
+    constexpr std::integral_constant<int, 3> C3{};
+    issue(C0);
+    issue(C1);
 
     // ---- rank-kp correction: [T_hi | T_lo | 0] against B_k, by the workgroup with the start of K -----------------------
     // (its tiles of T take the memory of the last two stages, which the loads on their way do not write)
@@ -750,7 +752,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     const int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4);
     // Asked for beside the first chunks instead of behind the last: rank 128 at 512 tokens 56 -> 54 us, 2-bit rank 256 at 64
     // tokens 51 -> 48 us a call; nothing slower.
-    uint8_t* const t_tiles = lds + (D - 2) * STAGE;
+    uint8_t* const t_tiles = lds + 2 * STAGE;
     for (int cc0 = 0; cc0 < my_tail; cc0 += 2) {   // two correction chunks at a time (ranks up to 64 need one round)
         u32x4 bw[2][2][TN];                        // B_k's codes and exponents of both chunks: asked for ahead of T
         uint32_t be[2][2][TN];
@@ -833,37 +835,40 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     }
     if (my_tail > 0) __syncthreads();              // the tiles of T have been read by everybody
 
-    issue(st_in);
-    st_in = next_stage(st_in);
-    staged_wait<(D - 2) * L>();
+    issue(C2);
+    staged_wait<2 * L>();
     WSet w0, w1;
-    read_x(xa, lds, 0);
+#pragma unroll
+    for (int s4 = 0; s4 < AHEAD; ++s4) read_x(xr[s4], lds, s4);
     read_w(w0, lds, 0);
     scales(w0, 0);
     expand(w0, 0);
-    uint32_t st = 0;                               // stage of chunk ch
-    auto step = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, int ch) {
-        if (ch + D <= chunks) {
-            // chunks ch and ch + 1 have landed; the stage of chunk ch - 1 has been read by everybody and takes chunk ch + D - 1
-            staged_wait<(D - 3) * L>();
-            issue(st_in);
-            st_in = next_stage(st_in);
-        } else {
-            staged_wait<0>();                      // nothing left to ask for
+    // A K tile.  Chunks CC and CC + 1 have landed when CC starts, for every wavefront; its predecessor has been read by
+    // everybody (the RA newest reads are of CC itself), and that stage takes chunk CC + 3: of the same K tile, or of the next
+    // one unless this is the last.
+    constexpr int RA = AHEAD * TM;
+    auto tile = [&](f32x16 (&acc)[TM][TN], auto last) {
+        constexpr bool LAST = decltype(last)::value;
+        staged_wait<L, RA>();
+        issue(C3);
+        chunk(acc, w0, w1, C0);
+        staged_wait<L, RA>();
+        if constexpr (!LAST) issue(C0);
+        chunk(acc, w1, w0, C1);
+        staged_wait<LAST ? 0 : L, RA>();
+        if constexpr (!LAST) issue(C1);
+        chunk(acc, w0, w1, C2);
+        if constexpr (!LAST) {
+            staged_wait<L, RA>();
+            issue(C2);
         }
-        const uint32_t nx = next_stage(st);
-        chunk(acc, w, wn, ch, lds + st, lds + nx);      // (the last one reads ahead what nobody uses)
-        st = nx;
+        chunk(acc, w1, w0, C3);                    // (the last one reads ahead what nobody uses)
     };
-    const int half = (kt1 - kt0 + 1) / 2 * 4;      // (four chunks per K tile)
-    for (int ch = 0; ch < half; ch += 2) {
-        step(acc0, w0, w1, ch);
-        step(acc0, w1, w0, ch + 1);
-    }
-    for (int ch = half; ch < chunks; ch += 2) {
-        step(acc1, w0, w1, ch);
-        step(acc1, w1, w0, ch + 1);
-    }
+    const int half = (tiles + 1) / 2;
+    int kt = 0;
+    for (; kt < half && kt + 1 < tiles; ++kt) tile(acc0, std::false_type{});
+    for (; kt + 1 < tiles; ++kt) tile(acc1, std::false_type{});
+    tile(acc1, std::true_type{});
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
@@ -1050,27 +1055,26 @@ static bool split_pays(const TileShape& sh, int64_t tiles, int64_t KT, int cus) 
 // workgroups, `fixed` per launch; every two chunks of the correction beyond the first two take corr[0] + corr[1] S, S the
 // partial sums of T, per round of workgroups that have it, and tile[0] + tile[1] S per output tile of the busiest compute unit
 // (two workgroups there share its way to the caches); Y takes `out` per MB; planes take `plane` and `plane_mb` per MB of partial
-// sums written and read.  Fitted to 25000 timings of 1900 calls (K 256 to 14336, N 256 to 28672, 33 to 65536 tokens, ranks 0 to
-// 256): mean error 3 to 8 % a shape.  Fitted to two thirds of them, its choice on the others is 1 % from the fastest form timed
-// on average, within 6 to 7 % on 95 % of the calls, 34 % off at the very worst (8720 x 896 with rank 256 at 3236 tokens).
-// Main product, best form of tiled_kernel against what is chosen: 4096 x 4096 at 64 tokens 43 us and 15 (64 x 128 in planes),
-// 11008 x 4096 at 64 tokens 65 and 21, 4112 x 11000 at 203 tokens 52 and 38 (64 x 128), 2-bit 4096 x 4096 with rank 256 at 2048
-// tokens 101 and 80 (64 x 512).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits and
+// sums written and read.  Fitted to 5000 timings of 769 calls (K 256 to 14336, N 256 to 28672, 33 to 65536 tokens, ranks 0 to
+// 256), 128 x 512 to 25000 older ones: mean error 4 to 7 % a shape.  Its choice is 0.6 % from the fastest form timed on average, within 4 % on
+// 95 % of the calls, 33 % off at the very worst (2.4 %, 17 %, 33 % with the figures of the staged kernel's loop before).
+// Main product, best form of tiled_kernel against what is chosen: 4096 x 4096 at 64 tokens 43 us and 12 (64 x 128 in planes),
+// 4112 x 11000 at 203 tokens 52 and 33 (64 x 128), 2-bit 4096 x 4096 with rank 256 at 2048 tokens 101 and 80 (64 x 512).  Forms of tiled_kernel belong to the choice as much as the staged ones, also at 2 bits and
 // large ranks: best staged form against what is chosen, 384 x 27648 with rank 128 at 4627 tokens 265 us and 243, 2-bit
 // 592 x 912 with rank 64 at 63752 tokens 170 and 140.
 struct SmallShape { int id, bm, bn, resident; double unit[2], round, fixed, corr[2], tile[2], out, plane, plane_mb; };
 static const SmallShape kSmallShapes4[] = {
-    {33, 64, 128, 2, {1.17, 1.77}, 2.6, 6.5, {0.0, 0.0}, {0.55, 0.65}, 0.058, 4.2, 0.116},
-    {31, 64, 256, 2, {1.91, 2.96}, 1.1, 7.2, {0.79, 0.04}, {0.74, 0.70}, 0.186, 4.6, 0.146},
-    {32, 64, 512, 1, {3.01, 0.0}, 2.7, 6.0, {0.0, 0.0}, {3.00, 0.46}, 0.205, 4.4, 0.157},
-    {12, 128, 256, 2, {3.18, 5.28}, 0.0, 8.1, {2.35, 1.05}, {0.0, 1.31}, 0.208, 0.0, 0.0},          // tiled_kernel, whole tiles
+    {33, 64, 128, 2, {0.83, 1.52}, 2.11, 5.75, {0.99, 0.0}, {0.0, 0.66}, 0.074, 3.6, 0.125},
+    {31, 64, 256, 2, {1.62, 2.80}, 1.27, 6.38, {2.48, 0.0}, {0.0, 0.58}, 0.191, 3.6, 0.169},
+    {32, 64, 512, 1, {2.61, 0.0}, 2.99, 6.01, {0.0, 0.31}, {3.72, 0.0}, 0.193, 3.5, 0.170},
+    {12, 128, 256, 2, {3.07, 5.26}, 2.24, 6.15, {2.03, 1.40}, {0.0, 1.11}, 0.188, 0.0, 0.0},        // tiled_kernel, whole tiles
     {11, 128, 512, 1, {4.69, 0.0}, 2.7, 7.2, {0.0, 0.0}, {4.15, 1.16}, 0.220, 0.0, 0.0},
 };
 static const SmallShape kSmallShapes2[] = {
-    {33, 64, 128, 2, {1.24, 1.82}, 3.0, 6.4, {0.0, 0.0}, {0.36, 0.65}, 0.042, 4.1, 0.119},
-    {31, 64, 256, 2, {1.93, 3.00}, 1.55, 7.1, {0.14, 0.26}, {0.98, 0.50}, 0.178, 4.4, 0.148},
-    {32, 64, 512, 1, {3.00, 0.0}, 3.2, 6.3, {0.0, 0.0}, {2.60, 0.48}, 0.186, 3.7, 0.163},
-    {12, 128, 256, 2, {3.19, 5.33}, 0.0, 8.7, {1.44, 1.44}, {0.41, 0.91}, 0.198, 0.0, 0.0},
+    {33, 64, 128, 2, {0.89, 1.52}, 1.18, 6.52, {0.20, 0.04}, {0.0, 0.61}, 0.116, 3.9, 0.148},
+    {31, 64, 256, 2, {1.63, 2.77}, 0.90, 6.87, {1.36, 0.02}, {0.0, 0.66}, 0.221, 3.7, 0.183},
+    {32, 64, 512, 1, {2.57, 0.0}, 3.85, 5.52, {0.0, 0.46}, {2.51, 0.0}, 0.168, 3.2, 0.189},
+    {12, 128, 256, 2, {3.08, 5.22}, 0.38, 8.44, {1.68, 2.03}, {0.0, 0.47}, 0.192, 0.0, 0.0},
     {11, 128, 512, 1, {4.53, 0.0}, 3.2, 7.8, {0.0, 0.0}, {3.50, 1.30}, 0.205, 0.0, 0.0},
 };
 // The 128 x 512 shape with tiles cut in pieces, for 4 and 2 bits: us per launch, K tile of a piece, K tile and number of whole
@@ -1209,18 +1213,18 @@ static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipS
 }
 
 // staged_kernel on whole tiles, or on K planes and then their sum.
-template <int WB, int TM, int TN, int WR, int WC, int D, int MINW>
+template <int WB, int TM, int TN, int WR, int WC, int MINW>
 static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_t s) {
     constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC, NW = WR * WC;
-    constexpr int LDS_BYTES = D * (BM * 128 + NW * TN * 1280);
+    constexpr int LDS_BYTES = 4 * (BM * 128 + NW * TN * 1280);
     a.grid_m = (int)((a.M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.dp_tiles = (int64_t)a.grid_m * a.grid_n;
     a.sk_share = pick.share;
     static KernelSetup setup_whole, setup_planes;
     if (pick.planes == 1)
-        return launch_kernel(staged_kernel<TM, TN, WR, WC, D, MINW, false, WB>, setup_whole, LDS_BYTES, a.dp_tiles, 64 * NW, a, s);
-    const hipError_t e = launch_kernel(staged_kernel<TM, TN, WR, WC, D, MINW, true, WB>, setup_planes, LDS_BYTES,
+        return launch_kernel(staged_kernel<TM, TN, WR, WC, MINW, false, WB>, setup_whole, LDS_BYTES, a.dp_tiles, 64 * NW, a, s);
+    const hipError_t e = launch_kernel(staged_kernel<TM, TN, WR, WC, MINW, true, WB>, setup_planes, LDS_BYTES,
                                        a.dp_tiles * pick.planes, 64 * NW, a, s);
     if (e != hipSuccess) return e;
     const int64_t items = a.M * (plane_ld(a.N) / 4);
@@ -1231,9 +1235,9 @@ static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_
 template <int WB>
 static hipError_t launch_staged(const TiledArgs& a, const SmallPick& pick, hipStream_t s) {
     switch (pick.id) {
-        case 31: return launch_staged_t<WB, 2, 2, 1, 4, 3, 2>(a, pick, s);      // 64 x 256, 54 KB: two workgroups per compute unit
-        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 5, 2>(a, pick, s);      // 64 x 512, 140 KB
-        default: return launch_staged_t<WB, 2, 1, 1, 4, 5, 2>(a, pick, s);      // 64 x 128, 65 KB: two workgroups per compute unit
+        case 31: return launch_staged_t<WB, 2, 2, 1, 4, 2>(a, pick, s);      // 64 x 256, 72 KB: two workgroups per compute unit
+        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 2>(a, pick, s);      // 64 x 512, 112 KB
+        default: return launch_staged_t<WB, 2, 1, 1, 4, 2>(a, pick, s);      // 64 x 128, 52 KB: two workgroups per compute unit
     }
 }
 

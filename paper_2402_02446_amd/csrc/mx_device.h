@@ -200,11 +200,11 @@ template <int ADD>
 __device__ __forceinline__ void lds_dma4(uint32_t at, uint32_t off, const uint8_t* base) {
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(at), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
 }
-// All but this wavefront's newest `LEFT` loads have landed, its LDS reads have returned, and so have everybody's.
-template <int LEFT>
+// All but this wavefront's newest LEFT loads have landed, all but its newest READS reads of LDS have returned, and so have everybody's.
+template <int LEFT, int READS = 0>
 __device__ __forceinline__ void staged_wait() {
-    static_assert(LEFT >= 0 && LEFT < 64, "a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+    static_assert(LEFT >= 0 && LEFT < 64 && READS >= 0 && READS < 16, "a 6-bit and a 4-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)\n\ts_barrier" ::"n"(LEFT), "n"(READS) : "memory");
 }
 
 }  // namespace lqer
