@@ -310,7 +310,8 @@ int lqer_int_layer_import(int64_t K, int64_t N, int k, const uint8_t* Wc, const 
     L.kp32 = (kp + 31) / 32;
     L.act_bits = 8; L.w_bits = 4; L.w_rec_bytes = 2048; L.w_exp_bias = -1;
     L.format = 1;
-    L.Wt = L.At = L.Bt = nullptr;
+    L.Wt = L.W6 = L.At = L.Bt = nullptr;
+    L.w6_ok = false;
     L.Wsc = L.Asc = L.Bsc = nullptr;
     const int64_t G = K / 128;
     int st = LQER_OK;

@@ -40,7 +40,9 @@ struct PrepArgs {
     int g_first;           // first rank group of plane 0
     const uint8_t* At;
     uint16_t* Xh; int64_t ldxh;
-    int64_t tail_cols;     // columns behind K_pad in Xh (T_hi | T_lo | zero padding)
+    uint16_t* Xt; int64_t ldxt;   // T_hi | T_lo | zero padding, row by row
+    int64_t tail_cols;     // its columns
+    uint8_t* Xe6;          // SIX: exponent bytes of the fp6 blocks (Xh: the images)
     float* Tpart;
     int64_t tp_rows;       // rows per slice of Tpart
     int lr;                // CELLS: log2 of the token rows per 16-byte cell column
@@ -72,9 +74,11 @@ __device__ __forceinline__ float dpp_quad(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
 
-template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false>
+// SIX: the activations are stored as fp6 operands (layout in lqer_internal.h) instead of bf16, and read back so by SRC 2.
+template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false, bool SIX = false>
 __device__ __forceinline__ void prep_body(const PrepArgs& a) {
-    static_assert(!RW || (SRC == 0 && !CELLS), "the row-wise form reads fp32 rows and writes row-major bf16");
+    static_assert(!RW || (SRC == 0 && !CELLS && !SIX), "the row-wise form reads fp32 rows and writes row-major bf16");
+    static_assert(!SIX || (!CELLS && SRC != 1), "fp6 operands are made of fp32 activations");
     // ROWWISE (fp32 X in, row-major bf16 out: the prefill case, bound by HBM): a wavefront reads and writes whole rows
     // of its 16 x 256 tile - 1 KiB per load, 512 B per store, every cache line touched by one instruction - with the
     // four lanes of a quad sharing a block, and turns the tile into the MFMA operand order (lane = token, 16-byte
@@ -228,6 +232,15 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
         const uint16_t* hrow = a.Xh + rowc * a.ldxh;
         const uint8_t* alane = a.At + lane * 16;
         const int units = (int)(tile_end - tile_begin) * 4;
+        // fp6 images: this lane's row in one, the image of a unit, the byte of its block's exponent
+        const int six_row = (int)((row_ok ? row : a.M - 1) & (kX6Rows - 1));
+        const int64_t six_rt = (row_ok ? row : a.M - 1) / kX6Rows;
+        auto six_image = [&](int unit) {
+            return reinterpret_cast<uint8_t*>(a.Xh) + ((six_rt * a.KT + tile_begin) * 4 + unit) * kX6Chunk;
+        };
+        auto six_exp = [&](int unit) {
+            return a.Xe6 + (six_rt * a.KT + tile_begin + (unit >> 2)) * kX6Scales + (q >> 1) * 1024 + six_row * 8 + 2 * (unit & 3) + (q & 1);
+        };
         auto load_a = [&](Frag (&af)[2], int g, int unit) {
             const int gc = g < ng ? g : 0;
             const uint8_t* rec = alane + ((int64_t)(g0 + gc) * a.KT + tile_begin + (unit >> 2)) * kARecordBytes + (unit & 3) * 2048;
@@ -243,7 +256,13 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                     for (int g = 0; g < MAXG; ++g) load_a(u.af[g], g, unit);
                 }
             }
-            if constexpr (SRC == 2) {
+            if constexpr (SRC == 2 && SIX) {
+                const uint8_t* img = six_image(unit);
+                u.x[0] = *reinterpret_cast<const u32x4*>(img + q * 2048 + six_row * 16);
+                const u32x2 w = *reinterpret_cast<const u32x2*>(img + 8192 + q * 1024 + six_row * 8);
+                u.x[1] = u32x4{w[0], w[1], 0u, 0u};
+                u.eb = *six_exp(unit);
+            } else if constexpr (SRC == 2) {
                 static_assert(SRC != 2 || !CELLS, "the stored matrix is read back in its row-major form only");
                 u.x[0] = *reinterpret_cast<const u32x4*>(hrow + kbc * 16);
                 u.x[1] = *reinterpret_cast<const u32x4*>(hrow + kbc * 16 + 8);
@@ -265,7 +284,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                     af[g][0] = cur.af[g][0];
                     af[g][1] = cur.af[g][1];
                 }
-            } else if (a.kp > 0) {
+            } else if (!SIX && a.kp > 0) {
 #pragma unroll
                 for (int g = 0; g < MAXG; ++g) load_a(af[g], g, unit);
             }
@@ -278,7 +297,14 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
             float r[16];
             u32x4 cw = u32x4{0, 0, 0, 0};                    // the block's 16 codes as bytes (SRC 1, or CELLS of 16+ rows)
             uint32_t eb = 0;
-            if constexpr (SRC == 2) {
+            if constexpr (SRC == 2 && SIX) {
+                const u32x6 v = {cur.x[0][0], cur.x[0][1], cur.x[0][2], cur.x[0][3], cur.x[1][0], cur.x[1][1]};
+                six_to_values(v, x_scale(cur.eb, 6), r);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) xf[h].u[i] = ok ? pack_bf16_exact(r[8 * h + 2 * i], r[8 * h + 2 * i + 1]) : 0u;
+            } else if constexpr (SRC == 2) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -329,7 +355,14 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                         xf[h].u[i] = pack_bf16_exact(r[8 * h + 2 * i] * scale, r[8 * h + 2 * i + 1] * scale);
             }
             if (store_x && row_ok) {
-                if (CELLS) {
+                if constexpr (SIX) {
+                    // six-bit codes (4 fraction bits) as multiples of 4 with the 8-bit codes' scale
+                    const u32x6 w = codes_to_six(r, (float)(64 >> a.act_frac));
+                    uint8_t* img = six_image(unit);
+                    *reinterpret_cast<u32x4*>(img + q * 2048 + six_row * 16) = u32x4{w[0], w[1], w[2], w[3]};
+                    *reinterpret_cast<u32x2*>(img + 8192 + q * 1024 + six_row * 8) = u32x2{w[4], w[5]};
+                    *six_exp(unit) = (uint8_t)eb;
+                } else if (CELLS) {
                     if (a.x8) {
                         // 16 token rows and more: MXINT8 as it is, 16 code bytes per (block, row), and the
                         // exponent bytes [block][row] behind all codes; the main kernel converts
@@ -349,6 +382,12 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                     *reinterpret_cast<u32x4*>(dst) = xf[0].u;
                     *reinterpret_cast<u32x4*>(dst + 8) = xf[1].u;
                 }
+            }
+            if constexpr (SIX) {
+                // (large calls, whose other wavefronts cover these loads; in front they would take the conversion's registers)
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int g = 0; g < MAXG; ++g) load_a(af[g], g, unit);
             }
             if (a.kp > 0) {
 #pragma unroll
@@ -395,7 +434,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                 uint16_t hi[4], lo[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) split_bf16(s[j], hi[j], lo[j]);
-                uint16_t* base = a.Xh + orow * a.ldxh + a.KT * kTileK;
+                uint16_t* base = a.Xt + orow * a.ldxt;
                 *reinterpret_cast<u32x2*>(base + r0) =
                     u32x2{(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
                 *reinterpret_cast<u32x2*>(base + a.kp + r0) =
@@ -410,14 +449,14 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
         const int pad = (int)(a.tail_cols - 2 * a.kp);
         for (int item = threadIdx.x; item < 16 * pad; item += nthreads) {
             const int64_t orow = (int64_t)blockIdx.x * 16 + item / pad;
-            if (orow < a.M) a.Xh[orow * a.ldxh + a.KT * kTileK + 2 * a.kp + item % pad] = 0;
+            if (orow < a.M) a.Xt[orow * a.ldxt + 2 * a.kp + item % pad] = 0;
         }
     }
 }
 
-template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false>
+template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false, bool SIX = false>
 __global__ __launch_bounds__(64 * (RW ? kPrepRowWaves : kPrepWaves), RW ? 4 : 1) void prep_kernel(PrepArgs a) {
-    prep_body<SRC, FINAL, MAXG, CELLS, RW>(a);
+    prep_body<SRC, FINAL, MAXG, CELLS, RW, SIX>(a);
 }
 
 // Several layers applied to the same few tokens: grid.z holds the rank groups of all of them (the first plane stores the
@@ -454,7 +493,13 @@ __global__ __launch_bounds__(64 * kPrepWaves) void prep_group_kernel(PrepGroup g
 }
 
 template <int SRC, bool FINAL, int MAXG, bool CELLS>
-static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& a, bool rowwise) {
+static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& a, bool rowwise, bool six) {
+    if constexpr (SRC != 1 && !CELLS) {
+        if (six) {
+            hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false, true>), grid, block, 0, s, a);
+            return;
+        }
+    }
     if constexpr (SRC == 0 && !CELLS) {
         if (rowwise) {
             hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, true>), grid, block, 0, s, a);
@@ -513,7 +558,9 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     if (!ws.cells && L.kp16 > 4) { gz = reuse_xh ? (L.kp16 + 3) / 4 : 1; a.groups_per_wg = 4; }
     a.g_first = 0;
     a.At = L.At; a.Xh = ws.Xh; a.ldxh = ws.ldxh;
+    a.Xt = ws.Xt; a.ldxt = ws.ldxt;
     a.tail_cols = ws.ldxh - L.KT * kTileK;
+    a.Xe6 = ws.six ? six_scales(ws, L) : nullptr;
     a.Tpart = ws.Tpart;
     a.tp_rows = ws.tp_rows;
     a.lr = ws.lr;
@@ -526,7 +573,8 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     const int src = reuse_xh ? 2 : (Xc != nullptr ? 1 : 0);
     const int64_t rg = (M + 15) / 16;
     // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
-    const bool rowwise = !cells && src == 0 && rg * ws.S * gz >= 2048;
+    if (ws.six && src == 1) return hipErrorInvalidValue;
+    const bool rowwise = !cells && !ws.six && src == 0 && rg * ws.S * gz >= 2048;
     a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S * gz >= 256);
     dim3 block(64 * a.nwaves);
     // clearing workgroups: about four 16-byte stores per thread
@@ -535,7 +583,7 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     const bool fin = (ws.Tpart == nullptr);          // T final (hi/lo behind the row) or partial sums
     if (cells && fin && L.kp > 0) return hipErrorInvalidValue;
     if (a.groups_per_wg > 4) return hipErrorInvalidValue;
-#define LQER_PREP(FC, FN, MG, CL) launch_prep_t<FC, FN, MG, CL>(grid, block, s, a, rowwise)
+#define LQER_PREP(FC, FN, MG, CL) launch_prep_t<FC, FN, MG, CL>(grid, block, s, a, rowwise, ws.six)
 #define LQER_PREP_G(FC, FN) do { if (a.groups_per_wg <= 1) LQER_PREP(FC, FN, 1, false); else if (a.groups_per_wg == 2) LQER_PREP(FC, FN, 2, false); else LQER_PREP(FC, FN, 4, false); } while (0)
 #define LQER_PREP_C(FN) do { if (src == 1) LQER_PREP_G(1, FN); else LQER_PREP_G(0, FN); } while (0)
     if (cells) {

@@ -28,6 +28,16 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
+// The fp6 form (WB = 6).  Above 1.5e11 operations a 4-bit layer's fp32 activations are not brought to bf16 but to fp6 operands:
+// an 8-bit code in two halves against the 4-bit code, exact as before, at half the matrix instructions' time (mfma32_six).  The chip's
+// clock under load is what bounds the bf16 form; this one moves 24 bytes of LDS per operand block instead of 32 and runs half as
+// many passes.  Bounds now: again the clock (4.0 us per K tile of a 128 x 512 tile on a full chip, 2.7 on a nearly empty one; the
+// bare MFMA loop's rate would be 3.2).  Whole calls, bf16 form -> this: 8192 x 28672 rank 64 at 4096 tokens 1477 -> 1093 us, 11008 x 4096
+// rank 32 at 2048 178 -> 138, 4096 x 4096 at 8192 263 -> 200, rank 16 at 65536 2005 -> 1571.  Distance from the 64-bit result unchanged
+// (2.65e-7, 2.38e-7, 2.29e-7, 2.07e-7; on data of wide exponents, where the bf16 chain rounds more often, 7.6e-8 against 1.2e-7
+// at K = 4096).  MXINT codes as input and layers of rank 0 keep bf16 operands: there an exponent byte of 255 (a block with
+// an infinity) is a large scale, to the block-scaled instruction a NaN; with a correction the row is NaN either way.
+//
 // Calls that do not fill the chip for long mostly take staged_kernel (pick_small says which): tiles of 64 rows, every
 // operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
 // the tiles are too few, several workgroups per tile, each with an equal range of K ("planes"), that store their partial
@@ -45,7 +55,9 @@ namespace lqer {
 
 struct TiledArgs {
     const uint8_t* Wt; const uint8_t* Bt;
-    const uint16_t* Xh; int64_t ldxh;
+    const uint16_t* Xh; int64_t ldxh;                // (fp6 form: the images)
+    const uint16_t* Xt; int64_t ldxt;                // T_hi | T_lo | 0, row by row
+    const uint8_t* Xe6;                              // fp6 form: exponent bytes of the activations' blocks
     const float* Tpart; int S; int64_t tp_stride;    // S > 1: T as S fp32 partial sums [S][tp_stride / kp rows][kp]
     float* Y; int64_t ldy;
     int8_t* Yc; uint8_t* Ye; int64_t ldyc;           // Yc != null: store Y as MXINT8 (blocks of 16 along N) instead of fp32
@@ -72,17 +84,21 @@ __host__ __device__ constexpr int64_t plane_ld(int64_t N) { return (N + 3) / 4 *
 // MINW = wavefronts per SIMD the register allocation must allow (2 lets two four-wavefront workgroups share a compute unit)
 // SPLIT = the workgroup walks a list of pieces (work split); otherwise it computes output tile blockIdx.x
 // whole, as straight-line code (the loop over pieces costs the main product a few percent)
-// WB = mantissa bits of W_q: 4, or 2 (half the code bytes per record, one 32-bit word per block)
+// WB = mantissa bits of W_q: 4, or 2 (half the code bytes per record, one 32-bit word per block); 6 = 4-bit weights and 8-bit activations
+// in their fp6 form (mfma32_six)
 template <int TM, int TN, int WR, int WC, int NS, int MINW, bool SPLIT, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) {
-    static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
+    static_assert(WB == 4 || WB == 2 || WB == 6, "weight mantissas of 4 or 2 bits, or the fp6 form");
+    constexpr bool SIX = WB == 6;
     constexpr int BM = 32 * TM * WR;
     constexpr int NW = WR * WC;
-    constexpr int STAGE = BM * 128;                // bytes: BM rows x 64 bf16
+    constexpr int TSTAGE = BM * 128;               // bytes: BM rows x 64 bf16
+    constexpr int STAGE = SIX ? kX6Chunk : TSTAGE;
     constexpr int NT = 64 * NW;
     constexpr int LPT = BM * 8 / NT;               // 16-byte cells each thread moves per chunk
     // chunks between fetching activations and using them: 3 where the registers allow a second set in flight
     constexpr int XD = (TM * TN * 16 + LPT * 8 <= 144) ? 3 : 2;
+    static_assert(!SIX || (BM == kX6Rows && (NT == 512 || NT == 256)), "a tile is as high as an image, and the loader moves whole ones");
     static_assert((BM * 8) % NT == 0, "loader must divide evenly");
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
@@ -103,15 +119,14 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     }
     __shared__ int wait_ok;
     const int KT = (int)a.KT;                                  // K tiles and chunks fit 32 bits: scalar compares
-    const int main_chunks = KT * 4;
     const int nb2 = 2 * a.kp16;
     const int tail_chunks = (nb2 + 3) / 4;
     static_assert(NS == 4, "stage and register-set indices below assume rings of four");
     constexpr int ROWS_PER_PASS = NT / 8;
     static_assert(ROWS_PER_PASS % 16 == 0, "swizzle must not depend on the pass");
-    const int ld_row0 = tid >> 3;
+    int ld_row0 = tid >> 3;
     // (row >> 1) & 7 is the same for every pass because ROWS_PER_PASS is a multiple of 16
-    const int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4);
+    int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4), ld_col = tid & 7;
     // ---- operand reader: in step s this lane reads logical cell 4 hh + s of its TM rows -----------
     // row = (wr TM + tm) 32 + t, so the swizzle term depends on t only
     int rd_off[4];
@@ -124,7 +139,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     const int es1 = exp4 ? 8 : 16, es0 = exp4 ? 4 : 8;
     const uint32_t emask = exp4 ? 0xFu : 0xFFu, ebias = exp4 ? (uint32_t)a.exp_bias : 0u;
     // nibbles sit in front of the codes (lane * 4), bytes behind them (lane * 8)
-    const int code_off = exp4 ? kWCompactCodeOffset : 0, exp_off = exp4 ? lane16 >> 2 : w_code_bytes(WB) + (lane16 >> 1);
+    const int code_off = exp4 ? kWCompactCodeOffset : 0, exp_off = exp4 ? lane16 >> 2 : w_code_bytes(WB == 2 ? 2 : 4) + (lane16 >> 1);
 
     int64_t dp_next = lin;                                     // next whole tile of this workgroup
     int64_t u = a.sk_share * lin;                              // its range of the shared K tiles
@@ -193,7 +208,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[tm][tn][r] = 0.f;
 
-    typedef typename std::conditional<WB == 4, u32x4, u32x2>::type WVec;   // a lane's two blocks of one chunk
+    typedef typename std::conditional<WB == 2, u32x2, u32x4>::type WVec;   // a lane's two blocks of one chunk
     struct WSet {                // packed codes of one chunk for this wavefront's TN column groups
         WVec c[TN];
     };
@@ -206,7 +221,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
             const uint8_t* rec = a.Wt + (tile * a.N32 + group_of(tn)) * a.rec_bytes;   // wave-uniform
-            if constexpr (WB == 4) w.c[tn] = *reinterpret_cast<const u32x4*>(rec + code_off + cc * 1024 + lane16);
+            if constexpr (WB != 2) w.c[tn] = *reinterpret_cast<const u32x4*>(rec + code_off + cc * 1024 + lane16);
             else w.c[tn] = *reinterpret_cast<const u32x2*>(rec + code_off + (cc >> 1) * 1024 + lane16 + (cc & 1) * 8);
         }
     };
@@ -224,11 +239,17 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 #pragma unroll
         for (int j = 0; j < LPT; ++j) st[j] = *reinterpret_cast<const u32x4*>(ld_base + j * ld_stride + (int64_t)ch * 64);
     };
+    // correction chunk tc when T is final
+    auto fetch_tail = [&](u32x4 (&st)[LPT], int tc) {
+        const uint16_t* src = a.Xt + (m0 + ld_row0) * a.ldxt + 8 * ld_col + tc * 64;
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) st[j] = *reinterpret_cast<const u32x4*>(src + j * ROWS_PER_PASS * a.ldxt);
+    };
     // Correction chunk tc when the projection kernel left T as S partial sums (it split K over
     // workgroups): add them in slice order and form the bf16 term this cell holds - T_hi for tail
     // columns below kp, T_lo for the next kp, zero behind.
     auto fetch_t = [&](u32x4 (&st)[LPT], int tc) {
-        const int col = (int)tc * 64 + 8 * (tid & 7);
+        const int col = (int)tc * 64 + 8 * ld_col;
         const bool lo = col >= a.kp;
         const int r0 = lo ? col - a.kp : col;
 #pragma unroll
@@ -254,15 +275,15 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
             st[j] = u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
         }
     };
-    // any chunk of the activation row: a main one or a correction chunk in either form
-    auto fetch_any = [&](u32x4 (&st)[LPT], int ch) {
-        if (ch < main_chunks || a.S <= 1) fetch_x(st, ch);
-        else fetch_t(st, ch - main_chunks);
+    // a correction chunk in either form
+    auto fetch_corr = [&](u32x4 (&st)[LPT], int tc) {
+        if (a.S <= 1) fetch_tail(st, tc);
+        else fetch_t(st, tc);
     };
     auto store_x = [&](const u32x4 (&st)[LPT], int stage) {
 #pragma unroll
         for (int j = 0; j < LPT; ++j)
-            *reinterpret_cast<u32x4*>(lds + stage * STAGE + ld_dst0 + j * ROWS_PER_PASS * 128) = st[j];
+            *reinterpret_cast<u32x4*>(lds + stage * TSTAGE + ld_dst0 + j * ROWS_PER_PASS * 128) = st[j];
     };
     // one 64-wide chunk of the main product: c = chunk index within its K tile = stage = register set.
     // The activation operands are read one MFMA step ahead: `xa` holds step 0 on entry and step 0
@@ -300,6 +321,157 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
         }
     };
 
+    if constexpr (SIX) {
+        // ---- main product on fp6 operands.  The same rings as below, a chunk being two MFMA steps of 32 of K (64 in fp6): an image of
+        // the activations is what LDS holds of it, cell for cell, so that operands are read without conflicts, and the exponent bytes of
+        // a K tile wait in LDS too (two of them, in turn).  An operand is read into the registers of the one just used, one step ahead.
+        constexpr int NP = 8192 / 16 / NT;             // 16-byte cells of an image's first part per thread (the second: as many of 8)
+        struct XSet { u32x4 p[NP]; u32x2 h[NP]; };
+        struct SSet { uint32_t w[NP]; };
+        constexpr uint32_t kAnySize = 0x7FFFFFFFu;     // (every offset used lies in the run the base points to)
+        // Addresses: a scalar one plus one lane offset of 32 bits for each kind of load, one lane offset for each kind of LDS access;
+        // the rest are constants.  (Opaque: left to itself the compiler keeps sums of them in fifty registers.)
+        const int rd_row = wr * TM * 32 + t;
+        uint32_t tid4 = tid * 4, tid8 = tid * 8, tid16 = tid * 16, lane_w = lane * 16, lane_e8 = lane * 8;
+        uint32_t rd16 = hh * 4096 + rd_row * 16, rd8 = hh * 2048 + rd_row * 8, rde = hh * 1024 + rd_row * 8;
+        asm volatile("" : "+v"(tid4), "+v"(tid8), "+v"(tid16), "+v"(lane_w), "+v"(lane_e8), "+v"(rd16), "+v"(rd8), "+v"(rde));
+        const uint8_t* const img0 = reinterpret_cast<const uint8_t*>(a.Xh) + (int64_t)tile_m * a.KT * (4 * kX6Chunk);
+        const uint8_t* const exp0 = a.Xe6 + (int64_t)tile_m * a.KT * kX6Scales;
+        const uint8_t* w_base[TN];
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) w_base[tn] = a.Wt + group_of(tn) * kW6RecordBytes;
+        const int64_t w_stride = a.N32 * kW6RecordBytes;
+        uint8_t* const lds_e = lds + 4 * STAGE;
+        auto fetch = [&](XSet& x, int ch) {
+            const uint8_t* img = img0 + (int64_t)ch * kX6Chunk;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) x.p[j] = buffer_load16(buffer_rsrc(img + j * NT * 16, kAnySize), tid16);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) x.h[j] = buffer_load8(buffer_rsrc(img + 8192 + j * NT * 8, kAnySize), tid8);
+        };
+        auto store = [&](const XSet& x, int stage) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) *reinterpret_cast<u32x4*>(lds + tid16 + (stage * STAGE + j * NT * 16)) = x.p[j];
+#pragma unroll
+            for (int j = 0; j < NP; ++j) *reinterpret_cast<u32x2*>(lds + tid8 + (stage * STAGE + 8192 + j * NT * 8)) = x.h[j];
+        };
+        auto fetch_e = [&](SSet& x, int tile) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) x.w[j] = buffer_load4(buffer_rsrc(exp0 + (int64_t)tile * kX6Scales + j * NT * 4, kAnySize), tid4);
+        };
+        auto store_e = [&](const SSet& x, int parity) {
+#pragma unroll
+            for (int j = 0; j < NP; ++j) *reinterpret_cast<uint32_t*>(lds_e + tid4 + (parity * kX6Scales + j * NT * 4)) = x.w[j];
+        };
+        auto load_w = [&](WSet& w, int ch) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                w.c[tn] = buffer_load16(buffer_rsrc(w_base[tn] + (int64_t)(ch >> 2) * w_stride + (ch & 3) * 1024, kAnySize), lane_w);
+        };
+        auto load_e = [&](ESet& x, int tile) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                x.e[tn] = buffer_load8(buffer_rsrc(w_base[tn] + (int64_t)tile * w_stride + kWExpOffset, kAnySize), lane_e8);
+        };
+        const int first_ch = kt0 * 4, last_main = kt1 * 4 - 1, last_tile = kt1 - 1;
+        u32x6 xa[TM];
+        u32x2 xe[TM];
+        auto read_op = [&](u32x6& x, int tm, int stage, int s) {
+            const u32x4 p = *reinterpret_cast<const u32x4*>(lds + rd16 + (stage * STAGE + s * 2048 + tm * 512));
+            const u32x2 h = *reinterpret_cast<const u32x2*>(lds + rd8 + (stage * STAGE + 8192 + s * 1024 + tm * 256));
+            x = u32x6{p[0], p[1], p[2], p[3], h[0], h[1]};
+        };
+        auto read_e = [&](u32x2& x, int tm, int parity) {
+            x = *reinterpret_cast<const u32x2*>(lds_e + rde + (parity * kX6Scales + tm * 256));
+        };
+        WSet w0, w1, w2, w3;
+        ESet ea, eb;
+        XSet xs0, xs1;
+        SSet se;
+        fetch(xs0, first_ch);
+        fetch_e(se, kt0);
+        load_e(ea, kt0);
+        load_w(w0, first_ch);
+        store(xs0, 0);
+        store_e(se, 0);
+        fetch(xs0, first_ch + 1);
+        load_w(w1, first_ch + 1);
+        store(xs0, 1);
+        fetch(xs0, first_ch + 2);
+        load_w(w2, first_ch + 2);
+        u32x6 wv = expand_six<0>(w0.c[0]);             // weights of the next MFMAs
+        // chunk cc of its K tile: barrier; loads of later chunks; arithmetic; the activations of chunk ch + 2 to LDS
+        auto step = [&](const WSet& cur, const WSet& next, const ESet& ecur, WSet& fill, ESet& enext, XSet& x_old, XSet& x_new, int ch, auto cc, auto pp) {
+            constexpr int C = decltype(cc)::value, P = decltype(pp)::value;   // P: which of the two exponent buffers this K tile's are in
+            // (behind this wavefront's newest LDS write are at least TM reads, of the chunk that starts here: they need not have returned)
+            if (C == 0 && P == 0 && ch == first_ch) {
+                __syncthreads();
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm) {
+                    read_op(xa[tm], tm, 0, 0);
+                    read_e(xe[tm], tm, 0);
+                }
+            } else {
+                staged_wait<63, TM>();
+            }
+            const int tile = ch >> 2, next_tile = tile + 1 < last_tile ? tile + 1 : last_tile;
+            if constexpr (XD == 3) fetch(x_new, ch + 3 < last_main ? ch + 3 : last_main);
+            if constexpr (C == 0) fetch_e(se, next_tile);
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(fill, ch + 3 < last_main ? ch + 3 : last_main);
+            if constexpr (C == 1) load_e(enext, next_tile);
+            // Per MFMA a few vector instructions of the next operand's expansion, and where an activation operand is used for the last
+            // time its registers take the next step's.
+            auto half = [&](const WSet& wn, auto ss) {
+                constexpr int S = decltype(ss)::value, BYTE = (2 * C + S) & 3;
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    const u32x6 now = wv;
+                    if (tn + 1 < TN) wv = expand_six<S>(cur.c[tn + 1]);
+                    else wv = expand_six<1 - S>(S == 0 ? cur.c[0] : wn.c[0]);
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm) {
+                        acc[tm][tn] = mfma32_six<BYTE>(now, xa[tm], acc[tm][tn], ecur.e[tn][C >> 1], xe[tm][C >> 1]);
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        if (tn == TN - 1) {
+                            if constexpr (S == 0) read_op(xa[tm], tm, C, 1);
+                            else read_op(xa[tm], tm, (C + 1) & 3, 0);
+                            if constexpr (S == 1 && C == 3) read_e(xe[tm], tm, 1 - P);
+                            __builtin_amdgcn_sched_group_barrier(0x100, S == 1 && C == 3 ? 3 : 2, 0);
+                        }
+                        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            half(next, std::integral_constant<int, 0>{});
+            store(x_old, (C + 2) & 3);
+            if constexpr (XD == 2) fetch(x_old, ch + 3 < last_main ? ch + 3 : last_main);
+            if constexpr (C == 1) store_e(se, 1 - P);
+            __builtin_amdgcn_sched_barrier(0);
+            half(next, std::integral_constant<int, 1>{});
+        };
+        constexpr std::integral_constant<int, 0> C0{};
+        constexpr std::integral_constant<int, 1> C1{};
+        constexpr std::integral_constant<int, 2> C2{};
+        constexpr std::integral_constant<int, 3> C3{};
+        // XD == 2: one set, written and fetched again in the middle of a chunk
+        XSet& ev_new = (XD == 3) ? xs1 : xs0;
+        XSet& od_old = (XD == 3) ? xs1 : xs0;
+        for (int tile = kt0; tile < kt1; tile += 2) {
+            step(w0, w1, ea, w3, eb, xs0, ev_new, tile * 4 + 0, C0, C0);
+            step(w1, w2, ea, w0, eb, od_old, xs0, tile * 4 + 1, C1, C0);
+            step(w2, w3, ea, w1, eb, xs0, ev_new, tile * 4 + 2, C2, C0);
+            step(w3, w0, ea, w2, eb, od_old, xs0, tile * 4 + 3, C3, C0);
+            if (tile + 1 < kt1) {
+                step(w0, w1, eb, w3, ea, xs0, ev_new, tile * 4 + 4, C0, C1);
+                step(w1, w2, eb, w0, ea, od_old, xs0, tile * 4 + 5, C1, C1);
+                step(w2, w3, eb, w1, ea, xs0, ev_new, tile * 4 + 6, C2, C1);
+                step(w3, w0, eb, w2, ea, od_old, xs0, tile * 4 + 7, C3, C1);
+            }
+        }
+        __syncthreads();                               // the correction's cells lie across the stages, and other threads' than these here
+    } else {
     // prologue: activations of the piece's first two chunks into stages 0 and 1, the weights of its
     // first three, and (XD == 3) the activations of the third in registers
     // (a K tile is four chunks, so a piece has at least four)
@@ -361,6 +533,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
             step(w3, eb, w2, ea, st_odd_old, st_odd_new, tile * 4 + 7, 3);
         }
     }
+    }
 
     // ---- rank-kp correction: [T_hi | T_lo | 0] against B_k ---------------------------------------
     // The correction chunks are fetched here rather than ahead from the main loop: B_k's
@@ -371,21 +544,29 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     // built from them would otherwise be computed once in front of the loop over pieces and
     // occupy registers all through the main product.
     int t_e = t, hh_e = hh, lane_e = lane;
-    if constexpr (SPLIT) asm volatile("" : "+v"(t_e), "+v"(hh_e), "+v"(lane_e));
+    if constexpr (SPLIT || SIX) asm volatile("" : "+v"(t_e), "+v"(hh_e), "+v"(lane_e));
+    if constexpr (SIX) {                                      // (what only the correction needs of them, too)
+        const int tid_e = lane_e + 64 * wave;
+        ld_row0 = tid_e >> 3;
+        ld_col = tid_e & 7;
+        ld_dst0 = ld_row0 * 128 + ((ld_col ^ ((ld_row0 >> 1) & 7)) << 4);
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) rd_off[s4] = (wr * TM * 32 + t_e) * 128 + (((4 * hh_e + s4) ^ ((t_e >> 1) & 7)) << 4);
+    }
     const int my_tail = owner ? tail_chunks : 0;              // the piece that stores the tile adds the correction
     // two correction chunks at a time through stages 0 and 1 (ranks up to 64 need one round, 256 four)
     for (int cc0 = 0; cc0 < my_tail; cc0 += 2) {
         {
             u32x4 tst[2][LPT];
             if (cc0 > 0) __syncthreads();                      // every wavefront has read the previous pair of chunks
-            fetch_any(tst[0], main_chunks + cc0);
-            if (cc0 + 1 < tail_chunks) fetch_any(tst[1], main_chunks + cc0 + 1);
+            fetch_corr(tst[0], cc0);
+            if (cc0 + 1 < tail_chunks) fetch_corr(tst[1], cc0 + 1);
             store_x(tst[0], 0);
             if (cc0 + 1 < tail_chunks) store_x(tst[1], 1);
             __syncthreads();
         }
         for (int cc = cc0; cc < cc0 + 2 && cc < my_tail; ++cc) {
-            const uint8_t* stage = lds + (cc & 1) * STAGE;
+            const uint8_t* stage = lds + (cc & 1) * TSTAGE;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int jb = 4 * cc + 2 * hh_e + j;
@@ -779,7 +960,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
                 tst[q][j] = u32x4{0, 0, 0, 0};
                 if (col >= 2 * a.kp) continue;
                 if (a.S <= 1) {
-                    tst[q][j] = *reinterpret_cast<const u32x4*>(a.Xh + row * a.ldxh + (int64_t)KT * kTileK + col);
+                    tst[q][j] = *reinterpret_cast<const u32x4*>(a.Xt + row * a.ldxt + col);
                     continue;
                 }
                 // T as S fp32 partial sums: added in slice order, then the bf16 term this cell holds
@@ -1143,6 +1324,55 @@ static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes
     return best;
 }
 
+// ---- the fp6 form: which tile, cut along K or not -----------------------------------------------------------------------
+// Time model of the main product in us: `unit` per K tile of a full round of workgroups, `few` of a round of one workgroup on next to no
+// compute unit, `pair_few` of one with two on next to none (what lies between goes by how full it is: a full chip's clock is
+// lower); `round`, `fixed`, `out` per MB of Y and `corr` as above.  Fitted to 140 calls of 1e10 to 2e12 operations (K 512 to 12288, N 1024 to
+// 28672, 64 to 32768 tokens, ranks 8 to 128): mean error 4 %, 10 % at the 95th percentile.  The choice is 1.1 % from the
+// fastest of the forms on average.
+struct SixShape { int id, bn, resident; double unit, few, pair_few, round, fixed, out, corr[2]; };
+static const SixShape kSixShapes[] = {
+    {21, 512, 1, 3.952, 2.685, 0.0, 7.621, 3.716, 0.117, {3.551, 2.391}},
+    {22, 256, 2, 3.967, 2.13, 3.446, 4.983, 7.637, 0.135, {4.162, 3.246}},
+};
+// 128 x 512 with tiles cut in whole pieces, and in equal shares (a rough estimate: it has to promise 3 %)
+static const SmallPieces kSixWhole = {38.0, 3.352, 4.026, 11.96, 4.168, 8.11, 0.0};
+static const SmallPieces kSixShares = {36.3, 3.974, 4.178, 13.52, 0.0, 7.85, 0.0};
+
+struct SixPick { int id; bool cut; double us; };
+
+static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int cus) {
+    const int64_t tiles = ((M + kX6Rows - 1) / kX6Rows) * ((L.N + sh.bn - 1) / sh.bn), per_round = (int64_t)cus * sh.resident;
+    const int64_t full = tiles / per_round, rest = tiles - full * per_round;
+    const double rounds = (double)(full + (rest > 0 ? 1 : 0));
+    double unit = (double)full * sh.unit;
+    if (rest > 0) {
+        const double fill = (double)(rest > cus ? rest - cus : rest) / (double)cus;
+        if (sh.resident == 1) unit += fill * sh.unit + (1.0 - fill) * sh.few;
+        else unit += rest <= cus ? sh.few : fill * sh.unit + (1.0 - fill) * sh.pair_few;
+    }
+    return (double)L.KT * unit + rounds * sh.round + sh.fixed + sh.out * (double)M * (double)L.N * 4e-6 +
+           more_pairs(L.kp) * rounds * (sh.corr[0] + sh.corr[1] * (double)S);
+}
+
+// can_cut: there is room for the pieces' accumulators
+static SixPick pick_six(const Layer& L, int64_t M, int S, bool can_cut, int cus) {
+    SixPick best{0, false, 0.0};
+    for (const SixShape& sh : kSixShapes) {
+        const double us = six_us(sh, L, M, S, cus);
+        if (best.id == 0 || us < best.us) best = SixPick{sh.id, false, us};
+    }
+    if (can_cut) {
+        const int64_t tiles = ((M + kX6Rows - 1) / kX6Rows) * ((L.N + 511) / 512);
+        const Split sp = split_tiles(tiles, L.KT, cus, true);
+        if (sp.sk_units > 0) {
+            const double us = pieces_us(sp.aligned ? kSixWhole : kSixShares, L, S, sp) * (sp.aligned ? 1.0 : 1.03);
+            if (us < best.us) best = SixPick{21, true, us};
+        }
+    }
+    return best;
+}
+
 // What has to be established once per kernel instance and process: the dynamic LDS limit, and how many of its
 // workgroups one compute unit really holds (the work split launches exactly as many workgroups as are resident
 // at once, because owners wait for flags that later workgroups raise).
@@ -1176,7 +1406,7 @@ static hipError_t launch_kernel(Kern kern, KernelSetup& ks, int lds_bytes, int64
 template <int WB, int TM, int TN, int WR, int WC, int NS, int MINW = 1, bool CAN_SPLIT = false>
 static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipStream_t s) {
     constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
-    constexpr int LDS_BYTES = NS * BM * 128;
+    constexpr int LDS_BYTES = WB == 6 ? 4 * kX6Chunk + 2 * kX6Scales : NS * BM * 128;
     a.grid_m = (int)((M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.group_m = 8;
@@ -1241,6 +1471,65 @@ static hipError_t launch_staged(const TiledArgs& a, const SmallPick& pick, hipSt
     }
 }
 
+// W_q records -> fp6 records (layouts in lqer_internal.h): a thread turns the 16 bytes of one lane and chunk.
+__global__ __launch_bounds__(256) void widen_six_kernel(const uint8_t* Wt, int rec_bytes, int exp_bias, uint8_t* W6, int64_t records) {
+    const int64_t rec = blockIdx.x;
+    if (rec >= records) return;
+    const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;
+    const uint8_t* src = Wt + rec * rec_bytes;
+    uint8_t* dst = W6 + rec * kW6RecordBytes;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(src + (exp_bias >= 0 ? kWCompactCodeOffset : 0) + c * 1024 + lane * 16);
+    uint32_t out[4] = {0u, 0u, 0u, 0u}, any[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {                      // the lane's two blocks
+        any[b] = 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const uint32_t word = w[2 * b + (e >> 3)];
+            const int i = e & 3;
+            const uint32_t mag = (e & 4) ? (word >> (8 * i + 4)) & 7u : (word >> (8 * i)) & 7u;
+            const uint32_t sg = (e & 4) ? (word >> (8 * ((i + 1) & 3) + 3)) & 1u : (word >> (8 * i + 7)) & 1u;
+            any[b] |= mag;
+            const int bit = 6 * e + 3 * b, at = bit & 31;
+            out[bit >> 5] |= mag << at;
+            if (at > 29) out[(bit >> 5) + 1] |= mag >> (32 - at);
+            out[3] |= sg << (((6 * e + 5) & 31) - b);   // a field's sixth bit: an odd one
+        }
+    }
+    *reinterpret_cast<u32x4*>(dst + c * 1024 + lane * 16) = u32x4{out[0], out[1], out[2], out[3]};
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        uint32_t e;
+        if (exp_bias >= 0) e = ((src[lane * 4 + c] >> (4 * b)) & 15u) + (uint32_t)exp_bias;
+        else e = src[kWExpOffset + lane * 8 + 2 * c + b];
+        dst[kWExpOffset + lane * 8 + 2 * c + b] = (uint8_t)(any[b] != 0u && e >= 2u ? e - 2u : 0u);
+    }
+}
+
+hipError_t launch_widen_six(const Layer& L, hipStream_t s) {
+    const int64_t records = L.N32 * L.KT;
+    hipLaunchKernelGGL(widen_six_kernel, dim3((unsigned)records), dim3(256), 0, s, L.Wt, L.w_rec_bytes, L.w_exp_bias, L.W6, records);
+    return hipGetLastError();
+}
+
+bool tiled_takes_six(const Layer& L, int64_t M, bool codes_in, int variant) {
+    if (L.W6 == nullptr || L.kp == 0 || codes_in) return false;
+    const int shape = variant % 100;
+    if (shape != 0) return shape == 21 || shape == 22;
+    return 2.0 * (double)M * (double)L.N * (double)L.K > kSmallFlops;
+}
+
+uint8_t* six_scales(const Workspace& ws, const Layer& L) {
+    return reinterpret_cast<uint8_t*>(ws.Xh) + ws.xh_rows / kX6Rows * L.KT * (4 * kX6Chunk);
+}
+
+// images, exponent bytes and T in the room the bf16 rows have (400 and 512 bytes per row and K tile)
+void set_six_layout(Workspace& ws, const Layer& L) {
+    ws.six = true;
+    ws.ldxt = ws.ldxh - L.KT * kTileK;
+    ws.Xt = reinterpret_cast<uint16_t*>(six_scales(ws, L) + ws.xh_rows / kX6Rows * L.KT * kX6Scales);
+}
+
 __global__ void clear_flags_kernel(uint32_t* flags, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) flags[i] = 0u;
@@ -1274,6 +1563,7 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     TiledArgs a;
     a.Wt = L.Wt; a.Bt = L.Bt; a.Xh = ws.Xh; a.ldxh = ws.ldxh; a.Y = Y; a.ldy = ldy;
     a.Yc = rq.codes; a.Ye = rq.exps; a.ldyc = rq.ld;
+    a.Xt = ws.Xt; a.ldxt = ws.ldxt; a.Xe6 = nullptr;
     a.Tpart = ws.Tpart; a.S = ws.S; a.tp_stride = ws.tp_rows * L.kp;
     a.M = M; a.N = L.N; a.KT = L.KT; a.N32 = L.N32; a.kp = L.kp; a.kp16 = L.kp16;
     a.grid_m = a.grid_n = 0; a.group_m = 8;
@@ -1287,6 +1577,17 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     int mode = variant / 100;
     variant %= 100;
     if (mode < 0 || mode > 3) return hipErrorInvalidValue;
+    if (ws.six) {
+        a.Wt = L.W6; a.rec_bytes = kW6RecordBytes; a.exp_bias = -1;
+        a.Xe6 = six_scales(ws, L);
+        if (variant == 0) {
+            const SixPick pick = pick_six(L, M, ws.S, mode == 0 && ws.Part != nullptr, cus);
+            variant = pick.id;
+            mode = pick.cut ? 4 : 1;
+        }
+        if (variant == 22) return launch_tiled_t<6, 4, 2, 1, 4, 4, 2, true>(a, M, mode, cus, s);
+        return launch_tiled_t<6, 4, 2, 1, 8, 4, 1, true>(a, M, mode, cus, s);
+    }
     if (variant >= 31 && variant <= 33) {
         // a shape of the staged kernel by force: 0 = planes when the estimate says so, 1 = whole tiles, 2 = planes
         if (mode == 3) return hipErrorInvalidValue;

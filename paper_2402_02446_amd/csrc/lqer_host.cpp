@@ -116,7 +116,7 @@ static int tile_weights(Layer& L, const uint8_t* Wc, const uint8_t* We, std::vec
     const int kRec = L.w_rec_bytes, bias = L.w_exp_bias;
     const int code_off = compact ? kWCompactCodeOffset : 0, exp_off = w_code_bytes(bits);
     out.assign((size_t)(L.N32 * L.KT) * kRec + kWTailPad, 0);
-    std::atomic<int> bad{0};
+    std::atomic<int> bad{0}, tiny{0};
     parallel_for(L.N32, [&](int64_t g) {
         for (int64_t tile = 0; tile < L.KT; ++tile) {
             uint8_t* rec = out.data() + (size_t)(tile * L.N32 + g) * kRec;
@@ -132,6 +132,7 @@ static int tile_weights(Layer& L, const uint8_t* Wc, const uint8_t* We, std::vec
                             if (!canonical_block(Wc, bits, L.K, n, kb, codes)) bad.store(1, std::memory_order_relaxed);
                             eb = We[n * nblk + kb];
                         }
+                        if (eb < 2 && std::any_of(codes, codes + 16, [](int8_t v) { return v != 0; })) tiny.store(1, std::memory_order_relaxed);
                         if (bits == 4) {
                             const uint32_t w0 = encode_word(codes), w1 = encode_word(codes + 8);
                             uint8_t* dst = rec + code_off + c * 1024 + lane * 16 + j * 8;
@@ -151,6 +152,7 @@ static int tile_weights(Layer& L, const uint8_t* Wc, const uint8_t* We, std::vec
             }
         }
     });
+    L.w6_ok = tiny.load() == 0;
     return bad.load() ? LQER_ERR_VALUE : LQER_OK;
 }
 
@@ -291,12 +293,13 @@ static void untile_b(const Layer& L, const std::vector<uint8_t>& in, int8_t* Bc,
 
 void free_device(Layer& L) {
     if (L.Wt) (void)hipFree(L.Wt);
+    if (L.W6) (void)hipFree(L.W6);
     if (L.At) (void)hipFree(L.At);
     if (L.Bt) (void)hipFree(L.Bt);
     if (L.Wsc) (void)hipFree(L.Wsc);
     if (L.Asc) (void)hipFree(L.Asc);
     if (L.Bsc) (void)hipFree(L.Bsc);
-    L.Wt = L.At = L.Bt = nullptr;
+    L.Wt = L.W6 = L.At = L.Bt = nullptr;
     L.Wsc = L.Asc = L.Bsc = nullptr;
 }
 
@@ -305,6 +308,17 @@ int upload(const std::vector<uint8_t>& host, uint8_t** dev) {
     if (host.empty()) return LQER_OK;
     if (hipMalloc((void**)dev, host.size()) != hipSuccess) return LQER_ERR_HIP;
     if (hipMemcpy(*dev, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return LQER_ERR_HIP;
+    return LQER_OK;
+}
+
+// The layer's fp6 records, made on the device from its W_q records.  (No room for them: the layer goes without.)
+static int add_six(Layer& L) {
+    if (hipMalloc((void**)&L.W6, (size_t)(L.N32 * L.KT) * kW6RecordBytes) != hipSuccess) {
+        L.W6 = nullptr;
+        (void)hipGetLastError();
+        return LQER_OK;
+    }
+    if (launch_widen_six(L, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) return LQER_ERR_HIP;
     return LQER_OK;
 }
 
@@ -334,6 +348,10 @@ static Workspace plan_workspace(const Layer& L, int64_t M, int path, void* base,
     ws.Xh = (uint16_t*)base;
     ws.Tpart = partial ? (float*)((uint8_t*)base + xh_bytes) : nullptr;
     ws.bytes = xh_bytes + tp_bytes;
+    ws.six = false;
+    ws.Xt = path == 2 ? (uint16_t*)base + L.KT * kTileK : nullptr;
+    ws.ldxt = ws.ldxh;
+    ws.xh_rows = xh_rows;
     // tiled path: slots for accumulators handed between workgroups, and their flags
     ws.Part = nullptr;
     ws.flags = nullptr;
@@ -423,6 +441,7 @@ static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, co
     if (!wsp || ((uintptr_t)wsp & 255) != 0) return LQER_ERR_WORKSPACE;
     Workspace ws = plan_workspace(L, M, path, wsp, with_slots);
     if (ws.bytes > ws_bytes) return LQER_ERR_WORKSPACE;
+    if (path == 2 && tiled_takes_six(L, M, Xc != nullptr, variant)) set_six_layout(ws, L);
     if (path == 1) ws.x8 = stream_takes_codes(stream_variant(L, M, variant), ws.lr);
     hipStream_t s = (hipStream_t)stream;
     if (stages & 1) {
@@ -592,7 +611,8 @@ int lqer_layer_import_w(int w_bits, int64_t K, int64_t N, int k, const uint8_t* 
     L.w_bits = w_bits;
     L.w_rec_bytes = w_record_bytes(w_bits, false);
     L.w_exp_bias = -1;
-    L.Wt = L.At = L.Bt = nullptr;
+    L.Wt = L.W6 = L.At = L.Bt = nullptr;
+    L.w6_ok = false;
     if (hipGetDevice(&L.device) != hipSuccess) { delete h; return LQER_ERR_HIP; }
     int st;
     try {
@@ -600,6 +620,7 @@ int lqer_layer_import_w(int w_bits, int64_t K, int64_t N, int k, const uint8_t* 
             std::vector<uint8_t> buf;
             st = tile_weights(L, Wc, We, buf);
             if (st == LQER_OK) st = upload(buf, &L.Wt);
+            if (st == LQER_OK && w_bits == 4 && L.w6_ok) st = add_six(L);
         }
         if (st == LQER_OK && kp > 0) {
             std::vector<uint8_t> buf;
@@ -747,7 +768,11 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
         }
         return LQER_OK;
     }
-    const Workspace ws = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, workspace_dev);
+    Workspace ws = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, workspace_dev);
+    // one form of the activations for all: fp6 if every layer's main kernel takes it
+    bool six = true;
+    for (int i = 0; i < n_layers; ++i) six = six && tiled_takes_six(layers[i]->L, M, false, 0);
+    if (six) set_six_layout(ws, layers[0]->L);
     hipStream_t s = (hipStream_t)hip_stream;
     for (int i = 0; i < n_layers; ++i) {
         const Layer& L = layers[i]->L;

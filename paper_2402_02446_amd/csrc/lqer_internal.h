@@ -58,6 +58,22 @@ namespace lqer {
 //   rotr(w, 2 x) & 0x81818181  -> bytes e[4x], e[4x+1], e[4x+2], e[4x+3]
 // MFMA step s of a chunk uses elements 8 (s % 2) .. + 7 of block s / 2: extractions x = 2 (s % 2) and x + 1.
 
+//
+// fp6 record (4-bit layers; tiled_kernel's form on fp6 matrix instructions): [32 columns] x [256 K], 4608 B, ordered as the W_q
+// records, lane (i, hh) owning the same blocks a = 4c + 2hh and b = a + 1 of chunk c:
+//   codes[4 chunks][64 lanes][16 B]  three words of magnitudes, 96 bits: |a_i| at bits 6 i .. + 2, |b_i| at bits 6 i + 3 .. + 5; a word of
+//                                    signs: those of a at the bits that, of the three words, are the sixth ones of a field (odd bits:
+//                                    word 0's in order, then word 1's, word 2's), those of b one bit below
+//   exps[64 lanes][8 B]              byte 2c + j = exponent byte of block 4c + 2hh + j minus 2 (0 for an all-zero block)
+// so that each word of an operand [2 w | w] is one shift and two mask operations.  A second copy of the weights, because the
+// streaming kernel's bytes of fp8 cannot be turned into fields of six bits at that price.
+//
+// Activations for that kernel: [row / 128][K / 64] images of 12288 B, [4 blocks][128 rows][16 B] and [4 blocks][128 rows][8 B], the six
+// words of a block's operand [8 h | l]; behind all of them exponent bytes [row / 128][K tile][hh][128 rows][8 B], byte 2c + j of block
+// 4c + 2hh + j; behind these T_hi | T_lo | 0 row by row.
+
+constexpr int kW6RecordBytes = 4608;
+constexpr int kX6Rows = 128, kX6Chunk = 12288, kX6Scales = 2048;     // rows of an image, its bytes, exponent bytes per K tile
 constexpr int kTileK = 256;          // K covered by one W / A record
 constexpr int kWRecordBytes = 4608;  // with one exponent byte per block
 constexpr int kWRecordBytesCompact = 4352;   // with exponent nibbles (below)
@@ -84,6 +100,8 @@ struct Layer {
     int w_exp_bias;    // compact records: exponent byte = nibble + this; -1: one byte per block
     int act_bits;      // width of the activation codes: 8 or 6
     uint8_t* Wt;       // device, N32*KT records
+    uint8_t* W6;       // device, N32*KT fp6 records, or null (2-bit weights; exponents too small for the matrix instruction's scales)
+    bool w6_ok;        // every non-zero block's exponent byte is at least 2
     uint8_t* At;       // device, kp16*KT records
     uint8_t* Bt;       // device, N32*kp16 records
     // The scaled-integer variant (Table 2 "L2QER-INT"; kernels_int.hip): format 1.  Wt then holds [N32][K/128] records of
@@ -105,6 +123,10 @@ struct Workspace {
     int64_t tp_rows;     // rows per slice of Tpart (M, or M padded to the tile height for the tiled kernel)
     bool cells;          // streaming kernel: Xh holds 16-byte cells [KT*32][1 << lr token rows]
     int lr;
+    bool six;            // tiled kernel: Xh holds fp6 operands (set per launch)
+    uint16_t* Xt;        // tiled path: T_hi | T_lo | 0 of row 0, the row stride in elements
+    int64_t ldxt;
+    int64_t xh_rows;     // rows Xh holds
     bool x8;             // streaming kernel: the cells hold MXINT8 codes and exponent bytes (set per launch)
     float* Part;         // tiled kernel: accumulators handed from one workgroup to another, or null
     uint32_t* flags;     // tiled kernel: kTiledFlags words, cleared by the projection kernel
@@ -162,6 +184,13 @@ int stream_cell_rows_log2(int64_t M);
 // Tiled MFMA (large M) main kernel.
 hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y, int64_t ldy, const Requant& rq,
                         int variant, hipStream_t s);
+
+// Whether this call's main kernel takes fp6 operands: launch_prep has to leave them so (ws.six).
+bool tiled_takes_six(const Layer& L, int64_t M, bool codes_in, int variant);
+void set_six_layout(Workspace& ws, const Layer& L);
+uint8_t* six_scales(const Workspace& ws, const Layer& L);        // the exponent bytes behind all images
+// W_q records -> fp6 records
+hipError_t launch_widen_six(const Layer& L, hipStream_t s);
 
 hipError_t launch_clear_flags(const Workspace& ws, hipStream_t s);
 

@@ -102,6 +102,72 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// ---- both operands as fp6 -------------------------------------------------------------------------------------------------
+// The block-scaled MFMA on fp6 operands (E2M3: integers 0 to 16 in units of 1/8 carry their own value as code, above that the
+// even ones to 32 and the multiples of 4 to 60) runs at four times bf16's rate.  An MXINT8 code x = 16 h + l (h and l with x's
+// sign, |h| <= 7, |l| <= 15) against an MXINT4 code w is (8 h) (2 w) + l w: two fp6 products, all four factors exact, and
+// a block of 16 of both operands is one scaled block of 32 - the instruction's own size - [8 h | l] against [2 w | w].  The
+// scales are the blocks' exponent bytes.  Half of four times bf16's rate is left: a loop of these MFMAs on random operands
+// delivers 5170 to 5580 TFLOP/s of fp6 products (2600 to 2800 of the product's own), bf16's 1610 to 1850.
+typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+// D[i][j] += 2^(sa + sb - 254) sum_k A[i][k] B[k][j], 32 x 32 x 64: lane (l % 32, l / 32) supplies the 32 elements k = 32 (l / 32) .. of
+// its row of A and column of B, element i at bit 6 i, and their scales as byte BYTE of a word each; D as of mfma32.
+template <int BYTE>
+__device__ __forceinline__ f32x16 mfma32_six(u32x6 a, u32x6 b, f32x16 c, uint32_t sa, uint32_t sb) {
+    const i32x8 av = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)a[4], (int)a[5], 0, 0};
+    const i32x8 bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], (int)b[4], (int)b[5], 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 2, 2, BYTE, (int)sa, BYTE, (int)sb);
+}
+
+// Bit g of three words, g mod 6 in the set given by `six` (bits 0 to 5), as the mask of word j.
+constexpr uint32_t six_mask(uint32_t six, int j) {
+    uint32_t m = 0;
+    for (int p = 0; p < 32; ++p)
+        if ((six >> ((32 * j + p) % 6)) & 1u) m |= 1u << p;
+    return m;
+}
+
+// A lane's two blocks of one chunk (layout in lqer_internal.h) -> the operand [2 w | w] of its block S.
+template <int S>
+__device__ __forceinline__ u32x6 expand_six(u32x4 c) {
+    const uint32_t sg = S == 0 ? c[3] : c[3] << 1;
+    u32x6 r;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const uint32_t sign = sg & six_mask(0x20, j);
+        const uint32_t lo = j > 0 ? c[j - 1] : 0u, hi = j < 2 ? c[j + 1] : 0u;      // neighbours in the run of 96 bits
+        const uint32_t one = S == 0 ? c[j] : __builtin_amdgcn_alignbit(hi, c[j], 3);
+        const uint32_t two = S == 0 ? __builtin_amdgcn_alignbit(c[j], lo, 31) : __builtin_amdgcn_alignbit(hi, c[j], 2);
+        r[j] = (two & six_mask(0x0E, j)) | sign;
+        r[3 + j] = (one & six_mask(0x07, j)) | sign;
+    }
+    return r;
+}
+
+// 16 codes of a block (as floats, at most 127 in size when multiplied by `up`) -> the operand [8 h | l].  The conversion takes its
+// 32 values alternately from two registers' runs.
+__device__ __forceinline__ u32x6 codes_to_six(const float (&r)[16], float up) {
+    const float per16 = 0.0625f * up, per8 = 0.125f * up;
+    f32x16 even, odd;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const float h = __builtin_truncf(r[i] * per16), l = __builtin_fmaf(h, -2.0f, r[i] * per8);
+        if (i & 1) { odd[i >> 1] = h; odd[8 + (i >> 1)] = l; }
+        else { even[i >> 1] = h; even[8 + (i >> 1)] = l; }
+    }
+    return __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, 1.0f);
+}
+
+// Back: the codes times `scale` (a power of two).
+__device__ __forceinline__ void six_to_values(u32x6 v, float scale, float (&r)[16]) {
+    typedef float f32x32 __attribute__((ext_vector_type(32)));
+    const f32x32 e = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(v, 1.0f);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) r[i] = __builtin_fmaf(e[i], 16.0f, e[16 + i] * 8.0f) * scale;
+}
+
 // Eight values of one MXINT8 block held by this lane (the other eight sit in lane ^ 32): the block's
 // exponent byte from the maximum over both lanes, and this lane's codes as two words of four bytes.
 __device__ __forceinline__ uint32_t requant_half_block(const float (&v)[8], uint32_t& w0, uint32_t& w1) {
@@ -185,6 +251,7 @@ __device__ __forceinline__ BufferRsrc buffer_rsrc(const void* p, uint32_t bytes)
 }
 __device__ __forceinline__ u32x4 buffer_load16(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
 __device__ __forceinline__ u32x4 buffer_load16_nt(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 2); }
+__device__ __forceinline__ u32x2 buffer_load8(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0); }
 __device__ __forceinline__ uint32_t buffer_load4(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
 __device__ __forceinline__ uint32_t buffer_load1(BufferRsrc r, int off) { return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0); }
 
