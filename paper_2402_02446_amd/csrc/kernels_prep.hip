@@ -78,7 +78,7 @@ __device__ __forceinline__ float dpp_quad(float v) {
 template <int SRC, bool FINAL, int MAXG, bool CELLS, bool RW = false, bool SIX = false>
 __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     static_assert(!RW || (SRC == 0 && !CELLS && !SIX), "the row-wise form reads fp32 rows and writes row-major bf16");
-    static_assert(!SIX || (!CELLS && SRC != 1), "fp6 operands are made of fp32 activations");
+    static_assert(!SIX || !CELLS, "the streaming kernel takes no fp6 operands");
     // ROWWISE (fp32 X in, row-major bf16 out: the prefill case, bound by HBM): a wavefront reads and writes whole rows
     // of its 16 x 256 tile - 1 KiB per load, 512 B per store, every cache line touched by one instruction - with the
     // four lanes of a quad sharing a block, and turns the tile into the MFMA operand order (lane = token, 16-byte
@@ -356,12 +356,23 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
             }
             if (store_x && row_ok) {
                 if constexpr (SIX) {
-                    // six-bit codes (4 fraction bits) as multiples of 4 with the 8-bit codes' scale
-                    const u32x6 w = codes_to_six(r, (float)(64 >> a.act_frac));
+                    // The exponent byte is that of 6 fraction bits.  Beyond 254 (a byte of 255 is a NaN to the matrix instruction) the codes
+                    // take the rest, and where they cannot, the block's values are infinities in fp32, which T makes NaNs of as well.
+                    int e6 = (int)eb + 6 - a.act_frac;
+                    float up = 1.0f;
+                    if (__builtin_expect(e6 > 254, 0)) {
+                        up = f32_from_bits((uint32_t)(e6 - 254 + 127) << 23);
+                        float m = 0.f;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(r[i]));
+                        e6 = m * up >= 128.0f ? 255 : 254;
+                        if (e6 == 255) up = 1.0f;
+                    }
+                    const u32x6 w = codes_to_six<SRC == 1>(r, up);
                     uint8_t* img = six_image(unit);
                     *reinterpret_cast<u32x4*>(img + q * 2048 + six_row * 16) = u32x4{w[0], w[1], w[2], w[3]};
                     *reinterpret_cast<u32x2*>(img + 8192 + q * 1024 + six_row * 8) = u32x2{w[4], w[5]};
-                    *six_exp(unit) = (uint8_t)eb;
+                    *six_exp(unit) = (uint8_t)e6;
                 } else if (CELLS) {
                     if (a.x8) {
                         // 16 token rows and more: MXINT8 as it is, 16 code bytes per (block, row), and the
@@ -494,7 +505,7 @@ __global__ __launch_bounds__(64 * kPrepWaves) void prep_group_kernel(PrepGroup g
 
 template <int SRC, bool FINAL, int MAXG, bool CELLS>
 static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& a, bool rowwise, bool six) {
-    if constexpr (SRC != 1 && !CELLS) {
+    if constexpr (!CELLS) {
         if (six) {
             hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false, true>), grid, block, 0, s, a);
             return;
@@ -573,7 +584,6 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     const int src = reuse_xh ? 2 : (Xc != nullptr ? 1 : 0);
     const int64_t rg = (M + 15) / 16;
     // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
-    if (ws.six && src == 1) return hipErrorInvalidValue;
     const bool rowwise = !cells && !ws.six && src == 0 && rg * ws.S * gz >= 2048;
     a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S * gz >= 256);
     dim3 block(64 * a.nwaves);

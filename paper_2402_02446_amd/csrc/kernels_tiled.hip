@@ -28,15 +28,15 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
-// The fp6 form (WB = 6).  Above 1.5e11 operations a 4-bit layer's fp32 activations are not brought to bf16 but to fp6 operands:
+// The fp6 form (WB = 6).  Above 1.5e11 operations, and below where the time models say so, a 4-bit layer's fp32 activations are not brought to bf16 but to fp6 operands:
 // an 8-bit code in two halves against the 4-bit code, exact as before, at half the matrix instructions' time (mfma32_six).  The chip's
 // clock under load is what bounds the bf16 form; this one moves 24 bytes of LDS per operand block instead of 32 and runs half as
 // many passes.  Bounds now: again the clock (4.0 us per K tile of a 128 x 512 tile on a full chip, 2.7 on a nearly empty one; the
 // bare MFMA loop's rate would be 3.2).  Whole calls, bf16 form -> this: 8192 x 28672 rank 64 at 4096 tokens 1477 -> 1093 us, 11008 x 4096
 // rank 32 at 2048 178 -> 138, 4096 x 4096 at 8192 263 -> 200, rank 16 at 65536 2005 -> 1571.  Distance from the 64-bit result unchanged
 // (2.65e-7, 2.38e-7, 2.29e-7, 2.07e-7; on data of wide exponents, where the bf16 chain rounds more often, 7.6e-8 against 1.2e-7
-// at K = 4096).  MXINT codes as input and layers of rank 0 keep bf16 operands: there an exponent byte of 255 (a block with
-// an infinity) is a large scale, to the block-scaled instruction a NaN; with a correction the row is NaN either way.
+// at K = 4096).  Layers of rank 0 keep bf16 operands: an exponent byte of 255, a block with an infinity, is a NaN to the block-scaled
+// instruction, where bf16 has infinities; with a correction the row is NaN either way.
 //
 // Calls that do not fill the chip for long mostly take staged_kernel (pick_small says which): tiles of 64 rows, every
 // operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
@@ -80,6 +80,17 @@ struct TiledArgs {
 
 // row stride of a plane of partial sums
 __host__ __device__ constexpr int64_t plane_ld(int64_t N) { return (N + 3) / 4 * 4; }
+
+// The product ends here, in front of the stores' conditions.  Left alone the compiler moves the last block-scaled MFMAs behind the
+// test of a lane's row, together with reloads of their operands, which then happen in the lanes with rows only; a matrix
+// instruction takes every lane's.
+template <int TM, int TN>
+__device__ __forceinline__ void settle(f32x16 (&acc)[TM][TN]) {
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) asm volatile("" : "+v"(acc[tm][tn]));
+}
 
 // MINW = wavefronts per SIMD the register allocation must allow (2 lets two four-wavefront workgroups share a compute unit)
 // SPLIT = the workgroup walks a list of pieces (work split); otherwise it computes output tile blockIdx.x
@@ -599,6 +610,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
         }
     }
 
+    if constexpr (SIX) settle(acc);
     // ---- a piece that starts inside the tile hands its accumulators over ---------------------------
     // The slot is written and read with device-scope relaxed atomic accesses of 8 bytes: they pass
     // through the XCD's L2 to where every XCD sees them, so neither side needs a cache write-back or
@@ -735,15 +747,21 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 // Whole calls, that loop -> this one: 4096 x 4096 at 40 tokens 16.9 -> 15.9 us, 4096 x 11008 at 128 32.7 -> 27.2,
 // 4112 x 11000 at 203 44.9 -> 38.9, 4096 x 4096 at 512 36.8 -> 31.2, rank 64 at 1024 57.4 -> 53.9; 2-bit rank 128 at 512 50.0 -> 43.5.
 // (The correction's operands are asked for in one go per two chunks: 2-bit weights with rank 256 at 64 tokens 84 -> 30 us.)
+// Its fp6 form (WB = 6, mfma32_six) has half the matrix instructions and three quarters of the LDS bytes for the activations; the
+// vector instructions, which are what a 64 x 128 tile waits for, are as many: 4112 x 11000 at 203 tokens 39.9 -> 36.0 us a call,
+// 4096 x 4096 at 2048 75.9 -> 68.4 (64 x 512 -> 64 x 256), main product of 2064 x 6592 rank 128 at 1720 tokens 74 -> 68.5.
 // Four stages of 64 K in LDS, one per chunk of a K tile: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN]
 // 1 KiB of codes [wave][TN] 256 B of exponent words; chunk ch + 3 is asked for when chunk ch starts.
 template <int TM, int TN, int WR, int WC, int MINW, bool PLANES, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a) {
-    static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
+    static_assert(WB == 4 || WB == 2 || WB == 6, "weight mantissas of 4 or 2 bits, or the fp6 form");
+    constexpr bool SIX = WB == 6;
     constexpr int BM = 32 * TM * WR, NW = WR * WC, NT = 64 * NW;
-    constexpr int XB = BM * 128, WOFF = XB, EOFF = XB + NW * TN * 1024, STAGE = EOFF + NW * TN * 256;
-    constexpr int XL = XB / 1024 / NW;             // activation loads per wavefront and chunk
-    static_assert(XB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
+    static_assert(!SIX || (BM == kX6Rows / 2 && NW % 4 == 0), "half an image's rows; loads that four wavefronts share");
+    constexpr int TB = BM * 128;                   // two chunks of T
+    constexpr int XB = SIX ? kX6Chunk / 2 + BM * 8 : TB, WOFF = XB, EOFF = XB + NW * TN * 1024, STAGE = EOFF + NW * TN * 256;
+    constexpr int XL = SIX ? 3 : TB / 1024 / NW;   // activation loads per wavefront and chunk
+    static_assert(TB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
     constexpr int L = XL + 2 * TN;                 // loads per wavefront and chunk
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
@@ -783,31 +801,52 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     // lane % 8, which holds the row's cell (lane % 8) ^ ((row >> 1) & 7).  (Rows past M are workspace rows: see there.)
     // What differs between the loads of a chunk is in the lanes' offsets, so that one scalar address serves all of a kind.
     uint32_t x_off[XL], w_off[TN], e_off[TN];
+    if constexpr (SIX) {
+        // Half the rows of an image: four loads of 16-byte cells, one a block, two of 8-byte cells of two blocks each, two of the exponent
+        // words of this half of the K tile, one a lane half; wavefronts beyond bring the same bytes once more.
+        const int hb = (tile_m & 1) * 64;
+        x_off[0] = (wave & 3) * 2048 + (hb + lane) * 16;
+        x_off[1] = 8192 + (2 * (wave & 1) + (lane >> 5)) * 1024 + hb * 8 + (lane & 31) * 16;
+        x_off[2] = (wave & 1) * 1024 + (hb + lane) * 8;
+    } else {
 #pragma unroll
-    for (int j = 0; j < XL; ++j)
-        x_off[j] = (uint32_t)((8 * (NW * j + wave) + (lane >> 3)) * (int)a.ldxh * 2) +
-                   (((uint32_t)(lane & 7) ^ (uint32_t)(((wave & 1) * 4 + (lane >> 4)) & 7)) << 4);
+        for (int j = 0; j < XL; ++j)
+            x_off[j] = (uint32_t)((8 * (NW * j + wave) + (lane >> 3)) * (int)a.ldxh * 2) +
+                       (((uint32_t)(lane & 7) ^ (uint32_t)(((wave & 1) * 4 + (lane >> 4)) & 7)) << 4);
+    }
     const bool exp4 = a.exp_bias >= 0;             // wave-uniform
     const int64_t g_first = group_of(0);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const uint32_t rec = (uint32_t)(group_of(tn) - g_first) * (uint32_t)a.rec_bytes;
         w_off[tn] = rec + lane * 16 + (exp4 ? kWCompactCodeOffset : 0);
-        e_off[tn] = rec + (exp4 ? lane * 4 : w_code_bytes(WB) + lane * 8);
+        e_off[tn] = rec + (exp4 ? lane * 4 : w_code_bytes(WB == 2 ? 2 : 4) + lane * 8);
     }
     const int64_t tile_stride = a.N32 * a.rec_bytes;
     const uint8_t* x_ptr = reinterpret_cast<const uint8_t*>(a.Xh + m0 * a.ldxh + kt0 * kTileK);
+    const uint8_t* xe_ptr = nullptr;
+    if constexpr (SIX) {
+        const int64_t kt = (int64_t)(tile_m >> 1) * KT + kt0;
+        x_ptr = reinterpret_cast<const uint8_t*>(a.Xh) + kt * (4 * kX6Chunk);
+        xe_ptr = a.Xe6 + kt * kX6Scales;
+    }
     const uint8_t* w_ptr = a.Wt + g_first * a.rec_bytes + kt0 * tile_stride;       // record of the K tile being asked for
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds);
     const uint32_t at_x = lds0 + wave * 1024, at_w = lds0 + wave * (TN * 1024), at_e = lds0 + wave * (TN * 256);
     const uint32_t e_half = exp4 ? 0 : 4;          // exponent words: with nibbles the record's only one, with bytes the first or second four of a lane's eight
     auto issue = [&](auto cc) {                    // the next chunk of the row, number CC of its K tile -> stage CC
         constexpr int CC = decltype(cc)::value, ST = CC * STAGE;
-        lds_dma16<ST>(at_x, x_off[0], x_ptr);
-        if constexpr (XL > 1) lds_dma16<ST + NW * 1024>(at_x, x_off[1], x_ptr);
-        if constexpr (XL > 2) lds_dma16<ST + 2 * NW * 1024>(at_x, x_off[2], x_ptr);
-        if constexpr (XL > 3) lds_dma16<ST + 3 * NW * 1024>(at_x, x_off[3], x_ptr);
-        const uint8_t* wp = w_ptr + (WB == 4 ? CC : CC >> 1) * 1024;
+        if constexpr (SIX) {
+            lds_dma16<ST>(lds0 + (wave & 3) * 1024, x_off[0], x_ptr);
+            lds_dma16<ST + 4096>(lds0 + (wave & 1) * 1024, x_off[1], x_ptr);
+            lds_dma4<ST + 6144>(lds0 + (wave & 1) * 256, x_off[2], CC < 2 ? xe_ptr : xe_ptr + 4);
+        } else {
+            lds_dma16<ST>(at_x, x_off[0], x_ptr);
+        }
+        if constexpr (!SIX && XL > 1) lds_dma16<ST + NW * 1024>(at_x, x_off[1], x_ptr);
+        if constexpr (!SIX && XL > 2) lds_dma16<ST + 2 * NW * 1024>(at_x, x_off[2], x_ptr);
+        if constexpr (!SIX && XL > 3) lds_dma16<ST + 3 * NW * 1024>(at_x, x_off[3], x_ptr);
+        const uint8_t* wp = w_ptr + (WB == 2 ? CC >> 1 : CC) * 1024;
         const uint8_t* ep = CC < 2 ? w_ptr : w_ptr + e_half;
         lds_dma16<ST + WOFF>(at_w, w_off[0], wp);
         lds_dma4<ST + EOFF>(at_e, e_off[0], ep);
@@ -815,8 +854,11 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             lds_dma16<ST + WOFF + 1024>(at_w, w_off[TN - 1], wp);
             lds_dma4<ST + EOFF + 256>(at_e, e_off[TN - 1], ep);
         }
-        x_ptr += 128;
-        if constexpr (CC == 3) w_ptr += tile_stride;
+        x_ptr += SIX ? kX6Chunk : 128;
+        if constexpr (CC == 3) {
+            w_ptr += tile_stride;
+            if constexpr (SIX) xe_ptr += kX6Scales;
+        }
     };
     static_assert(XL <= 4 && TN <= 2, "issue() spells its loads out");
 
@@ -828,13 +870,13 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) dst[tm].u = *reinterpret_cast<const u32x4*>(stage + rd_off[s4] + tm * 4096);
     };
-    typedef typename std::conditional<WB == 4, u32x4, u32x2>::type WVec;   // a lane's two blocks of one chunk
+    typedef typename std::conditional<WB == 2, u32x2, u32x4>::type WVec;   // a lane's two blocks of one chunk
     struct WSet { WVec c[TN]; uint32_t e[TN]; };
     auto read_w = [&](WSet& w, const uint8_t* stage, int cc) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
             const uint8_t* src = stage + WOFF + (wave * TN + tn) * 1024 + lane * 16;
-            if constexpr (WB == 4) w.c[tn] = *reinterpret_cast<const u32x4*>(src);
+            if constexpr (WB != 2) w.c[tn] = *reinterpret_cast<const u32x4*>(src);
             else w.c[tn] = *reinterpret_cast<const u32x2*>(src + (cc & 1) * 8);
             w.e[tn] = *reinterpret_cast<const uint32_t*>(stage + EOFF + (wave * TN + tn) * 256 + lane * 4);
         }
@@ -883,8 +925,54 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             else wv[tn] = unpack_w8_b2(w.c[tn][s4 >> 1], s4 & 1, sc[tn][s4 >> 1]);
         }
     };
+    // The fp6 form: two steps to a chunk.  Operands are read into the registers of the ones just used, a whole chunk ahead.
+    u32x6 x6[2][TM], w6[TN];
+    uint32_t xe[2][TM];                            // exponent words, of even and odd chunks
+    auto read_x6 = [&](u32x6& x, const uint8_t* stage, int tm, int s) {
+        const u32x4 p = *reinterpret_cast<const u32x4*>(stage + (2 * hh + s) * 1024 + (tm * 32 + t) * 16);
+        const u32x2 h = *reinterpret_cast<const u32x2*>(stage + 4096 + (2 * hh + s) * 512 + (tm * 32 + t) * 8);
+        x = u32x6{p[0], p[1], p[2], p[3], h[0], h[1]};
+    };
+    auto read_xe = [&](uint32_t (&e)[TM], const uint8_t* stage) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) e[tm] = *reinterpret_cast<const uint32_t*>(stage + 6144 + hh * 256 + (tm * 32 + t) * 4);
+    };
+    auto chunk6 = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, auto cc) {
+        constexpr int CC = decltype(cc)::value;
+        const uint8_t* const nxt = lds + (CC + 1) % 4 * STAGE;
+        read_w(wn, nxt, CC + 1);
+        read_xe(xe[(CC + 1) & 1], nxt);
+        auto step = [&](auto ss) {
+            constexpr int S = decltype(ss)::value;
+            u32x6 now[TN];
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) {
+                now[tn] = w6[tn];
+                w6[tn] = expand_six<1 - S>(S == 0 ? w.c[tn] : wn.c[tn]);
+            }
+            if (S == 0) __builtin_amdgcn_sched_group_barrier(0x100, TM + 2 * TN, 0);
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+                    acc[tm][tn] = mfma32_six<(2 * CC + S) & 3>(now[tn], x6[S][tm], acc[tm][tn], w.e[tn], xe[CC & 1][tm]);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, (14 + TM - 1) / TM, 0);
+                }
+                read_x6(x6[S][tm], nxt, tm, S);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+    };
     // Chunk CC: on entry xr holds its first AHEAD steps, wv the weights of step 0 and w its codes; on exit the same of the next chunk, in wn its codes.
     auto chunk = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, auto cc) {
+        if constexpr (SIX) {
+            chunk6(acc, w, wn, cc);
+            return;
+        }
         constexpr int CC = decltype(cc)::value;
         const uint8_t* const cur = lds + CC * STAGE;
         const uint8_t* const nxt = lds + (CC + 1) % 4 * STAGE;
@@ -990,7 +1078,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int j = 0; j < LPT; ++j)
-                *reinterpret_cast<u32x4*>(t_tiles + q * XB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
+                *reinterpret_cast<u32x4*>(t_tiles + q * TB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -1005,7 +1093,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     Frag xt[TM];
-                    read_x(xt, t_tiles + q * XB, 2 * j + h);
+                    read_x(xt, t_tiles + q * TB, 2 * j + h);
 #pragma unroll
                     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
@@ -1019,15 +1107,25 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     issue(C2);
     staged_wait<2 * L>();
     WSet w0, w1;
-#pragma unroll
-    for (int s4 = 0; s4 < AHEAD; ++s4) read_x(xr[s4], lds, s4);
     read_w(w0, lds, 0);
-    scales(w0, 0);
-    expand(w0, 0);
+    if constexpr (SIX) {
+        read_xe(xe[0], lds);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) read_x6(x6[s][tm], lds, tm, s);
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) w6[tn] = expand_six<0>(w0.c[tn]);
+    } else {
+#pragma unroll
+        for (int s4 = 0; s4 < AHEAD; ++s4) read_x(xr[s4], lds, s4);
+        scales(w0, 0);
+        expand(w0, 0);
+    }
     // A K tile.  Chunks CC and CC + 1 have landed when CC starts, for every wavefront; its predecessor has been read by
     // everybody (the RA newest reads are of CC itself), and that stage takes chunk CC + 3: of the same K tile, or of the next
     // one unless this is the last.
-    constexpr int RA = AHEAD * TM;
+    constexpr int RA = SIX ? 2 * TM : AHEAD * TM;  // (fp6: every read of a chunk's time is of the next chunk, half of its 16-byte ones are these)
     auto tile = [&](f32x16 (&acc)[TM][TN], auto last) {
         constexpr bool LAST = decltype(last)::value;
         staged_wait<L, RA>();
@@ -1056,6 +1154,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc0[tm][tn][r] += acc1[tm][tn][r];
+    if constexpr (SIX) settle(acc0);
 
     // ---- store: lane (t, hh) holds columns 8 r4 + 4 hh .. + 3 of token t for every MFMA tile ------------------------------
     if (!PLANES && a.Yc != nullptr) {              // as MXINT8: block b of a column group is registers 8 b .. + 7 of two lanes
@@ -1258,6 +1357,13 @@ static const SmallShape kSmallShapes2[] = {
     {12, 128, 256, 2, {3.08, 5.22}, 0.38, 8.44, {1.68, 2.03}, {0.0, 0.47}, 0.192, 0.0, 0.0},
     {11, 128, 512, 1, {4.53, 0.0}, 3.2, 7.8, {0.0, 0.0}, {3.50, 1.30}, 0.205, 0.0, 0.0},
 };
+// The staged kernel's fp6 form, fitted to 132 timings a shape of 77 calls of 1e9 to 1.6e11 operations (mean error 3 to 5 %); with
+// the fp6 shapes of tiled_kernel the choice is 0.3 % from the fastest on average, 2.7 % at the 95th percentile, 6.4 % at worst.
+static const SmallShape kSmallShapes6[] = {
+    {43, 64, 128, 2, {0.986, 1.474}, 0.22, 6.60, {0.85, 0.18}, {0.0, 0.71}, 0.210, 2.6, 0.178},
+    {41, 64, 256, 2, {1.524, 2.471}, 1.59, 6.86, {2.56, 0.0}, {0.0, 0.80}, 0.193, 2.7, 0.158},
+    {42, 64, 512, 1, {2.372, 0.0}, 5.54, 5.04, {0.0, 0.59}, {3.53, 0.0}, 0.141, 3.0, 0.139},
+};
 // The 128 x 512 shape with tiles cut in pieces, for 4 and 2 bits: us per launch, K tile of a piece, K tile and number of whole
 // rounds, piece beyond two, the correction per round.  Whole pieces per tile (460 timings, 5 %), and equal shares, whose
 // estimate is the rougher one (370 timings, 6 %): it counts only where the launch is long enough for them to pay, and has to
@@ -1272,7 +1378,7 @@ constexpr int kMaxPlanes = 16;
 // of 11008 x 4096 at 1500 tokens, 146 to 149 us by the estimate's forms, 142 by the model's choice).
 constexpr double kSmallFlops = 1.5e11;
 
-struct SmallPick { int id, planes, share; };      // share: K tiles per plane; planes 0: tiled_kernel in pieces
+struct SmallPick { int id, planes, share; double us; };      // share: K tiles per plane; planes 0: tiled_kernel in pieces
 
 // pairs of correction chunks beyond the first
 static int more_pairs(int kp) { return kp > 64 ? (kp + 63) / 64 - 1 : 0; }
@@ -1300,10 +1406,13 @@ static double pieces_us(const SmallPieces& c, const Layer& L, int S, const Split
 
 // S: partial sums of T.  part_bytes: room for planes (0: whole tiles only).  only: this shape of the staged kernel, in at
 // least min_planes planes (id 0: not to be had).
-static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus, int only = 0, int min_planes = 1) {
-    SmallPick best{0, 1, (int)L.KT};
-    double best_us = 0.0;
-    for (const SmallShape& sh : L.w_bits == 4 ? kSmallShapes4 : kSmallShapes2) {
+static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus, int only = 0, int min_planes = 1,
+                            bool six = false) {
+    SmallPick best{0, 1, (int)L.KT, 0.0};
+    const SmallShape* const table = six ? kSmallShapes6 : (L.w_bits == 4 ? kSmallShapes4 : kSmallShapes2);
+    const int n_shapes = six ? 3 : 5;
+    for (int i = 0; i < n_shapes; ++i) {
+        const SmallShape& sh = table[i];
         if (only != 0 && sh.id != only) continue;
         const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((L.N + sh.bn - 1) / sh.bn);
         for (int p = min_planes; p <= kMaxPlanes && p <= L.KT; ++p) {
@@ -1312,13 +1421,13 @@ static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes
             if (planes != p) continue;                       // the same planes as a smaller p
             if (p > 1 && (sh.bm == 128 || (int64_t)p * M * plane_ld(L.N) * 4 > part_bytes)) continue;
             const double us = small_us(sh, L, M, S, tiles, planes, share, cus);
-            if (best.id == 0 || us < best_us) { best = SmallPick{sh.id, planes, (int)share}; best_us = us; }
+            if (best.id == 0 || us < best.us) best = SmallPick{sh.id, planes, (int)share, us};
         }
         if (sh.id == 11 && part_bytes > 0) {
             const Split sp = split_tiles(tiles, L.KT, cus, true);
             if (sp.sk_units == 0 || (!sp.aligned && 2.0 * (double)M * (double)L.N * (double)L.K < kSharesFlops)) continue;
             const double us = pieces_us((sp.aligned ? kSmallWhole : kSmallShares)[L.w_bits == 4 ? 0 : 1], L, S, sp);
-            if (us * (sp.aligned ? 1.0 : 1.03) < best_us) { best = SmallPick{11, 0, (int)sp.sk_share}; best_us = us; }
+            if (us * (sp.aligned ? 1.0 : 1.03) < best.us) best = SmallPick{11, 0, (int)sp.sk_share, us};
         }
     }
     return best;
@@ -1339,7 +1448,7 @@ static const SixShape kSixShapes[] = {
 static const SmallPieces kSixWhole = {38.0, 3.352, 4.026, 11.96, 4.168, 8.11, 0.0};
 static const SmallPieces kSixShares = {36.3, 3.974, 4.178, 13.52, 0.0, 7.85, 0.0};
 
-struct SixPick { int id; bool cut; double us; };
+struct SixPick { int id; bool cut; double us; SmallPick staged; };   // id 0: the staged kernel's shape `staged`
 
 static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int cus) {
     const int64_t tiles = ((M + kX6Rows - 1) / kX6Rows) * ((L.N + sh.bn - 1) / sh.bn), per_round = (int64_t)cus * sh.resident;
@@ -1355,20 +1464,24 @@ static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int c
            more_pairs(L.kp) * rounds * (sh.corr[0] + sh.corr[1] * (double)S);
 }
 
-// can_cut: there is room for the pieces' accumulators
-static SixPick pick_six(const Layer& L, int64_t M, int S, bool can_cut, int cus) {
-    SixPick best{0, false, 0.0};
+// part_bytes: room for the pieces' accumulators or the planes (0: whole tiles only)
+static SixPick pick_six(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus) {
+    SixPick best{-1, false, 0.0, {}};
     for (const SixShape& sh : kSixShapes) {
         const double us = six_us(sh, L, M, S, cus);
-        if (best.id == 0 || us < best.us) best = SixPick{sh.id, false, us};
+        if (best.id < 0 || us < best.us) best = SixPick{sh.id, false, us, {}};
     }
-    if (can_cut) {
+    if (part_bytes > 0) {
         const int64_t tiles = ((M + kX6Rows - 1) / kX6Rows) * ((L.N + 511) / 512);
         const Split sp = split_tiles(tiles, L.KT, cus, true);
         if (sp.sk_units > 0) {
             const double us = pieces_us(sp.aligned ? kSixWhole : kSixShares, L, S, sp) * (sp.aligned ? 1.0 : 1.03);
-            if (us < best.us) best = SixPick{21, true, us};
+            if (us < best.us) best = SixPick{21, true, us, {}};
         }
+    }
+    if (2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
+        const SmallPick staged = pick_small(L, M, S, part_bytes, cus, 0, 1, true);
+        if (staged.us < best.us) best = SixPick{0, false, staged.us, staged};
     }
     return best;
 }
@@ -1446,7 +1559,7 @@ static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipS
 template <int WB, int TM, int TN, int WR, int WC, int MINW>
 static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_t s) {
     constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC, NW = WR * WC;
-    constexpr int LDS_BYTES = 4 * (BM * 128 + NW * TN * 1280);
+    constexpr int LDS_BYTES = 4 * ((WB == 6 ? kX6Chunk / 2 + BM * 8 : BM * 128) + NW * TN * 1280);
     a.grid_m = (int)((a.M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.dp_tiles = (int64_t)a.grid_m * a.grid_n;
@@ -1464,9 +1577,9 @@ static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_
 
 template <int WB>
 static hipError_t launch_staged(const TiledArgs& a, const SmallPick& pick, hipStream_t s) {
-    switch (pick.id) {
+    switch (WB == 6 ? pick.id - 10 : pick.id) {
         case 31: return launch_staged_t<WB, 2, 2, 1, 4, 2>(a, pick, s);      // 64 x 256, 72 KB: two workgroups per compute unit
-        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 2>(a, pick, s);      // 64 x 512, 112 KB
+        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 2>(a, pick, s);      // 64 x 512, 112 KB (fp6: 41 to 43, less)
         default: return launch_staged_t<WB, 2, 1, 1, 4, 2>(a, pick, s);      // 64 x 128, 52 KB: two workgroups per compute unit
     }
 }
@@ -1512,11 +1625,15 @@ hipError_t launch_widen_six(const Layer& L, hipStream_t s) {
     return hipGetLastError();
 }
 
-bool tiled_takes_six(const Layer& L, int64_t M, bool codes_in, int variant) {
-    if (L.W6 == nullptr || L.kp == 0 || codes_in) return false;
-    const int shape = variant % 100;
-    if (shape != 0) return shape == 21 || shape == 22;
-    return 2.0 * (double)M * (double)L.N * (double)L.K > kSmallFlops;
+bool tiled_takes_six(const Layer& L, int64_t M, const Workspace& ws, int variant) {
+    if (L.W6 == nullptr || L.kp == 0) return false;
+    const int shape = variant % 100, mode = variant / 100;
+    if (shape != 0) return shape == 21 || shape == 22 || (shape >= 41 && shape <= 43);
+    if (mode > 1) return false;                              // cut by force: the bf16 shapes
+    if (2.0 * (double)M * (double)L.N * (double)L.K > kSmallFlops) return true;
+    const int cus = compute_units();
+    const int64_t room = mode == 0 && ws.Part != nullptr ? kTiledPartBytesPerCu * (int64_t)cus : 0;
+    return pick_six(L, M, ws.S, room, cus).us < pick_small(L, M, ws.S, room, cus).us;
 }
 
 uint8_t* six_scales(const Workspace& ws, const Layer& L) {
@@ -1580,8 +1697,14 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     if (ws.six) {
         a.Wt = L.W6; a.rec_bytes = kW6RecordBytes; a.exp_bias = -1;
         a.Xe6 = six_scales(ws, L);
+        const int64_t part_bytes = (mode != 1 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
+        if (variant >= 41) {                                 // the staged kernel's shapes by force, as below
+            const SmallPick pick = mode == 3 ? SmallPick{} : pick_small(L, M, ws.S, part_bytes, cus, variant, mode == 2 ? 2 : 1, true);
+            return pick.id == 0 ? hipErrorInvalidValue : launch_staged<6>(a, pick, s);
+        }
         if (variant == 0) {
-            const SixPick pick = pick_six(L, M, ws.S, mode == 0 && ws.Part != nullptr, cus);
+            const SixPick pick = pick_six(L, M, ws.S, part_bytes, cus);
+            if (pick.id == 0) return launch_staged<6>(a, pick.staged, s);
             variant = pick.id;
             mode = pick.cut ? 4 : 1;
         }

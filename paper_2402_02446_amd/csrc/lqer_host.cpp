@@ -293,7 +293,6 @@ static void untile_b(const Layer& L, const std::vector<uint8_t>& in, int8_t* Bc,
 
 void free_device(Layer& L) {
     if (L.Wt) (void)hipFree(L.Wt);
-    if (L.W6) (void)hipFree(L.W6);
     if (L.At) (void)hipFree(L.At);
     if (L.Bt) (void)hipFree(L.Bt);
     if (L.Wsc) (void)hipFree(L.Wsc);
@@ -311,13 +310,16 @@ int upload(const std::vector<uint8_t>& host, uint8_t** dev) {
     return LQER_OK;
 }
 
-// The layer's fp6 records, made on the device from its W_q records.  (No room for them: the layer goes without.)
-static int add_six(Layer& L) {
-    if (hipMalloc((void**)&L.W6, (size_t)(L.N32 * L.KT) * kW6RecordBytes) != hipSuccess) {
-        L.W6 = nullptr;
+// The W_q records, and behind them in the same allocation the fp6 records, made of these on the device.  (No room for both:
+// the layer goes without.)
+static int upload_weights(Layer& L, const std::vector<uint8_t>& records) {
+    const size_t at = ((size_t)records.size() + 255) / 256 * 256, bytes = at + (size_t)(L.N32 * L.KT) * kW6RecordBytes;
+    if (L.w_bits != 4 || !L.w6_ok || records.empty() || hipMalloc((void**)&L.Wt, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        return LQER_OK;
+        return upload(records, &L.Wt);
     }
+    L.W6 = L.Wt + at;
+    if (hipMemcpy(L.Wt, records.data(), records.size(), hipMemcpyHostToDevice) != hipSuccess) return LQER_ERR_HIP;
     if (launch_widen_six(L, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) return LQER_ERR_HIP;
     return LQER_OK;
 }
@@ -441,7 +443,7 @@ static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, co
     if (!wsp || ((uintptr_t)wsp & 255) != 0) return LQER_ERR_WORKSPACE;
     Workspace ws = plan_workspace(L, M, path, wsp, with_slots);
     if (ws.bytes > ws_bytes) return LQER_ERR_WORKSPACE;
-    if (path == 2 && tiled_takes_six(L, M, Xc != nullptr, variant)) set_six_layout(ws, L);
+    if (path == 2 && tiled_takes_six(L, M, ws, variant)) set_six_layout(ws, L);
     if (path == 1) ws.x8 = stream_takes_codes(stream_variant(L, M, variant), ws.lr);
     hipStream_t s = (hipStream_t)stream;
     if (stages & 1) {
@@ -619,8 +621,7 @@ int lqer_layer_import_w(int w_bits, int64_t K, int64_t N, int k, const uint8_t* 
         {
             std::vector<uint8_t> buf;
             st = tile_weights(L, Wc, We, buf);
-            if (st == LQER_OK) st = upload(buf, &L.Wt);
-            if (st == LQER_OK && w_bits == 4 && L.w6_ok) st = add_six(L);
+            if (st == LQER_OK) st = upload_weights(L, buf);
         }
         if (st == LQER_OK && kp > 0) {
             std::vector<uint8_t> buf;
@@ -768,22 +769,26 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
         }
         return LQER_OK;
     }
-    Workspace ws = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, workspace_dev);
-    // one form of the activations for all: fp6 if every layer's main kernel takes it
-    bool six = true;
-    for (int i = 0; i < n_layers; ++i) six = six && tiled_takes_six(layers[i]->L, M, false, 0);
-    if (six) set_six_layout(ws, layers[0]->L);
+    const Workspace ws = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, workspace_dev);
     hipStream_t s = (hipStream_t)hip_stream;
-    for (int i = 0; i < n_layers; ++i) {
-        const Layer& L = layers[i]->L;
-        hipError_t e;
-        if (i == 0) e = launch_prep(L, X_dev, ldx, nullptr, nullptr, M, ws, nullptr, 0, s);
-        else if (L.kp > 0) e = launch_prep(L, nullptr, 0, nullptr, nullptr, M, ws, nullptr, 0, s, true);
-        else e = launch_clear_flags(ws, s);          // nothing to project; the main kernel still wants its flags cleared
-        if (e != hipSuccess) return LQER_ERR_HIP;
-        e = launch_tiled(L, M, ws, Y_dev[i], ldy[i], Requant{nullptr, nullptr, 0}, 0, s);
-        if (e == hipErrorInvalidValue) return LQER_ERR_SHAPE;
-        if (e != hipSuccess) return LQER_ERR_HIP;
+    // Every layer in the form it has alone: those that take fp6 operands first, then those that take bf16, one quantization each.
+    for (int six = 1; six >= 0; --six) {
+        Workspace w = ws;
+        if (six) set_six_layout(w, layers[0]->L);
+        bool first = true;
+        for (int i = 0; i < n_layers; ++i) {
+            const Layer& L = layers[i]->L;
+            if ((int)tiled_takes_six(L, M, ws, 0) != six) continue;
+            hipError_t e;
+            if (first) e = launch_prep(L, X_dev, ldx, nullptr, nullptr, M, w, nullptr, 0, s);
+            else if (L.kp > 0) e = launch_prep(L, nullptr, 0, nullptr, nullptr, M, w, nullptr, 0, s, true);
+            else e = launch_clear_flags(w, s);       // nothing to project; the main kernel still wants its flags cleared
+            if (e != hipSuccess) return LQER_ERR_HIP;
+            first = false;
+            e = launch_tiled(L, M, w, Y_dev[i], ldy[i], Requant{nullptr, nullptr, 0}, 0, s);
+            if (e == hipErrorInvalidValue) return LQER_ERR_SHAPE;
+            if (e != hipSuccess) return LQER_ERR_HIP;
+        }
     }
     return LQER_OK;
 }

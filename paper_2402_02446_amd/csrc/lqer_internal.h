@@ -100,7 +100,7 @@ struct Layer {
     int w_exp_bias;    // compact records: exponent byte = nibble + this; -1: one byte per block
     int act_bits;      // width of the activation codes: 8 or 6
     uint8_t* Wt;       // device, N32*KT records
-    uint8_t* W6;       // device, N32*KT fp6 records, or null (2-bit weights; exponents too small for the matrix instruction's scales)
+    uint8_t* W6;       // N32*KT fp6 records behind Wt's, or null (2-bit weights; exponents too small for the matrix instruction's scales)
     bool w6_ok;        // every non-zero block's exponent byte is at least 2
     uint8_t* At;       // device, kp16*KT records
     uint8_t* Bt;       // device, N32*kp16 records
@@ -186,7 +186,7 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
                         int variant, hipStream_t s);
 
 // Whether this call's main kernel takes fp6 operands: launch_prep has to leave them so (ws.six).
-bool tiled_takes_six(const Layer& L, int64_t M, bool codes_in, int variant);
+bool tiled_takes_six(const Layer& L, int64_t M, const Workspace& ws, int variant);
 void set_six_layout(Workspace& ws, const Layer& L);
 uint8_t* six_scales(const Workspace& ws, const Layer& L);        // the exponent bytes behind all images
 // W_q records -> fp6 records

@@ -146,14 +146,17 @@ __device__ __forceinline__ u32x6 expand_six(u32x4 c) {
     return r;
 }
 
-// 16 codes of a block (as floats, at most 127 in size when multiplied by `up`) -> the operand [8 h | l].  The conversion takes its
-// 32 values alternately from two registers' runs.
+// 16 codes of a block (as floats, times `up` at most 128 in size) -> the operand [8 h | l].  (|h| <= 7 also for a code of -128, whose l
+// is then -16.)  The conversion takes its 32 values alternately from two registers' runs.
+template <bool CLAMP>
 __device__ __forceinline__ u32x6 codes_to_six(const float (&r)[16], float up) {
     const float per16 = 0.0625f * up, per8 = 0.125f * up;
     f32x16 even, odd;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const float h = __builtin_truncf(r[i] * per16), l = __builtin_fmaf(h, -2.0f, r[i] * per8);
+        float h = __builtin_truncf(r[i] * per16);
+        if (CLAMP) h = __builtin_fmaxf(h, -7.0f);
+        const float l = __builtin_fmaf(h, -2.0f, r[i] * per8);
         if (i & 1) { odd[i >> 1] = h; odd[8 + (i >> 1)] = l; }
         else { even[i >> 1] = h; even[8 + (i >> 1)] = l; }
     }
