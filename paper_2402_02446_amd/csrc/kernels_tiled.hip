@@ -576,6 +576,50 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
             if (cc0 + 1 < tail_chunks) store_x(tst[1], 1);
             __syncthreads();
         }
+        if constexpr (SIX) {
+            // The two chunks' steps are summed by themselves, two MFMA tiles at a time, and added once: an fp32 chain rounds at the
+            // size its sum has reached, and the product of fp6 operands mostly is exact up to here.
+            static_assert(TM % 2 == 0, "pairs of tiles");
+#pragma unroll
+            for (int pair = 0; pair < TN * TM / 2; ++pair) {
+                const int tn = pair / (TM / 2), tm0 = pair % (TM / 2) * 2;
+                f32x16 corr[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) corr[i][r] = 0.f;
+#pragma unroll 1
+                for (int cc = cc0; cc < cc0 + 2 && cc < my_tail; ++cc) {
+                    const uint8_t* stage = lds + (cc & 1) * TSTAGE + tm0 * 4096;
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int jb = 4 * cc + 2 * hh_e + j;
+                        const bool live = jb < nb2;
+                        const int rb = live ? (jb < a.kp16 ? jb : jb - a.kp16) : 0;
+                        const uint8_t* rec = a.Bt + (group_of(tn) * a.kp16 + rb) * kBRecordBytes;
+                        u32x4 cw = *reinterpret_cast<const u32x4*>(rec + t_e * 16);
+                        const uint32_t eb = rec[512 + t_e];
+                        if (!live) cw = u32x4{0, 0, 0, 0};
+                        Frag bf[2];
+                        int8x16_to_frags(cw, h_scale(eb), bf[0], bf[1]);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) {
+                                Frag xt;
+                                xt.u = *reinterpret_cast<const u32x4*>(stage + rd_off[2 * j + h] + i * 4096);
+                                corr[i] = mfma32(bf[h].v, xt.v, corr[i]);
+                            }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[tm0 + i][tn][r] += corr[i][r];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            continue;
+        }
         for (int cc = cc0; cc < cc0 + 2 && cc < my_tail; ++cc) {
             const uint8_t* stage = lds + (cc & 1) * TSTAGE;
 #pragma unroll
