@@ -32,11 +32,13 @@
 // an 8-bit code in two halves against the 4-bit code, exact as before, at half the matrix instructions' time (mfma32_six).  The chip's
 // clock under load is what bounds the bf16 form; this one moves 24 bytes of LDS per operand block instead of 32 and runs half as
 // many passes.  Bounds now: again the clock (4.0 us per K tile of a 128 x 512 tile on a full chip, 2.7 on a nearly empty one; the
-// bare MFMA loop's rate would be 3.2).  Whole calls, bf16 form -> this: 8192 x 28672 rank 64 at 4096 tokens 1477 -> 1093 us, 11008 x 4096
-// rank 32 at 2048 178 -> 138, 4096 x 4096 at 8192 263 -> 200, rank 16 at 65536 2005 -> 1571.  Distance from the 64-bit result unchanged
-// (2.65e-7, 2.38e-7, 2.29e-7, 2.07e-7; on data of wide exponents, where the bf16 chain rounds more often, 7.6e-8 against 1.2e-7
-// at K = 4096).  Layers of rank 0 keep bf16 operands: an exponent byte of 255, a block with an infinity, is a NaN to the block-scaled
-// instruction, where bf16 has infinities; with a correction the row is NaN either way.
+// bare MFMA loop's rate would be 3.2).  Whole calls, bf16 form -> this: 8192 x 28672 rank 64 at 4096 tokens 1463 -> 1152 us, 11008 x 4096
+// rank 32 at 2048 193 -> 157, three layers of 4096 x 4096 at 8192 738 -> 600.  Distance from the 64-bit result: 2.65e-7 -> 2.47e-7,
+// 2.35e-7 -> 2.30e-7, 2.29e-7 -> 2.20e-7; on data of wide exponents, where the bf16 chain rounds more often, 1.2e-7 -> 7.6e-8 at
+// K = 4096.  (The correction in the same chain, as the last of its sums, took 1088, 149 and 542 us, but 2.38e-7 in the second case; its
+// B_k records asked for in one go ahead of the sums: no faster, the registers it takes are spilled.)  Layers of rank 0 keep bf16
+// operands: an exponent byte of 255, a block with an infinity, is a NaN to the block-scaled instruction, where bf16 has
+// infinities; with a correction the row is NaN either way.
 //
 // Calls that do not fill the chip for long mostly take staged_kernel (pick_small says which): tiles of 64 rows, every
 // operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
