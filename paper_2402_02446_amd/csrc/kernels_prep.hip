@@ -537,8 +537,10 @@ int prep_slices(const Layer& L, int64_t M, int path) {
     return (int)s;
 }
 
-// wavefronts of a workgroup: one per tile of the slice where the launch fills the chip anyway, otherwise one per quarter of a tile
-// in as few and as even rounds as fit
+// Wavefronts of a workgroup: one per tile of the slice where the launch fills the chip anyway, otherwise one per quarter of a tile
+// in as few and as even rounds as fit.  Which quarters a wavefront adds up before the wavefronts' sums meet decides the bits of T, so
+// `filled` goes by token rows and slices alone: not by the planes of rank groups, which differ between a layer's own call and
+// one that finds its activations stored.
 static int prep_waves(int tiles, bool filled) {
     if (filled) return tiles < kPrepRowWaves ? (tiles < 1 ? 1 : tiles) : kPrepRowWaves;
     const int units = 4 * tiles;
@@ -585,7 +587,7 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     const int64_t rg = (M + 15) / 16;
     // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
     const bool rowwise = !cells && !ws.six && src == 0 && rg * ws.S * gz >= 2048;
-    a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S * gz >= 256);
+    a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S >= 256);
     dim3 block(64 * a.nwaves);
     // clearing workgroups: about four 16-byte stores per thread
     const int64_t zero_wgs = y_zero ? (M * ((L.N + 3) / 4) + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;
@@ -609,8 +611,6 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
         a.g_first = 4;
         grid.z = (unsigned)((L.kp16 - 4 + 3) / 4);
         grid.y = (unsigned)ws.S;
-        a.nwaves = prep_waves(a.tiles_per_slice, rg * ws.S * grid.z >= 256);
-        block.x = 64 * a.nwaves;
         if (fin) LQER_PREP_G(2, true); else LQER_PREP_G(2, false);
     }
 #undef LQER_PREP_C
