@@ -3,7 +3,7 @@
 // matmul).
 //
 // One workgroup owns 16 token rows and a K slice; its wavefronts take the quarters (64 columns) of the
-// slice's 256-wide K tiles in turn.  Lane (t = lane % 16, q = lane / 16) owns block q of a quarter for
+// slice's 256-wide K tiles in turn (its tiles, quarter by quarter, where the row-wise form below exists beside it).  Lane (t = lane % 16, q = lane / 16) owns block q of a quarter for
 // token t: it finds the block maximum, quantizes, and keeps the dequantized values
 // code * 2^(e-6) - exact in bf16 - both for the store to the bf16 activation matrix the main
 // kernels read and as its MFMA operand.  A_k arrives already dequantized to bf16 (exactly, at
@@ -13,7 +13,7 @@
 // block's arithmetic per wavefront.  With whole tiles per wavefront and each quarter's loads behind a branch it was four round
 // trips and 64 values' arithmetic one after the other; whole calls replayed from a graph (4-bit weights, rank 32):
 // 4096 x 4096 at 1 token 9.4 -> 8.4 us, at 16 11.4 -> 10.4, at 40 20.6 -> 16.9, 2048 x 2048 at 64 19.0 -> 15.3,
-// 4096 x 11008 at 128 36.6 -> 32.7.  Launches of 256 and more workgroups take as many wavefronts as tiles, four quarters each:
+// 4096 x 11008 at 128 36.6 -> 32.7.  Launches of 256 and more row blocks x K slices take as many wavefronts as tiles, four quarters each:
 // there the chip is full, and 16 wavefronts of a quarter each were 3 % slower for a call of 2048 tokens at rank 256.
 //
 // S == 1: T is final; it is split into two bf16 terms T_hi + T_lo and stored behind the
@@ -50,6 +50,7 @@ struct PrepArgs {
     bool x8;               // CELLS: store MXINT8 codes [block][row][16] and exponent bytes [block][row] instead of bf16 cells
     float* Yz; int64_t ldy, N;   // Yz != null: extra workgroups clear Y[M][N] for a main kernel that adds into it
     int nslices;                 // K slices = the part of grid.y that does the projection
+    bool by_tiles;               // a wavefront takes whole tiles, otherwise quarters of them
     int nwaves;                  // wavefronts of a workgroup (an argument: blockDim costs a vector load ahead of everything else)
     uint32_t* flags; int nflags; // flags != null: words the first workgroup clears for the main kernel
 };
@@ -274,6 +275,10 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                 for (int i = 0; i < 4; ++i) u.x[i] = *reinterpret_cast<const u32x4*>(xrow + kbc * 16 + 4 * i);
             }
         };
+        // Where fp32 input takes the row-wise form, a wavefront takes its tiles' four quarters one after the other here too: T is then
+        // added up in the same order whatever the activations come from.  (Elsewhere quarters in turn are the faster: 4-bit layers
+        // on codes, 8192 tokens, 4096 wide 39.7 us a call, 42.0 by tiles.)
+        auto next_unit = [&](int unit) { return a.by_tiles ? unit + ((unit & 3) == 3 ? 4 * nwaves - 3 : 1) : unit + nwaves; };
         // more: the wavefront has another unit behind this one.  (Two instances: where loads may or may not follow, the compiler
         // waits for all of them.)
         auto process = [&](Unit& cur, Unit& nxt, int unit, auto more) {
@@ -288,7 +293,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
 #pragma unroll
                 for (int g = 0; g < MAXG; ++g) load_a(af[g], g, unit);
             }
-            if constexpr (decltype(more)::value) load_unit(nxt, unit + nwaves);
+            if constexpr (decltype(more)::value) load_unit(nxt, next_unit(unit));
             __builtin_amdgcn_sched_barrier(0);
             const int64_t blk = (tile_begin + (unit >> 2)) * 16 + q + 4 * (unit & 3);   // block index along K
             const bool ok = row_ok && blk < nblk;
@@ -409,10 +414,10 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
             }
         };
         Unit cur, nxt;
-        int unit = wave;
+        int unit = a.by_tiles ? 4 * wave : wave;
         if (unit < units) {
             load_unit(cur, unit);
-            for (; unit + nwaves < units; unit += nwaves) {
+            for (; next_unit(unit) < units; unit = next_unit(unit)) {
                 process(cur, nxt, unit, std::true_type{});
                 cur = nxt;
             }
@@ -586,7 +591,8 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     const int src = reuse_xh ? 2 : (Xc != nullptr ? 1 : 0);
     const int64_t rg = (M + 15) / 16;
     // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
-    const bool rowwise = !cells && !ws.six && src == 0 && rg * ws.S * gz >= 2048;
+    a.by_tiles = !cells && !ws.six && rg * ws.S >= 2048;
+    const bool rowwise = a.by_tiles && src == 0;
     a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S >= 256);
     dim3 block(64 * a.nwaves);
     // clearing workgroups: about four 16-byte stores per thread
@@ -642,6 +648,7 @@ hipError_t launch_prep_group(const Layer* const* layers, int n, const float* X, 
         z += L.kp16;
         cols4 += (L.N + 3) / 4;
     }
+    a.by_tiles = false;
     a.nwaves = prep_waves(a.tiles_per_slice, false);
     const dim3 block(64 * a.nwaves);
     const int64_t rg = (M + 15) / 16;

@@ -11,8 +11,8 @@ from helpers import assert_forward_matches, oracle_layer_big, upload
 pytestmark = pytest.mark.gpu
 
 
-# cells (M <= 32), code cells (16 < .. of single workgroups per column block), rows (M > 32), the last one with more than 256
-# workgroups, where a wavefront takes whole tiles of quarters
+# cells (M <= 32), code cells (16 < .. of single workgroups per column block), rows (M > 32), the last one with as
+# many wavefronts as tiles, four quarters each
 @pytest.mark.parametrize("M", [1, 5, 17, 33, 47, 1043])
 @pytest.mark.parametrize("K,N,k,w_bits", [(16, 40, 8, 4), (80, 100, 0, 4), (272, 64, 24, 4), (1040, 96, 40, 4), (4176, 70, 64, 4),
                                           (11056, 48, 16, 4), (4112, 64, 256, 2), (33040, 32, 33, 2)])

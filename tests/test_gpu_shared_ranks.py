@@ -28,3 +28,20 @@ def test_large_ranks_behind_another_layer(M, w_bits):
     for g, h in zip(binding.lqer_linear_forward_shared(hs, X), hs):
         assert torch.equal(g, binding.lqer_linear_forward(h, X))
         h.free()
+
+
+# 2048 blocks of 16 rows and more, where fp32 rows are read by the row-wise form, codes and stored activations by the other one;
+# 4-bit layers of these sizes take other operands, and the same form whatever the source
+@pytest.mark.parametrize("w_bits", [2, 4])
+@pytest.mark.parametrize("M,K,ranks", [(33000, 1040, (16, 33)), (32768, 2304, (64, 256))])
+def test_many_tokens_from_every_source(M, K, ranks, w_bits):
+    import torch
+    from paper_2402_02446_amd import binding
+    hs = [upload(oracle_layer_big(K, 256, k, seed=50 + i, w_bits=w_bits)[0]) for i, k in enumerate(ranks)]
+    X = torch.from_numpy(_wide(K, M, K)).cuda()
+    codes, exps = binding.lqer_quantize_mx(X, 8)
+    for g, h in zip(binding.lqer_linear_forward_shared(hs, X), hs):
+        Y = binding.lqer_linear_forward(h, X)
+        assert torch.equal(g, Y)
+        assert torch.equal(binding.lqer_linear_forward_q(h, codes, exps), Y)
+        h.free()
