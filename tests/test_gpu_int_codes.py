@@ -34,8 +34,8 @@ def test_ties_and_their_neighbours():
     _check(X)
 
 
-# maxima from 127 2^-26 (a scale of zero) to 127 2^16 (an infinite one); rows around 4 x 1024 and 12 x 1024 values
-@pytest.mark.parametrize("K", [4, 252, 1024, 4092, 4100, 11008, 12288, 12292, 28672])
+# maxima from 127 2^-26 (a scale of zero) to 127 2^16 (an infinite one); rows around 1024, 4 x 1024 and 12 x 1024 values
+@pytest.mark.parametrize("K", [4, 252, 1024, 1028, 4092, 4100, 11008, 12288, 12292, 28672])
 def test_scales_and_lengths(K):
     rng = np.random.default_rng(K)
     X = rng.standard_normal((48, K)).astype(np.float32)
