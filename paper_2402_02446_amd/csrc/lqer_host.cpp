@@ -311,10 +311,10 @@ int upload(const std::vector<uint8_t>& host, uint8_t** dev) {
 }
 
 // The W_q records, and behind them in the same allocation the fp6 records, made of these on the device.  (No room for both:
-// the layer goes without.)
+// the layer goes without.  A layer of rank 0 has no use for them, see tiled_takes_six.)
 static int upload_weights(Layer& L, const std::vector<uint8_t>& records) {
     const size_t at = ((size_t)records.size() + 255) / 256 * 256, bytes = at + (size_t)(L.N32 * L.KT) * kW6RecordBytes;
-    if (L.w_bits != 4 || !L.w6_ok || records.empty() || hipMalloc((void**)&L.Wt, bytes) != hipSuccess) {
+    if (L.w_bits != 4 || L.kp == 0 || !L.w6_ok || records.empty() || hipMalloc((void**)&L.Wt, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return upload(records, &L.Wt);
     }

@@ -1,0 +1,30 @@
+"""Device memory that a layer takes beside its records: the fp6 copy of 4-bit weights."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+K, N = 8192, 4096
+RECORDS = K // 256 * (N // 32) * 4608               # bytes of one form of the weights, at most
+
+
+def _import(k):
+    """A layer of zero codes, and the device memory its import took."""
+    import torch
+    from paper_2402_02446_amd import binding
+    kp = (k + 15) // 16 * 16
+    fac = () if k == 0 else (np.zeros((kp, K), np.int8), np.full((kp, K // 16), 127, np.uint8),
+                             np.zeros((N, kp), np.int8), np.full((N, kp // 16), 127, np.uint8))
+    We = np.full((N, K // 16), 120, np.uint8)
+    We[0, 0] = 100                                  # the wider form of the records
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    h = binding.lqer_layer_import(K, N, k, np.zeros((N, K // 2), np.uint8), We, *fac)
+    return h, free - torch.cuda.mem_get_info()[0]
+
+
+def test_rank_zero_has_one_form_of_the_weights():
+    _import(0)[0].free()                            # (what a process's first import takes for good)
+    h, taken = _import(0)
+    h.free()
+    assert taken < 1.5 * RECORDS
