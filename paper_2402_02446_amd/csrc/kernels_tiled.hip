@@ -28,7 +28,7 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
-// The fp6 form (WB = 6).  Above 1.5e11 operations, and below where the time models say so, a 4-bit layer's fp32 activations are not brought to bf16 but to fp6 operands:
+// The fp6 form (WB = 6).  Mostly (tiled_takes_six) a 4-bit layer's activations are not brought to bf16 but to fp6 operands:
 // an 8-bit code in two halves against the 4-bit code, exact as before, at half the matrix instructions' time (mfma32_six).  The chip's
 // clock under load is what bounds the bf16 form; this one moves 24 bytes of LDS per operand block instead of 32 and runs half as
 // many passes.  Bounds now: again the clock (4.0 us per K tile of a 128 x 512 tile on a full chip, 2.7 on a nearly empty one; the
@@ -1403,12 +1403,11 @@ static const SmallShape kSmallShapes2[] = {
     {12, 128, 256, 2, {3.08, 5.22}, 0.38, 8.44, {1.68, 2.03}, {0.0, 0.47}, 0.192, 0.0, 0.0},
     {11, 128, 512, 1, {4.53, 0.0}, 3.2, 7.8, {0.0, 0.0}, {3.50, 1.30}, 0.205, 0.0, 0.0},
 };
-// The staged kernel's fp6 form, fitted to 132 timings a shape of 77 calls of 1e9 to 1.6e11 operations (mean error 3 to 5 %); with
-// the fp6 shapes of tiled_kernel the choice is 0.3 % from the fastest on average, 2.7 % at the 95th percentile, 6.4 % at worst.
+// The staged kernel's fp6 form (fitted with the fp6 shapes of tiled_kernel, below; mean error 4 to 6 %).
 static const SmallShape kSmallShapes6[] = {
-    {43, 64, 128, 2, {0.986, 1.474}, 0.22, 6.60, {0.85, 0.18}, {0.0, 0.71}, 0.210, 2.6, 0.178},
-    {41, 64, 256, 2, {1.524, 2.471}, 1.59, 6.86, {2.56, 0.0}, {0.0, 0.80}, 0.193, 2.7, 0.158},
-    {42, 64, 512, 1, {2.372, 0.0}, 5.54, 5.04, {0.0, 0.59}, {3.53, 0.0}, 0.141, 3.0, 0.139},
+    {43, 64, 128, 2, {1.012, 1.562}, 0.16, 5.87, {0.485, 0.580}, {0.0, 0.239}, 0.186, 3.29, 0.165},
+    {41, 64, 256, 2, {1.507, 2.570}, 0.76, 6.91, {1.811, 0.501}, {0.0, 0.301}, 0.193, 3.06, 0.167},
+    {42, 64, 512, 1, {2.600, 0.0}, 2.33, 5.45, {2.568, 0.566}, {0.0, 0.0}, 0.202, 3.59, 0.158},
 };
 // The 128 x 512 shape with tiles cut in pieces, for 4 and 2 bits: us per launch, K tile of a piece, K tile and number of whole
 // rounds, piece beyond two, the correction per round.  Whole pieces per tile (460 timings, 5 %), and equal shares, whose
@@ -1482,17 +1481,21 @@ static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes
 // ---- the fp6 form: which tile, cut along K or not -----------------------------------------------------------------------
 // Time model of the main product in us: `unit` per K tile of a full round of workgroups, `few` of a round of one workgroup on next to no
 // compute unit, `pair_few` of one with two on next to none (what lies between goes by how full it is: a full chip's clock is
-// lower); `round`, `fixed`, `out` per MB of Y and `corr` as above.  Fitted to 140 calls of 1e10 to 2e12 operations (K 512 to 12288, N 1024 to
-// 28672, 64 to 32768 tokens, ranks 8 to 128): mean error 4 %, 10 % at the 95th percentile.  The choice is 1.1 % from the
-// fastest of the forms on average.
-struct SixShape { int id, bn, resident; double unit, few, pair_few, round, fixed, out, corr[2]; };
+// lower); `round`, `fixed`, `out` per MB of Y as above; corr[0] per round and chunk of the correction beyond the first, corr[1] per round,
+// pair of chunks and partial sum of T, corr[2] per round and pair beyond the first.  Fitted, with kSmallShapes6, to all forms of 4705 calls of
+// 3e8 to 1e12 operations (K 64 to 12288, N 64 to 28672, 33 to 65536 tokens, ranks 8 to 256), timed on a warm chip: mean error 3 to 5 %.
+// The choice is 0.3, 0.4, 1.0 and 0.5 % from the fastest form on average for calls below 3e9, 3e10 and 1.5e11 operations and above; 3, 3, 5 and
+// 4 % at the 95th percentile, 17 % at the very worst.  The staged shapes belong to it at every size: their correction, in front and in
+// registers, costs a tenth of what it costs in tiled_kernel.  Without them above 1.5e11 operations calls took 1.07 times as long on
+// average, 1.9 at worst (whole calls: 3449 x 3872 x 5424 rank 256 368 us, now 245; 3549 x 2048 x 11008 rank 256 440, now 292).
+struct SixShape { int id, bn, resident; double unit, few, pair_few, round, fixed, out, corr[3]; };
 static const SixShape kSixShapes[] = {
-    {21, 512, 1, 3.952, 2.685, 0.0, 7.621, 3.716, 0.117, {3.551, 2.391}},
-    {22, 256, 2, 3.967, 2.13, 3.446, 4.983, 7.637, 0.135, {4.162, 3.246}},
+    {21, 512, 1, 3.946, 2.303, 0.0, 12.00, 1.16, 0.097, {4.580, 1.411, 2.243}},
+    {22, 256, 2, 3.969, 1.931, 3.412, 0.0, 9.46, 0.246, {5.419, 2.096, 0.385}},
 };
 // 128 x 512 with tiles cut in whole pieces, and in equal shares (a rough estimate: it has to promise 3 %)
-static const SmallPieces kSixWhole = {38.0, 3.352, 4.026, 11.96, 4.168, 8.11, 0.0};
-static const SmallPieces kSixShares = {36.3, 3.974, 4.178, 13.52, 0.0, 7.85, 0.0};
+static const SmallPieces kSixWhole = {41.9, 4.202, 3.788, 33.46, 6.72, 12.97, 1.893};
+static const SmallPieces kSixShares = {56.3, 4.407, 4.031, 31.98, 0.0, 12.37, 2.599};
 
 struct SixPick { int id; bool cut; double us; SmallPick staged; };   // id 0: the staged kernel's shape `staged`
 
@@ -1506,8 +1509,9 @@ static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int c
         if (sh.resident == 1) unit += fill * sh.unit + (1.0 - fill) * sh.few;
         else unit += rest <= cus ? sh.few : fill * sh.unit + (1.0 - fill) * sh.pair_few;
     }
+    const int chunks = (2 * L.kp + 63) / 64, pairs = (chunks + 1) / 2;
     return (double)L.KT * unit + rounds * sh.round + sh.fixed + sh.out * (double)M * (double)L.N * 4e-6 +
-           more_pairs(L.kp) * rounds * (sh.corr[0] + sh.corr[1] * (double)S);
+           rounds * (sh.corr[0] * (chunks - 1) + sh.corr[1] * pairs * (double)S + sh.corr[2] * (pairs - 1));
 }
 
 // part_bytes: room for the pieces' accumulators or the planes (0: whole tiles only)
@@ -1525,10 +1529,8 @@ static SixPick pick_six(const Layer& L, int64_t M, int S, int64_t part_bytes, in
             if (us < best.us) best = SixPick{21, true, us, {}};
         }
     }
-    if (2.0 * (double)M * (double)L.N * (double)L.K <= kSmallFlops) {
-        const SmallPick staged = pick_small(L, M, S, part_bytes, cus, 0, 1, true);
-        if (staged.us < best.us) best = SixPick{0, false, staged.us, staged};
-    }
+    const SmallPick staged = pick_small(L, M, S, part_bytes, cus, 0, 1, true);
+    if (staged.us < best.us) best = SixPick{0, false, staged.us, staged};
     return best;
 }
 
@@ -1671,15 +1673,19 @@ hipError_t launch_widen_six(const Layer& L, hipStream_t s) {
     return hipGetLastError();
 }
 
-bool tiled_takes_six(const Layer& L, int64_t M, const Workspace& ws, int variant) {
+// Where a layer's calls take fp6 operands: with at least as many K tiles as its correction has chunks of 64 columns beyond the first
+// (always up to rank 64, from K = 513 at rank 128, from 1537 at rank 256), and where the activations are more than next to nothing.
+// On 4705 calls the fp6 form the models choose takes 0.89 of the fastest bf16 form's time above 1.5e11 operations and 0.97 below
+// (never taken: 1 and 1; always: 0.89 and 0.975, 18 and 19 % slower at worst); this line is 0.4 and 0.9 % from the faster of both on
+// average, 3 % slower than bf16 at the 97th and 95th percentile, 14 % at worst.  A forest of decision trees that knows N and the
+// models' estimates as well comes to 0.2 and 0.4 %.  N has no say so that layers of one rank that share their activations share their
+// form, and one quantization.
+bool tiled_takes_six(const Layer& L, int64_t M, int variant) {
     if (L.W6 == nullptr || L.kp == 0) return false;
     const int shape = variant % 100, mode = variant / 100;
     if (shape != 0) return shape == 21 || shape == 22 || (shape >= 41 && shape <= 43);
     if (mode > 1) return false;                              // cut by force: the bf16 shapes
-    if (2.0 * (double)M * (double)L.N * (double)L.K > kSmallFlops) return true;
-    const int cus = compute_units();
-    const int64_t room = mode == 0 && ws.Part != nullptr ? kTiledPartBytesPerCu * (int64_t)cus : 0;
-    return pick_six(L, M, ws.S, room, cus).us < pick_small(L, M, ws.S, room, cus).us;
+    return M * L.K > 500000 && L.KT >= (2 * L.kp + 63) / 64 - 1;
 }
 
 uint8_t* six_scales(const Workspace& ws, const Layer& L) {

@@ -443,7 +443,7 @@ static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, co
     if (!wsp || ((uintptr_t)wsp & 255) != 0) return LQER_ERR_WORKSPACE;
     Workspace ws = plan_workspace(L, M, path, wsp, with_slots);
     if (ws.bytes > ws_bytes) return LQER_ERR_WORKSPACE;
-    if (path == 2 && tiled_takes_six(L, M, ws, variant)) set_six_layout(ws, L);
+    if (path == 2 && tiled_takes_six(L, M, variant)) set_six_layout(ws, L);
     if (path == 1) ws.x8 = stream_takes_codes(stream_variant(L, M, variant), ws.lr);
     hipStream_t s = (hipStream_t)stream;
     if (stages & 1) {
@@ -772,13 +772,14 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
     const Workspace ws = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, workspace_dev);
     hipStream_t s = (hipStream_t)hip_stream;
     // Every layer in the form it has alone: those that take fp6 operands first, then those that take bf16, one quantization each.
+    // (One in all where the ranks are alike: see tiled_takes_six.)
     for (int six = 1; six >= 0; --six) {
         Workspace w = ws;
         if (six) set_six_layout(w, layers[0]->L);
         bool first = true;
         for (int i = 0; i < n_layers; ++i) {
             const Layer& L = layers[i]->L;
-            if ((int)tiled_takes_six(L, M, ws, 0) != six) continue;
+            if ((int)tiled_takes_six(L, M, 0) != six) continue;
             hipError_t e;
             if (first) e = launch_prep(L, X_dev, ldx, nullptr, nullptr, M, w, nullptr, 0, s);
             else if (L.kp > 0) e = launch_prep(L, nullptr, 0, nullptr, nullptr, M, w, nullptr, 0, s, true);

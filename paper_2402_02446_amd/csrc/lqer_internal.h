@@ -186,7 +186,7 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
                         int variant, hipStream_t s);
 
 // Whether this call's main kernel takes fp6 operands: launch_prep has to leave them so (ws.six).
-bool tiled_takes_six(const Layer& L, int64_t M, const Workspace& ws, int variant);
+bool tiled_takes_six(const Layer& L, int64_t M, int variant);
 void set_six_layout(Workspace& ws, const Layer& L);
 uint8_t* six_scales(const Workspace& ws, const Layer& L);        // the exponent bytes behind all images
 // W_q records -> fp6 records
