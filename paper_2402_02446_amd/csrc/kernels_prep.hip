@@ -65,6 +65,12 @@ __device__ __forceinline__ void split_bf16(float t, uint16_t& hi, uint16_t& lo) 
 constexpr int kPrepWaves = 16;     // quarter-tile form, at most
 constexpr int kPrepRowWaves = 8;   // row-wise form
 
+// LDS of a workgroup: a wavefront's sums of up to maxg rank groups, or its 16 x 256 tile in the row-wise form.  By the wavefronts there
+// are: room for 16 of them where a launch has one to eight leaves two workgroups to a compute unit (ranks above 64; 24734 x 224
+// x 144 rank 144 65 us a call, 53 like this).
+static_assert(4 * 64 * 16 <= 8192 && kPrepWaves * 4 * 64 * 16 <= 64 * 1024, "the sums fit the tiles, and the default limit");
+constexpr int prep_lds_bytes(int nwaves, int maxg, bool rowwise) { return nwaves * (rowwise ? 8192 : maxg * 64 * 16); }
+
 // CELLS: the activations are stored for the streaming kernel, as 16-byte cells (8 consecutive K
 // elements) ordered [K / 8][token row]; otherwise row-major for the tiled kernel.
 // SRC: where the activations come from: 0 = fp32 X (quantized here), 1 = MXINT codes and exponent bytes,
@@ -89,9 +95,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
     // compute unit cost more than the coalescing gains (measured: 8192 wide, 4096 tokens 46 -> 52 us; 65536 tokens of
     // 4096 channels 373 -> 308 us), and the lane-per-block form below is used.
     constexpr bool ROWWISE = RW;
-    constexpr int RED_BYTES = (RW ? kPrepRowWaves : kPrepWaves) * MAXG * 64 * 16;
-    constexpr int SMEM_BYTES = ROWWISE ? (kPrepRowWaves * 8192 > RED_BYTES ? kPrepRowWaves * 8192 : RED_BYTES) : RED_BYTES;
-    __shared__ __attribute__((aligned(16))) uint8_t smem[SMEM_BYTES];
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];    // prep_lds_bytes of it
     float (*red)[MAXG][64][4] = reinterpret_cast<float (*)[MAXG][64][4]>(smem);
 
     const int lane = threadIdx.x & 63;
@@ -512,17 +516,17 @@ template <int SRC, bool FINAL, int MAXG, bool CELLS>
 static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& a, bool rowwise, bool six) {
     if constexpr (!CELLS) {
         if (six) {
-            hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false, true>), grid, block, 0, s, a);
+            hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false, true>), grid, block, prep_lds_bytes(a.nwaves, MAXG, false), s, a);
             return;
         }
     }
     if constexpr (SRC == 0 && !CELLS) {
         if (rowwise) {
-            hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, true>), grid, block, 0, s, a);
+            hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, true>), grid, block, prep_lds_bytes(a.nwaves, MAXG, true), s, a);
             return;
         }
     }
-    hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false>), grid, block, prep_lds_bytes(a.nwaves, MAXG, false), s, a);
 }
 
 int prep_slices(const Layer& L, int64_t M, int path) {
@@ -653,7 +657,8 @@ hipError_t launch_prep_group(const Layer* const* layers, int n, const float* X, 
     const dim3 block(64 * a.nwaves);
     const int64_t rg = (M + 15) / 16;
     const int64_t zero_wgs = zero_y ? (M * cols4 + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;
-    hipLaunchKernelGGL(prep_group_kernel, dim3((unsigned)rg, (unsigned)(ws.S + zero_wgs), (unsigned)(z > 0 ? z : 1)), block, 0, s, g);
+    hipLaunchKernelGGL(prep_group_kernel, dim3((unsigned)rg, (unsigned)(ws.S + zero_wgs), (unsigned)(z > 0 ? z : 1)), block,
+                       prep_lds_bytes(a.nwaves, 1, false), s, g);
     return hipGetLastError();
 }
 
