@@ -138,6 +138,10 @@ int lqer_build_factors_device(const float* W_dev, int64_t K, int64_t N,
  * 2 bits Wc is [N][K/4]: four two's-complement bit pairs per byte, element 4i in bits 0-1; the
  * pair -2 is excluded (LQER_ERR_VALUE).  lqer_layer_export writes the width the layer has
  * (lqer_layer_weight_bits; 0 for a NULL handle).
+ * Device memory: 0.53 or 0.56 bytes per 4-bit weight (0.31 per 2-bit one).  A 4-bit layer of rank 1 and more
+ * takes 0.56 bytes per weight more for a second form of W_q, with which its calls on more than 64 tokens (33 on most
+ * layers) run faster, unless that would leave less than half of the device's memory free: such a layer runs
+ * without it, with Y equal up to the order of fp32 sums.
  */
 int lqer_layer_import(int64_t K, int64_t N, int k,
                       const uint8_t* Wc, const uint8_t* We,

@@ -310,11 +310,18 @@ int upload(const std::vector<uint8_t>& host, uint8_t** dev) {
     return LQER_OK;
 }
 
-// The W_q records, and behind them in the same allocation the fp6 records, made of these on the device.  (No room for both:
-// the layer goes without.  A layer of rank 0 has no use for them, see tiled_takes_six.)
+// The W_q records, and behind them in the same allocation the fp6 records, made of these on the device.  (A layer of rank 0 has
+// no use for them, see tiled_takes_six.)  They are there for speed alone and give way to what else is to fit the card: a
+// layer goes without where they would leave less than half of its memory free.
+static bool room_for_six(size_t bytes) {
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) return false;
+    return free_bytes >= bytes && free_bytes - bytes >= total / 2;
+}
+
 static int upload_weights(Layer& L, const std::vector<uint8_t>& records) {
     const size_t at = ((size_t)records.size() + 255) / 256 * 256, bytes = at + (size_t)(L.N32 * L.KT) * kW6RecordBytes;
-    if (L.w_bits != 4 || L.kp == 0 || !L.w6_ok || records.empty() || hipMalloc((void**)&L.Wt, bytes) != hipSuccess) {
+    if (L.w_bits != 4 || L.kp == 0 || !L.w6_ok || records.empty() || !room_for_six(bytes) || hipMalloc((void**)&L.Wt, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return upload(records, &L.Wt);
     }

@@ -28,3 +28,26 @@ def test_rank_zero_has_one_form_of_the_weights():
     h, taken = _import(0)
     h.free()
     assert taken < 1.5 * RECORDS
+
+
+def test_the_copy_gives_way_on_a_fuller_card():
+    import torch
+    _import(16)[0].free()
+    h, taken = _import(16)
+    h.free()
+    assert 1.5 * RECORDS < taken < 2.5 * RECORDS
+    total = torch.cuda.mem_get_info()[1]
+    held = torch.empty(total // 2, dtype=torch.uint8, device="cuda")
+    h, taken = _import(16)
+    Y = h_forward(h)
+    h.free()
+    del held
+    torch.cuda.empty_cache()
+    assert taken < 1.5 * RECORDS
+    assert not Y.any()                              # (zero codes)
+
+
+def h_forward(h):
+    import torch
+    from paper_2402_02446_amd import binding
+    return binding.lqer_linear_forward(h, torch.randn(300, K, device="cuda")).cpu()
