@@ -141,7 +141,7 @@ int lqer_build_factors_device(const float* W_dev, int64_t K, int64_t N,
  * Device memory: 0.53 or 0.56 bytes per 4-bit weight (0.31 per 2-bit one).  A 4-bit layer of rank 1 and more
  * takes 0.56 bytes per weight more for a second form of W_q, with which its calls on more than 64 tokens (33 on most
  * layers) run faster, unless that would leave less than half of the device's memory free: such a layer runs
- * without it, with Y equal up to the order of fp32 sums.
+ * without it, with Y equal up to the order of fp32 sums (lqer_layer_fp6_bytes tells).
  */
 int lqer_layer_import(int64_t K, int64_t N, int k,
                       const uint8_t* Wc, const uint8_t* We,
@@ -162,6 +162,14 @@ int lqer_layer_dims(const lqer_layer* layer, int64_t* K, int64_t* N, int* k, int
  * With 6 bits, block maxima of 2^125 and above are outside the supported range.
  */
 int lqer_layer_set_activation_bits(lqer_layer* layer, int bits);
+/*
+ * The second form of W_q (see the import functions): the device memory it takes, 0 where the layer has none; and
+ * giving it back, for layers that only see few tokens and for callers who want the memory, or the same bits on
+ * every card, more than its speed.  No call on the layer may be running then, and graphs captured with the layer's
+ * calls have to be captured again.  LQER_OK where there is nothing to give back.
+ */
+size_t lqer_layer_fp6_bytes(const lqer_layer* layer);
+int lqer_layer_drop_fp6(lqer_layer* layer);
 int lqer_layer_free(lqer_layer* layer);
 
 /*

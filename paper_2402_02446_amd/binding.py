@@ -22,7 +22,7 @@ STATUS_NAMES = {0: "LQER_OK", 1: "LQER_ERR_NULL", 2: "LQER_ERR_SHAPE", 3: "LQER_
 # every symbol include/lqer.h declares
 EXPORTS = ("lqer_status_string", "lqer_quantize_mx", "lqer_build_factors", "lqer_build_factors_device",
            "lqer_layer_import",
-           "lqer_layer_export", "lqer_layer_dims", "lqer_layer_set_activation_bits", "lqer_layer_free", "lqer_linear_workspace_bytes", "lqer_linear_workspace_bytes_ex",
+           "lqer_layer_export", "lqer_layer_dims", "lqer_layer_set_activation_bits", "lqer_layer_fp6_bytes", "lqer_layer_drop_fp6", "lqer_layer_free", "lqer_linear_workspace_bytes", "lqer_linear_workspace_bytes_ex",
            "lqer_linear_forward", "lqer_linear_forward_q", "lqer_linear_forward_ex", "lqer_linear_forward_requant", "lqer_linear_path",
            "lqer_linear_shared_workspace_bytes", "lqer_linear_forward_shared", "lqer_set_wait_limit",
            "lqer_linear_forward_static", "lqer_layer_import_w", "lqer_layer_weight_bits",
@@ -85,6 +85,10 @@ def lib() -> C.CDLL:
     L.lqer_layer_dims.argtypes = [vp, C.POINTER(i64), C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
     L.lqer_layer_set_activation_bits.restype = i32
     L.lqer_layer_set_activation_bits.argtypes = [vp, i32]
+    L.lqer_layer_fp6_bytes.restype = sz
+    L.lqer_layer_fp6_bytes.argtypes = [vp]
+    L.lqer_layer_drop_fp6.restype = i32
+    L.lqer_layer_drop_fp6.argtypes = [vp]
     L.lqer_layer_free.restype = i32
     L.lqer_layer_free.argtypes = [vp]
     L.lqer_linear_workspace_bytes.restype = sz
@@ -161,6 +165,12 @@ class Layer:
 
     def set_activation_bits(self, bits: int):
         _check(lib().lqer_layer_set_activation_bits(self.handle, int(bits)), "lqer_layer_set_activation_bits")
+
+    def fp6_bytes(self) -> int:
+        return int(lib().lqer_layer_fp6_bytes(self.handle))
+
+    def drop_fp6(self):
+        _check(lib().lqer_layer_drop_fp6(self.handle), "lqer_layer_drop_fp6")
 
     def free(self):
         if self.handle:

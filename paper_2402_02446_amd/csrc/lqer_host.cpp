@@ -293,6 +293,7 @@ static void untile_b(const Layer& L, const std::vector<uint8_t>& in, int8_t* Bc,
 
 void free_device(Layer& L) {
     if (L.Wt) (void)hipFree(L.Wt);
+    if (L.W6) (void)hipFree(L.W6);
     if (L.At) (void)hipFree(L.At);
     if (L.Bt) (void)hipFree(L.Bt);
     if (L.Wsc) (void)hipFree(L.Wsc);
@@ -310,23 +311,21 @@ int upload(const std::vector<uint8_t>& host, uint8_t** dev) {
     return LQER_OK;
 }
 
-// The W_q records, and behind them in the same allocation the fp6 records, made of these on the device.  (A layer of rank 0 has
-// no use for them, see tiled_takes_six.)  They are there for speed alone and give way to what else is to fit the card: a
-// layer goes without where they would leave less than half of its memory free.
-static bool room_for_six(size_t bytes) {
-    size_t free_bytes = 0, total = 0;
-    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) return false;
-    return free_bytes >= bytes && free_bytes - bytes >= total / 2;
-}
+// The fp6 records, made of the W_q records on the device.  (A layer of rank 0 has no use for them, see tiled_takes_six.)  They are
+// there for speed alone and give way to what else is to fit the card: a layer goes without where they would leave less
+// than half of its memory free.
+static size_t six_bytes(const Layer& L) { return (size_t)(L.N32 * L.KT) * kW6RecordBytes; }
 
-static int upload_weights(Layer& L, const std::vector<uint8_t>& records) {
-    const size_t at = ((size_t)records.size() + 255) / 256 * 256, bytes = at + (size_t)(L.N32 * L.KT) * kW6RecordBytes;
-    if (L.w_bits != 4 || L.kp == 0 || !L.w6_ok || records.empty() || !room_for_six(bytes) || hipMalloc((void**)&L.Wt, bytes) != hipSuccess) {
+static int make_six(Layer& L) {
+    const size_t bytes = six_bytes(L);
+    size_t free_bytes = 0, total = 0;
+    if (L.w_bits != 4 || L.kp == 0 || !L.w6_ok) return LQER_OK;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess || free_bytes < bytes || free_bytes - bytes < total / 2 ||
+        hipMalloc((void**)&L.W6, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        return upload(records, &L.Wt);
+        L.W6 = nullptr;
+        return LQER_OK;
     }
-    L.W6 = L.Wt + at;
-    if (hipMemcpy(L.Wt, records.data(), records.size(), hipMemcpyHostToDevice) != hipSuccess) return LQER_ERR_HIP;
     if (launch_widen_six(L, nullptr) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) return LQER_ERR_HIP;
     return LQER_OK;
 }
@@ -628,7 +627,8 @@ int lqer_layer_import_w(int w_bits, int64_t K, int64_t N, int k, const uint8_t* 
         {
             std::vector<uint8_t> buf;
             st = tile_weights(L, Wc, We, buf);
-            if (st == LQER_OK) st = upload_weights(L, buf);
+            if (st == LQER_OK) st = upload(buf, &L.Wt);
+            if (st == LQER_OK) st = make_six(L);
         }
         if (st == LQER_OK && kp > 0) {
             std::vector<uint8_t> buf;
@@ -696,6 +696,17 @@ int lqer_layer_set_activation_bits(lqer_layer* layer, int bits) {
     if ((bits != 8 && bits != 6) || layer->L.format != 0) return LQER_ERR_UNSUPPORTED;
     layer->L.act_bits = bits;
     return LQER_OK;
+}
+
+size_t lqer_layer_fp6_bytes(const lqer_layer* layer) {
+    return layer && layer->L.W6 ? six_bytes(layer->L) : 0;
+}
+
+int lqer_layer_drop_fp6(lqer_layer* layer) {
+    if (!layer) return LQER_ERR_NULL;
+    uint8_t* const held = layer->L.W6;
+    layer->L.W6 = nullptr;
+    return held && hipFree(held) != hipSuccess ? LQER_ERR_HIP : LQER_OK;
 }
 
 int lqer_layer_free(lqer_layer* layer) {

@@ -100,7 +100,7 @@ struct Layer {
     int w_exp_bias;    // compact records: exponent byte = nibble + this; -1: one byte per block
     int act_bits;      // width of the activation codes: 8 or 6
     uint8_t* Wt;       // device, N32*KT records
-    uint8_t* W6;       // N32*KT fp6 records behind Wt's, or null (2-bit weights; rank 0; exponents too small for the matrix instruction's scales; a card too full)
+    uint8_t* W6;       // N32*KT fp6 records, or null (2-bit weights; rank 0; exponents too small for the matrix instruction's scales; a card too full)
     bool w6_ok;        // every non-zero block's exponent byte is at least 2
     uint8_t* At;       // device, kp16*KT records
     uint8_t* Bt;       // device, N32*kp16 records

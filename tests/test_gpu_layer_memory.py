@@ -51,3 +51,28 @@ def h_forward(h):
     import torch
     from paper_2402_02446_amd import binding
     return binding.lqer_linear_forward(h, torch.randn(300, K, device="cuda")).cpu()
+
+
+def test_the_copy_can_be_seen_and_given_back():
+    import torch
+    from helpers import assert_forward_matches, oracle_layer_big, upload
+    from paper_2402_02446_amd import binding, synth
+    layer, ch = oracle_layer_big(1024, 416, 32, seed=5)
+    X = synth.gen_activations(np.random.default_rng(5), 700, 1024, ch, 50.0)
+    Xd = torch.from_numpy(X).cuda()
+    h = upload(layer)
+    assert h.fp6_bytes() == 4 * 13 * 4608
+    first = binding.lqer_linear_forward(h, Xd)
+    h.drop_fp6()
+    assert h.fp6_bytes() == 0
+    h.drop_fp6()                                    # (nothing left)
+    assert_forward_matches(binding.lqer_linear_forward(h, Xd).cpu().numpy(), X, layer)
+    assert_forward_matches(first.cpu().numpy(), X, layer)
+    with pytest.raises(binding.LqerError, match="LQER_ERR_SHAPE"):
+        binding.lqer_linear_forward_ex(h, Xd, path=2, variant=121)      # an fp6 shape by force
+    h.free()
+    for other in (upload(oracle_layer_big(1024, 416, 0, seed=6)[0]), upload(oracle_layer_big(1024, 416, 32, seed=7, w_bits=2)[0])):
+        assert other.fp6_bytes() == 0
+        other.drop_fp6()
+        other.free()
+    assert binding.lib().lqer_layer_fp6_bytes(None) == 0 and binding.lib().lqer_layer_drop_fp6(None) == 1
