@@ -8,7 +8,7 @@ Y = X_q W_q + T B_k - over one batch of synthetic activations already resident i
 
 The headline workload is the largest single-GPU configuration: the LLaMA-2-70B-shaped MLP layer
 (W 8192 x 28672, k = 64) at M = 4096 tokens, the compute-bound regime of Sec. 2.1, priced against the
-dense bf16 MFMA peak.  `cases` holds, first, the same layer at M = 16 and M = 1 (memory-bound regime,
+dense peak of the matrix instructions it runs on (fp6 ones, two for each product of an 8-bit and a 4-bit code).  `cases` holds, first, the same layer at M = 16 and M = 1 (memory-bound regime,
 priced against HBM bandwidth; consecutive steps walk a ring of distinct device copies whose packed
 weights exceed the 256 MB last-level cache, so weights really come from HBM), then the 7B-shaped
 decode and prefill layers, the stand-alone quantizer, the decode-to-prefill sweep of the 70B-shaped
@@ -46,6 +46,8 @@ METRIC = "LQER W4A8 linear: TFLOP/s + % roofline (HBM GB/s M<=16, MFMA util M>=2
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, vendor figure
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 MFMA, vendor figure
 MFMA_INT8_PEAK_TOPS = 5000.0    # dense int8 MFMA, vendor figure
+# 4-bit layers on the tiled path: dense fp6 MFMA, vendor figure 10 PFLOP/s; a product of codes takes two fp6 products
+MFMA_SIX_PEAK_TFLOPS = 5000.0
 LLC_BYTES = 256 << 20
 
 
@@ -64,9 +66,10 @@ def bytes_main_kernel(M, K, N, kp):
     return K * N * 0.5625 + kp * N * 1.0625 + M * K * 1.0625 + 4.0 * M * kp + 4.0 * M * N
 
 
-def bytes_prep_kernel(M, K, kp):
-    """Algorithmic bytes of the projection kernel at prefill sizes: fp32 X in, bf16 X_q out, A_k once, T out."""
-    return 4.0 * M * K + 2.0 * M * K + K * kp * 1.0625 + 4.0 * M * kp
+def bytes_prep_kernel(M, K, kp, six=False):
+    """Algorithmic bytes of the projection kernel at prefill sizes: fp32 X in, X_q out as bf16 or as fp6 pairs with their
+    exponent bytes (1.5 + 1/16 bytes), A_k once, T out."""
+    return 4.0 * M * K + (1.5625 if six else 2.0) * M * K + K * kp * 1.0625 + 4.0 * M * kp
 
 
 def _event_ms(fn, iters):
@@ -126,6 +129,7 @@ def probes():
         L.lqer_probe_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int, C.c_void_p]
         L.lqer_probe_mfma.argtypes = [C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p]
         L.lqer_probe_mfma_random.argtypes = [C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p]
+        L.lqer_probe_mfma_six.argtypes = [C.c_int, C.c_int, C.c_void_p, C.c_void_p]
         L.lqer_probe_mfma_valu.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p]
         _probes = L
     return _probes
@@ -187,6 +191,12 @@ def measure_peaks():
     f(0)
     ms = min(_event_ms(f, 3) for _ in range(3))
     out["mfma_bf16_tflops_random_operands"] = cus * 2 * 4 * 4096 * 4 * 32768.0 / (ms * 1e-3) / 1e12
+    # block-scaled fp6 MFMAs on random operands, in products of codes (two fp6 products each): what the tiled path of 4-bit
+    # layers is made of
+    f = lambda i: chk(P.lqer_probe_mfma_six(cus * 2, 4096, sink.data_ptr(), cur()))
+    f(0)
+    ms = min(_event_ms(f, 3) for _ in range(3))
+    out["mfma_six_tflops_random_operands"] = cus * 2 * 4 * 4096 * 4 * 65536.0 / (ms * 1e-3) / 1e12
     # the matrix pipe beside vector work: two wavefronts per SIMD, n independent fp32 instructions behind every MFMA
     # (the tiled MXINT kernel has 2.7 per MFMA, int_main_kernel 10: 8 of them the per-group conversion and scaling, 1.5 the
     # nibbles' expansion)
@@ -203,22 +213,33 @@ def measure_peaks():
     return out
 
 
-def roofline(bound, kernel, work, ms_kernel, ms_step, work_step, peaks, traffic=None):
-    """One roofline object: `work` algorithmic bytes (hbm) or flops (mfma) of the kernel per launch."""
+def takes_six(layer, M):
+    """Whether a call's main product runs on fp6 operands (tiled path, a layer that holds them; at the sizes timed here)."""
+    from paper_2402_02446_amd import binding
+    return binding.lqer_linear_path(layer, M) == 2 and layer.fp6_bytes() > 0
+
+
+def mfma_peak(six):
+    return MFMA_SIX_PEAK_TFLOPS if six else MFMA_BF16_PEAK_TFLOPS
+
+
+def roofline(bound, kernel, work, ms_kernel, ms_step, work_step, peaks, traffic=None, six=False):
+    """One roofline object: `work` algorithmic bytes (hbm) or flops (mfma) of the kernel per launch.  six: priced against
+    the fp6 matrix instructions the kernel issues, two for a product of codes, instead of bf16 ones."""
     if bound == "hbm":
         ach, peak, unit = work / (ms_kernel * 1e-3) / 1e9, HBM_PEAK_GBS, "GB/s"
         meas = peaks.get("hbm_read_gbs") if peaks else None
         step = work_step / (ms_step * 1e-3) / 1e9 if ms_step else None
     else:
-        ach, peak, unit = work / (ms_kernel * 1e-3) / 1e12, MFMA_BF16_PEAK_TFLOPS, "TFLOP/s"
-        meas = peaks.get("mfma_bf16_tflops") if peaks else None
+        ach, peak, unit = work / (ms_kernel * 1e-3) / 1e12, mfma_peak(six), "TFLOP/s"
+        meas = peaks.get("mfma_bf16_tflops") if peaks and not six else None
         step = work_step / (ms_step * 1e-3) / 1e12 if ms_step else None
     r = {"bound": bound, "kernel": kernel, "achieved": ach, "peak": peak, "unit": unit, "frac": ach / peak,
          "traffic": traffic}
     if meas:
         r["peak_measured"] = meas
         r["frac_measured"] = ach / meas
-    rnd = peaks.get("mfma_bf16_tflops_random_operands") if (peaks and bound != "hbm") else None
+    rnd = peaks.get("mfma_six_tflops_random_operands" if six else "mfma_bf16_tflops_random_operands") if (peaks and bound != "hbm") else None
     if rnd:
         # the MFMA loop alone on operands whose bits toggle like real data (the chip then clocks lower)
         r["peak_measured_random_operands"] = rnd
@@ -299,9 +320,11 @@ def run_case(name, K, N, k, Ms, steps, warmup, rng, ring_bytes, gain, peaks):
             res["roofline"] = roofline("hbm", "stream_kernel", bytes_main_kernel(M, K, N, kp), ms_main, ms_step,
                                        bytes_forward(M, K, N, kp), peaks)
         else:
-            res["roofline"] = roofline("mfma", "tiled_kernel", fl, ms_main, ms_step, fl, peaks)
+            six = takes_six(layers[0], M)
+            res["operands"] = "fp6 pairs, exact" if six else "bf16, exact"
+            res["roofline"] = roofline("mfma", "tiled_kernel", fl, ms_main, ms_step, fl, peaks, six=six)
             if M >= 2048:
-                res["roofline_prep_kernel"] = roofline("hbm", "prep_kernel", bytes_prep_kernel(M, K, kp), ms_prep, None, None, peaks)
+                res["roofline_prep_kernel"] = roofline("hbm", "prep_kernel", bytes_prep_kernel(M, K, kp, six), ms_prep, None, None, peaks)
         results.append(res)
         if ctx0 is None:
             # leave the result of layer 0 in Y for the oracle leg
@@ -369,10 +392,11 @@ def run_cfg5(steps, rng, peaks):
             torch.cuda.synchronize()
             ms, ms_prep, ms_main = med(f, steps), med(f_prep, steps), med(f_main, steps)
             fl = flops_forward(M, K, N, layer.kp)
+            six = takes_six(layer, M)
             per_shape.append({"K": K, "N": N, "linears": names, "ms_per_linear": ms, "ms_prep_kernel": ms_prep,
                               "ms_main_kernel": ms_main, "tflops": fl / (ms * 1e-3) / 1e12,
-                              "roofline": roofline("mfma", "tiled_kernel", fl, ms_main, ms, fl, peaks),
-                              "roofline_prep_kernel": roofline("hbm", "prep_kernel", bytes_prep_kernel(M, K, layer.kp),
+                              "roofline": roofline("mfma", "tiled_kernel", fl, ms_main, ms, fl, peaks, six=six),
+                              "roofline_prep_kernel": roofline("hbm", "prep_kernel", bytes_prep_kernel(M, K, layer.kp, six),
                                                                ms_prep, None, None, peaks)})
             total_ms += ms * len(names)
             total_fl += fl * len(names)
@@ -399,10 +423,10 @@ def run_cfg5(steps, rng, peaks):
         tf = total_fl / (total_ms * 1e-3) / 1e12
         tf_sh = total_fl / ((total_ms - saved_ms) * 1e-3) / 1e12
         out.append({"workload": "cfg5: LLaMA-7B decoder block, 7 LQER linears, M=%d" % M, "k": k,
-                    "ms_per_block": total_ms, "tflops": tf, "frac_of_mfma_peak": tf / MFMA_BF16_PEAK_TFLOPS,
+                    "ms_per_block": total_ms, "tflops": tf, "frac_of_mfma_peak": tf / mfma_peak(six),
                     "per_shape": per_shape, "shared_activations": shared,
                     "ms_per_block_shared": total_ms - saved_ms, "tflops_shared": tf_sh,
-                    "frac_of_mfma_peak_shared": tf_sh / MFMA_BF16_PEAK_TFLOPS})
+                    "frac_of_mfma_peak_shared": tf_sh / mfma_peak(six)})
     return out
 
 
@@ -411,7 +435,8 @@ def run_crossover(rng, peaks, steps=10):
     being bound by the weight stream (Sec. 2.1: memory-bound few-token regime against compute-bound
     prefill).  One layer (132 MB of weights, so successive steps may find part of it in the 256 MB
     last-level cache: this sweep compares M against M, it is not a bandwidth claim).  Each point gives the
-    whole step against the roofline that binds at that M: max(bytes / 8 TB/s, flops / 2.5 PFLOP/s)."""
+    whole step against the roofline that binds at that M: max(bytes / 8 TB/s, flops / the peak of the matrix
+    instructions it runs on)."""
     import torch
     from paper_2402_02446_amd import binding, synth
     K, N, k = 8192, 28672, 64
@@ -428,7 +453,7 @@ def run_crossover(rng, peaks, steps=10):
         ms = _graph_ms(f, steps)
         ms_main = _graph_ms(f_main, steps)
         fl, by = flops_forward(M, K, N, layer.kp), bytes_forward(M, K, N, layer.kp)
-        t_hbm, t_mfma = by / (HBM_PEAK_GBS * 1e9) * 1e3, fl / (MFMA_BF16_PEAK_TFLOPS * 1e12) * 1e3
+        t_hbm, t_mfma = by / (HBM_PEAK_GBS * 1e9) * 1e3, fl / (mfma_peak(takes_six(layer, M)) * 1e12) * 1e3
         out.append({"M": M, "path": "streaming" if binding.lqer_linear_path(layer, M) == 1 else "tiled",
                     "ms_per_step": ms, "ms_main_kernel": ms_main, "tflops": fl / (ms * 1e-3) / 1e12, "gbs": by / (ms * 1e-3) / 1e9,
                     "bound": "hbm" if t_hbm >= t_mfma else "mfma",
@@ -801,7 +826,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": "cfg4: LLaMA-2-70B-shaped MLP layer on one GPU, W 8192x28672 MXINT4, X 4096x8192 fp32 -> MXINT8, "
                                "k=64 MXINT8 factors, prefill (largest single-GPU configuration)",
-                   "M": M, "K": K, "N": N, "k": k},
+                   "M": M, "K": K, "N": N, "k": k,
+                   "operands": "MXINT8 and MXINT4 codes as pairs of fp6 values, every product exact, fp32 sums; the correction in bf16"},
         "roofline": rf,
         "cpu_baseline": cpu,
         "measured_peaks": peaks,

@@ -7,7 +7,8 @@
 //   lqer_probe_mfma         register-resident loop of 32x32x16 bf16 MFMAs, `chains` independent accumulators
 //                           per wavefront, `waves` wavefronts per SIMD on every compute unit
 //   lqer_probe_mfma_random  the same with operands of random signs and significands
-//   lqer_probe_mfma_valu    the same loop (bf16 32x32x16 or int8 32x32x32) with a fixed number of independent fp32
+//   lqer_probe_mfma_six     block-scaled 32x32x64 MFMAs on fp6 operands of random bits
+//   lqer_probe_mfma_valu    the first loop (bf16 32x32x16 or int8 32x32x32) with a fixed number of independent fp32
 //                           vector instructions behind every MFMA: what the matrix pipe still delivers when a kernel
 //                           has that much vector work per MFMA (both kinds of instruction issue through one port)
 // All launches are asynchronous on the given stream; the caller times them with events.
@@ -75,6 +76,38 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, float* sink) {
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int c = 0; c < CHAINS; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c & 3].v, b[(c + (c >> 2)) & 3].v, acc[c], 0, 0, 0);
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < CHAINS; ++c) s += acc[c][0] + acc[c][15];
+    if (s == -1.2345f && sink != nullptr) sink[0] = s;       // keeps the arithmetic alive; not a value these sums take
+}
+
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+
+// Four independent accumulators, four operand pairs in turn, scales of one.
+__global__ __launch_bounds__(256) void mfma_six_kernel(int iters, float* sink) {
+    constexpr int CHAINS = 4;
+    f32x16 acc[CHAINS];
+#pragma unroll
+    for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+    i32x8 a[4], b[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            uint32_t x = (threadIdx.x * 8u + e) * 2654435761u + p * 40503u + blockIdx.x * 2246822519u;
+            x ^= x >> 15; x *= 2246822519u; x ^= x >> 13;
+            a[p][e] = e < 6 ? (int)x : 0;          // (six words hold 32 values)
+            b[p][e] = e < 6 ? (int)(x * 747796405u) : 0;
+        }
+    int one = 127;                                 // exponent byte of a scale of one; opaque, so that it stays in a register
+    asm volatile("" : "+v"(one));
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int c = 0; c < CHAINS; ++c) acc[c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[c], b[(c + 1) & 3], acc[c], 2, 2, 0, one, 0, one);
     }
     float s = 0.f;
 #pragma unroll
@@ -188,6 +221,13 @@ int lqer_probe_mfma_random(int workgroups, int iters, int chains, void* sink_dev
     if (chains == 4) hipLaunchKernelGGL((mfma_kernel<4, true>), dim3((unsigned)workgroups), dim3(256), 0, (hipStream_t)hip_stream, iters, (float*)sink_dev);
     else if (chains == 8) hipLaunchKernelGGL((mfma_kernel<8, true>), dim3((unsigned)workgroups), dim3(256), 0, (hipStream_t)hip_stream, iters, (float*)sink_dev);
     else return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
+}
+
+// Launches workgroups x 4 wavefronts, each doing iters x 4 block-scaled fp6 MFMAs (32 x 32 x 64, 131072 flops each).
+int lqer_probe_mfma_six(int workgroups, int iters, void* sink_dev, void* hip_stream) {
+    if (workgroups <= 0 || iters <= 0) return (int)hipErrorInvalidValue;
+    hipLaunchKernelGGL(mfma_six_kernel, dim3((unsigned)workgroups), dim3(256), 0, (hipStream_t)hip_stream, iters, (float*)sink_dev);
     return (int)hipGetLastError();
 }
 
