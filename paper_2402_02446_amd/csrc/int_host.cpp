@@ -122,7 +122,8 @@ static bool few_tokens(const Layer& L, int64_t M) {
     return few < 0.97 * general;
 }
 
-// K groups per slice of its projection: eight slices, and at most seven groups (28 KB of codes beside 32 KB of sums) each
+// K groups per slice of its projection: eight slices, and at most seven groups (a wavefront takes one, of the eight it has at least;
+// 28 KB of codes beside 28 KB of sums) each
 static int few_slice_groups(const Layer& L) {
     const int64_t G = L.K / 128, per = (G + 7) / 8;
     return (int)(per < 7 ? per : 7);

@@ -61,8 +61,10 @@ struct StreamArgs {
     int exp_bias;                  // >= 0: exponent nibbles (byte = nibble + exp_bias); -1: exponent bytes
 };
 
-// item / (kp / 4) = (item * this) >> 20 for the at most 1024 items of T (16 rows x 256 ranks, 64 x 64): this exceeds
-// 2^20 / (kp / 4) by less than 1, and 1024 * 64 < 2^20
+// item / (kp / 4) = (item * this) >> 20 for the at most 2048 items of T (32 rows x 256 ranks, 64 x 64): this exceeds
+// 2^20 / (kp / 4) by less than 1, and 2048 * 64 < 2^20
+constexpr int kMaxTItems = 2048;
+static_assert(kMaxTItems * (kMaxRank / 4) < 1 << 20, "the quotients are exact");
 static inline uint32_t stream_kp4_inv(int kp) { return kp > 0 ? ((1u << 20) + (uint32_t)(kp / 4) - 1) / (uint32_t)(kp / 4) : 0u; }
 
 // LR = log2 of the token rows per activation cell column (4, 16 or 32 rows).
@@ -269,6 +271,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     // once; ranks above 64 take up to four items a thread, 128 registers that one or two wavefronts on a SIMD have to spare.
     constexpr int TI = ((BIGK ? R * 64 : 32 * MB * 16) + NW * 64 - 1) / (NW * 64);
     constexpr int SMAX = 8;
+    static_assert((BIGK ? R * 64 : 32 * MB * 16) <= kMaxTItems || (BIGK && MB == 2), "stream_kp4_inv's range (two blocks of tokens exist up to rank 64)");
     const int t_rows = a.M < 32 * MB ? (int)a.M : 32 * MB;
     const int kp4 = a.kp >> 2;
     const int t_items = (kh == 0) ? t_rows * kp4 : 0;

@@ -1760,6 +1760,7 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
             variant = pick.id;
             mode = pick.cut ? 4 : 1;
         }
+        // (128 x 256 in pieces exists by force only)
         if (variant == 22) return launch_tiled_t<6, 4, 2, 1, 4, 4, 2, true>(a, M, mode, cus, s);
         return launch_tiled_t<6, 4, 2, 1, 8, 4, 1, true>(a, M, mode, cus, s);
     }
