@@ -238,13 +238,14 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
         const uint8_t* alane = a.At + lane * 16;
         const int units = (int)(tile_end - tile_begin) * 4;
         // fp6 images: this lane's row in one, the image of a unit, the byte of its block's exponent
-        const int six_row = (int)((row_ok ? row : a.M - 1) & (kX6Rows - 1));
-        const int64_t six_rt = (row_ok ? row : a.M - 1) / kX6Rows;
+        const int64_t six_rt = rowc / kX6Rows;
+        const int six_lane = (int)(rowc % kX6Rows / 32) * 64 + (q >> 1) * 32 + (int)(rowc % 32);     // row group, hh, row
+        const int six_cell = (q & 1) * 256 + six_lane;
         auto six_image = [&](int unit) {
             return reinterpret_cast<uint8_t*>(a.Xh) + ((six_rt * a.KT + tile_begin) * 4 + unit) * kX6Chunk;
         };
         auto six_exp = [&](int unit) {
-            return a.Xe6 + (six_rt * a.KT + tile_begin + (unit >> 2)) * kX6Scales + (q >> 1) * 1024 + six_row * 8 + 2 * (unit & 3) + (q & 1);
+            return a.Xe6 + (six_rt * a.KT + tile_begin + (unit >> 2)) * kX6Scales + six_lane * 8 + 2 * (unit & 3) + (q & 1);
         };
         auto load_a = [&](Frag (&af)[2], int g, int unit) {
             const int gc = g < ng ? g : 0;
@@ -263,8 +264,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
             }
             if constexpr (SRC == 2 && SIX) {
                 const uint8_t* img = six_image(unit);
-                u.x[0] = *reinterpret_cast<const u32x4*>(img + q * 2048 + six_row * 16);
-                const u32x2 w = *reinterpret_cast<const u32x2*>(img + 8192 + q * 1024 + six_row * 8);
+                u.x[0] = *reinterpret_cast<const u32x4*>(img + six_cell * 16);
+                const u32x2 w = *reinterpret_cast<const u32x2*>(img + 8192 + six_cell * 8);
                 u.x[1] = u32x4{w[0], w[1], 0u, 0u};
                 u.eb = *six_exp(unit);
             } else if constexpr (SRC == 2) {
@@ -379,8 +380,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a) {
                     }
                     const u32x6 w = codes_to_six<SRC == 1>(r, up);
                     uint8_t* img = six_image(unit);
-                    *reinterpret_cast<u32x4*>(img + q * 2048 + six_row * 16) = u32x4{w[0], w[1], w[2], w[3]};
-                    *reinterpret_cast<u32x2*>(img + 8192 + q * 1024 + six_row * 8) = u32x2{w[4], w[5]};
+                    *reinterpret_cast<u32x4*>(img + six_cell * 16) = u32x4{w[0], w[1], w[2], w[3]};
+                    *reinterpret_cast<u32x2*>(img + 8192 + six_cell * 8) = u32x2{w[4], w[5]};
                     *six_exp(unit) = (uint8_t)e6;
                 } else if (CELLS) {
                     if (a.x8) {
@@ -531,11 +532,12 @@ static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& 
 
 int prep_slices(const Layer& L, int64_t M, int path) {
     if (path != 1) {
-        // tiled path: one workgroup per 16 token rows; when that leaves compute units idle, split K
-        // as well (each slice keeps at least two tiles) and let the tiled kernel add the partial T
+        // tiled path: one workgroup per 16 token rows; when that leaves compute units idle, split K as well (each slice keeps
+        // at least two tiles) and let the main kernel add the partial T.  From 4081 tokens on T is final: 256 workgroups of 16
+        // wavefronts take what 512 of eight did (8192 wide, 4096 tokens: main kernel's start 6.0 -> 4.4 us a round)
         const int64_t rg = (M + 15) / 16;
         int64_t s = 1;
-        while (rg * s < 512 && s < 8 && L.KT / (2 * s) >= 2) s *= 2;
+        while (rg * s < 256 && s < 8 && L.KT / (2 * s) >= 2) s *= 2;
         return (int)s;
     }
     // streaming path: at most two row groups, so K is spread over workgroups (the main kernel adds
@@ -546,12 +548,15 @@ int prep_slices(const Layer& L, int64_t M, int path) {
     return (int)s;
 }
 
-// Wavefronts of a workgroup: one per tile of the slice where the launch fills the chip anyway, otherwise one per quarter of a tile
-// in as few and as even rounds as fit.  Which quarters a wavefront adds up before the wavefronts' sums meet decides the bits of T, so
-// `filled` goes by token rows and slices alone: not by the planes of rank groups, which differ between a layer's own call and
+// Wavefronts of a workgroup: one per tile of the slice where the launch's workgroups (`wgs`: row blocks x slices) fill the chip anyway,
+// up to 16, or eight of two to a compute unit; otherwise one per quarter of a tile in as few and as even rounds as fit.  Which quarters
+// a wavefront adds up before the wavefronts' sums meet decides the bits of T, so that goes by token rows and slices alone: not by the planes of rank groups, which differ between a layer's own call and
 // one that finds its activations stored.
-static int prep_waves(int tiles, bool filled) {
-    if (filled) return tiles < kPrepRowWaves ? (tiles < 1 ? 1 : tiles) : kPrepRowWaves;
+static int prep_waves(int tiles, int64_t wgs) {
+    if (wgs >= 256) {
+        const int most = wgs >= 512 ? kPrepRowWaves : kPrepWaves;
+        return tiles < most ? (tiles < 1 ? 1 : tiles) : most;
+    }
     const int units = 4 * tiles;
     if (units <= kPrepWaves) return units < 1 ? 1 : units;
     const int rounds = (units + kPrepWaves - 1) / kPrepWaves;
@@ -597,7 +602,7 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     // the row-wise form for fp32 input in row-major layout when the launch has workgroups to spare
     a.by_tiles = !cells && !ws.six && rg * ws.S >= 2048;
     const bool rowwise = a.by_tiles && src == 0;
-    a.nwaves = prep_waves(a.tiles_per_slice, !cells && rg * ws.S >= 256);
+    a.nwaves = prep_waves(a.tiles_per_slice, cells ? 0 : rg * ws.S);
     dim3 block(64 * a.nwaves);
     // clearing workgroups: about four 16-byte stores per thread
     const int64_t zero_wgs = y_zero ? (M * ((L.N + 3) / 4) + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;
@@ -653,7 +658,7 @@ hipError_t launch_prep_group(const Layer* const* layers, int n, const float* X, 
         cols4 += (L.N + 3) / 4;
     }
     a.by_tiles = false;
-    a.nwaves = prep_waves(a.tiles_per_slice, false);
+    a.nwaves = prep_waves(a.tiles_per_slice, 0);
     const dim3 block(64 * a.nwaves);
     const int64_t rg = (M + 15) / 16;
     const int64_t zero_wgs = zero_y ? (M * cols4 + 4 * block.x * rg - 1) / (4 * block.x * rg) : 0;

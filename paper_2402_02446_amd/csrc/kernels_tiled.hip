@@ -28,17 +28,8 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
-// The fp6 form (WB = 6).  Mostly (tiled_takes_six) a 4-bit layer's activations are not brought to bf16 but to fp6 operands:
-// an 8-bit code in two halves against the 4-bit code, exact as before, at half the matrix instructions' time (mfma32_six).  The chip's
-// clock under load is what bounds the bf16 form; this one moves 24 bytes of LDS per operand block instead of 32 and runs half as
-// many passes.  Bounds now: again the clock (4.0 us per K tile of a 128 x 512 tile on a full chip, 2.7 on a nearly empty one; the
-// bare MFMA loop's rate would be 3.2).  Whole calls, bf16 form -> this: 8192 x 28672 rank 64 at 4096 tokens 1463 -> 1152 us, 11008 x 4096
-// rank 32 at 2048 193 -> 157, three layers of 4096 x 4096 at 8192 738 -> 600.  Distance from the 64-bit result: 2.65e-7 -> 2.47e-7,
-// 2.35e-7 -> 2.30e-7, 2.29e-7 -> 2.20e-7; on data of wide exponents, where the bf16 chain rounds more often, 1.2e-7 -> 7.6e-8 at
-// K = 4096.  (The correction in the same chain, as the last of its sums, took 1088, 149 and 542 us, but 2.38e-7 in the second case; its
-// B_k records asked for in one go ahead of the sums: no faster, the registers it takes are spilled.)  Layers of rank 0 keep bf16
-// operands: an exponent byte of 255, a block with an infinity, is a NaN to the block-scaled instruction, where bf16 has
-// infinities; with a correction the row is NaN either way.
+// 4-bit layers mostly run on fp6 operands instead, in kernels of their own (kernels_six.hip); what is here serves 2-bit layers, layers
+// of rank 0 and those whose correction outweighs K.
 //
 // Calls that do not fill the chip for long mostly take staged_kernel (pick_small says which): tiles of 64 rows, every
 // operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
@@ -52,66 +43,24 @@
 
 #include "lqer_internal.h"
 #include "mx_device.h"
+#include "tiled_common.h"
 
 namespace lqer {
-
-struct TiledArgs {
-    const uint8_t* Wt; const uint8_t* Bt;
-    const uint16_t* Xh; int64_t ldxh;                // (fp6 form: the images)
-    const uint16_t* Xt; int64_t ldxt;                // T_hi | T_lo | 0, row by row
-    const uint8_t* Xe6;                              // fp6 form: exponent bytes of the activations' blocks
-    const float* Tpart; int S; int64_t tp_stride;    // S > 1: T as S fp32 partial sums [S][tp_stride / kp rows][kp]
-    float* Y; int64_t ldy;
-    int8_t* Yc; uint8_t* Ye; int64_t ldyc;           // Yc != null: store Y as MXINT8 (blocks of 16 along N) instead of fp32
-    int64_t M, N, KT, N32;
-    int kp, kp16;
-    int grid_m, grid_n;
-    int group_m;
-    // work split (see the head of this file)
-    int64_t dp_tiles;          // output tiles taken whole, tile i by workgroup i % gridDim.x
-    int64_t sk_units;          // K tile units of the remaining output tiles, shared out in ranges of ...
-    int64_t sk_share;          // ... this many per workgroup
-    int64_t sk_tile_units;     // units per remaining tile: KT, or KT rounded up to whole shares so that no share
-                               // crosses a tile (the units past KT are empty)
-    float* Part;               // [gridDim.x][BM * BN] accumulators handed over
-    uint32_t* flags;           // [gridDim.x], zero before the launch; 1 = slot written
-    int spin_limit;            // polls of a flag before the waiting workgroup gives up (and stores NaN)
-    int rec_bytes;             // bytes of a weight record
-    int exp_bias;              // >= 0: exponent nibbles (byte = nibble + exp_bias); -1: exponent bytes
-};
-
-// row stride of a plane of partial sums
-__host__ __device__ constexpr int64_t plane_ld(int64_t N) { return (N + 3) / 4 * 4; }
-
-// The product ends here, in front of the stores' conditions.  Left alone the compiler moves the last block-scaled MFMAs behind the
-// test of a lane's row, together with reloads of their operands, which then happen in the lanes with rows only; a matrix
-// instruction takes every lane's.
-template <int TM, int TN>
-__device__ __forceinline__ void settle(f32x16 (&acc)[TM][TN]) {
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) asm volatile("" : "+v"(acc[tm][tn]));
-}
 
 // MINW = wavefronts per SIMD the register allocation must allow (2 lets two four-wavefront workgroups share a compute unit)
 // SPLIT = the workgroup walks a list of pieces (work split); otherwise it computes output tile blockIdx.x
 // whole, as straight-line code (the loop over pieces costs the main product a few percent)
-// WB = mantissa bits of W_q: 4, or 2 (half the code bytes per record, one 32-bit word per block); 6 = 4-bit weights and 8-bit activations
-// in their fp6 form (mfma32_six)
+// WB = mantissa bits of W_q: 4, or 2 (half the code bytes per record, one 32-bit word per block)
 template <int TM, int TN, int WR, int WC, int NS, int MINW, bool SPLIT, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) {
-    static_assert(WB == 4 || WB == 2 || WB == 6, "weight mantissas of 4 or 2 bits, or the fp6 form");
-    constexpr bool SIX = WB == 6;
+    static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
     constexpr int BM = 32 * TM * WR;
     constexpr int NW = WR * WC;
-    constexpr int TSTAGE = BM * 128;               // bytes: BM rows x 64 bf16
-    constexpr int STAGE = SIX ? kX6Chunk : TSTAGE;
+    constexpr int STAGE = BM * 128;                // bytes: BM rows x 64 bf16
     constexpr int NT = 64 * NW;
     constexpr int LPT = BM * 8 / NT;               // 16-byte cells each thread moves per chunk
     // chunks between fetching activations and using them: 3 where the registers allow a second set in flight
     constexpr int XD = (TM * TN * 16 + LPT * 8 <= 144) ? 3 : 2;
-    static_assert(!SIX || (BM == kX6Rows && (NT == 512 || NT == 256)), "a tile is as high as an image, and the loader moves whole ones");
     static_assert((BM * 8) % NT == 0, "loader must divide evenly");
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
@@ -137,9 +86,9 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     static_assert(NS == 4, "stage and register-set indices below assume rings of four");
     constexpr int ROWS_PER_PASS = NT / 8;
     static_assert(ROWS_PER_PASS % 16 == 0, "swizzle must not depend on the pass");
-    int ld_row0 = tid >> 3;
+    const int ld_row0 = tid >> 3;
     // (row >> 1) & 7 is the same for every pass because ROWS_PER_PASS is a multiple of 16
-    int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4), ld_col = tid & 7;
+    const int ld_dst0 = ld_row0 * 128 + (((tid & 7) ^ ((ld_row0 >> 1) & 7)) << 4), ld_col = tid & 7;
     // ---- operand reader: in step s this lane reads logical cell 4 hh + s of its TM rows -----------
     // row = (wr TM + tm) 32 + t, so the swizzle term depends on t only
     int rd_off[4];
@@ -152,7 +101,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     const int es1 = exp4 ? 8 : 16, es0 = exp4 ? 4 : 8;
     const uint32_t emask = exp4 ? 0xFu : 0xFFu, ebias = exp4 ? (uint32_t)a.exp_bias : 0u;
     // nibbles sit in front of the codes (lane * 4), bytes behind them (lane * 8)
-    const int code_off = exp4 ? kWCompactCodeOffset : 0, exp_off = exp4 ? lane16 >> 2 : w_code_bytes(WB == 2 ? 2 : 4) + (lane16 >> 1);
+    const int code_off = exp4 ? kWCompactCodeOffset : 0, exp_off = exp4 ? lane16 >> 2 : w_code_bytes(WB) + (lane16 >> 1);
 
     int64_t dp_next = lin;                                     // next whole tile of this workgroup
     int64_t u = a.sk_share * lin;                              // its range of the shared K tiles
@@ -296,7 +245,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     auto store_x = [&](const u32x4 (&st)[LPT], int stage) {
 #pragma unroll
         for (int j = 0; j < LPT; ++j)
-            *reinterpret_cast<u32x4*>(lds + stage * TSTAGE + ld_dst0 + j * ROWS_PER_PASS * 128) = st[j];
+            *reinterpret_cast<u32x4*>(lds + stage * STAGE + ld_dst0 + j * ROWS_PER_PASS * 128) = st[j];
     };
     // one 64-wide chunk of the main product: c = chunk index within its K tile = stage = register set.
     // The activation operands are read one MFMA step ahead: `xa` holds step 0 on entry and step 0
@@ -334,157 +283,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
         }
     };
 
-    if constexpr (SIX) {
-        // ---- main product on fp6 operands.  The same rings as below, a chunk being two MFMA steps of 32 of K (64 in fp6): an image of
-        // the activations is what LDS holds of it, cell for cell, so that operands are read without conflicts, and the exponent bytes of
-        // a K tile wait in LDS too (two of them, in turn).  An operand is read into the registers of the one just used, one step ahead.
-        constexpr int NP = 8192 / 16 / NT;             // 16-byte cells of an image's first part per thread (the second: as many of 8)
-        struct XSet { u32x4 p[NP]; u32x2 h[NP]; };
-        struct SSet { uint32_t w[NP]; };
-        constexpr uint32_t kAnySize = 0x7FFFFFFFu;     // (every offset used lies in the run the base points to)
-        // Addresses: a scalar one plus one lane offset of 32 bits for each kind of load, one lane offset for each kind of LDS access;
-        // the rest are constants.  (Opaque: left to itself the compiler keeps sums of them in fifty registers.)
-        const int rd_row = wr * TM * 32 + t;
-        uint32_t tid4 = tid * 4, tid8 = tid * 8, tid16 = tid * 16, lane_w = lane * 16, lane_e8 = lane * 8;
-        uint32_t rd16 = hh * 4096 + rd_row * 16, rd8 = hh * 2048 + rd_row * 8, rde = hh * 1024 + rd_row * 8;
-        asm volatile("" : "+v"(tid4), "+v"(tid8), "+v"(tid16), "+v"(lane_w), "+v"(lane_e8), "+v"(rd16), "+v"(rd8), "+v"(rde));
-        const uint8_t* const img0 = reinterpret_cast<const uint8_t*>(a.Xh) + (int64_t)tile_m * a.KT * (4 * kX6Chunk);
-        const uint8_t* const exp0 = a.Xe6 + (int64_t)tile_m * a.KT * kX6Scales;
-        const uint8_t* w_base[TN];
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) w_base[tn] = a.Wt + group_of(tn) * kW6RecordBytes;
-        const int64_t w_stride = a.N32 * kW6RecordBytes;
-        uint8_t* const lds_e = lds + 4 * STAGE;
-        auto fetch = [&](XSet& x, int ch) {
-            const uint8_t* img = img0 + (int64_t)ch * kX6Chunk;
-#pragma unroll
-            for (int j = 0; j < NP; ++j) x.p[j] = buffer_load16(buffer_rsrc(img + j * NT * 16, kAnySize), tid16);
-#pragma unroll
-            for (int j = 0; j < NP; ++j) x.h[j] = buffer_load8(buffer_rsrc(img + 8192 + j * NT * 8, kAnySize), tid8);
-        };
-        auto store = [&](const XSet& x, int stage) {
-#pragma unroll
-            for (int j = 0; j < NP; ++j) *reinterpret_cast<u32x4*>(lds + tid16 + (stage * STAGE + j * NT * 16)) = x.p[j];
-#pragma unroll
-            for (int j = 0; j < NP; ++j) *reinterpret_cast<u32x2*>(lds + tid8 + (stage * STAGE + 8192 + j * NT * 8)) = x.h[j];
-        };
-        auto fetch_e = [&](SSet& x, int tile) {
-#pragma unroll
-            for (int j = 0; j < NP; ++j) x.w[j] = buffer_load4(buffer_rsrc(exp0 + (int64_t)tile * kX6Scales + j * NT * 4, kAnySize), tid4);
-        };
-        auto store_e = [&](const SSet& x, int parity) {
-#pragma unroll
-            for (int j = 0; j < NP; ++j) *reinterpret_cast<uint32_t*>(lds_e + tid4 + (parity * kX6Scales + j * NT * 4)) = x.w[j];
-        };
-        auto load_w = [&](WSet& w, int ch) {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                w.c[tn] = buffer_load16(buffer_rsrc(w_base[tn] + (int64_t)(ch >> 2) * w_stride + (ch & 3) * 1024, kAnySize), lane_w);
-        };
-        auto load_e = [&](ESet& x, int tile) {
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                x.e[tn] = buffer_load8(buffer_rsrc(w_base[tn] + (int64_t)tile * w_stride + kWExpOffset, kAnySize), lane_e8);
-        };
-        const int first_ch = kt0 * 4, last_main = kt1 * 4 - 1, last_tile = kt1 - 1;
-        u32x6 xa[TM];
-        u32x2 xe[TM];
-        auto read_op = [&](u32x6& x, int tm, int stage, int s) {
-            const u32x4 p = *reinterpret_cast<const u32x4*>(lds + rd16 + (stage * STAGE + s * 2048 + tm * 512));
-            const u32x2 h = *reinterpret_cast<const u32x2*>(lds + rd8 + (stage * STAGE + 8192 + s * 1024 + tm * 256));
-            x = u32x6{p[0], p[1], p[2], p[3], h[0], h[1]};
-        };
-        auto read_e = [&](u32x2& x, int tm, int parity) {
-            x = *reinterpret_cast<const u32x2*>(lds_e + rde + (parity * kX6Scales + tm * 256));
-        };
-        WSet w0, w1, w2, w3;
-        ESet ea, eb;
-        XSet xs0, xs1;
-        SSet se;
-        fetch(xs0, first_ch);
-        fetch_e(se, kt0);
-        load_e(ea, kt0);
-        load_w(w0, first_ch);
-        store(xs0, 0);
-        store_e(se, 0);
-        fetch(xs0, first_ch + 1);
-        load_w(w1, first_ch + 1);
-        store(xs0, 1);
-        fetch(xs0, first_ch + 2);
-        load_w(w2, first_ch + 2);
-        u32x6 wv = expand_six<0>(w0.c[0]);             // weights of the next MFMAs
-        // chunk cc of its K tile: barrier; loads of later chunks; arithmetic; the activations of chunk ch + 2 to LDS
-        auto step = [&](const WSet& cur, const WSet& next, const ESet& ecur, WSet& fill, ESet& enext, XSet& x_old, XSet& x_new, int ch, auto cc, auto pp) {
-            constexpr int C = decltype(cc)::value, P = decltype(pp)::value;   // P: which of the two exponent buffers this K tile's are in
-            // (behind this wavefront's newest LDS write are at least TM reads, of the chunk that starts here: they need not have returned)
-            if (C == 0 && P == 0 && ch == first_ch) {
-                __syncthreads();
-#pragma unroll
-                for (int tm = 0; tm < TM; ++tm) {
-                    read_op(xa[tm], tm, 0, 0);
-                    read_e(xe[tm], tm, 0);
-                }
-            } else {
-                staged_wait<63, TM>();
-            }
-            const int tile = ch >> 2, next_tile = tile + 1 < last_tile ? tile + 1 : last_tile;
-            if constexpr (XD == 3) fetch(x_new, ch + 3 < last_main ? ch + 3 : last_main);
-            if constexpr (C == 0) fetch_e(se, next_tile);
-            __builtin_amdgcn_sched_barrier(0);
-            load_w(fill, ch + 3 < last_main ? ch + 3 : last_main);
-            if constexpr (C == 1) load_e(enext, next_tile);
-            // Per MFMA a few vector instructions of the next operand's expansion, and where an activation operand is used for the last
-            // time its registers take the next step's.
-            auto half = [&](const WSet& wn, auto ss) {
-                constexpr int S = decltype(ss)::value, BYTE = (2 * C + S) & 3;
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    const u32x6 now = wv;
-                    if (tn + 1 < TN) wv = expand_six<S>(cur.c[tn + 1]);
-                    else wv = expand_six<1 - S>(S == 0 ? cur.c[0] : wn.c[0]);
-#pragma unroll
-                    for (int tm = 0; tm < TM; ++tm) {
-                        acc[tm][tn] = mfma32_six<BYTE>(now, xa[tm], acc[tm][tn], ecur.e[tn][C >> 1], xe[tm][C >> 1]);
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        if (tn == TN - 1) {
-                            if constexpr (S == 0) read_op(xa[tm], tm, C, 1);
-                            else read_op(xa[tm], tm, (C + 1) & 3, 0);
-                            if constexpr (S == 1 && C == 3) read_e(xe[tm], tm, 1 - P);
-                            __builtin_amdgcn_sched_group_barrier(0x100, S == 1 && C == 3 ? 3 : 2, 0);
-                        }
-                        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            half(next, std::integral_constant<int, 0>{});
-            store(x_old, (C + 2) & 3);
-            if constexpr (XD == 2) fetch(x_old, ch + 3 < last_main ? ch + 3 : last_main);
-            if constexpr (C == 1) store_e(se, 1 - P);
-            __builtin_amdgcn_sched_barrier(0);
-            half(next, std::integral_constant<int, 1>{});
-        };
-        constexpr std::integral_constant<int, 0> C0{};
-        constexpr std::integral_constant<int, 1> C1{};
-        constexpr std::integral_constant<int, 2> C2{};
-        constexpr std::integral_constant<int, 3> C3{};
-        // XD == 2: one set, written and fetched again in the middle of a chunk
-        XSet& ev_new = (XD == 3) ? xs1 : xs0;
-        XSet& od_old = (XD == 3) ? xs1 : xs0;
-        for (int tile = kt0; tile < kt1; tile += 2) {
-            step(w0, w1, ea, w3, eb, xs0, ev_new, tile * 4 + 0, C0, C0);
-            step(w1, w2, ea, w0, eb, od_old, xs0, tile * 4 + 1, C1, C0);
-            step(w2, w3, ea, w1, eb, xs0, ev_new, tile * 4 + 2, C2, C0);
-            step(w3, w0, ea, w2, eb, od_old, xs0, tile * 4 + 3, C3, C0);
-            if (tile + 1 < kt1) {
-                step(w0, w1, eb, w3, ea, xs0, ev_new, tile * 4 + 4, C0, C1);
-                step(w1, w2, eb, w0, ea, od_old, xs0, tile * 4 + 5, C1, C1);
-                step(w2, w3, eb, w1, ea, xs0, ev_new, tile * 4 + 6, C2, C1);
-                step(w3, w0, eb, w2, ea, od_old, xs0, tile * 4 + 7, C3, C1);
-            }
-        }
-        __syncthreads();                               // the correction's cells lie across the stages, and other threads' than these here
-    } else {
     // prologue: activations of the piece's first two chunks into stages 0 and 1, the weights of its
     // first three, and (XD == 3) the activations of the third in registers
     // (a K tile is four chunks, so a piece has at least four)
@@ -546,7 +344,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
             step(w3, eb, w2, ea, st_odd_old, st_odd_new, tile * 4 + 7, 3);
         }
     }
-    }
 
     // ---- rank-kp correction: [T_hi | T_lo | 0] against B_k ---------------------------------------
     // The correction chunks are fetched here rather than ahead from the main loop: B_k's
@@ -557,15 +354,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
     // built from them would otherwise be computed once in front of the loop over pieces and
     // occupy registers all through the main product.
     int t_e = t, hh_e = hh, lane_e = lane;
-    if constexpr (SPLIT || SIX) asm volatile("" : "+v"(t_e), "+v"(hh_e), "+v"(lane_e));
-    if constexpr (SIX) {                                      // (what only the correction needs of them, too)
-        const int tid_e = lane_e + 64 * wave;
-        ld_row0 = tid_e >> 3;
-        ld_col = tid_e & 7;
-        ld_dst0 = ld_row0 * 128 + ((ld_col ^ ((ld_row0 >> 1) & 7)) << 4);
-#pragma unroll
-        for (int s4 = 0; s4 < 4; ++s4) rd_off[s4] = (wr * TM * 32 + t_e) * 128 + (((4 * hh_e + s4) ^ ((t_e >> 1) & 7)) << 4);
-    }
+    if constexpr (SPLIT) asm volatile("" : "+v"(t_e), "+v"(hh_e), "+v"(lane_e));
     const int my_tail = owner ? tail_chunks : 0;              // the piece that stores the tile adds the correction
     // two correction chunks at a time through stages 0 and 1 (ranks up to 64 need one round, 256 four)
     for (int cc0 = 0; cc0 < my_tail; cc0 += 2) {
@@ -578,52 +367,8 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
             if (cc0 + 1 < tail_chunks) store_x(tst[1], 1);
             __syncthreads();
         }
-        if constexpr (SIX) {
-            // The two chunks' steps are summed by themselves, two MFMA tiles at a time, and added once: an fp32 chain rounds at the
-            // size its sum has reached, and the product of fp6 operands mostly is exact up to here.
-            static_assert(TM % 2 == 0, "pairs of tiles");
-#pragma unroll
-            for (int pair = 0; pair < TN * TM / 2; ++pair) {
-                const int tn = pair / (TM / 2), tm0 = pair % (TM / 2) * 2;
-                f32x16 corr[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) corr[i][r] = 0.f;
-#pragma unroll 1
-                for (int cc = cc0; cc < cc0 + 2 && cc < my_tail; ++cc) {
-                    const uint8_t* stage = lds + (cc & 1) * TSTAGE + tm0 * 4096;
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const int jb = 4 * cc + 2 * hh_e + j;
-                        const bool live = jb < nb2;
-                        const int rb = live ? (jb < a.kp16 ? jb : jb - a.kp16) : 0;
-                        const uint8_t* rec = a.Bt + (group_of(tn) * a.kp16 + rb) * kBRecordBytes;
-                        u32x4 cw = *reinterpret_cast<const u32x4*>(rec + t_e * 16);
-                        const uint32_t eb = rec[512 + t_e];
-                        if (!live) cw = u32x4{0, 0, 0, 0};
-                        Frag bf[2];
-                        int8x16_to_frags(cw, h_scale(eb), bf[0], bf[1]);
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-#pragma unroll
-                            for (int i = 0; i < 2; ++i) {
-                                Frag xt;
-                                xt.u = *reinterpret_cast<const u32x4*>(stage + rd_off[2 * j + h] + i * 4096);
-                                corr[i] = mfma32(bf[h].v, xt.v, corr[i]);
-                            }
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[tm0 + i][tn][r] += corr[i][r];
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            continue;
-        }
         for (int cc = cc0; cc < cc0 + 2 && cc < my_tail; ++cc) {
-            const uint8_t* stage = lds + (cc & 1) * TSTAGE;
+            const uint8_t* stage = lds + (cc & 1) * STAGE;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int jb = 4 * cc + 2 * hh_e + j;
@@ -656,7 +401,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
         }
     }
 
-    if constexpr (SIX) settle(acc);
     // ---- a piece that starts inside the tile hands its accumulators over ---------------------------
     // The slot is written and read with device-scope relaxed atomic accesses of 8 bytes: they pass
     // through the XCD's L2 to where every XCD sees them, so neither side needs a cache write-back or
@@ -793,21 +537,15 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void tiled_kernel(TiledArgs a) 
 // Whole calls, that loop -> this one: 4096 x 4096 at 40 tokens 16.9 -> 15.9 us, 4096 x 11008 at 128 32.7 -> 27.2,
 // 4112 x 11000 at 203 44.9 -> 38.9, 4096 x 4096 at 512 36.8 -> 31.2, rank 64 at 1024 57.4 -> 53.9; 2-bit rank 128 at 512 50.0 -> 43.5.
 // (The correction's operands are asked for in one go per two chunks: 2-bit weights with rank 256 at 64 tokens 84 -> 30 us.)
-// Its fp6 form (WB = 6, mfma32_six) has half the matrix instructions and three quarters of the LDS bytes for the activations; the
-// vector instructions, which are what a 64 x 128 tile waits for, are as many: 4112 x 11000 at 203 tokens 39.9 -> 36.0 us a call,
-// 4096 x 4096 at 2048 75.9 -> 68.4 (64 x 512 -> 64 x 256), main product of 2064 x 6592 rank 128 at 1720 tokens 74 -> 68.5.
 // Four stages of 64 K in LDS, one per chunk of a K tile: [BM rows x 64 activations, 16-byte cells XOR-swizzled][wave][TN]
 // 1 KiB of codes [wave][TN] 256 B of exponent words; chunk ch + 3 is asked for when chunk ch starts.
 template <int TM, int TN, int WR, int WC, int MINW, bool PLANES, int WB>
 __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a) {
-    static_assert(WB == 4 || WB == 2 || WB == 6, "weight mantissas of 4 or 2 bits, or the fp6 form");
-    constexpr bool SIX = WB == 6;
+    static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
     constexpr int BM = 32 * TM * WR, NW = WR * WC, NT = 64 * NW;
-    static_assert(!SIX || (BM == kX6Rows / 2 && NW % 4 == 0), "half an image's rows; loads that four wavefronts share");
-    constexpr int TB = BM * 128;                   // two chunks of T
-    constexpr int XB = SIX ? kX6Chunk / 2 + BM * 8 : TB, WOFF = XB, EOFF = XB + NW * TN * 1024, STAGE = EOFF + NW * TN * 256;
-    constexpr int XL = SIX ? 3 : TB / 1024 / NW;   // activation loads per wavefront and chunk
-    static_assert(TB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
+    constexpr int XB = BM * 128, WOFF = XB, EOFF = XB + NW * TN * 1024, STAGE = EOFF + NW * TN * 256;
+    constexpr int XL = XB / 1024 / NW;             // activation loads per wavefront and chunk
+    static_assert(XB % (1024 * NW) == 0 && NW % 2 == 0, "whole loads, and a swizzle that is the same for all of a wavefront's");
     constexpr int L = XL + 2 * TN;                 // loads per wavefront and chunk
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
@@ -847,51 +585,30 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     // lane % 8, which holds the row's cell (lane % 8) ^ ((row >> 1) & 7).  (Rows past M are workspace rows: see there.)
     // What differs between the loads of a chunk is in the lanes' offsets, so that one scalar address serves all of a kind.
     uint32_t x_off[XL], w_off[TN], e_off[TN];
-    if constexpr (SIX) {
-        // Half the rows of an image: four loads of 16-byte cells, one a block, two of 8-byte cells of two blocks each, two of the exponent
-        // words of this half of the K tile, one a lane half; wavefronts beyond bring the same bytes once more.
-        const int hb = (tile_m & 1) * 64;
-        x_off[0] = (wave & 3) * 2048 + (hb + lane) * 16;
-        x_off[1] = 8192 + (2 * (wave & 1) + (lane >> 5)) * 1024 + hb * 8 + (lane & 31) * 16;
-        x_off[2] = (wave & 1) * 1024 + (hb + lane) * 8;
-    } else {
 #pragma unroll
-        for (int j = 0; j < XL; ++j)
-            x_off[j] = (uint32_t)((8 * (NW * j + wave) + (lane >> 3)) * (int)a.ldxh * 2) +
-                       (((uint32_t)(lane & 7) ^ (uint32_t)(((wave & 1) * 4 + (lane >> 4)) & 7)) << 4);
-    }
+    for (int j = 0; j < XL; ++j)
+        x_off[j] = (uint32_t)((8 * (NW * j + wave) + (lane >> 3)) * (int)a.ldxh * 2) +
+                   (((uint32_t)(lane & 7) ^ (uint32_t)(((wave & 1) * 4 + (lane >> 4)) & 7)) << 4);
     const bool exp4 = a.exp_bias >= 0;             // wave-uniform
     const int64_t g_first = group_of(0);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
         const uint32_t rec = (uint32_t)(group_of(tn) - g_first) * (uint32_t)a.rec_bytes;
         w_off[tn] = rec + lane * 16 + (exp4 ? kWCompactCodeOffset : 0);
-        e_off[tn] = rec + (exp4 ? lane * 4 : w_code_bytes(WB == 2 ? 2 : 4) + lane * 8);
+        e_off[tn] = rec + (exp4 ? lane * 4 : w_code_bytes(WB) + lane * 8);
     }
     const int64_t tile_stride = a.N32 * a.rec_bytes;
     const uint8_t* x_ptr = reinterpret_cast<const uint8_t*>(a.Xh + m0 * a.ldxh + kt0 * kTileK);
-    const uint8_t* xe_ptr = nullptr;
-    if constexpr (SIX) {
-        const int64_t kt = (int64_t)(tile_m >> 1) * KT + kt0;
-        x_ptr = reinterpret_cast<const uint8_t*>(a.Xh) + kt * (4 * kX6Chunk);
-        xe_ptr = a.Xe6 + kt * kX6Scales;
-    }
     const uint8_t* w_ptr = a.Wt + g_first * a.rec_bytes + kt0 * tile_stride;       // record of the K tile being asked for
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds);
     const uint32_t at_x = lds0 + wave * 1024, at_w = lds0 + wave * (TN * 1024), at_e = lds0 + wave * (TN * 256);
     const uint32_t e_half = exp4 ? 0 : 4;          // exponent words: with nibbles the record's only one, with bytes the first or second four of a lane's eight
     auto issue = [&](auto cc) {                    // the next chunk of the row, number CC of its K tile -> stage CC
         constexpr int CC = decltype(cc)::value, ST = CC * STAGE;
-        if constexpr (SIX) {
-            lds_dma16<ST>(lds0 + (wave & 3) * 1024, x_off[0], x_ptr);
-            lds_dma16<ST + 4096>(lds0 + (wave & 1) * 1024, x_off[1], x_ptr);
-            lds_dma4<ST + 6144>(lds0 + (wave & 1) * 256, x_off[2], CC < 2 ? xe_ptr : xe_ptr + 4);
-        } else {
-            lds_dma16<ST>(at_x, x_off[0], x_ptr);
-        }
-        if constexpr (!SIX && XL > 1) lds_dma16<ST + NW * 1024>(at_x, x_off[1], x_ptr);
-        if constexpr (!SIX && XL > 2) lds_dma16<ST + 2 * NW * 1024>(at_x, x_off[2], x_ptr);
-        if constexpr (!SIX && XL > 3) lds_dma16<ST + 3 * NW * 1024>(at_x, x_off[3], x_ptr);
+        lds_dma16<ST>(at_x, x_off[0], x_ptr);
+        if constexpr (XL > 1) lds_dma16<ST + NW * 1024>(at_x, x_off[1], x_ptr);
+        if constexpr (XL > 2) lds_dma16<ST + 2 * NW * 1024>(at_x, x_off[2], x_ptr);
+        if constexpr (XL > 3) lds_dma16<ST + 3 * NW * 1024>(at_x, x_off[3], x_ptr);
         const uint8_t* wp = w_ptr + (WB == 2 ? CC >> 1 : CC) * 1024;
         const uint8_t* ep = CC < 2 ? w_ptr : w_ptr + e_half;
         lds_dma16<ST + WOFF>(at_w, w_off[0], wp);
@@ -900,11 +617,8 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             lds_dma16<ST + WOFF + 1024>(at_w, w_off[TN - 1], wp);
             lds_dma4<ST + EOFF + 256>(at_e, e_off[TN - 1], ep);
         }
-        x_ptr += SIX ? kX6Chunk : 128;
-        if constexpr (CC == 3) {
-            w_ptr += tile_stride;
-            if constexpr (SIX) xe_ptr += kX6Scales;
-        }
+        x_ptr += 128;
+        if constexpr (CC == 3) w_ptr += tile_stride;
     };
     static_assert(XL <= 4 && TN <= 2, "issue() spells its loads out");
 
@@ -971,54 +685,8 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
             else wv[tn] = unpack_w8_b2(w.c[tn][s4 >> 1], s4 & 1, sc[tn][s4 >> 1]);
         }
     };
-    // The fp6 form: two steps to a chunk.  Operands are read into the registers of the ones just used, a whole chunk ahead.
-    u32x6 x6[2][TM], w6[TN];
-    uint32_t xe[2][TM];                            // exponent words, of even and odd chunks
-    auto read_x6 = [&](u32x6& x, const uint8_t* stage, int tm, int s) {
-        const u32x4 p = *reinterpret_cast<const u32x4*>(stage + (2 * hh + s) * 1024 + (tm * 32 + t) * 16);
-        const u32x2 h = *reinterpret_cast<const u32x2*>(stage + 4096 + (2 * hh + s) * 512 + (tm * 32 + t) * 8);
-        x = u32x6{p[0], p[1], p[2], p[3], h[0], h[1]};
-    };
-    auto read_xe = [&](uint32_t (&e)[TM], const uint8_t* stage) {
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) e[tm] = *reinterpret_cast<const uint32_t*>(stage + 6144 + hh * 256 + (tm * 32 + t) * 4);
-    };
-    auto chunk6 = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, auto cc) {
-        constexpr int CC = decltype(cc)::value;
-        const uint8_t* const nxt = lds + (CC + 1) % 4 * STAGE;
-        read_w(wn, nxt, CC + 1);
-        read_xe(xe[(CC + 1) & 1], nxt);
-        auto step = [&](auto ss) {
-            constexpr int S = decltype(ss)::value;
-            u32x6 now[TN];
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                now[tn] = w6[tn];
-                w6[tn] = expand_six<1 - S>(S == 0 ? w.c[tn] : wn.c[tn]);
-            }
-            if (S == 0) __builtin_amdgcn_sched_group_barrier(0x100, TM + 2 * TN, 0);
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) {
-                    acc[tm][tn] = mfma32_six<(2 * CC + S) & 3>(now[tn], x6[S][tm], acc[tm][tn], w.e[tn], xe[CC & 1][tm]);
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, (14 + TM - 1) / TM, 0);
-                }
-                read_x6(x6[S][tm], nxt, tm, S);
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        step(std::integral_constant<int, 0>{});
-        step(std::integral_constant<int, 1>{});
-    };
     // Chunk CC: on entry xr holds its first AHEAD steps, wv the weights of step 0 and w its codes; on exit the same of the next chunk, in wn its codes.
     auto chunk = [&](f32x16 (&acc)[TM][TN], const WSet& w, WSet& wn, auto cc) {
-        if constexpr (SIX) {
-            chunk6(acc, w, wn, cc);
-            return;
-        }
         constexpr int CC = decltype(cc)::value;
         const uint8_t* const cur = lds + CC * STAGE;
         const uint8_t* const nxt = lds + (CC + 1) % 4 * STAGE;
@@ -1124,7 +792,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
         for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int j = 0; j < LPT; ++j)
-                *reinterpret_cast<u32x4*>(t_tiles + q * TB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
+                *reinterpret_cast<u32x4*>(t_tiles + q * XB + ld_dst0 + j * ROWS_PER_PASS * 128) = tst[q][j];
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -1139,7 +807,7 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     Frag xt[TM];
-                    read_x(xt, t_tiles + q * TB, 2 * j + h);
+                    read_x(xt, t_tiles + q * XB, 2 * j + h);
 #pragma unroll
                     for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
@@ -1154,24 +822,14 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
     staged_wait<2 * L>();
     WSet w0, w1;
     read_w(w0, lds, 0);
-    if constexpr (SIX) {
-        read_xe(xe[0], lds);
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) read_x6(x6[s][tm], lds, tm, s);
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) w6[tn] = expand_six<0>(w0.c[tn]);
-    } else {
-#pragma unroll
-        for (int s4 = 0; s4 < AHEAD; ++s4) read_x(xr[s4], lds, s4);
-        scales(w0, 0);
-        expand(w0, 0);
-    }
+    for (int s4 = 0; s4 < AHEAD; ++s4) read_x(xr[s4], lds, s4);
+    scales(w0, 0);
+    expand(w0, 0);
     // A K tile.  Chunks CC and CC + 1 have landed when CC starts, for every wavefront; its predecessor has been read by
     // everybody (the RA newest reads are of CC itself), and that stage takes chunk CC + 3: of the same K tile, or of the next
     // one unless this is the last.
-    constexpr int RA = SIX ? 2 * TM : AHEAD * TM;  // (fp6: every read of a chunk's time is of the next chunk, half of its 16-byte ones are these)
+    constexpr int RA = AHEAD * TM;
     auto tile = [&](f32x16 (&acc)[TM][TN], auto last) {
         constexpr bool LAST = decltype(last)::value;
         staged_wait<L, RA>();
@@ -1200,7 +858,6 @@ __global__ __launch_bounds__(64 * WR * WC, MINW) void staged_kernel(TiledArgs a)
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc0[tm][tn][r] += acc1[tm][tn][r];
-    if constexpr (SIX) settle(acc0);
 
     // ---- store: lane (t, hh) holds columns 8 r4 + 4 hh .. + 3 of token t for every MFMA tile ------------------------------
     if (!PLANES && a.Yc != nullptr) {              // as MXINT8: block b of a column group is registers 8 b .. + 7 of two lanes
@@ -1300,6 +957,12 @@ __global__ __launch_bounds__(256) void reduce_planes_kernel(TiledArgs a, int pla
     }
 }
 
+hipError_t launch_reduce_planes(const TiledArgs& a, int planes, hipStream_t s) {
+    const int64_t items = a.M * (plane_ld(a.N) / 4);
+    hipLaunchKernelGGL(reduce_planes_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, a, planes);
+    return hipGetLastError();
+}
+
 // Time estimates in microseconds for one tile shape, launched as one workgroup per tile or with the
 // work split described at the head of this file.
 struct TileShape { int id, bm, bn, share; double pair, single, cut; };
@@ -1311,37 +974,6 @@ static const TileShape kShapes[] = {
 constexpr double kPieceUs = 4.0;       // filling the pipeline and storing the tile, per piece
 constexpr double kSplitFixedUs = 38.0; // what a split launch was measured to take beyond this, per workgroup sharing a compute unit: the
                                        // pieces' drain and refill, not the slots' way through memory (the time is the same without them)
-
-struct Split { int64_t grid, dp_tiles, sk_units, sk_share, sk_tile_units; bool aligned; };
-
-static Split whole_tiles(int64_t tiles, int64_t KT) { return Split{tiles, tiles, 0, 1, KT, false}; }
-
-// slots = workgroups the chip holds at once.
-// aligned: where the chip holds two or more workgroups per remaining tile, every such tile is cut into the same
-// whole number of pieces, one per workgroup, instead of equal shares of all remaining K tiles: a share then never
-// crosses a tile, so no workgroup gets a second (possibly tiny) piece.  Measured on 11008 x 4096 at M = 2048
-// (128 tiles of 43 K tiles on 256 workgroups): 157 us against 172 us with equal shares.
-static Split split_tiles(int64_t tiles, int64_t KT, int64_t slots, bool aligned) {
-    Split sp;
-    sp.grid = slots;
-    sp.dp_tiles = (tiles / slots) * slots;
-    const int64_t rem = tiles - sp.dp_tiles;
-    if (rem == 0) return whole_tiles(tiles, KT);
-    const int64_t p = slots / rem;                           // pieces per remaining tile
-    if (aligned && p >= 2 && KT / p >= 2) {
-        sp.sk_share = (KT + p - 1) / p;
-        sp.sk_tile_units = sp.sk_share * p;
-        sp.sk_units = rem * sp.sk_tile_units;
-        sp.aligned = true;
-        return sp;
-    }
-    sp.aligned = false;
-    sp.sk_tile_units = KT;
-    sp.sk_units = rem * KT;
-    sp.sk_share = (sp.sk_units + slots - 1) / slots;
-    if (sp.sk_share < 2) sp.sk_share = 2;                    // a piece is worth its hand-over
-    return sp;
-}
 
 // one K tile (256 deep) of one output tile, with `share` workgroups on every compute unit
 static double unit_us(const TileShape& sh, int share, int cus) {
@@ -1403,12 +1035,6 @@ static const SmallShape kSmallShapes2[] = {
     {12, 128, 256, 2, {3.08, 5.22}, 0.38, 8.44, {1.68, 2.03}, {0.0, 0.47}, 0.192, 0.0, 0.0},
     {11, 128, 512, 1, {4.53, 0.0}, 3.2, 7.8, {0.0, 0.0}, {3.50, 1.30}, 0.205, 0.0, 0.0},
 };
-// The staged kernel's fp6 form (fitted with the fp6 shapes of tiled_kernel, below; mean error 4 to 6 %).
-static const SmallShape kSmallShapes6[] = {
-    {43, 64, 128, 2, {1.012, 1.562}, 0.16, 5.87, {0.485, 0.580}, {0.0, 0.239}, 0.186, 3.29, 0.165},
-    {41, 64, 256, 2, {1.507, 2.570}, 0.76, 6.91, {1.811, 0.501}, {0.0, 0.301}, 0.193, 3.06, 0.167},
-    {42, 64, 512, 1, {2.600, 0.0}, 2.33, 5.45, {2.568, 0.566}, {0.0, 0.0}, 0.202, 3.59, 0.158},
-};
 // The 128 x 512 shape with tiles cut in pieces, for 4 and 2 bits: us per launch, K tile of a piece, K tile and number of whole
 // rounds, piece beyond two, the correction per round.  Whole pieces per tile (460 timings, 5 %), and equal shares, whose
 // estimate is the rougher one (370 timings, 6 %): it counts only where the launch is long enough for them to pay, and has to
@@ -1451,11 +1077,10 @@ static double pieces_us(const SmallPieces& c, const Layer& L, int S, const Split
 
 // S: partial sums of T.  part_bytes: room for planes (0: whole tiles only).  only: this shape of the staged kernel, in at
 // least min_planes planes (id 0: not to be had).
-static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus, int only = 0, int min_planes = 1,
-                            bool six = false) {
+static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus, int only = 0, int min_planes = 1) {
     SmallPick best{0, 1, (int)L.KT, 0.0};
-    const SmallShape* const table = six ? kSmallShapes6 : (L.w_bits == 4 ? kSmallShapes4 : kSmallShapes2);
-    const int n_shapes = six ? 3 : 5;
+    const SmallShape* const table = L.w_bits == 4 ? kSmallShapes4 : kSmallShapes2;
+    const int n_shapes = 5;
     for (int i = 0; i < n_shapes; ++i) {
         const SmallShape& sh = table[i];
         if (only != 0 && sh.id != only) continue;
@@ -1478,96 +1103,11 @@ static SmallPick pick_small(const Layer& L, int64_t M, int S, int64_t part_bytes
     return best;
 }
 
-// ---- the fp6 form: which tile, cut along K or not -----------------------------------------------------------------------
-// Time model of the main product in us: `unit` per K tile of a full round of workgroups, `few` of a round of one workgroup on next to no
-// compute unit, `pair_few` of one with two on next to none (what lies between goes by how full it is: a full chip's clock is
-// lower); `round`, `fixed`, `out` per MB of Y as above; corr[0] per round and chunk of the correction beyond the first, corr[1] per round,
-// pair of chunks and partial sum of T, corr[2] per round and pair beyond the first.  Fitted, with kSmallShapes6, to all forms of 4705 calls of
-// 3e8 to 1e12 operations (K 64 to 12288, N 64 to 28672, 33 to 65536 tokens, ranks 8 to 256), timed on a warm chip: mean error 3 to 5 %.
-// The choice is 0.3, 0.4, 1.0 and 0.5 % from the fastest form on average for calls below 3e9, 3e10 and 1.5e11 operations and above; 3, 3, 5 and
-// 4 % at the 95th percentile, 17 % at the very worst.  The staged shapes belong to it at every size: their correction, in front and in
-// registers, costs a tenth of what it costs in tiled_kernel.  Without them above 1.5e11 operations calls took 1.07 times as long on
-// average, 1.9 at worst (whole calls: 3449 x 3872 x 5424 rank 256 368 us, now 245; 3549 x 2048 x 11008 rank 256 440, now 292).
-struct SixShape { int id, bn, resident; double unit, few, pair_few, round, fixed, out, corr[3]; };
-static const SixShape kSixShapes[] = {
-    {21, 512, 1, 3.946, 2.303, 0.0, 12.00, 1.16, 0.097, {4.580, 1.411, 2.243}},
-    {22, 256, 2, 3.969, 1.931, 3.412, 0.0, 9.46, 0.246, {5.419, 2.096, 0.385}},
-};
-// 128 x 512 with tiles cut in whole pieces, and in equal shares (a rough estimate: it has to promise 3 %)
-static const SmallPieces kSixWhole = {41.9, 4.202, 3.788, 33.46, 6.72, 12.97, 1.893};
-static const SmallPieces kSixShares = {56.3, 4.407, 4.031, 31.98, 0.0, 12.37, 2.599};
-
-struct SixPick { int id; bool cut; double us; SmallPick staged; };   // id 0: the staged kernel's shape `staged`
-
-static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int cus) {
-    const int64_t tiles = ((M + kX6Rows - 1) / kX6Rows) * ((L.N + sh.bn - 1) / sh.bn), per_round = (int64_t)cus * sh.resident;
-    const int64_t full = tiles / per_round, rest = tiles - full * per_round;
-    const double rounds = (double)(full + (rest > 0 ? 1 : 0));
-    double unit = (double)full * sh.unit;
-    if (rest > 0) {
-        const double fill = (double)(rest > cus ? rest - cus : rest) / (double)cus;
-        if (sh.resident == 1) unit += fill * sh.unit + (1.0 - fill) * sh.few;
-        else unit += rest <= cus ? sh.few : fill * sh.unit + (1.0 - fill) * sh.pair_few;
-    }
-    const int chunks = (2 * L.kp + 63) / 64, pairs = (chunks + 1) / 2;
-    return (double)L.KT * unit + rounds * sh.round + sh.fixed + sh.out * (double)M * (double)L.N * 4e-6 +
-           rounds * (sh.corr[0] * (chunks - 1) + sh.corr[1] * pairs * (double)S + sh.corr[2] * (pairs - 1));
-}
-
-// part_bytes: room for the pieces' accumulators or the planes (0: whole tiles only)
-static SixPick pick_six(const Layer& L, int64_t M, int S, int64_t part_bytes, int cus) {
-    SixPick best{-1, false, 0.0, {}};
-    for (const SixShape& sh : kSixShapes) {
-        const double us = six_us(sh, L, M, S, cus);
-        if (best.id < 0 || us < best.us) best = SixPick{sh.id, false, us, {}};
-    }
-    if (part_bytes > 0) {
-        const int64_t tiles = ((M + kX6Rows - 1) / kX6Rows) * ((L.N + 511) / 512);
-        const Split sp = split_tiles(tiles, L.KT, cus, true);
-        if (sp.sk_units > 0) {
-            const double us = pieces_us(sp.aligned ? kSixWhole : kSixShares, L, S, sp) * (sp.aligned ? 1.0 : 1.03);
-            if (us < best.us) best = SixPick{21, true, us, {}};
-        }
-    }
-    const SmallPick staged = pick_small(L, M, S, part_bytes, cus, 0, 1, true);
-    if (staged.us < best.us) best = SixPick{0, false, staged.us, staged};
-    return best;
-}
-
-// What has to be established once per kernel instance and process: the dynamic LDS limit, and how many of its
-// workgroups one compute unit really holds (the work split launches exactly as many workgroups as are resident
-// at once, because owners wait for flags that later workgroups raise).
-struct KernelSetup {
-    std::once_flag once;
-    hipError_t err = hipSuccess;
-    int resident = 0;            // workgroups per compute unit
-};
-
-template <typename Kern>
-static hipError_t prepare_kernel(Kern kern, KernelSetup& ks, int lds_bytes, int threads) {
-    std::call_once(ks.once, [&] {
-        ks.err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        if (ks.err != hipSuccess) return;
-        int n = 0;
-        ks.err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, threads, (size_t)lds_bytes);
-        ks.resident = n;
-    });
-    return ks.err;
-}
-
-template <typename Kern>
-static hipError_t launch_kernel(Kern kern, KernelSetup& ks, int lds_bytes, int64_t grid_x, int threads, const TiledArgs& a, hipStream_t s) {
-    const hipError_t e = prepare_kernel(kern, ks, lds_bytes, threads);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid_x), dim3(threads), lds_bytes, s, a);
-    return hipGetLastError();
-}
-
 // CAN_SPLIT: the shape also exists in the form that walks a list of pieces
 template <int WB, int TM, int TN, int WR, int WC, int NS, int MINW = 1, bool CAN_SPLIT = false>
 static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipStream_t s) {
     constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC;
-    constexpr int LDS_BYTES = WB == 6 ? 4 * kX6Chunk + 2 * kX6Scales : NS * BM * 128;
+    constexpr int LDS_BYTES = NS * BM * 128;
     a.grid_m = (int)((M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.group_m = 8;
@@ -1607,7 +1147,7 @@ static hipError_t launch_tiled_t(TiledArgs a, int64_t M, int mode, int cus, hipS
 template <int WB, int TM, int TN, int WR, int WC, int MINW>
 static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_t s) {
     constexpr int BM = 32 * TM * WR, BN = 32 * TN * WC, NW = WR * WC;
-    constexpr int LDS_BYTES = 4 * ((WB == 6 ? kX6Chunk / 2 + BM * 8 : BM * 128) + NW * TN * 1280);
+    constexpr int LDS_BYTES = 4 * (BM * 128 + NW * TN * 1280);
     a.grid_m = (int)((a.M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.dp_tiles = (int64_t)a.grid_m * a.grid_n;
@@ -1618,85 +1158,16 @@ static hipError_t launch_staged_t(TiledArgs a, const SmallPick& pick, hipStream_
     const hipError_t e = launch_kernel(staged_kernel<TM, TN, WR, WC, MINW, true, WB>, setup_planes, LDS_BYTES,
                                        a.dp_tiles * pick.planes, 64 * NW, a, s);
     if (e != hipSuccess) return e;
-    const int64_t items = a.M * (plane_ld(a.N) / 4);
-    hipLaunchKernelGGL(reduce_planes_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, a, pick.planes);
-    return hipGetLastError();
+    return launch_reduce_planes(a, pick.planes, s);
 }
 
 template <int WB>
 static hipError_t launch_staged(const TiledArgs& a, const SmallPick& pick, hipStream_t s) {
-    switch (WB == 6 ? pick.id - 10 : pick.id) {
+    switch (pick.id) {
         case 31: return launch_staged_t<WB, 2, 2, 1, 4, 2>(a, pick, s);      // 64 x 256, 72 KB: two workgroups per compute unit
-        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 2>(a, pick, s);      // 64 x 512, 112 KB (fp6: 41 to 43, less)
+        case 32: return launch_staged_t<WB, 2, 2, 1, 8, 2>(a, pick, s);      // 64 x 512, 112 KB
         default: return launch_staged_t<WB, 2, 1, 1, 4, 2>(a, pick, s);      // 64 x 128, 52 KB: two workgroups per compute unit
     }
-}
-
-// W_q records -> fp6 records (layouts in lqer_internal.h): a thread turns the 16 bytes of one lane and chunk.
-__global__ __launch_bounds__(256) void widen_six_kernel(const uint8_t* Wt, int rec_bytes, int exp_bias, uint8_t* W6, int64_t records) {
-    const int64_t rec = blockIdx.x;
-    if (rec >= records) return;
-    const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;
-    const uint8_t* src = Wt + rec * rec_bytes;
-    uint8_t* dst = W6 + rec * kW6RecordBytes;
-    const u32x4 w = *reinterpret_cast<const u32x4*>(src + (exp_bias >= 0 ? kWCompactCodeOffset : 0) + c * 1024 + lane * 16);
-    uint32_t out[4] = {0u, 0u, 0u, 0u}, any[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {                      // the lane's two blocks
-        any[b] = 0;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const uint32_t word = w[2 * b + (e >> 3)];
-            const int i = e & 3;
-            const uint32_t mag = (e & 4) ? (word >> (8 * i + 4)) & 7u : (word >> (8 * i)) & 7u;
-            const uint32_t sg = (e & 4) ? (word >> (8 * ((i + 1) & 3) + 3)) & 1u : (word >> (8 * i + 7)) & 1u;
-            any[b] |= mag;
-            const int bit = 6 * e + 3 * b, at = bit & 31;
-            out[bit >> 5] |= mag << at;
-            if (at > 29) out[(bit >> 5) + 1] |= mag >> (32 - at);
-            out[3] |= sg << (((6 * e + 5) & 31) - b);   // a field's sixth bit: an odd one
-        }
-    }
-    *reinterpret_cast<u32x4*>(dst + c * 1024 + lane * 16) = u32x4{out[0], out[1], out[2], out[3]};
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        uint32_t e;
-        if (exp_bias >= 0) e = ((src[lane * 4 + c] >> (4 * b)) & 15u) + (uint32_t)exp_bias;
-        else e = src[kWExpOffset + lane * 8 + 2 * c + b];
-        dst[kWExpOffset + lane * 8 + 2 * c + b] = (uint8_t)(any[b] != 0u && e >= 2u ? e - 2u : 0u);
-    }
-}
-
-hipError_t launch_widen_six(const Layer& L, hipStream_t s) {
-    const int64_t records = L.N32 * L.KT;
-    hipLaunchKernelGGL(widen_six_kernel, dim3((unsigned)records), dim3(256), 0, s, L.Wt, L.w_rec_bytes, L.w_exp_bias, L.W6, records);
-    return hipGetLastError();
-}
-
-// Where a layer's calls take fp6 operands: with at least as many K tiles as its correction has chunks of 64 columns beyond the first
-// (always up to rank 64, from K = 513 at rank 128, from 1537 at rank 256), and where the activations are more than next to nothing.
-// On 4705 calls the fp6 form the models choose takes 0.89 of the fastest bf16 form's time above 1.5e11 operations and 0.97 below
-// (never taken: 1 and 1; always: 0.89 and 0.975, 18 and 19 % slower at worst); this line is 0.4 and 0.9 % from the faster of both on
-// average, 3 % slower than bf16 at the 97th and 95th percentile, 14 % at worst.  A forest of decision trees that knows N and the
-// models' estimates as well comes to 0.2 and 0.4 %.  N has no say so that layers of one rank that share their activations share their
-// form, and one quantization.
-bool tiled_takes_six(const Layer& L, int64_t M, int variant) {
-    if (L.W6 == nullptr || L.kp == 0) return false;
-    const int shape = variant % 100, mode = variant / 100;
-    if (shape != 0) return shape == 21 || shape == 22 || (shape >= 41 && shape <= 43);
-    if (mode > 1) return false;                              // cut by force: the bf16 shapes
-    return M * L.K > 500000 && L.KT >= (2 * L.kp + 63) / 64 - 1;
-}
-
-uint8_t* six_scales(const Workspace& ws, const Layer& L) {
-    return reinterpret_cast<uint8_t*>(ws.Xh) + ws.xh_rows / kX6Rows * L.KT * (4 * kX6Chunk);
-}
-
-// images, exponent bytes and T in the room the bf16 rows have (400 and 512 bytes per row and K tile)
-void set_six_layout(Workspace& ws, const Layer& L) {
-    ws.six = true;
-    ws.ldxt = ws.ldxh - L.KT * kTileK;
-    ws.Xt = reinterpret_cast<uint16_t*>(six_scales(ws, L) + ws.xh_rows / kX6Rows * L.KT * kX6Scales);
 }
 
 __global__ void clear_flags_kernel(uint32_t* flags, int n) {
@@ -1746,24 +1217,7 @@ hipError_t launch_tiled(const Layer& L, int64_t M, const Workspace& ws, float* Y
     int mode = variant / 100;
     variant %= 100;
     if (mode < 0 || mode > 3) return hipErrorInvalidValue;
-    if (ws.six) {
-        a.Wt = L.W6; a.rec_bytes = kW6RecordBytes; a.exp_bias = -1;
-        a.Xe6 = six_scales(ws, L);
-        const int64_t part_bytes = (mode != 1 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
-        if (variant >= 41) {                                 // the staged kernel's shapes by force, as below
-            const SmallPick pick = mode == 3 ? SmallPick{} : pick_small(L, M, ws.S, part_bytes, cus, variant, mode == 2 ? 2 : 1, true);
-            return pick.id == 0 ? hipErrorInvalidValue : launch_staged<6>(a, pick, s);
-        }
-        if (variant == 0) {
-            const SixPick pick = pick_six(L, M, ws.S, part_bytes, cus);
-            if (pick.id == 0) return launch_staged<6>(a, pick.staged, s);
-            variant = pick.id;
-            mode = pick.cut ? 4 : 1;
-        }
-        // (128 x 256 in pieces exists by force only)
-        if (variant == 22) return launch_tiled_t<6, 4, 2, 1, 4, 4, 2, true>(a, M, mode, cus, s);
-        return launch_tiled_t<6, 4, 2, 1, 8, 4, 1, true>(a, M, mode, cus, s);
-    }
+    if (ws.six) return launch_six(a, L, ws, mode, variant, cus, s);
     if (variant >= 31 && variant <= 33) {
         // a shape of the staged kernel by force: 0 = planes when the estimate says so, 1 = whole tiles, 2 = planes
         if (mode == 3) return hipErrorInvalidValue;

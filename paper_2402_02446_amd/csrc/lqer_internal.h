@@ -59,7 +59,7 @@ namespace lqer {
 // MFMA step s of a chunk uses elements 8 (s % 2) .. + 7 of block s / 2: extractions x = 2 (s % 2) and x + 1.
 
 //
-// fp6 record (4-bit layers; tiled_kernel's form on fp6 matrix instructions): [32 columns] x [256 K], 4608 B, ordered as the W_q
+// fp6 record (4-bit layers; kernels_six.hip): [32 columns] x [256 K], 4608 B, ordered as the W_q
 // records, lane (i, hh) owning the same blocks a = 4c + 2hh and b = a + 1 of chunk c:
 //   codes[4 chunks][64 lanes][16 B]  three words of magnitudes, 96 bits: |a_i| at bits 6 i .. + 2, |b_i| at bits 6 i + 3 .. + 5; a word of
 //                                    signs: those of a at the bits that, of the three words, are the sixth ones of a field (odd bits:
@@ -68,9 +68,10 @@ namespace lqer {
 // so that each word of an operand [2 w | w] is one shift and two mask operations.  A second copy of the weights, because the
 // streaming kernel's bytes of fp8 cannot be turned into fields of six bits at that price.
 //
-// Activations for that kernel: [row / 128][K / 64] images of 12288 B, [4 blocks][128 rows][16 B] and [4 blocks][128 rows][8 B], the six
-// words of a block's operand [8 h | l]; behind all of them exponent bytes [row / 128][K tile][hh][128 rows][8 B], byte 2c + j of block
-// 4c + 2hh + j; behind these T_hi | T_lo | 0 row by row.
+// Activations for that kernel: [row / 128][K / 64] images of 12288 B, the six words of a block's operand [8 h | l] as cells of 16 B
+// [2 MFMA steps s][4 row groups][hh][32 rows] (block 2 hh + s), and cells of 8 B in the same order, so that an operand of the MFMA is 64 cells
+// in a row; behind all of them exponent bytes [row / 128][K tile][4 row groups][hh][32 rows][8 B], byte 2c + s; behind these
+// T_hi | T_lo | 0 row by row.
 
 constexpr int kW6RecordBytes = 4608;
 constexpr int kX6Rows = 128, kX6Chunk = 12288, kX6Scales = 2048;     // rows of an image, its bytes, exponent bytes per K tile
