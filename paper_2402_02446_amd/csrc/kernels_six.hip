@@ -1,6 +1,6 @@
-// Stage 2, large M, on fp6 operands: the form of the main product (Eq. 3 / Eq. 6) that 4-bit layers with a correction mostly take
+// Stage 2, large M, on fp6 operands: the form of the main product (Eq. 3 / Eq. 6) that layers with a correction mostly take
 // (tiled_takes_six).  An 8-bit activation code in two halves against the 4-bit code, exact, two products on the block-scaled fp6
-// MFMA (mfma32_six) for one of codes.
+// MFMA (mfma32_six) for one of codes; 2-bit codes as fp4 (mfma32_four), from their records as they are.
 //
 // Workgroup tile 32 TM rows x 32 TN NW columns, NW wavefronts side by side, each all the rows of 32 TN columns: TM x TN tiles of the
 // 32x32x64 MFMA.  The contraction axis is walked in chunks of 64, two MFMA steps: lane (i = lane % 32, hh = lane / 32) owns block 2 hh + s
@@ -15,6 +15,8 @@
 //
 // Work split: whole tiles; K planes, whose partial sums reduce_planes_kernel adds; or pieces handed from one workgroup to another as
 // in tiled_kernel (kernels_tiled.hip says how).
+#include <type_traits>
+
 #include "lqer_internal.h"
 #include "mx_device.h"
 #include "tiled_common.h"
@@ -39,15 +41,15 @@ enum { kWhole = 0, kPlanes = 1, kPieces = 2 };
 
 // LDS of a workgroup: four stages of activations and weights, the exponent bytes of a K tile (activations, weights), T of 64 ranks - in the last
 // two stages' memory where two workgroups share a compute unit (their correction comes first).
-template <int TM, int TN, int NW>
+template <int TM, int TN, int NW, int BITS>
 struct SixLds {
     static constexpr bool OVER = NW == 4;
     static constexpr int XB = TM * 3072, WB = NW * TN * 1024;                  // a stage
     static constexpr int SX = OVER ? XB + WB : XB, SW = OVER ? XB + WB : WB;   // from one stage to the next
     static constexpr int W_AT = OVER ? XB : 4 * XB;
-    static constexpr int XE_AT = 4 * (XB + WB), WE_AT = XE_AT + TM * 512;
-    static constexpr int T_AT = OVER ? 2 * (XB + WB) : WE_AT + NW * TN * 512;
-    static constexpr int BYTES = OVER ? WE_AT + NW * TN * 512 : T_AT + TM * 8192;
+    static constexpr int XE_AT = 4 * (XB + WB), WE_AT = XE_AT + TM * 512, WE = BITS == 4 ? 512 : 256;     // WE: exponents of a column group
+    static constexpr int T_AT = OVER ? 2 * (XB + WB) : WE_AT + NW * TN * WE;
+    static constexpr int BYTES = OVER ? WE_AT + NW * TN * WE : T_AT + TM * 8192;
     static_assert(!OVER || 2 * (XB + WB) >= TM * 8192, "T fits two stages");
     static_assert(BYTES <= (OVER ? 80 : 159) * 1024, "one workgroup per compute unit, or two");
 };
@@ -62,10 +64,13 @@ struct SixLds {
 // Whole calls, operands through registers and the correction's behind the last chunk -> this: 8192 x 28672 rank 64 at 4096 tokens
 // 1108 -> 981 us, 11008 x 4096 rank 32 at 2048 154 -> 136, three layers of 4096 x 4096 rank 32 at 8192 587 -> 534, 4112 x 11000 rank 24
 // at 203 33.5 -> 32.0.  Distance from the 64-bit result as before: 2.5e-7, 2.4e-7, 2.2e-7, 2.1e-7.
-template <int TM, int TN, int NW, int CHAINS, int MODE>
+template <int TM, int TN, int NW, int CHAINS, int MODE, int BITS>
 __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
     constexpr int BM = 32 * TM, NT = 64 * NW;
-    typedef SixLds<TM, TN, NW> Lds;
+    typedef SixLds<TM, TN, NW, BITS> Lds;
+    static_assert(BITS == 4 || BITS == 2, "fp6 records, or the 2-bit ones with exponent nibbles");
+    constexpr int REC = BITS == 4 ? kW6RecordBytes : w_record_bytes(2, true), CODES = BITS == 4 ? 0 : kWCompactCodeOffset;
+    constexpr int EG = BITS == 4 ? 2 : 4;          // column groups whose exponents a load of 1 KiB brings
     constexpr int XB = Lds::XB, WB = Lds::WB, SX = Lds::SX, SW = Lds::SW;
     constexpr int XF = XB / 1024 / NW, XR = XB / 1024 % NW;    // 1 KiB pieces of a stage: every wavefront's, and how many wavefronts take one more
     constexpr int L = XF + TN;                     // loads of a wavefront per chunk (one more in the first XR), and with a K tile's first chunk ...
@@ -85,12 +90,12 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
         lin = (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
     }
     const int KT = (int)a.KT;
-    const int64_t tile_stride = a.N32 * kW6RecordBytes;
+    const int64_t tile_stride = a.N32 * REC;
     constexpr bool XE4 = NW * 256 >= TM * 512;     // exponents of the activations: 256 B from each wavefront, or 1 KiB
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)lds);
     const uint32_t at_x = lds0 + wave * 1024, at_w = lds0 + Lds::W_AT + wave * (TN * 1024);
     const uint32_t at_xe = lds0 + Lds::XE_AT + (XE4 ? wave % (2 * TM) * 256 : (wave & 1) * 1024);
-    const uint32_t at_we = lds0 + Lds::WE_AT + (TN == 2 ? wave : wave >> 1) * 1024;
+    const uint32_t at_we = lds0 + Lds::WE_AT + wave * TN / EG * 1024;
     uint32_t rd16 = lane * 16, rdw = Lds::W_AT + wave * (TN * 1024) + lane * 16;
 
     int64_t dp_next = lin;                         // kPieces: the next whole tile of this workgroup, and its range of the shared K tiles
@@ -150,8 +155,8 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
     const uint8_t* x_ptr = reinterpret_cast<const uint8_t*>(a.Xh) + ((int64_t)img * KT + kt0) * (4 * kX6Chunk);
     const uint8_t* xe_ptr = a.Xe6 + ((int64_t)img * KT + kt0) * kX6Scales + half * 1024 + (XE4 ? wave % (2 * TM) * 256 : (wave & 1) * 1024);
     const int64_t g_first = clamped(g0);
-    const uint8_t* w_ptr = a.Wt + g_first * kW6RecordBytes + (int64_t)kt0 * tile_stride;
-    const int64_t w_second = (clamped(g0 + 1) - g_first) * kW6RecordBytes;
+    const uint8_t* w_ptr = a.Wt + g_first * REC + (int64_t)kt0 * tile_stride;
+    const int64_t w_second = (clamped(g0 + 1) - g_first) * REC;
     // piece p of a stage, in the image: all of it, or the tile's half of each of its four runs
     auto piece = [&](int p) {
         if (TM == 4) return p * 1024;
@@ -159,11 +164,11 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
     };
     x_ptr += piece(wave);
     const int x_second = piece(wave + NW) - piece(wave);
-    // exponents of two neighbouring column groups, a wavefront's own or a pair's
-    const int64_t ge = n_first + (TN == 2 ? wave * 2 : wave & ~1);
+    // exponents of EG neighbouring column groups, this wavefront's among them
+    const int64_t ge = n_first + wave * TN / EG * EG;
     const int64_t ge_first = clamped(ge);
-    const int64_t ge_rel = (ge_first - g_first) * kW6RecordBytes;
-    uint32_t we_off = (uint32_t)(clamped(ge + (lane >> 5)) - ge_first) * kW6RecordBytes + kWExpOffset + (lane & 31) * 16;
+    const int64_t ge_rel = (ge_first - g_first) * REC;
+    uint32_t we_off = (uint32_t)(clamped(ge + lane / (64 / EG)) - ge_first) * REC + (BITS == 4 ? kWExpOffset : 0) + lane % (64 / EG) * 16;
     // (Opaque, so that addresses are one scalar and one of these each: left alone, sums of them take the registers of the product.)
     asm volatile("" : "+v"(we_off), "+v"(rd16), "+v"(rdw));
     // The next chunk, number CC of its K tile -> stage CC, in three parts: a chunk's loads in one go would queue up, and the wavefronts behind them.
@@ -176,11 +181,11 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
         if constexpr (P == 1) {
             if constexpr (XF > 2) lds_dma16<CC * SX + 2 * NW * 1024>(at_x, rd16, x_ptr + 2 * NW * 1024);
             if constexpr (XR > 0) lds_dma16_below<CC * SX + XF * NW * 1024, XR>(wave, at_x, rd16, XF == 1 ? x_ptr + x_second : x_ptr);
-            lds_dma16<CC * SW>(at_w, rd16, w_ptr + CC * 1024);
+            lds_dma16<CC * SW>(at_w, rd16, w_ptr + CODES + (BITS == 4 ? CC : CC >> 1) * 1024);
             x_ptr += kX6Chunk;
         }
         if constexpr (P == 2) {
-            if constexpr (TN == 2) lds_dma16<CC * SW + 1024>(at_w, rd16, w_ptr + CC * 1024 + w_second);
+            if constexpr (TN == 2) lds_dma16<CC * SW + 1024>(at_w, rd16, w_ptr + CODES + (BITS == 4 ? CC : CC >> 1) * 1024 + w_second);
             if constexpr (CC == 0) {
                 if constexpr (XE4) lds_dma4<0>(at_xe, rd16 >> 2, xe_ptr);
                 else lds_dma16<0>(at_xe, rd16, xe_ptr);
@@ -405,17 +410,34 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
     // ---- main product ----------------------------------------------------------------------------------------------------------
     // Two MFMA steps of 32 to a chunk.  Operands are read a chunk ahead, into the registers of those just used; so is what a lane
     // has of the weights' codes, and of the exponents, in a K tile's last chunk.
-    u32x6 x[2][TM], w;
-    u32x2 xe[TM], we[TN];
-    u32x4 raw[TN];
+    typedef typename std::conditional<BITS == 4, u32x6, u32x4>::type WOp;      // a weight operand, and what it is made of
+    typedef typename std::conditional<BITS == 4, u32x4, u32x2>::type WRaw;
+    u32x6 x[2][TM];
+    WOp w;
+    u32x2 xe[TM], we[TN];                          // we: byte 2c + s of eight as in xe; BITS = 2: byte c of word s
+    WRaw raw[TN];
     auto read_x = [&](int stage, int s, int tm) {
         const u32x4 p = *reinterpret_cast<const u32x4*>(lds + rd16 + (stage * SX + (s * TM + tm) * 1024));
         const u32x2 h = *reinterpret_cast<const u32x2*>(lds + (rd16 >> 1) + (stage * SX + TM * 2048 + (s * TM + tm) * 512));
         return u32x6{p[0], p[1], p[2], p[3], h[0], h[1]};
     };
-    auto read_raw = [&](int stage, int tn) { return *reinterpret_cast<const u32x4*>(lds + rdw + (stage * SW + tn * 1024)); };
+    // (2 bits: a stage holds two chunks' codes)
+    auto read_raw = [&](int stage, int tn) { return *reinterpret_cast<const WRaw*>(lds + rdw + (stage * SW + tn * 1024 + (BITS == 4 ? 0 : (stage & 1) * 8))); };
     auto read_xe = [&](int tm) { return *reinterpret_cast<const u32x2*>(lds + Lds::XE_AT + (rd16 >> 1) + tm * 512); };
-    auto read_we = [&](int tn) { return *reinterpret_cast<const u32x2*>(lds + Lds::WE_AT + (wave * TN + tn) * 512 + (rd16 >> 1)); };
+    const uint32_t bias4 = (uint32_t)(a.exp_bias - 2) * 0x01010101u;           // BITS = 2 (see expand_four)
+    auto read_we = [&](int tn) {
+        const uint8_t* at = lds + Lds::WE_AT + (wave * TN + tn) * Lds::WE;
+        if constexpr (BITS == 4) {
+            return *reinterpret_cast<const u32x2*>(at + (rd16 >> 1));
+        } else {
+            const uint32_t v = *reinterpret_cast<const uint32_t*>(at + (rd16 >> 2));
+            return u32x2{(v & 0x0F0F0F0Fu) + bias4, ((v >> 4) & 0x0F0F0F0Fu) + bias4};
+        }
+    };
+    auto expand = [&](const WRaw& v, auto ss) {
+        if constexpr (BITS == 4) return expand_six<decltype(ss)::value>(v);
+        else return expand_four(v[decltype(ss)::value]);
+    };
     BSet b_last;                                   // CHAINS = 1: B_k for the correction, asked for in the middle of the last chunk
     // Chunk CC of its K tile.  On entry x, raw and w, the first step's and column group's weights, are its own; on exit the next chunk's.  more:
     // there is a K tile behind this one.
@@ -423,7 +445,7 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
         constexpr int CC = decltype(cc)::value;
         constexpr bool MORE = decltype(more)::value, NEXT = MORE || CC < 3;
         constexpr int NS = (CC + 1) & 3;
-        u32x4 rawn;
+        WRaw rawn;
         u32x2 wen;
         auto phase = [&](auto ss, auto nn) {
             constexpr int S = decltype(ss)::value, N = decltype(nn)::value, BYTE = (2 * CC + S) & 3;
@@ -453,13 +475,14 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
             }
             if (reads == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             else if (reads == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            const u32x6 now = w;
-            if constexpr (!LAST) w = expand_six<S>(raw[TN - 1]);
-            else if constexpr (S == 0) w = expand_six<1>(raw[0]);
-            else if constexpr (NEXT) w = expand_six<0>(TN == 2 ? raw[0] : rawn);
+            const WOp now = w;
+            if constexpr (!LAST) w = expand(raw[TN - 1], ss);
+            else if constexpr (S == 0) w = expand(raw[0], C1);
+            else if constexpr (NEXT) w = expand(TN == 2 ? raw[0] : rawn, C0);
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
-                sum[tm][N] = mfma32_six<BYTE>(now, x[S][tm], sum[tm][N], we[N][CC >> 1], xe[tm][CC >> 1]);
+                if constexpr (BITS == 4) sum[tm][N] = mfma32_six<BYTE>(now, x[S][tm], sum[tm][N], we[N][CC >> 1], xe[tm][CC >> 1]);
+                else sum[tm][N] = mfma32_four<CC, BYTE>(now, x[S][tm], sum[tm][N], we[N][S], xe[tm][CC >> 1]);
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if constexpr (NEXT && LAST) {
                     x[S][tm] = read_x(NS, S, tm);
@@ -499,7 +522,7 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
         x[1][tm] = read_x(0, 1, tm);
         xe[tm] = read_xe(tm);
     }
-    w = expand_six<0>(raw[0]);
+    w = expand(raw[0], C0);
     auto tile = [&](f32x16 (&sum)[TM][TN], auto more) {
         chunk(sum, C0, more);
         chunk(sum, C1, more);
@@ -787,10 +810,10 @@ __global__ __launch_bounds__(256) void widen_six_kernel(const uint8_t* Wt, int r
             const uint32_t mag = (e & 4) ? (word >> (8 * i + 4)) & 7u : (word >> (8 * i)) & 7u;
             const uint32_t sg = (e & 4) ? (word >> (8 * ((i + 1) & 3) + 3)) & 1u : (word >> (8 * i + 7)) & 1u;
             any[b] |= mag;
-            const int bit = 6 * e + 3 * b, at = bit & 31;
+            const int f = six_field(e), bit = 6 * f + 3 * b, at = bit & 31;
             out[bit >> 5] |= mag << at;
             if (at > 29) out[(bit >> 5) + 1] |= mag >> (32 - at);
-            out[3] |= sg << (((6 * e + 5) & 31) - b);   // a field's sixth bit: an odd one
+            out[3] |= sg << (((6 * f + 5) & 31) - b);   // a field's sixth bit: an odd one
         }
     }
     *reinterpret_cast<u32x4*>(dst + c * 1024 + lane * 16) = u32x4{out[0], out[1], out[2], out[3]};
@@ -814,11 +837,15 @@ hipError_t launch_widen_six(const Layer& L, hipStream_t s) {
 // 3600 calls whole calls in the fp6 form are 1.20 times as fast as in the fastest bf16 one on average, this line is 0.9 % from the faster of
 // both, 6 % at the 95th percentile; below 1e5 values of activations both take the same time, above 4e5 the fp6 form 0.92 of it.
 // N has no say so that layers of one rank that share their activations share their form, and one quantization.
+// 2-bit layers: where their exponents are nibbles (a K tile's eight scales are then two words of bytes, with a bias), and from four K tiles on
+// (below, a call is projection and store: both forms within 3 %).  166 random calls of 33 to 8192 tokens, ranks 64 to 256: 0.90 of the
+// bf16 form's time on average, 1.04 at worst; 4096 x 4096 rank 256 at 2048 tokens 109 -> 87 us.
 bool tiled_takes_six(const Layer& L, int64_t M, int variant) {
-    if (L.W6 == nullptr || L.kp == 0) return false;
+    if (L.kp == 0 || (L.w_bits == 4 ? L.W6 == nullptr : L.w_exp_bias < 2)) return false;
     const int shape = variant % 100, mode = variant / 100;
     if (shape != 0) return shape == 21 || shape == 22 || (shape >= 41 && shape <= 44);
     if (mode > 1) return false;                              // cut by force: the bf16 shapes
+    if (L.w_bits == 2 && L.KT < 4) return false;
     return M * L.K > 150000 && 2 * L.KT >= (2 * L.kp + 63) / 64 - 1;
 }
 
@@ -835,9 +862,9 @@ void set_six_layout(Workspace& ws, const Layer& L) {
 
 // ---- launches --------------------------------------------------------------------------------------------------------------------
 // pieces: 0 = whole tiles, 2 = cut the tiles that do not fill a round, 3 = the same in equal shares of their K tiles
-template <int TM, int TN, int NW, int CHAINS>
+template <int TM, int TN, int NW, int CHAINS, int BITS>
 static hipError_t launch_large(TiledArgs a, int pieces, bool by_force, int cus, hipStream_t s) {
-    constexpr int BM = 32 * TM, BN = 32 * TN * NW, LDS = SixLds<TM, TN, NW>::BYTES;
+    constexpr int BM = 32 * TM, BN = 32 * TN * NW, LDS = SixLds<TM, TN, NW, BITS>::BYTES;
     a.grid_m = (int)((a.M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     const int64_t tiles = (int64_t)a.grid_m * a.grid_n;
@@ -845,34 +872,46 @@ static hipError_t launch_large(TiledArgs a, int pieces, bool by_force, int cus, 
     Split sp = whole_tiles(tiles, a.KT);
     if (pieces != 0) {
         // One workgroup per compute unit, and owners wait for workgroups with higher numbers: all of them must be resident at once.
-        const hipError_t e = prepare_kernel(six_kernel<TM, TN, NW, CHAINS, kPieces>, setup_pieces, LDS, 64 * NW);
+        const hipError_t e = prepare_kernel(six_kernel<TM, TN, NW, CHAINS, kPieces, BITS>, setup_pieces, LDS, 64 * NW);
         if (e != hipSuccess) return e;
         const bool fits = a.Part != nullptr && setup_pieces.resident >= 1 && (int64_t)BM * BN * 4 <= kTiledPartBytesPerCu && cus <= kTiledFlags;
         if (fits) sp = split_tiles(tiles, a.KT, cus, pieces != 3);
         else if (by_force) return hipErrorInvalidValue;
     }
     a.dp_tiles = sp.dp_tiles; a.sk_units = sp.sk_units; a.sk_share = sp.sk_share; a.sk_tile_units = sp.sk_tile_units;
-    if (sp.sk_units > 0) return launch_kernel(six_kernel<TM, TN, NW, CHAINS, kPieces>, setup_pieces, LDS, sp.grid, 64 * NW, a, s);
-    return launch_kernel(six_kernel<TM, TN, NW, CHAINS, kWhole>, setup_whole, LDS, tiles, 64 * NW, a, s);
+    if (sp.sk_units > 0) return launch_kernel(six_kernel<TM, TN, NW, CHAINS, kPieces, BITS>, setup_pieces, LDS, sp.grid, 64 * NW, a, s);
+    return launch_kernel(six_kernel<TM, TN, NW, CHAINS, kWhole, BITS>, setup_whole, LDS, tiles, 64 * NW, a, s);
 }
 
 // whole tiles, or K planes and then their sum
-template <int TM, int TN, int NW>
+template <int TM, int TN, int NW, int BITS>
 static hipError_t launch_small(TiledArgs a, const SixPick& pick, hipStream_t s) {
-    constexpr int BM = 32 * TM, BN = 32 * TN * NW, LDS = SixLds<TM, TN, NW>::BYTES;
+    constexpr int BM = 32 * TM, BN = 32 * TN * NW, LDS = SixLds<TM, TN, NW, BITS>::BYTES;
     a.grid_m = (int)((a.M + BM - 1) / BM);
     a.grid_n = (int)((a.N + BN - 1) / BN);
     a.dp_tiles = (int64_t)a.grid_m * a.grid_n;
     a.sk_share = pick.share;
     static KernelSetup setup_whole, setup_planes;
-    if (pick.planes == 1) return launch_kernel(six_kernel<TM, TN, NW, 2, kWhole>, setup_whole, LDS, a.dp_tiles, 64 * NW, a, s);
-    const hipError_t e = launch_kernel(six_kernel<TM, TN, NW, 2, kPlanes>, setup_planes, LDS, a.dp_tiles * pick.planes, 64 * NW, a, s);
+    if (pick.planes == 1) return launch_kernel(six_kernel<TM, TN, NW, 2, kWhole, BITS>, setup_whole, LDS, a.dp_tiles, 64 * NW, a, s);
+    const hipError_t e = launch_kernel(six_kernel<TM, TN, NW, 2, kPlanes, BITS>, setup_planes, LDS, a.dp_tiles * pick.planes, 64 * NW, a, s);
     if (e != hipSuccess) return e;
     return launch_reduce_planes(a, pick.planes, s);
 }
 
+template <int BITS>
+static hipError_t launch_pick(const TiledArgs& a, const SixPick& pick, int pieces, bool by_force, int cus, hipStream_t s) {
+    switch (pick.id) {
+        case 21: return launch_large<4, 2, 8, 1, BITS>(a, pieces, by_force, cus, s);     // 128 x 512
+        case 22: return launch_large<4, 1, 8, 2, BITS>(a, pieces, by_force, cus, s);     // 128 x 256
+        case 41: return launch_small<2, 2, 4, BITS>(a, pick, s);     // 64 x 256, 61 KB: two workgroups per compute unit
+        case 42: return launch_small<2, 2, 8, BITS>(a, pick, s);     // 64 x 512, 113 KB
+        case 44: return launch_small<4, 1, 4, BITS>(a, pick, s);     // 128 x 128, 68 KB: two workgroups per compute unit
+        default: return launch_small<2, 1, 4, BITS>(a, pick, s);     // 64 x 128, 43 KB: three workgroups per compute unit
+    }
+}
+
 hipError_t launch_six(TiledArgs a, const Layer& L, const Workspace& ws, int mode, int variant, int cus, hipStream_t s) {
-    a.Wt = L.W6;
+    if (L.w_bits == 4) a.Wt = L.W6;                          // (2-bit weights: the records as they are)
     a.Xe6 = six_scales(ws, L);
     const int64_t part_bytes = (mode != 1 && ws.Part != nullptr) ? kTiledPartBytesPerCu * (int64_t)cus : 0;
     // By force: mode 0 = cut when the estimate says so, 1 = whole tiles, 2 = pieces or planes, 3 = pieces in equal shares
@@ -883,14 +922,7 @@ hipError_t launch_six(TiledArgs a, const Layer& L, const Workspace& ws, int mode
     int pieces = pick.planes == 0 ? 2 : 0;
     const bool by_force = variant != 0 && !small && mode >= 2;
     if (by_force) pieces = mode;
-    switch (pick.id) {
-        case 21: return launch_large<4, 2, 8, 1>(a, pieces, by_force, cus, s);       // 128 x 512
-        case 22: return launch_large<4, 1, 8, 2>(a, pieces, by_force, cus, s);       // 128 x 256
-        case 41: return launch_small<2, 2, 4>(a, pick, s);   // 64 x 256, 61 KB: two workgroups per compute unit
-        case 42: return launch_small<2, 2, 8>(a, pick, s);   // 64 x 512, 113 KB
-        case 44: return launch_small<4, 1, 4>(a, pick, s);   // 128 x 128, 68 KB: two workgroups per compute unit
-        default: return launch_small<2, 1, 4>(a, pick, s);   // 64 x 128, 43 KB: three workgroups per compute unit
-    }
+    return L.w_bits == 4 ? launch_pick<4>(a, pick, pieces, by_force, cus, s) : launch_pick<2>(a, pick, pieces, by_force, cus, s);
 }
 
 }  // namespace lqer

@@ -61,7 +61,7 @@ namespace lqer {
 //
 // fp6 record (4-bit layers; kernels_six.hip): [32 columns] x [256 K], 4608 B, ordered as the W_q
 // records, lane (i, hh) owning the same blocks a = 4c + 2hh and b = a + 1 of chunk c:
-//   codes[4 chunks][64 lanes][16 B]  three words of magnitudes, 96 bits: |a_i| at bits 6 i .. + 2, |b_i| at bits 6 i + 3 .. + 5; a word of
+//   codes[4 chunks][64 lanes][16 B]  three words of magnitudes, 96 bits: |a_i| at bits 6 f .. + 2, |b_i| at bits 6 f + 3 .. + 5, f = six_field(i); a word of
 //                                    signs: those of a at the bits that, of the three words, are the sixth ones of a field (odd bits:
 //                                    word 0's in order, then word 1's, word 2's), those of b one bit below
 //   exps[64 lanes][8 B]              byte 2c + j = exponent byte of block 4c + 2hh + j minus 2 (0 for an all-zero block)

@@ -121,6 +121,27 @@ __device__ __forceinline__ f32x16 mfma32_six(u32x6 a, u32x6 b, f32x16 c, uint32_
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 2, 2, BYTE, (int)sa, BYTE, (int)sb);
 }
 
+// The same with fp4 (E2M1) as the first operand: element i at bit 4 i.
+template <int BA, int BB>
+__device__ __forceinline__ f32x16 mfma32_four(u32x4 a, u32x6 b, f32x16 c, uint32_t sa, uint32_t sb) {
+    const i32x8 av = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], 0, 0, 0, 0};
+    const i32x8 bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], (int)b[4], (int)b[5], 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 2, BA, (int)sa, BB, (int)sb);
+}
+
+// Where element e of a block lies among an operand's 16 fields of each half: 0, 8, 1, 9 .. 3, 11, 4, 12 .., the order in which
+// expand_four finds 2-bit codes.
+constexpr int six_field(int e) { return (e & 3) * 2 + ((e >> 3) & 1) + ((e >> 2) & 1) * 8; }
+
+// The 2-bit codes of a block (layout in lqer_internal.h) -> the operand [w | w / 2] in fp4, where 1 is code 2 and 1/2 code 1.  Against
+// [8 h | l], whose values are h and l / 8, the sum is x w / 16; with 4 bits it is x w / 64 for weights w / 4, so both take the block's
+// exponent byte less 2 as the weights' scale.  Nine instructions for 16 codes, from the records the other kernels read.
+__device__ __forceinline__ u32x4 expand_four(uint32_t p) {
+    const uint32_t r = (p & 0x55555555u) | (__builtin_amdgcn_alignbit(p, p, 4) & 0xAAAAAAAAu);     // signs three above magnitudes
+    const uint32_t l0 = r & 0x99999999u, l1 = __builtin_amdgcn_alignbit(r, r, 2) & 0x99999999u;
+    return u32x4{l0 + (l0 & 0x11111111u), l1 + (l1 & 0x11111111u), l0, l1};
+}
+
 // Bit g of three words, g mod 6 in the set given by `six` (bits 0 to 5), as the mask of word j.
 constexpr uint32_t six_mask(uint32_t six, int j) {
     uint32_t m = 0;
@@ -146,8 +167,8 @@ __device__ __forceinline__ u32x6 expand_six(u32x4 c) {
     return r;
 }
 
-// 16 codes of a block (as floats, times `up` at most 128 in size) -> the operand [8 h | l].  (|h| <= 7 also for a code of -128, whose l
-// is then -16.)  The conversion takes its 32 values alternately from two registers' runs.
+// 16 codes of a block (as floats, times `up` at most 128 in size) -> the operand [8 h | l], its fields as six_field orders them.  (|h| <= 7 also
+// for a code of -128, whose l is then -16.)  The conversion takes its 32 values alternately from two registers' runs.
 template <bool CLAMP>
 __device__ __forceinline__ u32x6 codes_to_six(const float (&r)[16], float up) {
     const float per16 = 0.0625f * up, per8 = 0.125f * up;
@@ -157,8 +178,9 @@ __device__ __forceinline__ u32x6 codes_to_six(const float (&r)[16], float up) {
         float h = __builtin_truncf(r[i] * per16);
         if (CLAMP) h = __builtin_fmaxf(h, -7.0f);
         const float l = __builtin_fmaf(h, -2.0f, r[i] * per8);
-        if (i & 1) { odd[i >> 1] = h; odd[8 + (i >> 1)] = l; }
-        else { even[i >> 1] = h; even[8 + (i >> 1)] = l; }
+        const int f = six_field(i);
+        if (f & 1) { odd[f >> 1] = h; odd[8 + (f >> 1)] = l; }
+        else { even[f >> 1] = h; even[8 + (f >> 1)] = l; }
     }
     return __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(even, odd, 1.0f);
 }
@@ -168,7 +190,7 @@ __device__ __forceinline__ void six_to_values(u32x6 v, float scale, float (&r)[1
     typedef float f32x32 __attribute__((ext_vector_type(32)));
     const f32x32 e = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(v, 1.0f);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) r[i] = __builtin_fmaf(e[i], 16.0f, e[16 + i] * 8.0f) * scale;
+    for (int i = 0; i < 16; ++i) r[i] = __builtin_fmaf(e[six_field(i)], 16.0f, e[16 + six_field(i)] * 8.0f) * scale;
 }
 
 // Eight values of one MXINT8 block held by this lane (the other eight sit in lane ^ 32): the block's
