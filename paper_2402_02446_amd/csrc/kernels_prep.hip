@@ -480,6 +480,139 @@ __global__ __launch_bounds__(64 * (RW ? kPrepRowWaves : kPrepWaves), RW ? 4 : 1)
     prep_body<SRC, FINAL, MAXG, CELLS, RW, SIX>(a);
 }
 
+// Rank groups beyond the first four (ranks above 64) on the tiled path, large calls (launch_prep says which): T = X_q A_k from the activations the launch above has stored.
+// Bound by A_k's way from L2, 2 KiB per 64 of K and rank group: with 16 rows a workgroup, four groups at a time, that was 256 MB at rank
+// 256, 4096 wide and 2048 tokens.  Here a wavefront has 16 R rows and GRP groups, all operands of the next 64 of K in flight while it
+// multiplies these; the workgroup's eight split its K slice in turn and add up through LDS, in wavefront order, 16 rows at a time.
+constexpr int kProjectWaves = 8;
+template <bool SIX, int R, int GRP>
+__global__ __launch_bounds__(64 * kProjectWaves, 2) void project_kernel(PrepArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = lane & 15, q = lane >> 4;
+    const int slice = blockIdx.y, g0 = a.g_first + blockIdx.z * a.groups_per_wg;
+    const int ng = a.kp16 - g0 < a.groups_per_wg ? a.kp16 - g0 : a.groups_per_wg;
+    const int64_t row0 = (int64_t)blockIdx.x * (16 * R);
+    const int64_t tile_begin = (int64_t)slice * a.tiles_per_slice;
+    const int64_t tiles = a.KT - tile_begin < a.tiles_per_slice ? a.KT - tile_begin : a.tiles_per_slice;
+    const int units = tiles > 0 ? (int)tiles * 4 : 0;          // 64 of K each; a lane owns block q of a row
+
+    struct XRaw { u32x4 p; u32x4 h; uint32_t e; };             // fp6: six words and the exponent; bf16: the 16 values
+    struct Set { XRaw x[R]; Frag a[GRP][2]; };
+    // (Rows past M are workspace rows; their sums are not stored.)
+    auto load_x = [&](XRaw (&x)[R], int unit) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t row = row0 + 16 * r + t;
+            if constexpr (SIX) {
+                const int six_lane = (int)(row % kX6Rows / 32) * 64 + (q >> 1) * 32 + (int)(row % 32), six_cell = (q & 1) * 256 + six_lane;
+                const int64_t tile = row / kX6Rows * a.KT + tile_begin + (unit >> 2);
+                const uint8_t* img = reinterpret_cast<const uint8_t*>(a.Xh) + (tile * 4 + (unit & 3)) * kX6Chunk;
+                x[r].p = *reinterpret_cast<const u32x4*>(img + six_cell * 16);
+                const u32x2 w = *reinterpret_cast<const u32x2*>(img + 8192 + six_cell * 8);
+                x[r].h = u32x4{w[0], w[1], 0u, 0u};
+                x[r].e = a.Xe6[tile * kX6Scales + six_lane * 8 + 2 * (unit & 3) + (q & 1)];
+            } else {
+                const uint16_t* src = a.Xh + row * a.ldxh + (tile_begin * 16 + 4 * unit + q) * 16;
+                x[r].p = *reinterpret_cast<const u32x4*>(src);
+                x[r].h = *reinterpret_cast<const u32x4*>(src + 8);
+            }
+        }
+    };
+    auto load_a = [&](Frag (&f)[2], int g, int unit) {
+        const uint8_t* rec = a.At + ((int64_t)(g0 + (g < ng ? g : 0)) * a.KT + tile_begin + (unit >> 2)) * kARecordBytes + (unit & 3) * 2048 + lane * 16;
+        f[0].u = *reinterpret_cast<const u32x4*>(rec);
+        f[1].u = *reinterpret_cast<const u32x4*>(rec + 1024);
+    };
+    f32x4 acc[R][GRP];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int g = 0; g < GRP; ++g) acc[r][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (wave < units) {
+        XRaw x[R];
+        Frag af[GRP][2];
+        load_x(x, wave);
+#pragma unroll
+        for (int g = 0; g < GRP; ++g) load_a(af[g], g, wave);
+        for (int unit = wave; unit < units; unit += kProjectWaves) {
+            const int next = unit + kProjectWaves < units ? unit + kProjectWaves : unit;       // (the last one's once more: no branch)
+            Frag xf[R][2];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if constexpr (SIX) {
+                    float v[16];
+                    six_to_values(u32x6{x[r].p[0], x[r].p[1], x[r].p[2], x[r].p[3], x[r].h[0], x[r].h[1]}, x_scale(x[r].e, 6), v);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) xf[r][h].u[i] = pack_bf16_exact(v[8 * h + 2 * i], v[8 * h + 2 * i + 1]);
+                } else {
+                    xf[r][0].u = x[r].p;
+                    xf[r][1].u = x[r].h;
+                }
+            }
+            load_x(x, next);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < GRP; ++g) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r][g] = mfma16(af[g][h].v, xf[r][h].v, acc[r][g]);
+                load_a(af[g], g, next);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    f32x4* const red = reinterpret_cast<f32x4*>(smem);         // [wave][GRP][64]
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r > 0) __syncthreads();
+#pragma unroll
+        for (int g = 0; g < GRP; ++g) red[(wave * GRP + g) * 64 + lane] = acc[r][g];
+        __syncthreads();
+        for (int item = threadIdx.x; item < GRP * 64; item += 64 * kProjectWaves) {
+            const int l = item & 63, g = item >> 6;
+            const int64_t orow = row0 + 16 * r + (l & 15);
+            if (g >= ng || orow >= a.M) continue;
+            f32x4 s = red[item];
+#pragma unroll
+            for (int w = 1; w < kProjectWaves; ++w) s += red[w * GRP * 64 + item];
+            const int r0 = (g0 + g) * 16 + 4 * (l >> 4);
+            if (a.Tpart == nullptr) {
+                uint16_t hi[4], lo[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) split_bf16(s[j], hi[j], lo[j]);
+                uint16_t* base = a.Xt + orow * a.ldxt;
+                *reinterpret_cast<u32x2*>(base + r0) = u32x2{(uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16)};
+                *reinterpret_cast<u32x2*>(base + a.kp + r0) = u32x2{(uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16)};
+            } else {
+                *reinterpret_cast<f32x4*>(a.Tpart + ((int64_t)slice * a.tp_rows + orow) * a.kp + r0) = s;
+            }
+        }
+    }
+}
+
+template <bool SIX, int R>
+static void launch_project_t(dim3 grid, hipStream_t s, const PrepArgs& a) {
+    const dim3 block(64 * kProjectWaves);
+    if (a.groups_per_wg <= 4) hipLaunchKernelGGL((project_kernel<SIX, R, 4>), grid, block, kProjectWaves * 4 * 1024, s, a);
+    else hipLaunchKernelGGL((project_kernel<SIX, R, 6>), grid, block, kProjectWaves * 6 * 1024, s, a);
+}
+
+// Rank groups 4 and on.  64 rows a wavefront where that leaves a workgroup for every compute unit, else 32.
+static hipError_t launch_project(PrepArgs a, int S, bool six, hipStream_t s) {
+    const int rest = a.kp16 - 4, planes = (rest + 5) / 6;
+    a.g_first = 4;
+    a.groups_per_wg = (rest + planes - 1) / planes;
+    const int64_t tall = (a.M + 63) / 64;
+    const bool four = tall * S * planes >= 256;
+    const dim3 grid((unsigned)(four ? tall : (a.M + 31) / 32), (unsigned)S, (unsigned)planes);
+    if (six) four ? launch_project_t<true, 4>(grid, s, a) : launch_project_t<true, 2>(grid, s, a);
+    else four ? launch_project_t<false, 4>(grid, s, a) : launch_project_t<false, 2>(grid, s, a);
+    return hipGetLastError();
+}
+
 // Several layers applied to the same few tokens: grid.z holds the rank groups of all of them (the first plane stores the
 // activations), workgroups behind the K slices clear whichever Y a main kernel adds into.
 struct PrepLayer { const uint8_t* At; float* Tpart; float* Yz; int64_t ldy, N; int kp, kp16, z0; };
@@ -578,11 +711,17 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     // rows again; 1 us less on the 70B-shaped layer.
     int gz = 1;
     if (ws.cells && L.kp16 > 1) { gz = L.kp16; a.groups_per_wg = 1; }
-    // More than four rank groups (ranks above 64), row-major layout: this launch does the first four; the others
-    // follow in a second launch that reads the bf16 activations this one stores (half the bytes, nothing to
-    // quantize), in planes of four groups.  (An input that is already the stored matrix takes planes at once.)
-    const bool two_launches = !ws.cells && L.kp16 > 4 && !reuse_xh;
-    if (!ws.cells && L.kp16 > 4) { gz = reuse_xh ? (L.kp16 + 3) / 4 : 1; a.groups_per_wg = 4; }
+    // More than four rank groups (ranks above 64) on the tiled path: this launch does the first four, a second one the others from
+    // the activations this one stores (or an earlier one has; half the bytes, nothing to quantize): project_kernel, or this kernel in planes of
+    // four groups.  The line is where A_k's way from L2, a quarter or half of it here, outweighs what the other kernel takes longer to start
+    // and end, 2.3 us (138 random calls of ranks 128 and 256): whole calls, 4096 x 4096 rank 256 at 2048 tokens 87 -> 81 us, 0.92 of
+    // the time on average from 4096 tokens and K on; below the line up to 1.13 of it.
+    const bool two_launches = !ws.cells && L.kp16 > 4;
+    const bool project = a.tiles_per_slice >= 4 && (double)M * (double)L.K * (double)(L.kp - 64) > 1.3e9;
+    if (two_launches) {
+        a.groups_per_wg = 4;
+        if (reuse_xh && !project) gz = (L.kp16 + 3) / 4;
+    }
     a.g_first = 0;
     a.At = L.At; a.Xh = ws.Xh; a.ldxh = ws.ldxh;
     a.Xt = ws.Xt; a.ldxt = ws.ldxt;
@@ -623,10 +762,13 @@ hipError_t launch_prep(const Layer& L, const float* X, int64_t ldx, const int8_t
     if (two_launches) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        a.g_first = 4;
-        grid.z = (unsigned)((L.kp16 - 4 + 3) / 4);
-        grid.y = (unsigned)ws.S;
-        if (fin) LQER_PREP_G(2, true); else LQER_PREP_G(2, false);
+        if (project) return launch_project(a, ws.S, ws.six, s);
+        if (!reuse_xh) {
+            a.g_first = 4;
+            grid.z = (unsigned)((L.kp16 - 4 + 3) / 4);
+            grid.y = (unsigned)ws.S;
+            if (fin) LQER_PREP_G(2, true); else LQER_PREP_G(2, false);
+        }
     }
 #undef LQER_PREP_C
 #undef LQER_PREP_G

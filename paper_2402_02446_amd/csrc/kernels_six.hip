@@ -387,18 +387,23 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
         for (int r = 0; r < rounds; ++r) {
             if (r > 0) {
                 __syncthreads();                   // T has been read by everybody
-#pragma unroll
-                for (int tn = 0; tn < TN; ++tn) load_b(b_first[tn], tn, r);
-                bring_t(r);
+                if (a.S <= 2) put_t(t_first);
+                else sum_t(r);
             }
             __syncthreads();
+            BFrag bf[TN];
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-                BFrag bf;
-                expand_b(bf, b_first[tn], a.kp16 - 4 * r);
+            for (int tn = 0; tn < TN; ++tn) expand_b(bf[tn], b_first[tn], a.kp16 - 4 * r);
+            if (r + 1 < rounds) {                  // the next round's operands, beside this one's arithmetic
+                if (a.S <= 2) fetch_t(t_first, r + 1);
 #pragma unroll
-                for (int tm = 0; tm < TM; ++tm) correct(acc[0][tm][tn], bf, tm, std::integral_constant<int, 4>{});
+                for (int tn = 0; tn < TN; ++tn) load_b(b_first[tn], tn, r + 1);
+                __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm) correct(acc[0][tm][tn], bf[tn], tm, std::integral_constant<int, 4>{});
         }
     }
     if constexpr (Lds::OVER) {

@@ -33,3 +33,26 @@ def test_forward_and_codes(M, K, N, k, w_bits):
     ws.fill_(255)
     assert torch.equal(binding.lqer_linear_forward_q(h, codes, exps, Y=out(), workspace=ws), Y)
     h.free()
+
+
+# Ranks above 64 where project_kernel takes the groups beyond the fourth (M K (kp - 64) above 1.3e9, four K tiles a slice): planes of six, five
+# and four groups, the last one short; 64 and 32 rows a wavefront; T final and in slices; fp6 and (rank 0 first, so that they share) bf16 operands
+@pytest.mark.parametrize("M,K,k,w_bits,wide", [(2050, 4096, 256, 2, False), (4100, 2064, 192, 4, False), (8200, 2048, 140, 2, True), (1100, 8192, 256, 4, False)])
+def test_ranks_above_64_of_large_calls(M, K, k, w_bits, wide):
+    import torch
+    from paper_2402_02446_amd import binding
+    N = 288
+    layer, ch = oracle_layer_big(K, N, k, seed=M, w_bits=w_bits)
+    if wide:
+        layer.We[0, 0] = 90                                       # bf16 operands for a 2-bit layer
+    h = upload(layer)
+    X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
+    Xd = torch.from_numpy(X).cuda()
+    Y = binding.lqer_linear_forward(h, Xd)
+    rows, cols = np.array([0, 15, 16, 31, 32, 63, 64, M // 2, M - 1]), np.arange(0, N, 3)
+    assert_forward_matches(Y.cpu().numpy()[np.ix_(rows, cols)], X[rows], layer, cols=cols)
+    other = upload(oracle_layer_big(K, 96, 32, seed=1, w_bits=w_bits)[0])
+    for first, second in ((other, h), (h, h)):
+        assert torch.equal(binding.lqer_linear_forward_shared([first, second], Xd)[1], Y)      # from the stored activations: the same bits
+    other.free()
+    h.free()
