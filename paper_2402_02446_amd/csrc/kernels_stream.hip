@@ -75,7 +75,8 @@ static inline uint32_t stream_kp4_inv(int kp) { return kp > 0 ? ((1u << 20) + (u
 //      arrives first, so the result is the same bits on every run.
 // WB: mantissa bits of W_q, 4 or 2 (half the code bytes per record: two 1 KiB loads per record instead of four).
 // BIGK: padded ranks above 64 (up to 256): T takes 33 KB of LDS and up to four times as many registers on its way there.
-template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK>
+// SUB: K slices of a wavefront, summed apart: 2 has the bits of twice the wavefronts along K (steps alternate between them).
+template <int G, int NWC, int NWK, int DT, int LR, bool ONE, int KSP, int WB, bool BIGK, int SUB = 1>
 __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block) {
     static_assert(WB == 4 || WB == 2, "weight mantissas of 4 or 2 bits");
     constexpr int NC = (WB == 4) ? 4 : 2;            // 1 KiB loads per weight record
@@ -85,10 +86,12 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     static_assert(MB == 1 || KSP == 1, "pairs of workgroups take at most 32 tokens");
     static_assert(DT == 1 || DT == 2, "weights one or two steps ahead");
     static_assert(!ONE || DT == 1, "a single step prefetches nothing");
+    static_assert(SUB == 1 || (SUB == 2 && DT == 1 && KSP == 1 && !BIGK && 2 * G <= NWK), "two slices: the correction's jobs are the first's");
     constexpr int NW = NWC * NWK;
     constexpr int NG = NWC * G;                      // column groups of the workgroup
-    // 16 wavefronts have 128 registers each, too few to hold the partial sums of T through the main product
-    constexpr bool kTFirst = NW >= 16;
+    // 16 wavefronts have 128 registers each, too few to hold the partial sums of T through the main product; two slices' sums leave too few
+    // as well (4096 x 11008 twice, 16 tokens 23.0 against 21.0 us)
+    constexpr bool kTFirst = NW >= 16 || SUB == 2;
     constexpr int R = 1 << LR;
     constexpr int XT = NWK * R * 512;                // bytes of one stage in LDS: NWK tiles x R rows of bf16
     // With 16 token rows and more the activations travel as MXINT8 (16 code bytes per block and row,
@@ -223,13 +226,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
         return u32x2{w[0], exp4 ? w[0] >> 16 : w[1]};
     };
 
-    f32x16 acc[G][MB];
+    f32x16 accs[SUB][G][MB];
+    f32x16 (&acc)[G][MB] = accs[0];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+    for (int sub = 0; sub < SUB; ++sub)
 #pragma unroll
-        for (int b = 0; b < MB; ++b)
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[g][b][r] = 0.f;
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) accs[sub][g][b][r] = 0.f;
 
     // ---- rank-kp correction, part 1: its operands ----------------------------------------------------
     // The correction is 2 kp more "K columns" in 64-wide chunks of [T_hi | T_lo].  Lane half hh owns
@@ -351,7 +357,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
             if constexpr (kTFirst) finish_t();
         }
         // PFX: the step fetches the activations of the next one; PFW: it refills its weight set
-        auto step = [&](u32x4 (&wc_)[G][NC], u32x2 (&we_)[G], int64_t it, auto pfx, auto pfw) {
+        auto step = [&](u32x4 (&wc_)[G][NC], u32x2 (&we_)[G], int64_t it, auto pfx, auto pfw, auto sub) {
+            f32x16 (&sum)[G][MB] = accs[decltype(sub)::value];
             constexpr bool PFX = decltype(pfx)::value, PFW = decltype(pfw)::value;
             __syncthreads();         // stage it % 2 is complete; the other one is free again
             XStage st;
@@ -388,7 +395,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
                             if constexpr (WB == 4) wv = unpack_w8(wc_[g][c][s], w_scale(eb));
                             else wv = unpack_w8_b2(wc_[g][c >> 1][(c & 1) * 2 + (s >> 1)], s & 1, w2_scale(eb));
 #pragma unroll
-                            for (int b = 0; b < MB; ++b) acc[g][b] = mfma32(wv, xf[b][s].v, acc[g][b]);
+                            for (int b = 0; b < MB; ++b) sum[g][b] = mfma32(wv, xf[b][s].v, sum[g][b]);
                         }
                     }
                 }
@@ -412,27 +419,41 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
         };
         constexpr std::true_type Y_{};
         constexpr std::false_type N_{};
+        constexpr std::integral_constant<int, 0> S0{};
         if constexpr (ONE) {
-            step(wcd[0], wex[0], 0, N_, N_);
+            step(wcd[0], wex[0], 0, N_, N_, S0);
+        } else if constexpr (SUB == 2) {
+            constexpr std::integral_constant<int, 1> S1{};
+            int64_t it = 0;
+            for (; it + 2 < NI; it += 2) {
+                step(wcd[0], wex[0], it, Y_, Y_, S0);
+                step(wcd[0], wex[0], it + 1, Y_, Y_, S1);
+            }
+            if (it + 1 == NI) {
+                step(wcd[0], wex[0], it, N_, N_, S0);
+            } else {
+                step(wcd[0], wex[0], it, Y_, Y_, S0);
+                step(wcd[0], wex[0], it + 1, N_, N_, S1);
+            }
         } else if constexpr (DT == 1) {
-            for (int64_t it = 0; it + 1 < NI; ++it) step(wcd[0], wex[0], it, Y_, Y_);
-            step(wcd[0], wex[0], NI - 1, N_, N_);
+            for (int64_t it = 0; it + 1 < NI; ++it) step(wcd[0], wex[0], it, Y_, Y_, S0);
+            step(wcd[0], wex[0], NI - 1, N_, N_, S0);
         } else {
             int64_t it = 0;
             for (; it + 3 < NI; it += 2) {
-                step(wcd[0], wex[0], it, Y_, Y_);
-                step(wcd[1], wex[1], it + 1, Y_, Y_);
+                step(wcd[0], wex[0], it, Y_, Y_, S0);
+                step(wcd[1], wex[1], it + 1, Y_, Y_, S0);
             }
             // one to three steps remain; the tile of step it + j sits in set j % 2
             if (it + 1 == NI) {
-                step(wcd[0], wex[0], it, N_, N_);
+                step(wcd[0], wex[0], it, N_, N_, S0);
             } else if (it + 2 == NI) {
-                step(wcd[0], wex[0], it, Y_, N_);
-                step(wcd[1], wex[1], it + 1, N_, N_);
+                step(wcd[0], wex[0], it, Y_, N_, S0);
+                step(wcd[1], wex[1], it + 1, N_, N_, S0);
             } else {
-                step(wcd[0], wex[0], it, Y_, Y_);
-                step(wcd[1], wex[1], it + 1, Y_, N_);
-                step(wcd[0], wex[0], it + 2, N_, N_);
+                step(wcd[0], wex[0], it, Y_, Y_, S0);
+                step(wcd[1], wex[1], it + 1, Y_, N_, S0);
+                step(wcd[0], wex[0], it + 2, N_, N_, S0);
             }
         }
     }
@@ -482,14 +503,19 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
     // element (slice k, pair qv, column 4 b + j, token t): runs of 32 tokens x 4 columns, 8 floats apart so that 32 columns x
     // two tokens are in 64 different banks
     auto red_at = [&](int k, int qv, int b, int tok) { return red + ((k * NGV + qv) * 8 + b) * kRedRun + tok * 4; };
+    constexpr int NS = NWK * SUB;                    // K slices
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+    for (int sub = 0; sub < SUB; ++sub)
 #pragma unroll
-        for (int b = 0; b < MB; ++b)
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-                *reinterpret_cast<f32x4*>(red_at(wk, (wc * G + g) * MB + b, 2 * r4 + hh, t)) =
-                    f32x4{acc[g][b][4 * r4], acc[g][b][4 * r4 + 1], acc[g][b][4 * r4 + 2], acc[g][b][4 * r4 + 3]};
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const f32x16& v = accs[sub][g][b];
+                    *reinterpret_cast<f32x4*>(red_at(wk + NWK * sub, (wc * G + g) * MB + b, 2 * r4 + hh, t)) =
+                        f32x4{v[4 * r4], v[4 * r4 + 1], v[4 * r4 + 2], v[4 * r4 + 3]};
+                }
     __syncthreads();
     // As MXINT8 for the next layer (one workgroup per column block only): a unit is one block of 16
     // columns of a (group, token block) - quarters 2 b and 2 b + 1, eight values in this lane and
@@ -503,7 +529,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
             for (int h = 0; h < 2; ++h) {
                 f32x4 s4 = *reinterpret_cast<const f32x4*>(red_at(0, qv, 2 * (2 * b + h) + hh, t));
 #pragma unroll
-                for (int k = 1; k < NWK; ++k) s4 += *reinterpret_cast<const f32x4*>(red_at(k, qv, 2 * (2 * b + h) + hh, t));
+                for (int k = 1; k < NS; ++k) s4 += *reinterpret_cast<const f32x4*>(red_at(k, qv, 2 * (2 * b + h) + hh, t));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) v[4 * h + j] = s4[j];
             }
@@ -527,7 +553,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs& a, const int block
         if (row >= a.M || n >= a.N) continue;
         float v = red_at(0, qv, n32 >> 2, row & 31)[n32 & 3];
 #pragma unroll
-        for (int k = 1; k < NWK; ++k) v += red_at(k, qv, n32 >> 2, row & 31)[n32 & 3];
+        for (int k = 1; k < NS; ++k) v += red_at(k, qv, n32 >> 2, row & 31)[n32 & 3];
         float* dst = a.Y + (int64_t)row * a.ldy + n;
         if constexpr (KSP == 2) unsafeAtomicAdd(dst, v);
         else *dst = v;
@@ -557,24 +583,24 @@ struct StreamGroup {
     StreamLayer layer[kGroupLayers];
 };
 
-template <int G, int NWC, int NWK, int LR, bool ONE, int KSP>
+template <int G, int NWC, int NWK, int LR, bool ONE, int KSP, int SUB>
 __global__ __launch_bounds__(64 * NWC * NWK) void stream_group_kernel(StreamGroup g) {
     int li = 0;
     while (li + 1 < g.n && (int)blockIdx.x >= g.layer[li + 1].block0) ++li;
     const StreamLayer& L = g.layer[li];
     const StreamArgs a{L.Wt, L.Bt, g.Xcell, L.Tpart, g.S, L.Y, L.ldy, nullptr, nullptr, 0, g.M, L.N, g.KT, L.N32,
                        L.kp, L.kp16, L.kp4_inv, L.rec_bytes, L.exp_bias};
-    stream_body<G, NWC, NWK, 1, LR, ONE, KSP, 4, false>(a, (int)blockIdx.x - L.block0);
+    stream_body<G, NWC, NWK, 1, LR, ONE, KSP, 4, false, SUB>(a, (int)blockIdx.x - L.block0);
 }
 
 int stream_max_rows() { return 64; }
 int stream_cell_rows_log2(int64_t M) { return M <= 4 ? 2 : (M <= 16 ? 4 : (M <= 32 ? 5 : 6)); }
 
-template <int G, int NWC, int NWK, int LR, bool ONE, bool BIGK>
+template <int G, int NWC, int NWK, int LR, bool ONE, bool BIGK, int SUB = 1>
 constexpr int stream_lds_bytes() {
     constexpr int STAGING = (ONE ? 1 : 2) * NWK * (1 << LR) * 512;
     constexpr int MB = (LR == 6) ? 2 : 1;
-    constexpr int REDUCE = NWK * NWC * G * MB * 8 * kRedRun * 4;
+    constexpr int REDUCE = SUB * NWK * NWC * G * MB * 8 * kRedRun * 4;
     return (BIGK ? kStreamTBytesBig : kStreamTBytes) * MB + (STAGING > REDUCE ? STAGING : REDUCE);
 }
 
@@ -645,7 +671,10 @@ int stream_variant(const Layer& L, int64_t M, int variant) {
     // of up to 32 (and nothing for more tokens: the dispatcher sends those to the tiled kernel).
     const bool big = L.kp > 64;
     if (big && M > 16) return 11421;
-    if ((L.N32 + 3) / 4 >= 200) return 12241;        // wide layers
+    // Wide layers: from where two column groups a workgroup are more workgroups than compute units, of which one fills a compute unit's LDS at
+    // 5 tokens and more.  Main product, two groups and eight K slices against four and four, 512 and 600 groups: 4096 wide at 16
+    // tokens 12.0 us and 14.9, 19.8 and 15.6; 8192 wide 18.8 and 25.4, 32.0 and 26.8, at 1 token 16.0 and 22.6, 25.4 and 22.7.
+    if ((L.N32 + 1) / 2 > compute_units()) return 12241;
     const bool eight = M <= 16 && !big;
     if ((L.N32 + 1) / 2 >= 160) return eight ? 12181 : 12141;
     // narrow layers: one column group per workgroup, and a pair of workgroups per group when that
@@ -697,11 +726,11 @@ hipError_t launch_stream(const Layer& L, int64_t M, const Workspace& ws, float* 
 }
 
 // ---- groups of layers ---------------------------------------------------------------------------------------------------
-template <int G, int NWC, int NWK, int LR, bool ONE, int KSP>
+template <int G, int NWC, int NWK, int LR, bool ONE, int KSP, int SUB>
 static hipError_t launch_group_t(StreamGroup& g, hipStream_t s) {
-    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, false>();
+    constexpr int LDS_BYTES = stream_lds_bytes<G, NWC, NWK, LR, ONE, false, SUB>();
     static_assert(LDS_BYTES <= 160 * 1024, "fits");
-    auto kern = stream_group_kernel<G, NWC, NWK, LR, ONE, KSP>;
+    auto kern = stream_group_kernel<G, NWC, NWK, LR, ONE, KSP, SUB>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -717,9 +746,9 @@ static hipError_t launch_group_t(StreamGroup& g, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int G, int NWC, int NWK, int LR, int KSP>
+template <int G, int NWC, int NWK, int LR, int KSP, int SUB = 1>
 static hipError_t launch_group_one(StreamGroup& g, hipStream_t s) {
-    return g.KT <= NWK * KSP ? launch_group_t<G, NWC, NWK, LR, true, KSP>(g, s) : launch_group_t<G, NWC, NWK, LR, false, KSP>(g, s);
+    return g.KT <= NWK * KSP ? launch_group_t<G, NWC, NWK, LR, true, KSP, SUB>(g, s) : launch_group_t<G, NWC, NWK, LR, false, KSP, SUB>(g, s);
 }
 
 // the shapes the automatic choice has for up to 16 tokens, and for 17 to 32
@@ -738,6 +767,9 @@ hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, con
         if (!stream_group_takes(L, M) || stream_variant(L, M, 0) != v || L.KT != g.KT) return hipErrorInvalidValue;
         g.layer[i] = StreamLayer{L.Wt, L.Bt, Tpart[i], Y[i], ldy[i], L.N, L.N32, L.kp, L.kp16, stream_kp4_inv(L.kp), L.w_rec_bytes, L.w_exp_bias, 0};
     }
+    int64_t quads = 0;
+    for (int i = 0; i < n; ++i) quads += (layers[i]->N32 + 3) / 4;
+    const bool folded = quads <= compute_units();
     const int lr = stream_cell_rows_log2(M);
     if (lr == 5) {
         switch (v) {
@@ -751,11 +783,14 @@ hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, con
     switch (v) {
         case 12241: return lr == 2 ? launch_group_one<2, 2, 4, 2, 1>(g, s) : launch_group_one<2, 2, 4, 4, 1>(g, s);
         case 12181:
-            // One workgroup fills a compute unit's LDS at 5 to 16 tokens, and such layers have at least 160 of them each, more
-            // than a round of the chip together: two column groups share a workgroup (the same K slices and correction jobs
-            // per wavefront, hence the same bits).  16 tokens, two layers, whole call: 4096 x 11008 24.7 -> 22.8 us,
-            // 5120 x 13824 31.2 -> 28.8, 8192 x 10300 37.2 -> 30.9.  With up to 4 tokens several workgroups fit and the small
-            // ones are the faster: 20.7 against 21.7, 24.9 against 26.8.
+            // One workgroup fills a compute unit's LDS at 5 to 16 tokens, and such layers have at least 160 of them each, more than a round of
+            // the chip together: four column groups share a workgroup.  While those are one round, with four wavefronts along K that keep
+            // two slices each: all its registers are a wavefront's own then, and its loads run over four steps instead of two (the same slices
+            // and correction jobs, hence the same bits).  Two layers, whole call, 16 tokens, eight wavefronts along K -> four:
+            // 4096 x 11008 23.6 -> 21.0 us, 5120 x 13824 29.1 -> 24.7, 1024 x 10304 / 11000 12.4 -> 11.0; at 1 token, where
+            // the two groups of a wavefront were the workgroup, 20.3 -> 17.8, 25.1 -> 21.4, 12.4 -> 9.6.  Beyond a round as before:
+            // two groups with up to 4 tokens, several workgroups to a compute unit.
+            if (folded) return lr == 2 ? launch_group_one<2, 2, 4, 2, 1, 2>(g, s) : launch_group_one<2, 2, 4, 4, 1, 2>(g, s);
             return lr == 2 ? launch_group_one<2, 1, 8, 2, 1>(g, s) : launch_group_one<2, 2, 8, 4, 1>(g, s);
         case 21181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 2>(g, s) : launch_group_one<1, 1, 8, 4, 2>(g, s);
         case 11181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 1>(g, s) : launch_group_one<1, 1, 8, 4, 1>(g, s);
