@@ -319,7 +319,11 @@ __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
 //   * the sums of two 32 x 32 tiles are folded beside the MFMAs of the other two, laced instruction by instruction.
 // Whole calls at rank 32, by int_gemm_kernel's tiles -> so: 2048 tokens of 4096 x 11008 162 -> 141 us, of 11008 x 4096
 // 163 -> 149, 65536 tokens of 4096 x 4096 1849 -> 1672.  Left out one at a time, the loads cost 8 % of the time, the folding 12 %, the LDS reads 22 %,
-// three quarters of the MFMAs 24 %: what is left is the phases of a group waiting for each other.
+// three quarters of the MFMAs 24 %: what was left was the phases of a group waiting for each other, the two workgroups of a compute unit
+// in step.  So a wavefront's priority is raised while it has MFMAs to issue, the earlier half of a group above the later, and
+// falls for the wait, the reads and the folding before them: its neighbour then does these beside its MFMAs, and reads never hold up a
+// wavefront that could issue.  2048 tokens of 4096 x 11008, whole call, no priorities 150.5 us, raised for the later half 140.5, for both
+// alike 138.5, so 138.0; raised from the reads on 151.  (With X all zeros 138 -> 125: it is waiting that went, not power.)
 constexpr int kIntStages = 3, kIntStage = 128 * 128 + 4 * (2048 + 256);
 
 __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) w[q][e] = (int)(((q & 1) ? c[q >> 1][e] : c[q >> 1][e] << 4) & 0xF0F0F0F0u);
     };
-    auto group = [&](const uint8_t* st) {
+    auto group = [&](const uint8_t* st, bool more, uint32_t st_in) {   // more: the group two behind goes to the stage at st_in
         u32x4 cw[2];
         i32x4 x0[2][4], x1[2][4], w[4];
 #pragma unroll
@@ -438,9 +442,12 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) x1[i][q] = *reinterpret_cast<const i32x4*>(st + rd_x[q] + (2 + i) * 4096);
         __builtin_amdgcn_sched_barrier(0);
+        if (more) issue(st_in);                      // (behind the reads, which the group is waiting for: 1 us of 139)
+        __builtin_amdgcn_sched_barrier(0);
         fold(acc[2], pend[0], pend_sc);              // while the reads are on their way
         __builtin_amdgcn_sched_barrier(0);
         // behind every MFMA a few vector instructions: the rest of the group before, then the first two tiles
+        __builtin_amdgcn_s_setprio(2);
         i32x16 s[2];
         expand(w, cw);
         products(s, x0, w);
@@ -451,6 +458,7 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
             __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
         products(pend, x1, w);
         fold(acc[0], s[0], sc);
         fold(acc[1], s[1], sc);
@@ -460,6 +468,7 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
             __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
         pend_sc = sc;
     };
     auto next_stage = [](uint32_t s) { return s + kIntStage == kIntStages * kIntStage ? 0u : s + kIntStage; };
@@ -470,11 +479,8 @@ __global__ __launch_bounds__(256, 2) void int_main_kernel(IntGemmArgs a) {
         // group g has landed; the stage of group g - 1 has been read by everybody and takes group g + 2
         if (g + 1 < count) staged_wait<L>();
         else staged_wait<0>();
-        if (g + 2 < count) {
-            issue(st_in);
-            st_in = next_stage(st_in);
-        }
-        group(lds + st);
+        group(lds + st, g + 2 < count, st_in);
+        if (g + 2 < count) st_in = next_stage(st_in);
         st = next_stage(st);
     }
     // ---- token scales, rank-k correction (by one plane), store --------------------------------------------------
