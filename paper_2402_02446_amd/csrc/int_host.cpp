@@ -29,6 +29,13 @@ struct IntGemmArgs {
     int tail_plane;
     bool planes;
 };
+struct IntPrepArgs {                                 // (also in kernels_int.hip)
+    const float* X; int64_t ldx, M, K;
+    int8_t* Xc; float* Xs;
+    const uint8_t* At; const float* Asc;
+    float* T; int64_t ldt;
+};
+hipError_t launch_int_prep(const IntPrepArgs& a, hipStream_t s);
 hipError_t launch_int_projection(const IntGemmArgs& a, hipStream_t s);
 hipError_t launch_int_main(const IntGemmArgs& a, hipStream_t s);
 hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_stride, int64_t M, int64_t N, int64_t ldp,
@@ -89,6 +96,12 @@ static int projection_planes(const Layer& L, int64_t M) {
     while (tiles * s < 256 && s < 16 && G / (2 * s) >= 2) s *= 2;
     return (int)s;
 }
+
+// Quantizer and projection as one launch (kernels_int.hip), ranks 1 to 64.  It saves two launches and the planes' way through memory, and pays with
+// A_k read again for every 8 tokens, as many bytes as X itself per 32 ranks: the faster one up to about 24 million values.  Whole calls,
+// N = 512, rank 32 / 64, separate launches -> one: 2048 tokens of 11008 64.3 / 65.7 -> 56.4 / 60.2 us, 4096 of 5120 63.5 / 64.7 -> 56.5 /
+// 60.6, 130 of 11008 37.2 / 38.2 -> 32.6 / 36.3; beyond, 4096 of 8192 82.6 / 83.4 and 85.9 / 91.6.
+static bool fused_prep(const Layer& L, int64_t M) { return L.kp32 >= 1 && L.kp32 <= 2 && M * L.K <= 24000000; }
 
 // K planes of the main product: with few output tiles (few tokens) its K groups are spread over workgroups as well,
 // each plane leaving partial sums of Y in the workspace for a small kernel to add up; the rank-k correction then gets a
@@ -174,13 +187,19 @@ int forward_int(const Layer& L, const float* X, int64_t ldx, int64_t M, float* Y
     float* Xs = (float*)((uint8_t*)ws + round_up(mp * L.K, 256));
     float* T = (float*)((uint8_t*)Xs + round_up(mp * 4, 256));
     const int64_t ldt = (int64_t)L.kp32 * 32;
-    if (launch_quant_token(X, M, L.K, ldx, Xc, L.K, Xs, nullptr, true, s) != hipSuccess) return LQER_ERR_HIP;
+    const bool one_launch = fused_prep(L, M);
+    if (one_launch) {
+        const IntPrepArgs p{X, ldx, M, L.K, Xc, Xs, L.At, L.Asc, T, ldt};
+        if (launch_int_prep(p, s) != hipSuccess) return LQER_ERR_HIP;
+    } else if (launch_quant_token(X, M, L.K, ldx, Xc, L.K, Xs, nullptr, true, s) != hipSuccess) {
+        return LQER_ERR_HIP;
+    }
     IntGemmArgs a;
     a.Xc = Xc; a.ldxc = L.K; a.Xs = Xs; a.G = L.K / 128; a.M = M;
     const int S = projection_planes(L, M);
     a.T = nullptr; a.ldt = ldt; a.Bt = nullptr; a.Bsc = nullptr; a.kp16 = 0;
     a.tail_plane = 0;
-    if (L.kp > 0) {
+    if (L.kp > 0 && !one_launch) {
         a.Wt = L.At; a.Wsc = L.Asc; a.N = ldt; a.N32 = L.kp32; a.Out = T; a.ldo = ldt;
         a.g_per_z = (a.G + S - 1) / S; a.out_z_stride = mp * ldt;
         const int planes = (int)((a.G + a.g_per_z - 1) / a.g_per_z);

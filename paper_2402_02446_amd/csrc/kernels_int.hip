@@ -6,6 +6,7 @@
 // the int8 matrix cores (32x32x32, exact in i32) and every group's sum is converted and scaled once, in fp32.
 //
 //   quant_token_kernel   per-token INT8 quantizer (one workgroup per token row: row maximum, then codes)
+//   int_prep_kernel      the quantizer and the projection T = X_q A_k in one launch, 8 tokens per workgroup: ranks up to 64, smaller calls
 //   int_main_kernel      the main product with the rank-k correction (T_hi | T_lo against B_k's codes on the bf16 matrix
 //                        cores, one scale per column) in the epilogue; operands by direct-to-LDS loads.  Few tiles: K in
 //                        planes, one more for the correction, that int_reduce_planes_kernel adds and scales per token
@@ -113,6 +114,179 @@ hipError_t launch_quant_token(const float* X, int64_t rows, int64_t K, int64_t l
     if (rows == 0) return hipSuccess;
     if (perm) launch_quant_token_t<true>(X, rows, K, ldx, codes, ldc, scale_f32, scale_f16, s);
     else launch_quant_token_t<false>(X, rows, K, ldx, codes, ldc, scale_f32, scale_f16, s);
+    return hipGetLastError();
+}
+
+// ---- quantizer and projection in one launch ------------------------------------------------------------------------
+// A workgroup has 8 tokens, its wavefronts the K groups in turn: row maxima, then codes to the workspace and from LDS, as operands, into
+// T = X_q A_k, summed over the wavefronts in wavefront order.  The first kKeep groups of a wavefront stay in registers between the two
+// passes; later ones are read again.  A wavefront's loads cover two rows of a group each; its codes change hands through 1 KB of LDS, from
+// where a lane takes one cell of 16.  The 32 rows of an MFMA's operand are the tokens four times, each time with another cell of every
+// lane half: four MFMAs with a group's four A_k operands, of each of which one block of rows is the tokens' share of the sum.
+// Bound by latency and by A_k's way from L2 (32 bytes per K and rank group, a workgroup): which calls take it, fused_prep in int_host.cpp.
+// Beside quantizer, projection in planes and their sum (8.4 + 7.9 + 4.7 us and the gaps at 2048 tokens of 4096, rank 32), whole calls, N = 512:
+// 130 tokens of 512 21.3 -> 14.2 us, of 4096 23.8 -> 18.5, 2048 tokens of 4096 41.1 -> 34.2, of 11008 64.3 -> 56.4.  With 16 tokens
+// a workgroup 15.2, 23.2, 40.4 and 64.8: half the workgroups, each with twice the vector work.
+struct IntPrepArgs {
+    const float* X; int64_t ldx, M, K;
+    int8_t* Xc; float* Xs;               // codes [rows][K] in the product's order, token scales
+    const uint8_t* At; const float* Asc; // A_k records and scales, as IntGemmArgs' 8-bit weights
+    float* T; int64_t ldt;
+};
+constexpr int kIntPrepRows = 8, kIntPrepRun = 32 * 16 + 32;     // bytes of LDS per run of 32 of K, 8 banks apart
+
+template <int NW, int RG>
+__global__ __launch_bounds__(64 * NW) void int_prep_kernel(IntPrepArgs a) {
+    constexpr int ROWS = kIntPrepRows, J = ROWS / 2, kKeep = 4;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[NW * 4 * kIntPrepRun];       // a tile of codes, then 256 sums, per wavefront
+    __shared__ float pmax[ROWS][2 * NW], scale[ROWS], inverse[ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), t = lane & 31, hh = lane >> 5;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int rows = a.M - row0 < ROWS ? (int)(a.M - row0) : ROWS;
+    const int G = (int)(a.K >> 7);
+    const float* src[J];                             // rows 2 j + hh (past the last: that one again)
+#pragma unroll
+    for (int j = 0; j < J; ++j) src[j] = a.X + (row0 + (2 * j + hh < rows ? 2 * j + hh : rows - 1)) * a.ldx + 4 * t;
+    auto load = [&](f32x4 (&v)[J], int g) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) v[j] = *reinterpret_cast<const f32x4*>(src[j] + (int64_t)g * 128);
+    };
+    float m[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) m[j] = 0.f;
+    auto look = [&](const f32x4 (&v)[J]) {
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            m[j] = __builtin_fmaxf(m[j], __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v[j][0]), __builtin_fabsf(v[j][1])),
+                                                         __builtin_fmaxf(__builtin_fabsf(v[j][2]), __builtin_fabsf(v[j][3]))));
+    };
+    f32x4 kept[kKeep][J];
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (wave + i * NW < G) load(kept[i], wave + i * NW);
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (wave + i * NW < G) look(kept[i]);
+    for (int g = wave + kKeep * NW; g < G; g += NW) {
+        f32x4 v[J];
+        load(v, g);
+        look(v);
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        float x = m[j];                              // over 16 lanes, as in wave_max
+        x = __builtin_fmaxf(x, dpp_move<0xB1>(x));
+        x = __builtin_fmaxf(x, dpp_move<0x4E>(x));
+        x = __builtin_fmaxf(x, dpp_move<0x141>(x));
+        x = __builtin_fmaxf(x, dpp_move<0x140>(x));
+        if ((lane & 15) == 0) pmax[2 * j + hh][2 * wave + ((lane >> 4) & 1)] = x;
+    }
+    __syncthreads();
+    if (tid < 16 * ROWS) {                           // 16 lanes per row
+        const int row = tid >> 4, part = tid & 15;
+        float x = 2 * NW >= 16 || part < 2 * NW ? pmax[row][part] : 0.f;
+        if (2 * NW > 16) x = __builtin_fmaxf(x, pmax[row][(part + 16) % (2 * NW)]);
+        x = __builtin_fmaxf(x, dpp_move<0xB1>(x));
+        x = __builtin_fmaxf(x, dpp_move<0x4E>(x));
+        x = __builtin_fmaxf(x, dpp_move<0x141>(x));
+        x = __builtin_fmaxf(x, dpp_move<0x140>(x));
+        // s = fp16(amax / 127), the division in fp32 and correctly rounded; 1 for an all-zero row
+        const float s = (x == 0.f) ? 1.0f : (float)(_Float16)__fdiv_rn(x, 127.0f);
+        if (part == 0) {
+            scale[row] = s;
+            inverse[row] = __fdiv_rn(1.0f, s);
+            if (row < rows) a.Xs[row0 + row] = s;
+        }
+    }
+    __syncthreads();
+
+    float acc[RG][4];
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[rg][r] = 0.f;
+    uint8_t* tile = lds + wave * 4 * kIntPrepRun;
+    uint8_t* put = tile + (t >> 3) * kIntPrepRun + hh * 16 + 2 * (t & 7);            // [run of 32][even, odd][row][16 B]
+    const int row = t & 7, run = 2 * (t >> 4) + hh, odd = (t >> 3) & 1;              // as operand: row t % 8, cell 4 sp + 2 hh + p, 2 sp + p = t / 8
+    const uint8_t* get = tile + run * kIntPrepRun + odd * 256 + row * 16;
+    int8_t* dst = a.Xc + (row0 + row) * a.K + run * 32 + odd * 16;
+    auto group = [&](const f32x4 (&v)[J], int g) {
+        i32x4 w[4];
+        float sc;
+        auto load_a = [&](int rg) {
+            const uint8_t* rec = a.At + ((int64_t)rg * G + g) * 4096 + lane * 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const i32x4*>(rec + q * 1024);
+            sc = a.Asc[((int64_t)rg * G + g) * 32 + t];
+        };
+        load_a(0);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const f32x4 one[1] = {v[j]};
+            uint32_t c[1][4];
+            Int8Coder(scale[2 * j + hh], inverse[2 * j + hh]).codes(one, c);
+            *reinterpret_cast<uint16_t*>(put + 32 * j) = (uint16_t)(c[0][0] | (c[0][2] << 8));
+            *reinterpret_cast<uint16_t*>(put + 32 * j + 256) = (uint16_t)(c[0][1] | (c[0][3] << 8));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                           // (only this wavefront's lanes read them)
+        const i32x4 x = *reinterpret_cast<const i32x4*>(get);
+        asm volatile("" ::: "memory");
+        if (row < rows) *reinterpret_cast<i32x4*>(dst + (int64_t)g * 128) = x;
+#pragma unroll
+        for (int rg = 0; rg < RG; ++rg) {
+            if (rg > 0) load_a(rg);
+            i32x16 s[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[b][r] = 0;
+                s[b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(x, w[b], s[b], 0, 0, 0);
+            }
+            // rows 8 b .. + 7 of the product with w[b] are in its registers 4 b .. + 3
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[rg][r] += (float)(s[0][r] + s[1][4 + r] + s[2][8 + r] + s[3][12 + r]) * sc;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kKeep; ++i)
+        if (wave + i * NW < G) group(kept[i], wave + i * NW);
+    for (int g = wave + kKeep * NW; g < G; g += NW) {
+        f32x4 v[J];
+        load(v, g);
+        group(v, g);
+    }
+    // register r of lane (t, hh): token 4 hh + r, rank t
+    float* red = reinterpret_cast<float*>(lds);
+    static_assert(64 * 4 * 4 <= 4 * kIntPrepRun, "a wavefront's sums in its tile's place");
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) {
+        __syncthreads();                             // the tiles, or the sums before these, have been read
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(wave * 4 + r) * 64 + lane] = acc[rg][r];
+        __syncthreads();
+        for (int item = tid; item < 256; item += 64 * NW) {
+            float v = red[item];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += red[w * 256 + item];
+            const int orow = 4 * ((item >> 5) & 1) + (item >> 6);
+            if (orow < rows) a.T[(row0 + orow) * a.ldt + rg * 32 + (item & 31)] = v * scale[orow];
+        }
+    }
+}
+
+template <int NW>
+static void launch_int_prep_t(const IntPrepArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)((a.M + kIntPrepRows - 1) / kIntPrepRows)), block(64 * NW);
+    if (a.ldt == 32) hipLaunchKernelGGL((int_prep_kernel<NW, 1>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((int_prep_kernel<NW, 2>), grid, block, 0, s, a);
+}
+
+// Ranks up to 64.  About two K groups a wavefront: more wavefronts would be idle, fewer longer chains.
+hipError_t launch_int_prep(const IntPrepArgs& a, hipStream_t s) {
+    if (a.M == 0) return hipSuccess;
+    if (a.K <= 1024) launch_int_prep_t<4>(a, s);
+    else if (a.K <= 2048) launch_int_prep_t<8>(a, s);
+    else launch_int_prep_t<16>(a, s);
     return hipGetLastError();
 }
 

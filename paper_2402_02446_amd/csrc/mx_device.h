@@ -231,6 +231,7 @@ __device__ __forceinline__ int mx8_code(float v, int e_unbiased) {
 struct Int8Coder {
     float s, y;
     __device__ __forceinline__ explicit Int8Coder(float scale) : s(scale), y(__fdiv_rn(1.0f, scale)) {}
+    __device__ __forceinline__ Int8Coder(float scale, float inverse) : s(scale), y(inverse) {}   // inverse: 1 / scale, correctly rounded
     static __device__ __forceinline__ uint32_t clamp(float q) {
         q = __builtin_rintf(q);
         return (uint32_t)(int)__builtin_fminf(__builtin_fmaxf(q, -127.0f), 127.0f) & 0xFFu;
