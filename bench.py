@@ -214,9 +214,9 @@ def measure_peaks():
 
 
 def takes_six(layer, M):
-    """Whether a call's main product runs on fp6 operands (tiled path, a layer that holds them; at the sizes timed here)."""
+    """Whether a call's main product runs on fp6 operands (tiled path, a layer that holds them or 2-bit weights; at the sizes timed here)."""
     from paper_2402_02446_amd import binding
-    return binding.lqer_linear_path(layer, M) == 2 and layer.fp6_bytes() > 0
+    return binding.lqer_linear_path(layer, M) == 2 and (layer.fp6_bytes() > 0 or layer.w_bits == 2)
 
 
 def mfma_peak(six):
@@ -322,7 +322,7 @@ def run_case(name, K, N, k, Ms, steps, warmup, rng, ring_bytes, gain, peaks):
         else:
             six = takes_six(layers[0], M)
             res["operands"] = "fp6 pairs, exact" if six else "bf16, exact"
-            res["roofline"] = roofline("mfma", "tiled_kernel", fl, ms_main, ms_step, fl, peaks, six=six)
+            res["roofline"] = roofline("mfma", "six_kernel" if six else "tiled_kernel", fl, ms_main, ms_step, fl, peaks, six=six)
             if M >= 2048:
                 res["roofline_prep_kernel"] = roofline("hbm", "prep_kernel", bytes_prep_kernel(M, K, kp, six), ms_prep, None, None, peaks)
         results.append(res)
@@ -395,7 +395,7 @@ def run_cfg5(steps, rng, peaks):
             six = takes_six(layer, M)
             per_shape.append({"K": K, "N": N, "linears": names, "ms_per_linear": ms, "ms_prep_kernel": ms_prep,
                               "ms_main_kernel": ms_main, "tflops": fl / (ms * 1e-3) / 1e12,
-                              "roofline": roofline("mfma", "tiled_kernel", fl, ms_main, ms, fl, peaks, six=six),
+                              "roofline": roofline("mfma", "six_kernel" if six else "tiled_kernel", fl, ms_main, ms, fl, peaks, six=six),
                               "roofline_prep_kernel": roofline("hbm", "prep_kernel", bytes_prep_kernel(M, K, layer.kp, six),
                                                                ms_prep, None, None, peaks)})
             total_ms += ms * len(names)
@@ -529,7 +529,7 @@ def run_w2a8(rng, peaks):
                    "path": "streaming" if path == 1 else "tiled", "ms_per_step": ms, "ms_main_kernel": ms_main,
                    "tflops": fl / (ms * 1e-3) / 1e12}
             rec["roofline"] = (roofline("hbm", "stream_kernel", by_main, ms_main, ms, by_step, peaks) if path == 1
-                               else roofline("mfma", "tiled_kernel", fl, ms_main, ms, fl, peaks))
+                               else roofline("mfma", "six_kernel", fl, ms_main, ms, fl, peaks, six=takes_six(layers[0], M)))
             out.append(rec)
             del X, Y
         for l in layers:
@@ -818,7 +818,7 @@ def main():
         extra["build_factors_seconds_per_layer"] = time_build_factors(rng)
     t_gpu = time.perf_counter() - t_start
     cpu = cpu_baseline(ctx, K, N, kp)
-    rf = dict(head["roofline"], traffic=read_pmc_traffic("tiled_kernel.cfg4_M4096"))
+    rf = dict(head["roofline"], traffic=read_pmc_traffic("six_kernel.cfg4_M4096"))
     out = {
         "metric": METRIC, "value": head["tflops"], "unit": "TFLOP/s", "n_gpus": 1,
         "steps": steps, "warmup": args.warmup, "ms_per_step": head["ms_per_step"],

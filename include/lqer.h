@@ -216,8 +216,9 @@ int lqer_linear_forward_q(const lqer_layer* layer, const int8_t* Xc_dev, const u
  *           instead of along tile boundaries.  Shapes 31, 32, 33 (64 x 256, 64 x 512, 64 x 128) are the
  *           staged kernel's: mode 0 = planes of K when the estimate says they pay, 1 = whole tiles,
  *           2 = planes (LQER_ERR_SHAPE with K of one tile of 256), no mode 3
- *           Shapes 21 and 22 (128 x 512, 128 x 256; modes 0 to 3) and 41, 42, 43 (as 31, 32, 33) are those on
- *           fp6 operands, for 4-bit layers that hold the second form of W_q
+ *           Shapes 21 and 22 (128 x 512, 128 x 256; modes 0 to 3) and 41, 42, 43, 44 (as 31, 32, 33; 128 x 128) are
+ *           those on fp6 operands, for 4-bit layers that hold the second form of W_q and for 2-bit layers whose
+ *           exponent bytes span at most 16 values
  *   stages  bit 0 = quantize + T, bit 1 = main product; 0 = both
  * Same contract as lqer_linear_forward otherwise.  Running stage bit 1 alone reuses
  * what an earlier call with bit 0 left in the same workspace - with the same M, path and
