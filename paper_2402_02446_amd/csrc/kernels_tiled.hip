@@ -28,8 +28,8 @@
 // piece needs pieces that are computed first by the workgroups they belong to: no wait depends on
 // another wait.  The sum order is fixed by the split, so the result has the same bits every run.
 //
-// 4-bit layers mostly run on fp6 operands instead, in kernels of their own (kernels_six.hip); what is here serves 2-bit layers, layers
-// of rank 0 and those whose correction outweighs K.
+// Layers mostly run on fp6 operands instead, in a kernel of their own (kernels_six.hip); what is here serves layers of rank 0, those whose
+// correction outweighs K, calls of few activations, and 2-bit layers of few K tiles or of exponents that span more than 16 values.
 //
 // Calls that do not fill the chip for long mostly take staged_kernel (pick_small says which): tiles of 64 rows, every
 // operand - activations, packed weights, exponents - brought to LDS by direct loads several chunks ahead, and where
