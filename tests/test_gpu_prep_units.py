@@ -56,3 +56,23 @@ def test_ranks_above_64_of_large_calls(M, K, k, w_bits, wide):
         assert torch.equal(binding.lqer_linear_forward_shared([first, second], Xd)[1], Y)      # from the stored activations: the same bits
     other.free()
     h.free()
+
+
+# Slices of K: as many as make one workgroup to a compute unit of at least three quarters of them, else 512 workgroups.  The partial sums of
+# T are in the workspace: two layers of ranks 16 and 32, whose rows are equally long, differ by them alone.
+@pytest.mark.parametrize("M,K,slices", [(1024, 4096, 4), (1040, 4096, 8), (1536, 4096, 2), (2048, 4096, 2), (2049, 4096, 4), (3056, 4096, 4), (3057, 4096, 1),
+                                        (4096, 10704, 1), (4097, 10704, 2), (4133, 1008, 2), (4133, 768, 1), (8177, 4096, 1)])
+def test_slices_of_the_contraction(M, K, slices):
+    import torch
+    from paper_2402_02446_amd import binding
+    layers = [oracle_layer_big(K, 64, k, seed=k) for k in (16, 32)]
+    hs = [upload(layer) for layer, _ in layers]
+    need = [binding.lqer_linear_workspace_bytes(h, M) for h in hs]
+    rows = (M + 95 + 255) // 256 * 256
+    assert need[1] - need[0] == (rows * 16 * 4 * slices if slices > 1 else 0)
+    X = synth.gen_activations(np.random.default_rng(M), M, K, layers[1][1], 50.0)
+    Y = binding.lqer_linear_forward(hs[1], torch.from_numpy(X).cuda())
+    at = np.array([0, 15, 16, 127, 128, M // 2, M - 1])
+    assert_forward_matches(Y.cpu().numpy()[at], X[at], layers[1][0])
+    for h in hs:
+        h.free()
