@@ -66,3 +66,24 @@ def test_groups_of_unequal_layers(M, K, specs):
     for g, h in zip(binding.lqer_linear_forward_shared(hs, X), hs):
         assert torch.equal(g, binding.lqer_linear_forward(h, X))
         h.free()
+
+
+# Both sides of the lines: few K tiles and a rank up to 32, one tile at any rank, eight tiles and more on few activations.  A call on bf16
+# operands has the bits it has without the fp6 copy of the weights; one on fp6 operands sums in another order.
+@pytest.mark.parametrize("M,K,N,k,six", [(700, 512, 400, 32, False), (3125, 512, 400, 32, False), (3126, 512, 400, 32, True), (700, 512, 400, 33, True),
+                                         (12500, 256, 300, 64, False), (12501, 256, 300, 64, True), (780, 1024, 400, 8, False), (782, 1024, 400, 8, True),
+                                         (69, 4096, 640, 32, False), (74, 4096, 640, 32, True), (69, 4096, 640, 64, True), (150, 1040, 400, 32, True)])
+def test_which_calls_take_fp6_operands(M, K, N, k, six):
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, ch = oracle_layer_big(K, N, k, seed=5)
+    h = upload(layer)
+    X = synth.gen_activations(np.random.default_rng(4), M, K, ch, 50.0)
+    Xd = torch.from_numpy(X).cuda()
+    Y = binding.lqer_linear_forward(h, Xd)
+    h.drop_fp6()
+    assert torch.equal(binding.lqer_linear_forward(h, Xd), Y) != six
+    h.free()
+    rows, cols = _rows_and_cols(M, N)
+    rows = rows[rows < M]
+    assert_forward_matches(Y.cpu().numpy()[np.ix_(rows, cols)], X[rows], layer, cols=cols)
