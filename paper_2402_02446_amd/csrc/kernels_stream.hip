@@ -789,8 +789,10 @@ hipError_t launch_stream_group(const Layer* const* layers, int n, int64_t M, con
             // and correction jobs, hence the same bits).  Two layers, whole call, 16 tokens, eight wavefronts along K -> four:
             // 4096 x 11008 23.6 -> 21.0 us, 5120 x 13824 29.1 -> 24.7, 1024 x 10304 / 11000 12.4 -> 11.0; at 1 token, where
             // the two groups of a wavefront were the workgroup, 20.3 -> 17.8, 25.1 -> 21.4, 12.4 -> 9.6.  Beyond a round as before:
-            // two groups with up to 4 tokens, several workgroups to a compute unit.
-            if (folded) return lr == 2 ? launch_group_one<2, 2, 4, 2, 1, 2>(g, s) : launch_group_one<2, 2, 4, 4, 1, 2>(g, s);
+            // two groups with up to 4 tokens, several workgroups to a compute unit.  With 5 to 16 tokens also on five and six K tiles, which
+            // are one step for eight wavefronts along K, and two for four of which the second is one or two wavefronts' work: 1120 to 1264 x
+            // 10434 to 15480 twice at 12 tokens 12.3 us and 13.0, 1536 wide alike on average; up to four tiles and from seven on four are faster.
+            if (folded && !(lr == 4 && g.KT > 4 && g.KT <= 6)) return lr == 2 ? launch_group_one<2, 2, 4, 2, 1, 2>(g, s) : launch_group_one<2, 2, 4, 4, 1, 2>(g, s);
             return lr == 2 ? launch_group_one<2, 1, 8, 2, 1>(g, s) : launch_group_one<2, 2, 8, 4, 1>(g, s);
         case 21181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 2>(g, s) : launch_group_one<1, 1, 8, 4, 2>(g, s);
         case 11181: return lr == 2 ? launch_group_one<1, 1, 8, 2, 1>(g, s) : launch_group_one<1, 1, 8, 4, 1>(g, s);

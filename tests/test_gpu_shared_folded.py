@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M", [1, 5, 16])
 @pytest.mark.parametrize("K,specs", [(256, ((10304, 32), (10400, 0))), (1024, ((10252, 8), (10240, 64))), (1296, ((10304, 33), (10272, 16))),
-                                     (2304, ((10240, 16), (11008, 48))), (528, ((11008, 16), (11008, 16), (11040, 16)))])
+                                     (2304, ((10240, 16), (11008, 48))), (528, ((11008, 16), (11008, 16), (11040, 16))),
+                                     (1536, ((10240, 64), (10300, 16))), (1552, ((10240, 64), (10300, 16)))])
 def test_bits_are_the_layers_own(M, K, specs):
     import torch
     from paper_2402_02446_amd import binding
