@@ -725,19 +725,23 @@ __global__ __launch_bounds__(64 * NW, 2) void six_kernel(TiledArgs a) {
 
 // ---- which tile, cut along K or not -------------------------------------------------------------------------------------
 // Time model of the main product in us: a workgroup takes per K tile between unit[r][0] and unit[r][1] when r + 1 of them share a compute unit, by how
-// many compute units have that many (a full chip's clock is lower); `fixed` per launch, `round` per round of workgroups, `out` per MB
-// of Y; corr[0] + corr[1] S per round and 64 ranks of the correction beyond the first, S > 1 the partial sums of T, corr[2] per round above
-// rank 32; planes take `plane` and `plane_mb` per MB of partial sums written and read.  Fitted to 4300 (128 x 128: 5300) calls of
-// K 64 to 12288, N 64 to 28672, 33 to 16384 tokens and ranks 8 to 256, timed on a warm chip: mean error 3 to 4 % a shape.
-// The choice is 0.7 % from the fastest form on average, 5 % at the 95th percentile, 23 % at the very worst.
-struct SixShape { int id, bm, bn, resident; double unit[3][2], fixed, round, out, corr[3], plane, plane_mb; };
+// many compute units have that many (a full chip's clock is lower); `fixed` per launch, start[r - 1] more where r + 1 of them start on a
+// unit at once, `round` per round of workgroups beyond the first; out[0] per MB of Y, out[1] per MB beyond the 256 that the caches hold,
+// out[2] per MB of a Y beyond them whose rows share 128-byte lines (half-written ones go to memory twice); corr[0] + corr[1] S per
+// round and 64 ranks of the correction beyond the first, S > 1 the partial sums of T, corr[2] per round above rank 32; planes take
+// `plane` and `plane_mb` per MB of partial sums written and read.  Fitted to 130000 timings of 22800 calls of K 64 to 12288, N 256 to 28672, 33
+// to 65536 tokens and ranks 8 to 256, planes of every number among them, on a warm chip: mean error 3 to 5 % a shape.  Of the calls that
+// take fp6 operands, fitted on one half, the choice on the other is 0.5 % from the fastest form on average, 4 % at the 95th percentile, 26 % at
+// the very worst; without `start`, out[1] and out[2] it was 0.7 and 5 %: 129 tokens of 6672 x 1776 rank 32 took 14 planes for 6, 18.2 us for
+// 16.0, 8192 of 512 x 16244 rank 32 tiles of 128 x 512, 296 us for 231.
+struct SixShape { int id, bm, bn, resident; double unit[3][2], start[2], fixed, round, out[3], corr[3], plane, plane_mb; };
 static const SixShape kSixShapes[] = {
-    {21, 128, 512, 1, {{2.134, 3.469}}, 4.526, 10.035, 0.129, {4.369, 0.349, 2.049}, 0.0, 0.0},
-    {22, 128, 256, 1, {{1.342, 2.076}}, 5.259, 5.629, 0.15, {2.536, 0.335, 0.037}, 0.0, 0.0},
-    {41, 64, 256, 2, {{1.35, 1.513}, {2.02, 2.292}}, 8.486, 0.0, 0.249, {2.303, 0.208, 0.029}, 2.385, 0.179},
-    {42, 64, 512, 1, {{1.701, 2.225}}, 5.92, 4.136, 0.163, {2.649, 0.209, 0.06}, 2.5, 0.147},
-    {43, 64, 128, 3, {{0.974, 1.029}, {1.239, 1.459}, {1.952, 1.885}}, 6.825, 0.0, 0.258, {1.46, 0.254, 0.03}, 2.445, 0.189},
-    {44, 128, 128, 2, {{1.183, 1.324}, {1.648, 2.103}}, 7.945, 0.76, 0.289, {2.671, 0.393, 0.022}, 2.654, 0.182},
+    {21, 128, 512, 1, {{2.202, 3.530}}, {0.0}, 13.867, 7.088, {0.155, 0.000, 0.064}, {4.513, 0.375, 2.333}, 0.0, 0.0},
+    {22, 128, 256, 1, {{1.345, 2.098}}, {0.0}, 10.971, 4.711, {0.171, 0.000, 0.034}, {2.523, 0.357, 0.152}, 0.0, 0.0},
+    {41, 64, 256, 2, {{1.370, 1.575}, {2.032, 2.271}}, {1.574}, 8.721, 1.360, {0.209, 0.029, 0.011}, {2.167, 0.235, 0.077}, 2.482, 0.163},
+    {42, 64, 512, 1, {{1.712, 2.233}}, {0.0}, 10.153, 3.804, {0.171, 0.000, 0.017}, {2.427, 0.209, 0.193}, 2.538, 0.154},
+    {43, 64, 128, 3, {{0.981, 1.072}, {1.223, 1.421}, {1.854, 1.939}}, {1.396, 0.684}, 7.063, 0.271, {0.205, 0.053, 0.014}, {1.390, 0.228, 0.079}, 2.436, 0.174},
+    {44, 128, 128, 2, {{1.133, 1.352}, {1.705, 2.163}}, {1.761}, 9.148, 2.545, {0.211, 0.014, 0.031}, {2.630, 0.372, 0.112}, 2.665, 0.171},
 };
 // 128 x 512 with the tiles that do not fill a round cut in whole pieces: us per launch, K tile of a piece, K tile and number of whole
 // rounds, piece beyond two, 64 ranks of the correction beyond the first, MB of Y (1500 timings, 5 %).  In equal shares, and 128 x 256
@@ -753,8 +757,11 @@ static int more_rounds(int kp) { return kp > 64 ? (kp + 63) / 64 - 1 : 0; }
 
 static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int64_t tiles, int planes, int64_t share, int cus) {
     const int64_t wgs = tiles * planes, slots = (int64_t)cus * sh.resident, full = wgs / slots, rest = wgs - full * slots;
-    double t = sh.fixed + sh.round * (double)(full + (rest > 0 ? 1 : 0)) + sh.out * (double)M * (double)L.N * 4e-6 +
-               sh.unit[sh.resident - 1][1] * (double)full * (double)share;
+    const double mb = (double)M * (double)L.N * 4e-6;
+    double t = sh.fixed + sh.round * (double)(full + (rest > 0 ? 1 : 0) - 1) + sh.out[0] * mb + sh.unit[sh.resident - 1][1] * (double)full * (double)share;
+    if (mb > 256.0) t += sh.out[1] * (mb - 256.0) + (((L.N + 3) / 4 & 7) != 0 ? sh.out[2] * mb : 0.0);
+    for (int r = 1; r < sh.resident; ++r)
+        if (wgs > (int64_t)r * cus) t += sh.start[r - 1];
     if (rest > 0) {
         const int64_t r = (rest - 1) / cus;
         const double fill = (double)(rest - r * cus) / (double)cus;

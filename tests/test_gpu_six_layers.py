@@ -87,3 +87,17 @@ def test_which_calls_take_fp6_operands(M, K, N, k, six):
     rows, cols = _rows_and_cols(M, N)
     rows = rows[rows < M]
     assert_forward_matches(Y.cpu().numpy()[np.ix_(rows, cols)], X[rows], layer, cols=cols)
+
+
+def test_tiles_of_a_large_ragged_y():
+    """Two K tiles and a Y beyond the caches whose rows share cache lines: tiles of 64 rows, which sum two chains, not those of 128 x 512, which
+    sum one.  (Half of the time of the large ones is such lines' way to memory and back.)"""
+    import torch
+    from paper_2402_02446_amd import binding
+    M, K, N = 8192, 512, 16244
+    h = upload(oracle_layer_big(K, N, 32, seed=6)[0])
+    X = torch.randn(M, K, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    Y = binding.lqer_linear_forward(h, X)
+    assert torch.equal(Y, binding.lqer_linear_forward_ex(h, X, path=2, variant=143))
+    assert not torch.equal(Y, binding.lqer_linear_forward_ex(h, X, path=2, variant=121))
+    h.free()
