@@ -847,7 +847,7 @@ hipError_t launch_widen_six(const Layer& L, hipStream_t s) {
 // Where a layer's calls take fp6 operands: with at least half as many K tiles as its correction has chunks of 64 columns beyond the first
 // (always up to rank 64, from K = 257 at rank 128, from 769 at rank 256), and where the activations are more than next to nothing.  What
 // the fp6 form takes longer, it takes to start and to end; of a few K tiles and a small rank (whose chunks the bf16 form has as further
-// columns of K) it needs many rows to win that back: M KT^2 above 12500 up to four tiles and rank 32, and at one tile whatever the rank.
+// columns of K) it needs many rows to win that back: M KT^2 above 12500 up to three tiles and rank 32, above 8000 with four, and at one tile whatever the rank.
 // From 8 tiles on the bf16 form cuts K and is the faster up to 3e5 activations of such ranks.  On 18000 calls of 33 to 100000 tokens, K 64
 // to 11008: fp6 / bf16, rank 8 to 32, one tile 1.12 below 500 tokens, 1.08 at 4000 to 8000, 0.99 beyond 24000; two 1.11, 1.02, 1.00;
 // three 1.08, 0.97; rank 64 and above from two tiles on 0.85 to 1.03 everywhere.  Without the two lines calls below them were up to 1.13 of
@@ -862,7 +862,7 @@ bool tiled_takes_six(const Layer& L, int64_t M, int variant) {
     if (shape != 0) return shape == 21 || shape == 22 || (shape >= 41 && shape <= 44);
     if (mode > 1) return false;                              // cut by force: the bf16 shapes
     if (L.w_bits == 2 && L.KT < 4) return false;
-    if (L.KT < 5 && (L.KT == 1 || L.kp <= 32) && M * L.KT * L.KT <= 12500) return false;
+    if (L.KT < 5 && (L.KT == 1 || L.kp <= 32) && M * L.KT * L.KT <= (L.KT == 4 ? 8000 : 12500)) return false;
     if (L.KT >= 8 && L.kp <= 32 && M * L.K <= 300000) return false;
     return M * L.K > 150000 && 2 * L.KT >= (2 * L.kp + 63) / 64 - 1;
 }
