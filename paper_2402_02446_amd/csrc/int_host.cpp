@@ -116,11 +116,12 @@ static int main_planes(const Layer& L, int64_t M) {
     return (int)((G + g - 1) / g);
 }
 
-// Up to 128 tokens: the two launches of kernels_int_few.hip, 32 tokens and 32 columns per workgroup, or the general ones,
-// whichever two linear models (us; fitted to 620 timings of both, 128 to 28672 x 512 to 28672, ranks 0 to 128: 7 % and 4 %
-// mean error) say is the faster.  The choice is 0.2 % from the faster one on average, 20 % at worst; the few-token form
-// always 20 %, up to 32 tokens and 24576 workgroups x K groups beyond 7 %: 128 tokens of 512 x 11008 27.5 us by it, 18.5 by
-// the general launches, 32 tokens of 28672 x 1024 63 and 35; 64 tokens of 4096 x 4096 18 and 30.
+// Up to 128 tokens: the two launches of kernels_int_few.hip, 32 tokens and 32 columns per workgroup, or the general ones, whichever two
+// linear models (us) say is the faster.  Ranks 1 to 64 from 8 tokens on, whose general calls quantize and project in one launch: fitted to half of 10900
+// timings of both (8 to 128 tokens, 128 to 28672 x 256 to 28672), 7 and 4 % mean error; on the other half the choice is 0.6 % from the faster
+// one on average, 6 % at the 95th percentile (1.7 and 12 % by the models of three launches, the second pair); the few-token form always
+// 9 %.  65 tokens of 20096 x 4651 rank 64 79 us by it, 58 by the general launches; 9 of 1024 x 4283 rank 48 10 and 15.
+// Rank 0, ranks above 64, fewer tokens: 1.3, 0.7 and 0.2 % on 8900 such calls, 32 tokens of 28672 x 1024 63 and 35; 64 tokens of 4096 x 4096 18 and 30.
 static bool few_tokens(const Layer& L, int64_t M) {
     if (M > 128) return false;
     const double G = (double)(L.K / 128), rows = (double)std::min<int64_t>(M, 32), kp16 = (double)L.kp16;
@@ -129,6 +130,14 @@ static bool few_tokens(const Layer& L, int64_t M) {
     const double few = 8.9 + 0.0028 * G * rows + 0.0069 * kp16 * G + 0.00101 * (double)wgs * kp16 +
                        rounds * (2.13 + 0.029 * G + 0.0030 * G * rows + 0.33 * kp16);
     const int sm = main_planes(L, M), S = projection_planes(L, M);
+    if (M >= 8 && fused_prep(L, M)) {
+        const double per_wave = std::ceil(G / (L.K <= 1024 ? 4 : (L.K <= 2048 ? 8 : 16)));       // (launch_int_prep)
+        const double few2 = 7.31 + 0.00439 * G * rows + 0.00875 * kp16 * G + (0.00675 + 0.00027 * kp16) * (double)wgs +
+                            rounds * (0.89 + 0.00307 * G * rows + 0.311 * kp16);
+        const double one = 8.47 + 0.1128 * G + 0.591 * std::ceil(G / sm) + 3.7e-4 * G * (double)((L.N + 127) / 128) +
+                           2.353e-6 * (double)sm * (double)M * (double)L.N + (sm > 1 ? 1.026 : 0.0) + per_wave * (0.587 + 0.426 * (double)(L.kp32 - 1)) + 0.35 * kp16;
+        return few2 < one;
+    }
     double general = 10.8 + 0.07 * G + 0.76 * std::ceil(G / sm) + 1.04e-4 * G * (double)((L.N + 127) / 128) + 1.45e-6 * (double)sm * (double)M * (double)L.N;
     if (sm > 1) general += 3.3;
     if (L.kp > 0) general += 1.3 + 1.66 * std::ceil(G / S) + 0.51 * kp16;

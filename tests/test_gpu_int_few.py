@@ -83,3 +83,25 @@ def test_which_launches_and_either_workspace(M, K, N, general):
     with pytest.raises(binding.LqerError):
         binding.lqer_linear_forward(h, torch.from_numpy(X).cuda(), workspace=ws[:few - 256])
     h.free()
+
+
+# The same at ranks whose general launches quantize and project in one: the planes of T are reserved whatever its form.
+@pytest.mark.parametrize("M,K,N,k,general", [(9, 1024, 4288, 48, False), (55, 256, 11168, 8, True), (32, 128, 15168, 32, True), (16, 4096, 4096, 32, False),
+                                             (64, 11264, 544, 16, True), (24, 11264, 544, 16, False), (40, 2048, 2048, 33, False), (7, 640, 15808, 32, False)])
+def test_which_launches_with_a_small_rank(M, K, N, k, general):
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, ch = _standin_layer(K, N, k, seed=M)
+    h = _upload(layer)
+    need = binding.lqer_linear_workspace_bytes(h, M)
+    at = lambda n: (n + 255) // 256 * 256
+    per = min((K // 128 + 7) // 8, 7)
+    few = at((M + 31) // 32 * 32 * K) + at(512) + at((K // 128 + per - 1) // per * M * ((k + 31) // 32 * 32) * 4)
+    assert need > few if general else need == few
+    X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
+    cols = np.arange(0, N, 5)
+    for nbytes in (need, few):
+        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
+        Y = binding.lqer_linear_forward(h, torch.from_numpy(X).cuda(), workspace=ws)
+        _check(Y.cpu().numpy()[:, cols], X, layer, cols)
+    h.free()
