@@ -673,10 +673,14 @@ int stream_variant(const Layer& L, int64_t M, int variant) {
     if (big && M > 16) return 11421;
     // Wide layers: from where two column groups a workgroup are more workgroups than compute units, of which one fills a compute unit's LDS at
     // 5 tokens and more.  Main product, two groups and eight K slices against four and four, 512 and 600 groups: 4096 wide at 16
-    // tokens 12.0 us and 14.9, 19.8 and 15.6; 8192 wide 18.8 and 25.4, 32.0 and 26.8, at 1 token 16.0 and 22.6, 25.4 and 22.7.
+    // tokens 12.0 us and 14.9, 19.8 and 15.6; 8192 wide 18.8 and 25.4, 32.0 and 26.8, at 1 token 16.0 and 22.6, 25.4 and 22.7.  Where the
+    // other shape has four slices as well the line is the same: whole calls of 513 to 796 groups in this shape and in that one, averages over
+    // 1200 calls of 4- and 2-bit weights, 17 to 32 tokens 0.65, ranks above 64 at 5 to 16 tokens 0.69, at 1 to 4 0.97.
     if ((L.N32 + 1) / 2 > compute_units()) return 12241;
     const bool eight = M <= 16 && !big;
-    if ((L.N32 + 1) / 2 >= 160) return eight ? 12181 : 12141;
+    // (Up to 4 tokens eight slices fit beside them too, and are the faster from five K tiles on: main product, four slices and eight,
+    // 2 tokens of 6720 x 12290 rank 128 14.3 us and 12.6, 1280 x 13312 7.1 and 6.6; 1024 x 12288, one step of four, 5.5 and 5.8.)
+    if ((L.N32 + 1) / 2 >= 160) return eight || (M <= 4 && L.KT > 4) ? 12181 : 12141;
     // narrow layers: one column group per workgroup, and a pair of workgroups per group when that
     // still leaves half of the compute units idle and the K range is worth sharing
     if (L.N32 <= 160 && L.KT >= 8) return eight ? 21181 : 21141;

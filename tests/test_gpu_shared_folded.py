@@ -45,3 +45,22 @@ def test_wide_layers(M, N, k, w_bits):
     cols = np.r_[0:40, 8191:8200, N - 40:N]
     assert_forward_matches(Y[:, cols], X, layer, cols=cols)
     h.free()
+
+
+# Ranks above 64 on wide layers: eight K slices at up to 4 tokens from five K tiles on, else four; they add in another order.
+@pytest.mark.parametrize("M,K,N,k,w_bits,shape", [(1, 1024, 10272, 128, 4, 12141), (4, 1040, 10272, 80, 4, 12181), (2, 2320, 16384, 256, 2, 12181), (4, 4096, 10240, 256, 4, 12181),
+                                                  (5, 1040, 10272, 128, 2, 12141), (1, 1296, 16416, 128, 4, 12241)])
+def test_slices_of_wide_layers_of_a_large_rank(M, K, N, k, w_bits, shape):
+    import torch
+    from paper_2402_02446_amd import binding
+    layer, ch = oracle_layer_big(K, N, k, seed=K, w_bits=w_bits)
+    h = upload(layer)
+    X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
+    Xd = torch.from_numpy(X).cuda()
+    Y = binding.lqer_linear_forward(h, Xd)
+    assert torch.equal(binding.lqer_linear_forward_ex(h, Xd, path=1, variant=shape), Y)
+    if M <= 4:                                       # (beyond, eight slices do not fit)
+        assert torch.equal(binding.lqer_linear_forward_ex(h, Xd, path=1, variant=12181), Y) == (shape == 12181)
+    cols = np.r_[0:40, 5000:5040, N - 40:N]
+    assert_forward_matches(Y.cpu().numpy()[:, cols], X, layer, cols=cols)
+    h.free()
