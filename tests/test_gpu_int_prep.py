@@ -1,5 +1,5 @@
 """The INT variant's quantizer and projection in one launch (ranks 1 to 64): K groups below, at and past a wavefront count, past what stays in
-registers; token counts that 8 does not divide; both sides of the size from which the separate launches are the faster.  Results against the
+registers; token counts that 8 does not divide (of up to 128: test_which_launches_with_a_small_rank); both sides of the size from which the separate launches are the faster.  Results against the
 oracle; codes and scales in the workspace bit for bit the stand-alone quantizer's, for scales of zero, infinity and all between."""
 import numpy as np
 import pytest

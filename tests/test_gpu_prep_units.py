@@ -36,26 +36,41 @@ def test_forward_and_codes(M, K, N, k, w_bits):
 
 
 # Ranks above 64 where project_kernel takes the groups beyond the fourth (M K (kp - 64) above 1.3e9, four K tiles a slice): planes of six, five
-# and four groups, the last one short; 64 and 32 rows a wavefront; T final and in slices; fp6 and (rank 0 first, so that they share) bf16 operands
-@pytest.mark.parametrize("M,K,k,w_bits,wide", [(2050, 4096, 256, 2, False), (4100, 2064, 192, 4, False), (8200, 2048, 140, 2, True), (1100, 8192, 256, 4, False)])
-def test_ranks_above_64_of_large_calls(M, K, k, w_bits, wide):
+# and four groups, even ones and a last one that is short; 64 and 32 rows a wavefront; T final and in slices; fp6 operands, and bf16 ones (2-bit
+# layers whose exponents are far apart); 8- and 6-bit activations, as fp32, as codes and as another layer has stored them.
+@pytest.mark.parametrize("M,K,k,w_bits,wide,act_bits,rows", [
+    (2050, 4096, 256, 2, False, 8, 64), (4000, 2576, 192, 4, False, 8, 32), (4100, 2576, 192, 4, False, 6, 64), (8200, 2048, 140, 2, True, 8, 32),
+    (1100, 8192, 256, 4, False, 8, 64), (8200, 1296, 192, 4, False, 8, 64), (8200, 1040, 256, 2, True, 8, 64), (4100, 2064, 256, 4, False, 8, 64),
+    (8200, 1296, 240, 4, False, 6, 64), (3900, 2576, 208, 4, False, 8, 32), (8200, 3344, 112, 4, False, 8, 32)])
+def test_ranks_above_64_of_large_calls(M, K, k, w_bits, wide, act_bits, rows):
     import torch
     from paper_2402_02446_amd import binding
     N = 288
     layer, ch = oracle_layer_big(K, N, k, seed=M, w_bits=w_bits)
+    others = [oracle_layer_big(K, 96, r, seed=1, w_bits=w_bits)[0] for r in (32, 16)]
     if wide:
-        layer.We[0, 0] = 90                                       # bf16 operands for a 2-bit layer
-    h = upload(layer)
+        for l in [layer] + others:
+            l.We[0, 0] = 90
+    h, other, small = upload(layer), upload(others[0]), upload(others[1])
+    # the kernel, and its rows: what launch_prep and launch_project go by
+    tp_rows, KT, kp = (M + 95 + 255) // 256 * 256, (K + 255) // 256, (k + 15) // 16 * 16
+    slices = max(1, (binding.lqer_linear_workspace_bytes(other, M) - binding.lqer_linear_workspace_bytes(small, M)) // (tp_rows * 16 * 4))
+    planes = (kp // 16 - 4 + 5) // 6
+    assert M * K * (kp - 64) > 1.3e9 and -(-KT // slices) >= 4
+    assert rows == (64 if -(-M // 64) * slices * planes >= 256 else 32)
+    for x in (h, other):
+        x.set_activation_bits(act_bits)
     X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
     Xd = torch.from_numpy(X).cuda()
     Y = binding.lqer_linear_forward(h, Xd)
-    rows, cols = np.array([0, 15, 16, 31, 32, 63, 64, M // 2, M - 1]), np.arange(0, N, 3)
-    assert_forward_matches(Y.cpu().numpy()[np.ix_(rows, cols)], X[rows], layer, cols=cols)
-    other = upload(oracle_layer_big(K, 96, 32, seed=1, w_bits=w_bits)[0])
-    for first, second in ((other, h), (h, h)):
-        assert torch.equal(binding.lqer_linear_forward_shared([first, second], Xd)[1], Y)      # from the stored activations: the same bits
-    other.free()
-    h.free()
+    at, cols = np.array([0, 15, 16, 31, 32, 63, 64, M // 2, M - 1]), np.arange(0, N, 3)
+    assert_forward_matches(Y.cpu().numpy()[np.ix_(at, cols)], X[at], layer, cols=cols, act_bits=act_bits)
+    codes, exps = binding.lqer_quantize_mx(Xd, act_bits)
+    assert torch.equal(binding.lqer_linear_forward_q(h, codes, exps), Y)
+    for first in (other, h):                                        # from the stored activations: the same bits
+        assert torch.equal(binding.lqer_linear_forward_shared([first, h], Xd)[1], Y)
+    for x in (h, other, small):
+        x.free()
 
 
 # Slices of K: as many as make one workgroup to a compute unit of at least three quarters of them, else 384 workgroups.  The partial sums of
