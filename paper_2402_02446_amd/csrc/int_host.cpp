@@ -13,34 +13,6 @@
 
 namespace lqer {
 
-// declared in kernels_int.hip
-struct IntGemmArgs {
-    const int8_t* Xc; int64_t ldxc;
-    const float* Xs;
-    const uint8_t* Wt;
-    const float* Wsc;
-    int64_t M, N, N32, G;
-    float* Out; int64_t ldo;
-    int64_t g_per_z;
-    int64_t out_z_stride;
-    const float* T; int64_t ldt;
-    const uint8_t* Bt; const float* Bsc;
-    int kp16;
-    int tail_plane;
-    bool planes;
-};
-struct IntPrepArgs {                                 // (also in kernels_int.hip)
-    const float* X; int64_t ldx, M, K;
-    int8_t* Xc; float* Xs;
-    const uint8_t* At; const float* Asc;
-    float* T; int64_t ldt;
-};
-hipError_t launch_int_prep(const IntPrepArgs& a, hipStream_t s);
-hipError_t launch_int_projection(const IntGemmArgs& a, hipStream_t s);
-hipError_t launch_int_main(const IntGemmArgs& a, hipStream_t s);
-hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_stride, int64_t M, int64_t N, int64_t ldp,
-                                    float* Y, int64_t ldy, const float* Xs, int tail, hipStream_t s);
-
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 static float fp16_to_float(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }

@@ -127,12 +127,6 @@ hipError_t launch_quant_token(const float* X, int64_t rows, int64_t K, int64_t l
 // Beside quantizer, projection in planes and their sum (8.4 + 7.9 + 4.7 us and the gaps at 2048 tokens of 4096, rank 32), whole calls, N = 512:
 // 130 tokens of 512 21.3 -> 14.2 us, of 4096 23.8 -> 18.5, 2048 tokens of 4096 41.1 -> 34.2, of 11008 64.3 -> 56.4.  With 16 tokens
 // a workgroup 15.2, 23.2, 40.4 and 64.8: half the workgroups, each with twice the vector work.
-struct IntPrepArgs {
-    const float* X; int64_t ldx, M, K;
-    int8_t* Xc; float* Xs;               // codes [rows][K] in the product's order, token scales
-    const uint8_t* At; const float* Asc; // A_k records and scales, as IntGemmArgs' 8-bit weights
-    float* T; int64_t ldt;
-};
 constexpr int kIntPrepRows = 8, kIntPrepRun = 32 * 16 + 32;     // bytes of LDS per run of 32 of K, 8 banks apart
 
 template <int NW, int RG>
@@ -291,23 +285,6 @@ hipError_t launch_int_prep(const IntPrepArgs& a, hipStream_t s) {
 }
 
 // ---- the product kernel ------------------------------------------------------------------------------------------
-struct IntGemmArgs {
-    const int8_t* Xc; int64_t ldxc;      // activation codes [rows padded to 128][K], permuted order
-    const float* Xs;                     // token scales [rows padded]
-    const uint8_t* Wt;                   // weight records [N32][G][rec]: 4 bits: [2 spans][64 lanes][16 B]; 8 bits: [4 steps][64 lanes][16 B]
-    const float* Wsc;                    // scales [N32][G][32] (4 bits: already divided by 16)
-    int64_t M, N, N32, G;
-    float* Out; int64_t ldo;             // Y [M][ldo], or T [S][rows padded][ldo] for the projection
-    int64_t g_per_z;                     // K groups per plane of workgroups
-    int64_t out_z_stride;                // floats between the planes' outputs
-    // rank-k correction
-    const float* T; int64_t ldt;         // [rows padded][ldt] fp32
-    const uint8_t* Bt; const float* Bsc; // B_k records [N32][kp16][kBRecordBytes], scales [N32 * 32]
-    int kp16;
-    int tail_plane;                      // plane that adds the correction: 0, or one of its own behind the K planes
-    bool planes;                         // Out is planes of sums: int_reduce_planes_kernel gives them their token scales
-};
-
 __global__ __launch_bounds__(256, 2) void int_gemm_kernel(IntGemmArgs a) {
     constexpr int TM = 2, TN = 2;
     constexpr int NL = 4;                            // 16-byte loads per lane, column group and K group

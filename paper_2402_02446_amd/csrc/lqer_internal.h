@@ -217,6 +217,34 @@ int scale_from_magnitudes(const std::vector<double>& abar, std::vector<double>& 
 // ---- the scaled-integer variant (int_host.cpp, kernels_int.hip) ------------------------------------------------------
 hipError_t launch_quant_token(const float* X, int64_t rows, int64_t K, int64_t ldx, int8_t* codes, int64_t ldc,
                               float* scale_f32, uint16_t* scale_f16, bool perm, hipStream_t s);
+// Quantizer and projection in one launch, and the products of the general form (kernels_int.hip).
+struct IntPrepArgs {
+    const float* X; int64_t ldx, M, K;
+    int8_t* Xc; float* Xs;               // codes [rows][K] in the product's order, token scales
+    const uint8_t* At; const float* Asc; // A_k records and scales, as IntGemmArgs' 8-bit weights
+    float* T; int64_t ldt;
+};
+struct IntGemmArgs {
+    const int8_t* Xc; int64_t ldxc;      // activation codes [rows padded to 128][K], permuted order
+    const float* Xs;                     // token scales [rows padded]
+    const uint8_t* Wt;                   // weight records [N32][G][rec]: 4 bits: [2 spans][64 lanes][16 B]; 8 bits: [4 steps][64 lanes][16 B]
+    const float* Wsc;                    // scales [N32][G][32] (4 bits: already divided by 16)
+    int64_t M, N, N32, G;
+    float* Out; int64_t ldo;             // Y [M][ldo], or T [S][rows padded][ldo] for the projection
+    int64_t g_per_z;                     // K groups per plane of workgroups
+    int64_t out_z_stride;                // floats between the planes' outputs
+    // rank-k correction
+    const float* T; int64_t ldt;         // [rows padded][ldt] fp32
+    const uint8_t* Bt; const float* Bsc; // B_k records [N32][kp16][kBRecordBytes], scales [N32 * 32]
+    int kp16;
+    int tail_plane;                      // plane that adds the correction: 0, or one of its own behind the K planes
+    bool planes;                         // Out is planes of sums: int_reduce_planes_kernel gives them their token scales
+};
+hipError_t launch_int_prep(const IntPrepArgs& a, hipStream_t s);
+hipError_t launch_int_projection(const IntGemmArgs& a, hipStream_t s);
+hipError_t launch_int_main(const IntGemmArgs& a, hipStream_t s);
+hipError_t launch_int_reduce_planes(const float* P, int planes, int64_t plane_stride, int64_t M, int64_t N, int64_t ldp,
+                                    float* Y, int64_t ldy, const float* Xs, int tail, hipStream_t s);
 // The few-token form of the INT variant (kernels_int_few.hip).
 struct IntFewArgs {
     const float* X; int64_t ldx;
