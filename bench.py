@@ -214,9 +214,10 @@ def measure_peaks():
 
 
 def takes_six(layer, M):
-    """Whether a call's main product runs on fp6 operands (tiled path, a layer that holds them or 2-bit weights; at the sizes timed here)."""
+    """Whether a call's main product runs on fp6 operands, at the sizes timed here: tiled path, a correction, a layer that holds them or 2-bit weights
+    of four K tiles and more (these layers' exponents are nibbles).  Below 3e5 activations ranks up to 32 would not."""
     from paper_2402_02446_amd import binding
-    return binding.lqer_linear_path(layer, M) == 2 and (layer.fp6_bytes() > 0 or layer.w_bits == 2)
+    return binding.lqer_linear_path(layer, M) == 2 and layer.kp > 0 and (layer.fp6_bytes() > 0 or (layer.w_bits == 2 and layer.K > 768))
 
 
 def mfma_peak(six):
@@ -540,8 +541,9 @@ def run_w2a8(rng, peaks):
 def run_int_variant(rng, peaks):
     """The scaled-integer variant (Table 2 "L2QER-INT": INT4 g128 weights, INT8 per-token activations, k = 32) on the
     LLaMA-7B-shaped layers: decode on a ring of device copies beyond the last-level cache, prefill at M = 2048 and the
-    4096 x 4096 linear at 65536 tokens.  One step = per-token quantizer + projection + main product (three launches; with
-    few tokens both products split K over planes of workgroups and a small kernel adds the planes: five launches);
+    4096 x 4096 linear at 65536 tokens.  One step = per-token quantizer + projection + main product: a few-token form of two launches; else
+    quantizer and projection in one launch (ranks up to 64, up to 2.4e7 values) or two, and the main product, each product whose K is
+    split over planes followed by a small kernel that adds them;
     the fractions are of the whole step: against HBM for M = 16 (0.515625 B per weight), against the dense int8
     matrix-core peak (5.0 POP/s) for prefill."""
     import torch
@@ -575,7 +577,8 @@ def run_int_variant(rng, peaks):
                                    "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "traffic": None}
             else:
                 ach = ops / (ms * 1e-3) / 1e12
-                rec["roofline"] = {"bound": "mfma", "kernel": "whole step (quant_token_kernel + int_gemm_kernel + int_main_kernel, int_reduce_planes_kernel where K is split)", "achieved": ach,
+                prep = "int_prep_kernel" if 0 < kp <= 64 and M * K <= 24000000 else "quant_token_kernel + int_gemm_kernel"
+                rec["roofline"] = {"bound": "mfma", "kernel": f"whole step ({prep} + int_main_kernel, int_reduce_planes_kernel where K is split)", "achieved": ach,
                                    "peak": MFMA_INT8_PEAK_TOPS, "unit": "TOP/s", "frac": ach / MFMA_INT8_PEAK_TOPS, "traffic": None}
                 # what the int8 pipe delivers with int_main_kernel's 10 vector instructions per MFMA beside it (probe)
                 lim = (peaks or {}).get("mfma_beside_valu_tera_per_s", {}).get("int8_10_valu")

@@ -217,8 +217,8 @@ int lqer_linear_forward_q(const lqer_layer* layer, const int8_t* Xc_dev, const u
  *           staged kernel's: mode 0 = planes of K when the estimate says they pay, 1 = whole tiles,
  *           2 = planes (LQER_ERR_SHAPE with K of one tile of 256), no mode 3
  *           Shapes 21 and 22 (128 x 512, 128 x 256; modes 0 to 3) and 41, 42, 43, 44 (as 31, 32, 33; 128 x 128) are
- *           those on fp6 operands, for 4-bit layers that hold the second form of W_q and for 2-bit layers whose
- *           exponent bytes span at most 16 values
+ *           those on fp6 operands, for 4-bit layers that hold the second form of W_q and for 2-bit layers of a
+ *           rank above 0 whose exponent bytes are at least 2 and span at most 16 values
  *   stages  bit 0 = quantize + T, bit 1 = main product; 0 = both
  * Same contract as lqer_linear_forward otherwise.  Running stage bit 1 alone reuses
  * what an earlier call with bit 0 left in the same workspace - with the same M, path and
@@ -314,7 +314,7 @@ int lqer_quantize_int8_token(const float* x_dev, int64_t rows, int64_t cols, int
  * lqer_linear_forward for callers that cannot allocate device memory or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation.  Same arguments,
  * same kernels and the same bits in Y as lqer_linear_forward with an automatic launch whose tiles
- * are not cut between workgroups; the scratch that call takes as `workspace_dev` is a device array
+ * are not cut between workgroups (T in fewer partial sums where only those fit); the scratch that call takes as `workspace_dev` is a device array
  * inside the library, 32 MiB on every GPU the library is used on, held until the process ends.
  *   - Sizes whose scratch need exceeds 32 MiB return LQER_ERR_WORKSPACE before anything is launched
  *     (the need is about 2 (M + 255) (K + 128) bytes for more than 32 tokens - e.g. M = 1024 at

@@ -663,7 +663,7 @@ static void launch_prep_t(dim3 grid, dim3 block, hipStream_t s, const PrepArgs& 
     hipLaunchKernelGGL((prep_kernel<SRC, FINAL, MAXG, CELLS, false>), grid, block, prep_lds_bytes(a.nwaves, MAXG, false), s, a);
 }
 
-int prep_slices(const Layer& L, int64_t M, int path) {
+int prep_slices(const Layer& L, int64_t M, int path, bool least) {
     if (path != 1) {
         // tiled path: one workgroup per 16 token rows; when that leaves compute units idle, split K as well (each slice keeps at least
         // two tiles) and let the main kernel add the partial T.  Either one workgroup of up to 16 wavefronts to a compute unit, where they
@@ -677,7 +677,7 @@ int prep_slices(const Layer& L, int64_t M, int path) {
         auto more = [&] { return s < 8 && L.KT / (2 * s) >= 2; };
         while (2 * rg * s <= 256 && more()) s *= 2;
         if (rg * s >= 192 && rg * s <= 256) return (int)s;
-        while (rg * s < 384 && more()) s *= 2;
+        while (rg * s < (least ? 256 : 384) && more()) s *= 2;
         return (int)s;
     }
     // streaming path: at most two row groups, so K is spread over workgroups (the main kernel adds

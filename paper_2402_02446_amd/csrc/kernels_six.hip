@@ -57,7 +57,9 @@ struct SixLds {
 // What bounds it.  On a full chip the clock, that is, energy: 3.7 us per K tile of 128 x 512 with the values of a product, 2.6 with
 // activations of zero, at 1.45 and 2.0 GHz, where the bare MFMA loop's rate would be 2.6; 8 % fewer cycles (5820 to 5330, a chunk's loads
 // in three parts instead of one) gave 1 % of time.  Taken out one at a time, the loads cost 9 %, the expansion 8, the reads of activations
-// and the barrier 6 each.  On a chip that is not full, the vector port: a block-scaled MFMA holds it for 16 cycles whatever its shape
+// and the barrier 6 each.  On a chip that is not full it is neither: the matrix units are busy for a tenth of 203 tokens of 4112 x 11000 and the vector
+// port for a quarter, waits for memory and LDS take a third, and three workgroups on a unit are no faster per K tile than two; what they
+// share is not shown yet.  The shape: a block-scaled MFMA holds the vector port for 16 cycles whatever its shape
 // (loops of MFMAs with n vector instructions behind each: 32x32x64 max(32, 16 + 4 n) cycles, 16x16x128 16 + 4 n, of 16 bare), so that of the
 // two shapes only this one leaves room for the expansion, 3.5 instructions per MFMA where a wavefront has 128 rows.  (With 16x16x128 MFMAs,
 // whose bare loop is the faster by 13 % on such operands: 7660 cycles and 4.1 us.)

@@ -339,10 +339,11 @@ static int download(const uint8_t* dev, size_t bytes, std::vector<uint8_t>& host
 
 // path 1 = streaming kernel (activations as 16-byte cells, T as partial sums), 2 = tiled
 // with_slots = false leaves out the slots of the tiled kernel's work split (it then never cuts tiles)
-static Workspace plan_workspace(const Layer& L, int64_t M, int path, void* base, bool with_slots = true) {
+// least_slices: no more partial sums of T than keep every compute unit at work
+static Workspace plan_workspace(const Layer& L, int64_t M, int path, void* base, bool with_slots = true, bool least_slices = false) {
     Workspace ws;
     ws.ldxh = L.KT * kTileK + round_up(2 * (int64_t)L.kp, 64);
-    ws.S = prep_slices(L, M, path);
+    ws.S = prep_slices(L, M, path, least_slices);
     ws.cells = (path == 1);
     ws.lr = stream_cell_rows_log2(M);
     ws.x8 = false;
@@ -448,6 +449,9 @@ static int forward_impl(const lqer_layer* layer, const float* X, int64_t ldx, co
     if (stages == 0) stages = 3;
     if (!wsp || ((uintptr_t)wsp & 255) != 0) return LQER_ERR_WORKSPACE;
     Workspace ws = plan_workspace(L, M, path, wsp, with_slots);
+    // (the static scratch, or a workspace sized for other token counts: a call that fits with fewer partial sums of T is not refused for the
+    // faster number)
+    if (path == 2 && ws.bytes > ws_bytes) ws = plan_workspace(L, M, path, wsp, with_slots, true);
     if (ws.bytes > ws_bytes) return LQER_ERR_WORKSPACE;
     if (path == 2 && tiled_takes_six(L, M, variant)) set_six_layout(ws, L);
     if (path == 1) ws.x8 = stream_takes_codes(stream_variant(L, M, variant), ws.lr);
@@ -541,9 +545,9 @@ static size_t shared_least_bytes(const lqer_layer* const* layers, int n, int64_t
         const Layer& L = layers[i]->L;
         const int path = stream_takes_64(L, M) ? 1 : pick_path(L, M);
         all_tiled = all_tiled && path == 2;
-        need = std::max(need, plan_workspace(L, M, path, nullptr).bytes);
+        need = std::max(need, plan_workspace(L, M, path, nullptr, true, true).bytes);
     }
-    if (all_tiled) need = std::max(need, plan_workspace(shared_plan_layer(layers, n), M, 2, nullptr).bytes);
+    if (all_tiled) need = std::max(need, plan_workspace(shared_plan_layer(layers, n), M, 2, nullptr, true, true).bytes);
     return need;
 }
 
@@ -767,8 +771,15 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
         if (ldy[i] < layers[i]->L.N || (ldy[i] & 3) != 0 || ((uintptr_t)Y_dev[i] & 15) != 0) return LQER_ERR_SHAPE;
     if (!workspace_dev || ((uintptr_t)workspace_dev & 255) != 0) return LQER_ERR_WORKSPACE;
     if (workspace_bytes < shared_least_bytes(layers, n_layers, M)) return LQER_ERR_WORKSPACE;
-    const bool tiled = shared_group_tiled(layers, n_layers, M) &&
-                       plan_workspace(shared_plan_layer(layers, n_layers), M, 2, nullptr).bytes <= workspace_bytes;
+    // one plan for the group: as for a single layer, with fewer partial sums of T where only those fit
+    bool tiled = shared_group_tiled(layers, n_layers, M);
+    Workspace ws{};
+    if (tiled) {
+        const Layer plan = shared_plan_layer(layers, n_layers);
+        ws = plan_workspace(plan, M, 2, workspace_dev);
+        if (ws.bytes > workspace_bytes) ws = plan_workspace(plan, M, 2, workspace_dev, true, true);
+        tiled = ws.bytes <= workspace_bytes;
+    }
     if (!tiled) {
         // few tokens: layers that take the same shape of the streaming kernel share their launches, if the workspace has room
         // for all their T; the others are full calls
@@ -787,7 +798,6 @@ int lqer_linear_forward_shared(const lqer_layer* const* layers, int n_layers, co
         }
         return LQER_OK;
     }
-    const Workspace ws = plan_workspace(shared_plan_layer(layers, n_layers), M, 2, workspace_dev);
     hipStream_t s = (hipStream_t)hip_stream;
     // Every layer in the form it has alone: those that take fp6 operands first, then those that take bf16, one quantization each.
     // (One in all where the ranks are alike: see tiled_takes_six.)

@@ -270,7 +270,7 @@ int truncated_split(const std::vector<double>& G, int64_t K, int64_t N, const st
                     std::vector<double>& A, std::vector<double>& B);
 int build_factors_int(const float* W_host, int64_t K, int64_t N, const std::vector<double>& s, int k, lqer_layer** out);
 
-int prep_slices(const Layer& L, int64_t M, int path);
+int prep_slices(const Layer& L, int64_t M, int path, bool least = false);
 // lqer_linear_forward with the given scratch as its workspace, planned without the slots of the tiled kernel's
 // work split (output tiles are then never cut); LQER_ERR_WORKSPACE when the plan does not fit scratch_bytes
 int forward_in_scratch(const lqer_layer* layer, const float* X, int64_t M, int64_t ldx, float* Y, int64_t ldy,

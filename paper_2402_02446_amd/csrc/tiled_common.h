@@ -18,7 +18,7 @@ struct TiledArgs {
     int kp, kp16;
     int grid_m, grid_n;
     int group_m;
-    // work split (see the head of this file)
+    // work split (the head of kernels_tiled.hip says how)
     int64_t dp_tiles;          // output tiles taken whole, tile i by workgroup i % gridDim.x
     int64_t sk_units;          // K tile units of the remaining output tiles, shared out in ranges of ...
     int64_t sk_share;          // ... this many per workgroup
@@ -42,7 +42,7 @@ inline Split whole_tiles(int64_t tiles, int64_t KT) { return Split{tiles, tiles,
 // aligned: where the chip holds two or more workgroups per remaining tile, every such tile is cut into the same
 // whole number of pieces, one per workgroup, instead of equal shares of all remaining K tiles: a share then never
 // crosses a tile, so no workgroup gets a second (possibly tiny) piece.  Measured on 11008 x 4096 at M = 2048
-// (128 tiles of 43 K tiles on 256 workgroups): 157 us against 172 us with equal shares.
+// (128 tiles of 43 K tiles on 256 workgroups): 157 us against 172 us with equal shares (tiled_kernel, when it took that call).
 inline Split split_tiles(int64_t tiles, int64_t KT, int64_t slots, bool aligned) {
     Split sp;
     sp.grid = slots;

@@ -91,3 +91,30 @@ def test_slices_of_the_contraction(M, K, slices):
     assert_forward_matches(Y.cpu().numpy()[at], X[at], layers[1][0])
     for h in hs:
         h.free()
+
+
+# 188 blocks of 16 tokens take four slices of K; on the static scratch, which holds T in two but not in four, two; so in a workspace of that size.
+def test_fewer_slices_where_the_scratch_is_full():
+    import torch
+    from paper_2402_02446_amd import binding
+    M, K, N, k = 3000, 3072, 288, 256
+    layer, ch = oracle_layer_big(K, N, k, seed=9)
+    h = upload(layer)
+    rows, part = (M + 95 + 255) // 256 * 256, (M + 95 + 255) // 256 * 256 * k * 4
+    plan = rows * (K + 2 * k) * 2
+    assert plan + 2 * part < (32 << 20) < plan + 4 * part
+    X = synth.gen_activations(np.random.default_rng(M), M, K, ch, 50.0)
+    Xd = torch.from_numpy(X).cuda()
+    at = np.array([0, 15, 16, 127, 128, M // 2, M - 1])
+    need = binding.lqer_linear_workspace_bytes(h, M)
+    few = torch.full((need - 2 * part,), 255, dtype=torch.uint8, device="cuda")
+    Y = binding.lqer_linear_forward_static(h, Xd)
+    for y in (Y, binding.lqer_linear_forward(h, Xd, workspace=few), binding.lqer_linear_forward_shared([h, h], Xd, workspace=few)[1]):
+        assert_forward_matches(y.cpu().numpy()[at], X[at], layer)
+    with pytest.raises(binding.LqerError, match="LQER_ERR_WORKSPACE"):
+        binding.lqer_linear_forward(h, Xd, workspace=few[:-256])
+    with pytest.raises(binding.LqerError, match="LQER_ERR_WORKSPACE"):
+        binding.lqer_linear_forward_shared([h, h], Xd, workspace=few[:-256])
+    with pytest.raises(binding.LqerError, match="LQER_ERR_WORKSPACE"):
+        binding.lqer_linear_forward_static(h, torch.zeros(4700, K, device="cuda"))
+    h.free()
