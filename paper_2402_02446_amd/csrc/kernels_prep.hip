@@ -667,7 +667,9 @@ int prep_slices(const Layer& L, int64_t M, int path, bool least) {
     if (path != 1) {
         // tiled path: one workgroup per 16 token rows; when that leaves compute units idle, split K as well (each slice keeps at least
         // two tiles) and let the main kernel add the partial T.  Either one workgroup of up to 16 wavefronts to a compute unit, where they
-        // are at least three quarters of a round; or 384 of eight and more, two to a unit and so three quarters of one as well.
+        // are at least three quarters of a round; or 384 of eight and more, two to a unit and so three quarters of one as well, if that
+        // leaves a slice three tiles: more partial sums cost the main kernel as much whatever K (5072 tokens of 1088 x 6432 rank 16 in two
+        // slices 101.6 us, 97.6 in one).
         // 5700 calls of 700 to 9000 tokens, projection and main product: 1.6 % from the best of all slices and wavefront counts on average;
         // the first form wherever it fills 256 units once or more, however empty its last round, 3.3 % (4133 tokens of 10704 x 822 rank
         // 32 152 us, 127 by this), always 512 of the second 2.6 %, with a line at 512 instead of 384 (7823 tokens of 976 x 4707 rank 256
@@ -677,7 +679,8 @@ int prep_slices(const Layer& L, int64_t M, int path, bool least) {
         auto more = [&] { return s < 8 && L.KT / (2 * s) >= 2; };
         while (2 * rg * s <= 256 && more()) s *= 2;
         if (rg * s >= 192 && rg * s <= 256) return (int)s;
-        while (rg * s < (least ? 256 : 384) && more()) s *= 2;
+        while (rg * s < 192 && more()) s *= 2;
+        while (!least && rg * s < 384 && more() && L.KT >= 6 * s) s *= 2;
         return (int)s;
     }
     // streaming path: at most two row groups, so K is spread over workgroups (the main kernel adds

@@ -73,10 +73,10 @@ def test_ranks_above_64_of_large_calls(M, K, k, w_bits, wide, act_bits, rows):
         x.free()
 
 
-# Slices of K: as many as make one workgroup to a compute unit of at least three quarters of them, else 384 workgroups.  The partial sums of
+# Slices of K: as many as make one workgroup to a compute unit of at least three quarters of them, else 384 workgroups if a slice keeps three tiles.  The partial sums of
 # T are in the workspace: two layers of ranks 16 and 32, whose rows are equally long, differ by them alone.
-@pytest.mark.parametrize("M,K,slices", [(1024, 4096, 4), (1040, 4096, 8), (1536, 4096, 2), (2048, 4096, 2), (2049, 4096, 4), (3056, 4096, 4), (3057, 4096, 1),
-                                        (4096, 10704, 1), (4097, 10704, 2), (4133, 1008, 2), (4133, 768, 1), (6128, 4096, 2), (6129, 4096, 1), (8177, 4096, 1)])
+@pytest.mark.parametrize("M,K,slices", [(1024, 4096, 4), (1040, 4096, 4), (1040, 6144, 8), (1536, 4096, 2), (2048, 4096, 2), (2049, 4096, 4), (3056, 4096, 4), (3057, 4096, 1),
+                                        (4096, 10704, 1), (4097, 10704, 2), (4133, 1536, 2), (4133, 1280, 1), (4133, 768, 1), (2049, 3072, 4), (2049, 2816, 2), (6128, 4096, 2), (6129, 4096, 1), (8177, 4096, 1)])
 def test_slices_of_the_contraction(M, K, slices):
     import torch
     from paper_2402_02446_amd import binding
