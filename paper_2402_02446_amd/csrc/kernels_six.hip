@@ -746,10 +746,11 @@ static const SixShape kSixShapes[] = {
     {44, 128, 128, 2, {{1.133, 1.352}, {1.705, 2.163}}, {1.761}, 9.148, 2.545, {0.211, 0.014, 0.031}, {2.630, 0.372, 0.112}, 2.665, 0.171},
 };
 // 128 x 512 with the tiles that do not fill a round cut in whole pieces: us per launch, K tile of a piece, K tile and number of whole
-// rounds, piece beyond two, 64 ranks of the correction beyond the first, MB of Y (1500 timings, 5 %).  In equal shares, and 128 x 256
-// in pieces, by force only: 15 to 20 % from any such model.
-struct SixPieces { double fixed, share, unit, round, piece, corr, out; };
-static const SixPieces kSixPieces = {27.201, 3.469, 3.681, 1.503, 4.877, 7.734, 0.243};
+// rounds, piece beyond two, 64 ranks of the correction beyond the first, MB of Y, of one beyond the caches with rows that share lines (as
+// above).  Of 1600 timings one half fitted: 5 %; with the models above the choice on 4800 other calls is 0.4 % from the fastest form on average, 23 % at
+// worst (0.8 % before these).  In equal shares, and 128 x 256 in pieces, by force only: 15 to 20 % from any such model.
+struct SixPieces { double fixed, share, unit, round, piece, corr, out[2]; };
+static const SixPieces kSixPieces = {29.573, 3.535, 3.600, 11.348, 5.054, 7.626, {0.106, 0.049}};
 constexpr int kMostPlanes = 16;
 
 struct SixPick { int id, planes, share; double us; };        // share: K tiles per plane; planes 0: in pieces
@@ -757,11 +758,15 @@ struct SixPick { int id, planes, share; double us; };        // share: K tiles p
 // rounds of the correction beyond the first
 static int more_rounds(int kp) { return kp > 64 ? (kp + 63) / 64 - 1 : 0; }
 
+// Y, of mb MB, is more than the caches hold, and its rows do not start on 128 bytes (where they are as close as they can be)
+static bool ragged_beyond_caches(const Layer& L, double mb) { return mb > 256.0 && ((L.N + 3) / 4 & 7) != 0; }
+
 static double six_us(const SixShape& sh, const Layer& L, int64_t M, int S, int64_t tiles, int planes, int64_t share, int cus) {
     const int64_t wgs = tiles * planes, slots = (int64_t)cus * sh.resident, full = wgs / slots, rest = wgs - full * slots;
     const double mb = (double)M * (double)L.N * 4e-6;
     double t = sh.fixed + sh.round * (double)(full + (rest > 0 ? 1 : 0) - 1) + sh.out[0] * mb + sh.unit[sh.resident - 1][1] * (double)full * (double)share;
-    if (mb > 256.0) t += sh.out[1] * (mb - 256.0) + (((L.N + 3) / 4 & 7) != 0 ? sh.out[2] * mb : 0.0);
+    if (mb > 256.0) t += sh.out[1] * (mb - 256.0);
+    if (ragged_beyond_caches(L, mb)) t += sh.out[2] * mb;
     for (int r = 1; r < sh.resident; ++r)
         if (wgs > (int64_t)r * cus) t += sh.start[r - 1];
     if (rest > 0) {
@@ -795,10 +800,10 @@ static SixPick pick_six(const Layer& L, int64_t M, int S, int64_t part_bytes, in
             const Split sp = split_tiles(tiles, L.KT, cus, true);
             if (sp.sk_units == 0 || !sp.aligned) continue;
             const SixPieces& c = kSixPieces;
-            const double rounds = (double)(sp.dp_tiles / sp.grid);
+            const double rounds = (double)(sp.dp_tiles / sp.grid), mb = (double)M * (double)L.N * 4e-6;
             const double us = c.fixed + c.share * (double)sp.sk_share + rounds * (c.unit * (double)L.KT + c.round) +
                               c.piece * (double)(sp.sk_tile_units / sp.sk_share - 2) + c.corr * more_rounds(L.kp) * (rounds + 1.0) +
-                              c.out * (double)M * (double)L.N * 4e-6;
+                              (c.out[0] + (ragged_beyond_caches(L, mb) ? c.out[1] : 0.0)) * mb;
             if (us < best.us) best = SixPick{21, 0, (int)sp.sk_share, us};
         }
     }
